@@ -70,7 +70,8 @@ typedef struct bpe_table bpe_table;
 typedef struct {
     int64_t n_merges;
     int64_t capacity;       /* slots */
-    int64_t device_bytes;   /* 8-byte slots, the 65536-entry direct table for byte pairs (4 bytes each), two
+    int64_t device_bytes;   /* 8-byte slots, the whole-piece table (16 bytes a slot: every string of up to 12 bytes
+                             * that becomes one token), the 65536-entry direct table for byte pairs (4 bytes each), two
                              * rank-order arrays, 8 bytes per token id up to max_id */
     int32_t hash_attempt;   /* which multiplier set placed all keys (0 = first) */
     int32_t max_id;         /* largest token id the table can produce or consume */

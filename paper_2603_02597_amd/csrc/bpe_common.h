@@ -76,6 +76,8 @@ struct TableView {
     const int32_t *rank_of;    // [n_merges] caller's rank value by rank order
     const uint2 *sym_lr;       // [max_id + 1] per id: {lowest rank order of a rule with the id as its right part,
                                // ... as its left part}, kNoRank where there is none
+    const uint4 *words;        // whole-piece table (see WordHash): {bytes 0-3, 4-7, 8-11 (zero-padded), word of the slot}
+    int32_t word_shift;        // 32 - log2(slots of `words`)
     uint32_t half;             // slots per half (power of two, 2^16 .. 2^24)
     int low_bits;              // 24 - log2(half): bits of the mix below the slot index
     int index_bits;            // log2(half)
@@ -150,6 +152,29 @@ __device__ inline uint32_t merged_id_of(const TableView &t, uint32_t rank) {
     return t.merged_delta >= 0 ? rank + (uint32_t)t.merged_delta : (uint32_t)t.merged_of[rank];
 }
 
+// Whole-piece table: byte strings of up to kWordMax bytes that the merge loop turns into ONE
+// token (an id's expansion, where greedy merging of those bytes gives that id back; bytes too),
+// with that token.  In word-like text nearly every piece is such a string, and a piece that is
+// needs no merge loop at all: one probe instead of a chain of five or six merges, each with two
+// lookups.  Which strings these are follows from the rules alone and is found out when the
+// table is built.  Measured: merge_kernel on 13.5 MB of text (97 % of the pieces are one token) 91.8 -> 65.6 us,
+// merge_tiles_kernel on 840 KB 12.1 -> 9.4 us, merge_bytes_kernel on 840 KB 13.6 -> 10.7 us.
+// A string that has no room at either of its two slots is left out (the merge
+// loop handles it), so the table is a shortcut and never a condition.
+// A slot is 16 bytes: the string, zero-padded, and id << 8 | kWordMore | length (0: empty).
+constexpr int kWordMax = 12;
+constexpr uint32_t kWordLenMask = 15, kWordMore = 16;   // kWordMore: some string whose first slot this is sits in its second
+// 24-bit multiply-adds over the string's four 24-bit parts, then two slots from the sum.
+struct WordHash { uint32_t sum; };
+__host__ __device__ inline WordHash word_hash(uint32_t w0, uint32_t w1, uint32_t w2) {
+    const uint32_t c1 = (w0 >> 24) | (w1 << 8), c2 = (w1 >> 16) | (w2 << 16), c3 = w2 >> 8;
+    WordHash h;
+    h.sum = mul24(w0, 0x9E3779u) + mul24(c1, 0xC2B2AFu) + mul24(c2, 0x85EBCBu) + mul24(c3, 0xA54FF5u);
+    return h;
+}
+__host__ __device__ inline uint32_t word_slot1(const WordHash &h, int shift) { return (h.sum * 0x9E3779B1u) >> shift; }
+__host__ __device__ inline uint32_t word_slot2(const WordHash &h, int shift) { return ((h.sum ^ (h.sum >> 15)) * 0x85EBCA77u) >> shift; }
+
 void set_error(const char *fmt, ...);
 int hip_fail(hipError_t e, const char *what);
 // BPE_OK if `device` (where a handle's memory lives) is the calling thread's current device.
@@ -183,6 +208,6 @@ int launch_pretokenize(const uint8_t *bytes, int64_t n_bytes, const int32_t *seq
 struct bpe_table {
     bpe::TableView view;
     bpe_table_info_t info;
-    void *device_mem;     // one allocation: slots | byte_pairs | merged_of | rank_of | sym_lr
+    void *device_mem;     // one allocation: slots | words | byte_pairs | merged_of | rank_of | sym_lr
     int device;
 };

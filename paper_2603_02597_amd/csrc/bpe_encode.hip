@@ -47,14 +47,25 @@ namespace bpe {
 // LDS of a tile: the lane-per-piece state of the four wavefronts and the double
 // buffer of the workgroup path share the same bytes; a barrier separates the two
 // uses, and the lane-per-piece tokens are in the workspace by then.
+// Short pieces without a whole-piece token: up to two rounds of all wavefronts are merged one per
+// row of 16 lanes, more of them one per lane.
+__host__ __device__ constexpr int row_pieces(int waves) { return 2 * waves * (kWave / kTinyMax); }
+// The single kernel has helper wavefronts for the rows: its grids leave the chip idle (at most one
+// tile per compute unit), and a tile of a table with few whole words leaves 60 pieces over.
+constexpr int kFusedWaves = 16;
+constexpr int kFusedThreads = kFusedWaves * kWave;
 union MergeLds {
     TinyState tiny[kWavesPerGroup];
     struct { int32_t A[kLdsMaxLen]; int32_t B[kLdsMaxLen]; } group;
+    struct { uint4 bytes[kGroupThreads]; uint32_t tok[row_pieces(kFusedWaves)][kTinyMax]; } left;   // see merge_left_over
 };
 
 struct TileShared {
     MergeLds lds;
     GroupTmp tmp;
+    int left_n[kWavesPerGroup];    // pieces of a wavefront that find_word left over (| kAnyLonger: it has longer pieces),
+                                   // and per such piece (wavefront w's from 64 w on): its first byte in list, its
+                                   // length << 8 | thread in cnt_back
     int list[kGroupThreads];       // threads whose piece waits for the wavefront paths, then for the workgroup path
     int cnt_back[kGroupThreads];   // token counts handed back to the owning thread (long-piece workgroups: more list)
     int list_n, list_back;
@@ -63,16 +74,21 @@ struct TileShared {
 struct TilePiece {                 // what a thread knows about its piece after merge_tile
     int64_t q;
     int o, len, cnt;
-    int tok0;                      // several-kernel path: first token if known here, else -1 (it is in scratch)
-    bool has_piece, is_tiny, parked;
+    int tok0;                      // first token if the thread knows it, else -1
+    bool has_piece, is_tiny;
     bool long_path;                // the workgroup path took the piece (its thread is on TileShared::list)
-    uint32_t alive;                // lane-per-piece: positions of its LDS column that hold the tokens (unless parked)
+    int left_slot;                 // >= 0: find_word left the piece over, and this is its slot (see TileShared::left_n)
+    int others_cnt;                // tokens of other threads' left-over pieces that this thread accounts for
+    bool parked;                   // single kernel: the tokens of left-over pieces are in scratch, not in LDS
+    // single kernel: what the thread's lane holds of a left-over piece that it merged one per lane
+    uint32_t alive;
+    int n_left;                    // left-over pieces of the tile
 };
 
-// Merges every piece of tile `tile`.  Tokens of a piece end up at
-// p.scratch[off[q] ...], except lane-per-piece tokens when `keep_in_lds` and no
-// other path of this tile needed the LDS (then TilePiece::parked is false and
-// they are still in the thread's LDS column).  Sets p.status[0] on bad offsets.
+// Merges every piece of tile `tile`.  Tokens of a piece end up at p.scratch[off[q] ...]; the
+// first token of a short piece travels in its record instead (several kernels), and the single
+// kernel keeps the tokens of short pieces in registers and LDS unless the tile has longer
+// pieces, whose paths need the LDS (TilePiece::parked).  Sets p.status[0] on bad offsets.
 __device__ __forceinline__ const EncodeParams &kernel_params();
 // Where the pieces of a tile come from: the caller's (or the pre-tokenizer's) offsets array; the
 // offsets array through a list of pieces (de-duplication); or the piece starts that the workgroup
@@ -116,20 +132,109 @@ __device__ __forceinline__ void piece_bounds(const EncodeParams &p, const ByteTi
     }
 }
 
+// The short pieces of a tile that find_word left over (they fill no wavefront where they lie):
+// one per row of 16 lanes while they are few, else one per lane, packed from the first wavefront
+// on.  Several kernels: whoever merges a piece writes its record and its tokens from the second
+// on.  Single kernel (keep_in_lds): counts go back to the owners through sh.cnt_back[slot], the
+// tokens stay in sh.lds.left.tok or in the lane's column, or, if the tile has longer pieces
+// (`park`), go to scratch.
+__device__ __forceinline__ int left_slot_of(int e, const int (&n)[kWavesPerGroup]) {     // slot of left-over piece e
+    int base = 0;
+    for (int w = 0; w + 1 < kWavesPerGroup; ++w) {
+        if (e < n[w]) break;
+        e -= n[w];
+        base += kWave;
+    }
+    return base + e;
+}
+
+constexpr int kAnyLonger = 1 << 16;
+
+// Returns whether the tile has longer pieces.
+template <int SRC, int WAVES>
+__device__ __forceinline__ bool merge_left_over(const EncodeParams &p, TileShared &sh, TilePiece &t, int64_t tile_q0, int P,
+                                                bool keep_in_lds) {
+    const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    int n[kWavesPerGroup], all = 0;
+    t.n_left = 0;
+    for (int w = 0; w < kWavesPerGroup; ++w) {
+        const int v = __builtin_amdgcn_readfirstlane(sh.left_n[w]);
+        all |= v;
+        t.n_left += n[w] = v & (kAnyLonger - 1);
+    }
+    const bool park = (all & kAnyLonger) != 0;
+    t.parked = keep_in_lds && park;
+    if (t.n_left == 0) return park;
+    auto record_of = [&](int owner) {
+        return SRC == kFromBytes ? tile_q0 + owner : tile_q0 + (int64_t)(owner / kWave) * P + (owner % kWave);
+    };
+    if (t.n_left <= row_pieces(WAVES)) {
+        constexpr int kRows = kWave / kTinyMax;
+        for (int e0 = wv * kRows; e0 < t.n_left; e0 += WAVES * kRows) {
+            const int j = lane & (kTinyMax - 1), e = e0 + lane / kTinyMax;
+            const bool mine = e < t.n_left;
+            const int slot = mine ? left_slot_of(e, n) : 0;
+            const int o = sh.list[slot], meta = sh.cnt_back[slot];
+            uint32_t sym = ((const uint8_t *)&sh.lds.left.bytes[slot])[j] | (3u << 24);
+            const int c = row_merge(p, sym, mine ? meta >> 8 : 0);
+            sym &= 0xFFFFFFu;
+            if (keep_in_lds) {
+                if (park) { if (j < c) p.scratch[o + j] = (int)sym; }
+                else if (mine) sh.lds.left.tok[e][j] = sym;
+                if (mine && j == 0) sh.cnt_back[slot] = c;
+            } else {
+                if (j > 0 && j < c) p.scratch[o + j] = (int)sym;
+                if (mine && j == 0) {
+                    p.rec[record_of(meta & 255)] = make_int2(c, (int)sym);
+                    t.others_cnt += c;
+                }
+            }
+        }
+    } else {
+        const bool mine = tid < t.n_left;
+        const int slot = mine ? left_slot_of(tid, n) : 0;
+        const int o = sh.list[slot], meta = sh.cnt_back[slot];
+        const uint4 b = sh.lds.left.bytes[slot];
+        const uint32_t w[4] = {b.x, b.y, b.z, b.w};
+        __syncthreads();               // the columns take the place of the bytes
+        TinyState &L = sh.lds.tiny[wv & (kWavesPerGroup - 1)];         // (the single kernel's helpers have none of the pieces)
+        const uint32_t alive = tiny_merge(p, L, w, meta >> 8, mine);
+        const int c = __builtin_popcount(alive);
+        if (keep_in_lds) {
+            if (park) tiny_store(L, alive, p.scratch + o);
+            else t.alive = alive;
+            if (mine) sh.cnt_back[slot] = c;
+        } else {
+            tiny_store(L, alive & (alive - 1), p.scratch + o + 1);
+            if (mine) {
+                p.rec[record_of(meta & 255)] = make_int2(c, (int)(L.S[__builtin_ctz(alive)][lane] & 0xFFFFFFu));
+                t.others_cnt += c;
+            }
+        }
+    }
+    if (keep_in_lds) {
+        __syncthreads();
+        if (t.left_slot >= 0) t.cnt = sh.cnt_back[t.left_slot];
+    }
+    return park;
+}
+
 // n_pieces, P: the piece count and the pieces per wavefront of this launch (p's own
 // values, except on the raw path, where the kernel finds them out).
 // SKIP_LONG: the pieces beyond tiny_max are somebody else's (merge_kernel's long-piece
 // workgroups): they count as no tokens here and get no record from this tile.
 // SRC == kFromBytes: `tile` and n_pieces are not used; the thread's piece is number bt.k0 + threadIdx.x of
 // the tile (if that is below bt.n_t), and its record goes to slot bt_q0 + that number.
-template <int SRC = kFromOffsets, bool SKIP_LONG = false>
+// WAVES: wavefronts that merge left-over pieces in rows (0: always one per lane); the ones beyond the tile's four only help with left-over pieces.
+// EAGER: see find_word.
+template <int SRC = kFromOffsets, bool SKIP_LONG = false, int WAVES = kWavesPerGroup, bool EAGER = !SKIP_LONG>
 __device__ __forceinline__ TilePiece merge_tile(const EncodeParams &p, TileShared &sh, int tile, bool keep_in_lds,
                                                 int n_pieces, int P, const ByteTile &bt = ByteTile{}, int64_t bt_q0 = 0) {
     const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
     if (p.paper) {                 // the tile is piece number `tile`, merged by the paper's kernel
         TilePiece t = {};
         t.q = tile;
-        t.parked = true;
+        t.left_slot = -1;
         int o = 0, len = 0;
         if (tile < n_pieces) {
             o = p.off[tile];
@@ -179,24 +284,40 @@ __device__ __forceinline__ TilePiece merge_tile(const EncodeParams &p, TileShare
     const bool is_wave = t.has_piece && t.len > p.tiny_max && (t.len <= p.wave_lds_max || p.runs_by_best_rank);
     const bool is_long = t.has_piece && t.len > p.wave_lds_max && !p.runs_by_best_rank;
 
-    // lane-per-piece path
-    t.alive = tiny_merge(p, sh.lds.tiny[wv], t.o, t.len, t.is_tiny);
-    t.cnt = __builtin_popcount(t.alive);
-    t.parked = !keep_in_lds;
+    // Short pieces.  Nearly every piece of word-like text is one token, found by one probe of
+    // the whole-piece table; what that leaves over is compacted and merged by the workgroup.
+    uint32_t w[4] = {0, 0, 0, 0};
     t.tok0 = -1;
-    if (t.parked) {
-        // The first token travels with the count (one coalesced 8-byte record per piece);
-        // only the pieces of two or more tokens, few in word-like text, touch scratch.
-        if (t.alive) t.tok0 = (int)(sh.lds.tiny[wv].S[__builtin_ctz(t.alive)][lane] & 0xFFFFFFu);
-        tiny_store(sh.lds.tiny[wv], t.alive & (t.alive - 1), p.scratch + t.o + 1);
+    if (t.is_tiny) {
+        load_piece_bytes(p, t.o, w);
+        if (t.len <= kWordMax) t.tok0 = find_word<EAGER>(p.table, w, t.len);
     }
+    t.cnt = t.tok0 >= 0 ? 1 : 0;
+    t.others_cnt = 0;
+    t.alive = 0;
+    t.parked = false;
+    const bool left = t.is_tiny && t.tok0 < 0;
+    const uint64_t left_mask = __ballot(left);
+    t.left_slot = left ? wv * kWave + mbcnt(left_mask) : -1;
+    if (left) {
+        sh.lds.left.bytes[t.left_slot] = make_uint4(w[0], w[1], w[2], w[3]);
+        sh.list[t.left_slot] = t.o;
+        sh.cnt_back[t.left_slot] = t.len << 8 | tid;
+    }
+    // (longer pieces are rare in word-like text; with SKIP_LONG they are somebody else's)
+    const bool wave_longer = !SKIP_LONG && __ballot(is_wave || is_long) != 0;
+    if (lane == 0 && (WAVES <= kWavesPerGroup || wv < kWavesPerGroup))
+        sh.left_n[wv] = __builtin_popcountll(left_mask) | (wave_longer ? kAnyLonger : 0);
+    __syncthreads();
+    const bool any_longer = merge_left_over<SRC, WAVES>(p, sh, t, tile_q0, P, keep_in_lds);
 
     if (SKIP_LONG) {
         t.has_piece = t.has_piece && !is_wave && !is_long;     // whoever merges a piece writes its record
         return t;
     }
-    // Everything else is rare in word-like text: one barrier finds out whether the tile has any.
-    if (__syncthreads_count(is_wave || is_long) == 0) return t;
+    if (WAVES > kWavesPerGroup && wv >= kWavesPerGroup) return t;
+    if (!any_longer) return t;
+    __syncthreads();               // the longer pieces' paths reuse the lists and the LDS
     return merge_tile_long_pieces<SRC>(kernel_params(), sh, t, tile_q0, P, is_wave, is_long, bt);
 }
 
@@ -237,11 +358,6 @@ __device__ __forceinline__ TilePiece merge_tile_long_pieces(const EncodeParams &
                                                             int64_t tile_q0, int P, bool is_wave, bool is_long,
                                                             const ByteTile &bt) {
     const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
-    if (!t.parked) {               // the other paths reuse the LDS of the lane-per-piece state
-        tiny_store(sh.lds.tiny[wv], t.alive, p.scratch + t.o);
-        t.parked = true;
-    }
-
     // Wavefront paths.  The tile's wavefronts share these pieces through lists in
     // LDS, so that a wavefront that owns several of them does not become the tail:
     // pieces for the 64-entry columns from the front of the list, the longer ones
@@ -347,7 +463,7 @@ __device__ inline void raw_geometry(EncodeParams &p) {
     if (avg <= kTinyMax) return;
     const int wanted = max(min(p.n_pieces / 4096, (kWave * kTinyMax) / avg), 1);
     const int needed = (p.n_pieces + p.W * tiles_bound - 1) / (p.W * tiles_bound);
-    p.P = min(max(wanted, needed), kWave);
+    p.P = __builtin_amdgcn_readfirstlane(min(max(wanted, needed), kWave));     // (divisions are done in vector registers)
 }
 
 __device__ inline int tiles_of(const EncodeParams &p) {
@@ -357,12 +473,12 @@ __device__ inline int tiles_of(const EncodeParams &p) {
 
 // Several-kernel path, first kernel: tokens and counts of every piece to the
 // workspace, the tile's token total to tile_sum.
-template <int SRC = kFromOffsets, bool SKIP_LONG = false>
+template <int SRC = kFromOffsets, bool SKIP_LONG = false, int WAVES = kWavesPerGroup, bool EAGER = !SKIP_LONG>
 __device__ __forceinline__ void merge_and_count_tile(const EncodeParams &p, TileShared &sh, int *wave_tokens, int tile,
                                                      int n_pieces, int P) {
-    const TilePiece t = merge_tile<SRC, SKIP_LONG>(p, sh, tile, false, n_pieces, P);
-    if (t.has_piece) p.rec[t.q] = make_int2(t.cnt, t.tok0);
-    const int wave_total = __builtin_amdgcn_readlane(wave_scan_inclusive(t.cnt), kWave - 1);
+    const TilePiece t = merge_tile<SRC, SKIP_LONG, WAVES, EAGER>(p, sh, tile, false, n_pieces, P);
+    if (t.has_piece && t.left_slot < 0) p.rec[t.q] = make_int2(t.cnt, t.tok0);
+    const int wave_total = __builtin_amdgcn_readlane(wave_scan_inclusive(t.cnt + t.others_cnt), kWave - 1);
     if (lane_id() == 0) wave_tokens[threadIdx.x / kWave] = wave_total;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -636,14 +752,17 @@ __global__ void __launch_bounds__(kGroupThreads) merge_raw_groups_kernel(EncodeP
     if (tile < n_tiles) merge_and_count_tile<kFromOffsets, true>(p, sh, wave_tokens, tile, p.n_pieces, p.P);
 }
 
-__global__ void __launch_bounds__(kGroupThreads) merge_raw_rest_kernel(EncodeParams p, int first_tile) {
+__global__ void __launch_bounds__(kGroupThreads, 4) merge_raw_rest_kernel(EncodeParams p, int first_tile) {
     __shared__ TileShared sh;
     __shared__ int wave_tokens[kWavesPerGroup];
     raw_geometry(p);
-    const int n_tiles = tiles_of(p);
+    const int n_tiles = __builtin_amdgcn_readfirstlane(tiles_of(p)), n_pieces = p.n_pieces, P = p.P;
     for (int tile = first_tile + blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        if (p.long_sum && threadIdx.x == 0) p.long_sum[tile] = 0;      // nothing of this tile goes to a long-piece workgroup
-        merge_and_count_tile(p, sh, wave_tokens, tile, p.n_pieces, p.P);
+        // (the parameters are read anew for every tile: kept over the loop they cost the common path its registers)
+        const EncodeParams *kp = &kernel_params();
+        asm volatile("" : "+s"(kp));
+        if (kp->long_sum && threadIdx.x == 0) kp->long_sum[tile] = 0;      // nothing of this tile goes to a long-piece workgroup
+        merge_and_count_tile<kFromOffsets, false, 0, false>(*kp, sh, wave_tokens, tile, n_pieces, P);
         __syncthreads();   // the next tile reuses the LDS
     }
 }
@@ -811,10 +930,10 @@ __global__ void __launch_bounds__(kGroupThreads) merge_bytes_kernel(EncodeParams
     // the first 256 pieces: as in every other merge kernel
     const TilePiece t = merge_tile<kFromBytes>(p, sh, 0, false, 0, kWave, bt, q0);
     if (t.has_piece) {
-        p.rec[t.q] = make_int2(t.cnt, t.tok0);
+        if (t.left_slot < 0) p.rec[t.q] = make_int2(t.cnt, t.tok0);
         p.off_out[t.q] = t.o;
     }
-    int wave_total = __builtin_amdgcn_readlane(wave_scan_inclusive(t.cnt), kWave - 1);
+    int wave_total = __builtin_amdgcn_readlane(wave_scan_inclusive(t.cnt + t.others_cnt), kWave - 1);
     // More than 256 pieces start in the tile: fewer than six bytes per piece, so not word-like text (runs of
     // spaces, sequences of a few bytes).  The further ones one at a time by the whole workgroup: slow, and small.
     const EncodeParams &kp = kernel_params();
@@ -856,27 +975,28 @@ __global__ void __launch_bounds__(kGroupThreads) merge_mapped_kernel(EncodeParam
 // to their final place.
 constexpr int kFusedMaxTiles = 256;
 
-__global__ void __launch_bounds__(kGroupThreads) encode_kernel(EncodeParams p, int n_tiles) {
+__global__ void __launch_bounds__(kFusedThreads) encode_kernel(EncodeParams p, int n_tiles) {
     __shared__ TileShared sh;
     __shared__ LookbackTmp lb;
     __shared__ int long_src, long_dst, long_cnt;
     const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
     const int tile = blockIdx.x;
     if (tile == 0 && tid == 0) mark_call(p.status, p.call_id);
+    const int32_t epoch = p.status[kStatusEpochEncode];
 
-    const TilePiece t = merge_tile(p, sh, tile, true, p.n_pieces, p.P);
-    const bool has_piece = t.has_piece, is_tiny = t.is_tiny, parked = t.parked;
+    const TilePiece t = merge_tile<kFromOffsets, false, kFusedWaves>(p, sh, tile, true, p.n_pieces, p.P);
+    if (wv >= kWavesPerGroup) return;          // the helpers are done; barriers wait for the wavefronts that are left
+    const bool has_piece = t.has_piece;
     const int o = t.o, my_cnt = t.cnt;
     const int64_t q = t.q;
-    const uint32_t alive = t.alive;
     const bool is_long = t.long_path;
     const bool is_wave = has_piece && t.len > p.tiny_max && !is_long;
 
     // position of every piece's tokens in the output
     int total;
     const int ex = group_scan_sum_excl(my_cnt, sh.tmp, total);
-    const int base = total_before_tile(p.tile_state, p.status, p.call_id, p.status + kStatusEpochEncode, tile, n_tiles,
-                                       total, lb);
+    const int base = total_before_tile(p.tile_state, p.status, p.call_id, p.status + kStatusEpochEncode, epoch,
+                                       tile, n_tiles, total, lb);
     const int first = base + ex;
     if (has_piece) p.out_offsets[q] = first;
     if (tid == 0 && tile == n_tiles - 1) p.out_offsets[p.n_pieces] = base + total;
@@ -884,11 +1004,27 @@ __global__ void __launch_bounds__(kGroupThreads) encode_kernel(EncodeParams p, i
     const int room = first >= 0 && first < p.n_bytes ? p.n_bytes - first : 0;
     const int n_store = min(my_cnt, room);
 
-    if (!parked) {
-        tiny_store(sh.lds.tiny[wv], is_tiny && n_store == my_cnt ? alive : 0u, p.out_ids + first);
-    } else if (is_tiny) {
-        for (int i = 0; i < n_store; ++i) p.out_ids[first + i] = p.scratch[o + i];
+    if (t.tok0 >= 0 && n_store == 1) p.out_ids[first] = t.tok0;
+    if (t.parked) {
+        if (t.left_slot >= 0)
+            for (int i = 0; i < n_store; ++i) p.out_ids[first + i] = p.scratch[o + i];
+    } else if (t.n_left) {         // whoever merged a left-over piece stores its tokens: the owner says where
+        if (t.left_slot >= 0) sh.list[t.left_slot] = n_store == my_cnt ? first : -1;
+        __syncthreads();
+        int n[kWavesPerGroup];
+        for (int w = 0; w < kWavesPerGroup; ++w) n[w] = __builtin_amdgcn_readfirstlane(sh.left_n[w]);
+        if (t.n_left <= row_pieces(kFusedWaves)) {
+            for (int i = tid; i < t.n_left * kTinyMax; i += kGroupThreads) {
+                const int slot = left_slot_of(i / kTinyMax, n), j = i % kTinyMax;
+                const int dst = sh.list[slot];
+                if (dst >= 0 && j < sh.cnt_back[slot]) p.out_ids[dst + j] = (int)sh.lds.left.tok[i / kTinyMax][j];
+            }
+        } else {
+            const int dst = tid < t.n_left ? sh.list[left_slot_of(tid, n)] : -1;
+            tiny_store(sh.lds.tiny[wv], dst >= 0 ? t.alive : 0u, p.out_ids + dst);
+        }
     }
+    if (!t.parked) return;         // no longer pieces in this tile
     for (uint64_t m = __ballot(is_wave); m;) {             // tokens of the wavefront paths: from the workspace
         const int w = __builtin_ctzll(m);
         m &= m - 1;
@@ -926,6 +1062,7 @@ __device__ __forceinline__ bool has_long_sums(const EncodeParams &p) {
 __global__ void __launch_bounds__(kScanThreads) scan_tiles_kernel(EncodeParams p, int64_t n_tiles) {
     __shared__ LookbackTmp lb;
     __shared__ int wave_sum[kScanThreads / kWave];
+    const int32_t epoch = p.status[kStatusEpochEncode];
     const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
     if (p.n_pieces_dev) {          // raw path: only the tiles that exist; small grids add up by themselves in emit_kernel
         raw_geometry(p);
@@ -970,7 +1107,7 @@ __global__ void __launch_bounds__(kScanThreads) scan_tiles_kernel(EncodeParams p
     int before = 0;
     if (n_groups > 1)
         before = total_before_tile<1, kGroupThreads, kScanThreads / kWave>(
-            p.tile_state, p.status, p.call_id, p.status + kStatusEpochEncode, group, n_groups, total, lb);
+            p.tile_state, p.status, p.call_id, p.status + kStatusEpochEncode, epoch, group, n_groups, total, lb);
     ex += before;
 #pragma unroll
     for (int j = 0; j < kPerThread; ++j) {
@@ -1719,16 +1856,16 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
         run.run("emit_bytes_kernel", 3, emit_bytes_kernel, nt, kGroupThreads, p, (int)nt, self_scan);
         if (ev) { (void)hipEventRecord(ev[n_ev++], s); (void)hipEventRecord(ev[n_ev++], s); }
     } else if (fused) {
-        run.run("encode_kernel", 0, encode_kernel, n_tiles, kGroupThreads, p, (int)n_tiles);
+        run.run("encode_kernel", 0, encode_kernel, n_tiles, kFusedThreads, p, (int)n_tiles);
         if (ev) { (void)hipEventRecord(ev[1], s); (void)hipEventRecord(ev[2], s); (void)hipEventRecord(ev[3], s); }
     } else {
         // Raw path: n_tiles only bounds the tile count.  A capped grid strides over the
         // tiles that exist (at least one workgroup, which also handles "no piece at all").
         const int64_t grid = raw ? std::min<int64_t>(std::max<int64_t>(n_tiles, 1), kRawMaxGrid) : n_tiles;
         if (raw) {
-            // one tile per workgroup for as many tiles as are likely to exist (an eighth of
-            // the capacity-sized bound, at least kRawMaxGrid), a strided kernel for the rest
-            const int64_t direct = std::min<int64_t>(std::max<int64_t>(n_tiles, 1), std::max<int64_t>(kRawMaxGrid, n_tiles / 8));
+            // one tile per workgroup for as many tiles as are likely to exist (a fifth of
+            // the capacity-sized bound: pieces of five bytes, at least kRawMaxGrid), a strided kernel for the rest
+            const int64_t direct = std::min<int64_t>(std::max<int64_t>(n_tiles, 1), std::max<int64_t>(kRawMaxGrid, n_tiles / 5));
             // (the long-piece workgroups need tiles of 256 pieces: only if the caller fixed that, and from
             // as many tiles on as on the other path, or when asked for)
             if (!raw_auto_P && p.P == kWave && o.long_groups >= 0 && (o.long_groups > 0 || direct >= kLongGroupsMinTiles)) {

@@ -84,11 +84,14 @@ struct LookbackTmp {
 // together: a state word of another workgroup takes 1-2 us to arrive, so deep
 // grids (where the nearest published prefix is a thousand tiles back) want few,
 // wide rounds.
+//
+// epoch_value: *epoch as the kernel read it at its start, where the read costs nothing (read here it is
+// one more cold round trip, about 0.3 us, in front of the publication that the next tiles wait for).
 template <int LOOK = 1, int WINDOW = kGroupThreads, int WAVES = kWavesPerGroup>
 __device__ inline int total_before_tile(unsigned long long *state, int32_t *status, int32_t call_id, int32_t *epoch,
-                                        int tile, int n_tiles, int total, LookbackTmp &lb) {
+                                        int32_t epoch_value, int tile, int n_tiles, int total, LookbackTmp &lb) {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const uint32_t launch = (uint32_t)__builtin_amdgcn_readfirstlane(*epoch);
+    const uint32_t launch = (uint32_t)__builtin_amdgcn_readfirstlane(epoch_value);
     uint32_t tag = ((uint32_t)call_id + launch) & 0x3FFFFFFFu;
     if (tag == 0) tag = 1;
     if (tid == 0)

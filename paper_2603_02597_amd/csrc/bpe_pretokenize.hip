@@ -76,6 +76,7 @@ __global__ void __launch_bounds__(kGroupThreads) pretokenize_kernel(PretokParams
     const int64_t tile_v0 = (int64_t)tile * kTileBytes;
     const uint4 *src = (const uint4 *)(p.bytes - p.mis);
     if (tile == 0 && tid == 0) mark_call(p.status, p.call_id);
+    const int32_t epoch = p.status[kStatusEpochPretokenize];
 
     // Loads run kDepth KiB ahead of the arithmetic.  A 16-byte group that holds at
     // least one byte of the input lies in the same page as that byte, so reading all
@@ -168,7 +169,7 @@ __global__ void __launch_bounds__(kGroupThreads) pretokenize_kernel(PretokParams
         total += wave_total[w];
     }
     // the same value in every lane; telling the compiler keeps the output pointer of the tile scalar
-    const int base = __builtin_amdgcn_readfirstlane(total_before_tile<1, (STAGED ? kStagedWindow : kGroupThreads)>(p.tile_state, p.status, p.call_id, p.status + kStatusEpochPretokenize, tile, p.n_tiles, total, lb));
+    const int base = __builtin_amdgcn_readfirstlane(total_before_tile<1, (STAGED ? kStagedWindow : kGroupThreads)>(p.tile_state, p.status, p.call_id, p.status + kStatusEpochPretokenize, epoch, tile, p.n_tiles, total, lb));
 
     // The indices of the start bytes, densely, in order.  The tile's pieces are
     // addressed from its own first slot, so that a 32-bit offset is enough.

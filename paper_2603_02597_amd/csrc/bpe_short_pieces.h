@@ -25,35 +25,109 @@ struct alignas(16) TinyState {
     uint32_t R[kTinyMax][kWave];
 };
 
-// Merges the lane's piece bytes[o .. o + len) if `mine`; len <= kTinyMax.  Returns
+// The 16 bytes from bytes[o] on as 4 dwords: aligned loads, then a byte-granular funnel shift.
+// Offsets are counted from the aligned address at or below p.bytes, in 32 bits, so that
+// the loads take their base from scalar registers; a load that would start behind the
+// input is moved back onto its last dword instead of being branched around (what it
+// returns lies behind the piece and is never looked at).
+__device__ __forceinline__ void load_piece_bytes(const EncodeParams &p, int o, uint32_t (&w)[4]) {
+    const uint32_t mis = (uint32_t)((uintptr_t)p.bytes & 3);
+    const uint8_t *base = p.bytes - mis;
+    const uint32_t pos = (uint32_t)o + mis;
+    const uint32_t first = pos & ~3u, last = ((uint32_t)p.n_bytes + mis - 1u) & ~3u;
+    uint32_t raw[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) raw[k] = *(const uint32_t *)(base + min(first + 4u * (uint32_t)k, last));
+    const uint32_t sh = (pos & 3u) * 8u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        w[k] = (uint32_t)((((uint64_t)raw[k + 1] << 32) | raw[k]) >> sh);
+}
+
+// The token that the piece of `len` bytes in w becomes, or -1 if the whole-piece table does not
+// hold it (1 <= len <= kWordMax; w may hold anything behind the piece).  EAGER: both slots at
+// once, one round trip (grids the chip holds at a time: latency counts); otherwise the second
+// slot only where the first says that a word of its own sits in a second slot (deep grids: two
+// probes in three are spared, and the gathers are what the texture path is busy with).
+template <bool EAGER>
+__device__ __forceinline__ int find_word(const TableView &t, const uint32_t (&w)[4], int len) {
+    const uint32_t bits = 8u * (uint32_t)len;
+    uint64_t lo = ((uint64_t)w[1] << 32) | w[0];
+    lo = bits >= 64 ? lo : lo & ((1ull << bits) - 1);
+    const uint32_t w0 = (uint32_t)lo, w1 = (uint32_t)(lo >> 32);
+    const uint32_t w2 = bits >= 96 ? w[2] : bits > 64 ? w[2] & ((1u << (bits & 31u)) - 1u) : 0u;
+    const WordHash h = word_hash(w0, w1, w2);
+    auto slot = [&](uint32_t i) { return *(const uint4 *)((const char *)t.words + (i << 4)); };
+    auto hit = [&](const uint4 &s) {
+        return s.x == w0 && s.y == w1 && s.z == w2 && (s.w & kWordLenMask) == (uint32_t)len;
+    };
+    const uint4 a = slot(word_slot1(h, t.word_shift));
+    if (EAGER) {
+        const uint4 b = slot(word_slot2(h, t.word_shift));
+        return hit(a) ? (int)(a.w >> 8) : hit(b) ? (int)(b.w >> 8) : -1;
+    }
+    int id = hit(a) ? (int)(a.w >> 8) : -1;
+    if (id < 0 && (a.w & kWordMore)) {
+        const uint4 b = slot(word_slot2(h, t.word_shift));
+        if (hit(b)) id = (int)(b.w >> 8);
+    }
+    return id;
+}
+
+// ---------------------------------------------------------------------------
+// One piece per row of 16 lanes, one symbol per lane, in registers: the pieces that
+// find_word leaves over are a few per tile, too few to fill a wavefront of the lane-per-piece
+// path below, and a step is shorter here (about 40 instructions and one table round trip: the
+// minimum over a row is four data-parallel moves, the symbols behind a merge move down by one
+// lane, and the two new pairs, at lanes k - 1 and k, are one lookup of (own symbol, next lane's)
+// each).  sym: lane j < n of the row holds symbol j as id | flags << 24, bytes with both flags
+// set; n <= 16, 0 for a row without a piece.  Returns the number of tokens, in the row's first
+// lanes.  Every lane of the wavefront must call it.
+__device__ __forceinline__ uint32_t from_next_lane(uint32_t v, uint32_t last) {    // within a row of 16
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)v, 0x101, 0xF, 0xF, false);   // row_shl:1
+}
+__device__ __forceinline__ uint32_t row_min_u32(uint32_t v) {                      // to every lane of the row
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x128, 0xF, 0xF, false));   // row_ror:8
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x124, 0xF, 0xF, false));   // row_ror:4
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x122, 0xF, 0xF, false));   // row_ror:2
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x121, 0xF, 0xF, false));   // row_ror:1
+    return v;
+}
+__device__ __forceinline__ int row_merge(const EncodeParams &p, uint32_t &sym, int n) {
+    const int j = lane_id() & 15;
+    uint32_t next = from_next_lane(sym, 0u);
+    uint32_t r = kNoRank;                            // rank word of the pair that starts at this lane
+    if (j + 1 < n) r = p.table.byte_pairs[((sym & 0xFFu) << 8) | (next & 0xFFu)];
+    for (;;) {
+        const uint32_t best = row_min_u32(r | (uint32_t)j);          // kNoRank stays kNoRank
+        const bool act = best != kNoRank;
+        if (!__ballot(act)) break;
+        const int k = act ? (int)(best & 15u) : 16;                  // 16: nothing in this row
+        const uint32_t merged = (act ? merged_id_of(p.table, best >> 6) : 0u) | ((best >> 4) & 3u) << 24;
+        const uint32_t sym_up = from_next_lane(sym, 0u), r_up = from_next_lane(r, kNoRank);
+        sym = j == k ? merged : j > k ? sym_up : sym;
+        r = j == k || j + 1 == k ? kNoRank : j > k ? r_up : r;
+        n -= act ? 1 : 0;
+        next = from_next_lane(sym, 0u);
+        // a pair needs a lookup only if its symbols can be the left / right part of some rule
+        const bool need = (j == k || j + 1 == k) && j + 1 < n && ((sym >> 24) & 1u) && ((next >> 25) & 1u);
+        if (need) {
+            const SlotProbe q = slot_probe(p.table, sym, next);      // (flag bits: see slot_probe)
+            const uint2 s1 = slot_lower(p.table, q), s2 = slot_upper(p.table, q);
+            r = slot_match(s1, s2, q.rest1, q.rest2);
+        }
+    }
+    return n;
+}
+
+// Merges the lane's piece of len <= kTinyMax bytes, which are w, if `mine`.  Returns
 // the mask of positions that hold the final tokens (they stay in L.S[.][lane]).
-// Loads are batched so that dependent round trips stay few: all bytes of the
-// piece (five aligned dwords), then all byte-pair ranks, then per merge the two
-// neighbour symbols and the two new pairs' slots together.
-__device__ uint32_t tiny_merge(const EncodeParams &p, TinyState &L, int o, int len, bool mine) {
+// Loads are batched so that dependent round trips stay few: all byte-pair ranks,
+// then per merge the two neighbour symbols and the two new pairs' slots together.
+__device__ uint32_t tiny_merge(const EncodeParams &p, TinyState &L, const uint32_t (&w)[4], int len, bool mine) {
     const int lane = lane_id();
     const int my_len = mine ? len : 0;
     if (!__ballot(my_len > 0)) return 0u;
-
-    // the piece's bytes as 4 dwords: aligned loads, then a byte-granular funnel shift.
-    // Offsets are counted from the aligned address at or below p.bytes, in 32 bits, so that
-    // the loads take their base from scalar registers; a load that would start behind the
-    // input is moved back onto its last dword instead of being branched around (what it
-    // returns lies behind the piece and is never looked at).
-    uint32_t w[4] = {0, 0, 0, 0};
-    if (my_len) {
-        const uint32_t mis = (uint32_t)((uintptr_t)p.bytes & 3);
-        const uint8_t *base = p.bytes - mis;
-        const uint32_t pos = (uint32_t)o + mis;
-        const uint32_t first = pos & ~3u, last = ((uint32_t)p.n_bytes + mis - 1u) & ~3u;
-        uint32_t raw[5];
-#pragma unroll
-        for (int k = 0; k < 5; ++k) raw[k] = *(const uint32_t *)(base + min(first + 4u * (uint32_t)k, last));
-        const uint32_t sh = (pos & 3u) * 8u;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            w[k] = (uint32_t)((((uint64_t)raw[k + 1] << 32) | raw[k]) >> sh);
-    }
     uint32_t c[kTinyMax];
 #pragma unroll
     for (int j = 0; j < kTinyMax; ++j) c[j] = (w[j / 4] >> (8 * (j % 4))) & 0xFFu;

@@ -154,8 +154,7 @@ int order_rules(const int32_t *merges, const int32_t *ranks, const int32_t *merg
 }
 
 static int build_image(const int32_t *merges, const int32_t *ranks, const int32_t *merged_ids, int64_t n,
-                       HostImage &img) {
-    RuleOrder ro;
+                       HostImage &img, RuleOrder &ro) {
     const int rc = order_rules(merges, ranks, merged_ids, n, ro);
     if (rc != BPE_OK) return rc;
     const std::vector<std::pair<int64_t, int64_t>> &by_rank = ro.by_rank;
@@ -206,6 +205,121 @@ static int build_image(const int32_t *merges, const int32_t *ranks, const int32_
     return BPE_OK;
 }
 
+// The pair's rank order by the host image, or -1.
+static int64_t image_rank(const HostImage &img, const HashSeed &seed, int index_bits, uint32_t a, uint32_t b) {
+    const int low_bits = 24 - index_bits;
+    const uint64_t key = ((uint64_t)a << 32) | b;
+    const uint64_t p1 = slot_of(mix1(seed, a, b), low_bits, index_bits);
+    if (img.slots[2 * p1] == key) return (int64_t)(img.slots[2 * p1 + 1] & kRankMask);
+    const uint64_t p2 = (uint64_t)img.info.capacity / 2 + slot_of(mix2(seed, a, b), low_bits, index_bits);
+    return img.slots[2 * p2] == key ? (int64_t)(img.slots[2 * p2 + 1] & kRankMask) : -1;
+}
+
+// The whole-piece table of the device (see WordHash): every byte, and every merged id whose
+// expansion fits a slot and merges back to that id.  Rank order: what training merged early
+// is frequent, and the first to come gets its first slot, the one a kernel reads first.
+struct WordImage {
+    std::vector<uint32_t> slots;        // 4 words per slot
+    int shift;
+};
+
+static void build_words(const int32_t *merges, const RuleOrder &ro, const HostImage &img, WordImage &out) {
+    struct Word { uint8_t b[kWordMax]; uint8_t len; };
+    const int64_t n = (int64_t)ro.by_rank.size();
+    std::vector<Word> made((size_t)n);                 // expansion by rank order; len 0: too long
+    std::vector<std::pair<Word, uint32_t>> words;      // string, id
+    words.reserve((size_t)n + 256);
+    for (int b = 0; b < 256; ++b) {
+        Word w = {};
+        w.b[0] = (uint8_t)b;
+        w.len = 1;
+        words.push_back({w, (uint32_t)b});
+    }
+    const HashSeed seed = hash_seed(img.info.hash_attempt);
+    const int index_bits = log2_exact(img.info.capacity / 2);
+    for (int64_t k = 0; k < n; ++k) {
+        const int64_t row = ro.by_rank[k].second;
+        Word w = {};
+        bool fits = true;
+        for (int s = 0; s < 2 && fits; ++s) {
+            const int32_t part = merges[2 * row + s];
+            const int32_t at = ro.made_at[part];
+            Word byte = {};
+            byte.b[0] = (uint8_t)part;
+            byte.len = 1;
+            const Word &src = at < 0 ? byte : made[(size_t)at];
+            fits = src.len > 0 && w.len + src.len <= kWordMax;
+            if (!fits) break;
+            memcpy(w.b + w.len, src.b, src.len);
+            w.len = (uint8_t)(w.len + src.len);
+        }
+        if (!fits) { made[(size_t)k] = Word{}; continue; }
+        made[(size_t)k] = w;
+        // the merge loop on these bytes: lowest rank first, left-most on ties
+        uint32_t sym[kWordMax];
+        int64_t rank[kWordMax];
+        int len = w.len;
+        for (int i = 0; i < len; ++i) sym[i] = w.b[i];
+        for (int i = 0; i + 1 < len; ++i) rank[i] = image_rank(img, seed, index_bits, sym[i], sym[i + 1]);
+        while (len > 1) {
+            int at = -1;
+            for (int i = 0; i + 1 < len; ++i)
+                if (rank[i] >= 0 && (at < 0 || rank[i] < rank[at])) at = i;
+            if (at < 0) break;
+            sym[at] = (uint32_t)img.merged_of[(size_t)rank[at]];
+            --len;
+            for (int i = at + 1; i < len; ++i) { sym[i] = sym[i + 1]; rank[i] = rank[i + 1]; }
+            if (at + 1 < len) rank[at] = image_rank(img, seed, index_bits, sym[at], sym[at + 1]);
+            if (at > 0) rank[at - 1] = image_rank(img, seed, index_bits, sym[at - 1], sym[at]);
+        }
+        // (two rules may spell the same bytes; the one that the loop arrives at is the token)
+        if (len == 1 && sym[0] == (uint32_t)ro.merged_row[row]) words.push_back({w, sym[0]});
+    }
+    int bits = 10;
+    while ((1ll << bits) < 2 * (int64_t)words.size()) ++bits;      // at most half full
+    out.shift = 32 - bits;
+    out.slots.assign((size_t)4 << bits, 0u);
+    std::vector<int32_t> at((size_t)1 << bits, -1);                // which word a slot holds
+    auto hash_of = [&](int32_t i) {
+        uint32_t d[3];
+        memcpy(d, words[(size_t)i].first.b, kWordMax);
+        return word_hash(d[0], d[1], d[2]);
+    };
+    auto second_of = [&](int32_t i, uint32_t slot) {               // the other slot of word i
+        const WordHash h = hash_of(i);
+        const uint32_t s1 = word_slot1(h, out.shift);
+        return slot == s1 ? word_slot2(h, out.shift) : s1;
+    };
+    for (int32_t i = 0; i < (int32_t)words.size(); ++i) {
+        const WordHash h = hash_of(i);
+        const uint32_t s1 = word_slot1(h, out.shift), s2 = word_slot2(h, out.shift);
+        if (at[s1] < 0) { at[s1] = i; continue; }
+        if (at[s2] < 0) { at[s2] = i; continue; }
+        // move words along from the second slot on; if none of a bounded number of moves ends at
+        // an empty slot, put everything back and leave this word out
+        std::vector<uint32_t> path{s2};
+        while (path.size() < 64) {
+            const uint32_t next = second_of(at[path.back()], path.back());
+            bool seen = false;
+            for (uint32_t s : path) seen |= s == next;
+            if (seen) { path.clear(); break; }
+            path.push_back(next);
+            if (at[next] < 0) break;
+        }
+        if (path.size() < 2 || at[path.back()] >= 0) continue;
+        for (size_t k = path.size() - 1; k > 0; --k) at[path[k]] = at[path[k - 1]];
+        at[s2] = i;
+    }
+    for (size_t s = 0; s < at.size(); ++s) {
+        if (at[s] < 0) continue;
+        const Word &w = words[(size_t)at[s]].first;
+        memcpy(&out.slots[4 * s], w.b, kWordMax);
+        out.slots[4 * s + 3] |= words[(size_t)at[s]].second << 8 | w.len;
+        const uint32_t s1 = word_slot1(hash_of(at[s]), out.shift);
+        if (s1 != s) out.slots[4 * (size_t)s1 + 3] |= kWordMore;
+    }
+}
+
 }  // namespace bpe
 
 using namespace bpe;
@@ -231,7 +345,8 @@ extern "C" int bpe_table_image_build(const int32_t *merges, const int32_t *ranks
     if (cap < 0) { set_error("n_merges %lld out of range", (long long)n); return BPE_ERR_SIZE; }
     if (capacity_slots != cap) { set_error("capacity_slots must be %lld", (long long)cap); return BPE_ERR_SIZE; }
     HostImage img;
-    int rc = build_image(merges, ranks, merged_ids, n, img);
+    RuleOrder ro;
+    int rc = build_image(merges, ranks, merged_ids, n, img, ro);
     if (rc != BPE_OK) return rc;
     memcpy(slots, img.slots.data(), (size_t)cap * 16);
     if (info) *info = img.info;
@@ -243,7 +358,8 @@ extern "C" int bpe_table_build(const int32_t *merges, const int32_t *ranks, cons
     if (!out_table) { set_error("out_table is NULL"); return BPE_ERR_NULL; }
     *out_table = nullptr;
     HostImage img;
-    int rc = build_image(merges, ranks, merged_ids, n, img);
+    RuleOrder ro;
+    int rc = build_image(merges, ranks, merged_ids, n, img, ro);
     if (rc != BPE_OK) return rc;
     // device slots: 8 bytes each, from the image's {key, value} pairs
     const int64_t half = img.info.capacity / 2;
@@ -261,11 +377,15 @@ extern "C" int bpe_table_build(const int32_t *merges, const int32_t *ranks, cons
         dev_slots[2 * (size_t)i] = rest;
         dev_slots[2 * (size_t)i + 1] = word;
     }
-    const size_t slot_bytes = dev_slots.size() * 4, bp_bytes = img.byte_pairs.size() * 4;
+    WordImage words;
+    build_words(merges, ro, img, words);
+    const size_t word_bytes = words.slots.size() * 4;
+    const size_t slot_bytes = dev_slots.size() * 4 + word_bytes, bp_bytes = img.byte_pairs.size() * 4;
     const size_t arr_bytes = ((img.merged_of.size() * 4 + 255) / 256) * 256;
     const size_t lr_bytes = img.sym_lr.size() * 4;
     std::vector<char> blob(slot_bytes + bp_bytes + 2 * arr_bytes + lr_bytes, 0);
-    memcpy(blob.data(), dev_slots.data(), slot_bytes);
+    memcpy(blob.data(), dev_slots.data(), slot_bytes - word_bytes);
+    memcpy(blob.data() + (slot_bytes - word_bytes), words.slots.data(), word_bytes);
     memcpy(blob.data() + slot_bytes, img.byte_pairs.data(), bp_bytes);
     memcpy(blob.data() + slot_bytes + bp_bytes, img.merged_of.data(), img.merged_of.size() * 4);
     memcpy(blob.data() + slot_bytes + bp_bytes + arr_bytes, img.rank_of.data(), img.rank_of.size() * 4);
@@ -283,6 +403,8 @@ extern "C" int bpe_table_build(const int32_t *merges, const int32_t *ranks, cons
     t->info.device_bytes = (int64_t)blob.size();
     char *d = (char *)t->device_mem;
     t->view.slots = (const uint2 *)d;
+    t->view.words = (const uint4 *)(d + (slot_bytes - word_bytes));
+    t->view.word_shift = words.shift;
     t->view.byte_pairs = (const uint32_t *)(d + slot_bytes);
     t->view.merged_of = (const int32_t *)(d + slot_bytes + bp_bytes);
     t->view.rank_of = (const int32_t *)(d + slot_bytes + bp_bytes + arr_bytes);

@@ -87,16 +87,29 @@ struct LookbackTmp {
 //
 // epoch_value: *epoch as the kernel read it at its start, where the read costs nothing (read here it is
 // one more cold round trip, about 0.3 us, in front of the publication that the next tiles wait for).
-template <int LOOK = 1, int WINDOW = kGroupThreads, int WAVES = kWavesPerGroup>
+//
+// PUBLISHED: the workgroup has called publish_tile_total already, ahead of work that the tiles behind
+// it need not wait for.
+__device__ inline uint32_t lookback_tag(int32_t call_id, uint32_t launch) {
+    const uint32_t tag = ((uint32_t)call_id + launch) & 0x3FFFFFFFu;
+    return tag == 0 ? 1 : tag;
+}
+
+// By one thread.
+__device__ inline void publish_tile_total(unsigned long long *state, int32_t call_id, int32_t epoch_value, int tile, int total) {
+    __hip_atomic_store(&state[tile],
+                       state_word(lookback_tag(call_id, (uint32_t)epoch_value), tile == 0 ? kFlagPrefix : kFlagAggregate,
+                                  (uint32_t)total),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // the word is the whole message: no release needed
+}
+
+template <int LOOK = 1, int WINDOW = kGroupThreads, int WAVES = kWavesPerGroup, bool PUBLISHED = false>
 __device__ inline int total_before_tile(unsigned long long *state, int32_t *status, int32_t call_id, int32_t *epoch,
                                         int32_t epoch_value, int tile, int n_tiles, int total, LookbackTmp &lb) {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const uint32_t launch = (uint32_t)__builtin_amdgcn_readfirstlane(epoch_value);
-    uint32_t tag = ((uint32_t)call_id + launch) & 0x3FFFFFFFu;
-    if (tag == 0) tag = 1;
-    if (tid == 0)
-        __hip_atomic_store(&state[tile], state_word(tag, tile == 0 ? kFlagPrefix : kFlagAggregate, (uint32_t)total),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // the word is the whole message: no release needed
+    const uint32_t tag = lookback_tag(call_id, launch);
+    if (!PUBLISHED && tid == 0) publish_tile_total(state, call_id, (int32_t)launch, tile, total);
     if (tile == 0) {
         if (n_tiles == 1 && tid == 0) *epoch = (int32_t)(launch + 1);
         return 0;

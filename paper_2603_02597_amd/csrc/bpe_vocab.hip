@@ -16,10 +16,13 @@
 #include "bpe_common.h"
 #include "bpe_lookback.h"
 
+typedef uint32_t Record __attribute__((ext_vector_type(4)));
+
 struct bpe_vocab {
     bpe_vocab_info_t info;
-    void *device_mem;      // one allocation: tok | out_of | int_of | pool
-    const uint2 *tok;      // [n_ids] {offset of the expansion in the pool, its length; 0 = id not in use}
+    void *device_mem;      // one allocation: tok | tok_out | out_of | int_of | pool
+    const Record *tok;      // [n_ids] by internal id: see token_record
+    const Record *tok_out;  // [n_out] by output id, or nullptr
     const int32_t *out_of, *int_of;
     const uint8_t *pool;
     int32_t n_out;
@@ -34,11 +37,18 @@ constexpr int kStageBytes = 16384;            // a tile whose bytes fit is assem
 constexpr int64_t kMaxTokenBytes = 1 << 20;   // longest expansion a vocabulary may hold
 constexpr int64_t kMaxPoolBytes = 1ll << 30;
 
+// What a token stands for, as one 16-byte word: x = length in bytes (0 = id not in use); the bytes
+// themselves in y, z, w if they are at most kInlineBytes, else y = their offset in the pool (a
+// multiple of 4).  Word-like tokens (up to 12 bytes) are one gather instead of an {offset, length}
+// and, after it, one of the pool per four bytes: a gather of 64 unrelated lines costs the texture
+// path 64 line look-ups whatever its width.  2.1 M tokens (13.5 MB): 24.0 us with the two gathers,
+// 22.5 with the records (and the assembly moved in front of the look-back).
+constexpr uint32_t kInlineBytes = 12;
+
 struct DecodeParams {
-    const uint2 *tok;               // [n_ids] {offset in the pool (a multiple of 4), length (0 = id not in use)}
-    const int32_t *int_of;          // output id -> internal id, or nullptr: ids are internal ids
+    const Record *tok;               // [n_tok] records of the ids as the caller numbers them
     const uint8_t *pool;
-    int32_t n_ids, n_out;
+    int32_t n_tok;
     const int32_t *ids;
     int32_t n_tokens;
     const int32_t *n_tokens_dev;    // or nullptr
@@ -55,16 +65,93 @@ __device__ inline int token_count(const DecodeParams &p) {
     return p.n_tokens_dev ? min(max(__builtin_amdgcn_readfirstlane(*p.n_tokens_dev), 0), p.n_tokens) : p.n_tokens;
 }
 
+// Ids come in and the byte offsets of the tokens go out as 16-byte words
+// (at 4-byte alignment, which is all the caller promises and all the hardware asks for).
+typedef int32_t Int4 __attribute__((ext_vector_type(4), aligned(4)));
+static_assert(kTokPerThread == 4, "a thread's tokens are one Int4");
+
+// The records of the thread's four tokens from t0 on; returns whether one of the ids is unknown.
+__device__ __forceinline__ bool load_records(const DecodeParams &p, int t0, int n, Record (&rec)[kTokPerThread]) {
+    Int4 id;
+    if (t0 + kTokPerThread <= n) {
+        id = *(const Int4 *)(p.ids + t0);
+    } else {
+#pragma unroll
+        for (int j = 0; j < kTokPerThread; ++j) id[j] = t0 + j < n ? p.ids[t0 + j] : -1;
+    }
+    bool bad = false;
+#pragma unroll
+    for (int j = 0; j < kTokPerThread; ++j) {
+        rec[j] = Record{0, 0, 0, 0};
+        if (id[j] >= 0 && id[j] < p.n_tok) rec[j] = p.tok[id[j]];
+        bad |= rec[j].x == 0 && t0 + j < n;        // no token is empty: the id is not in the vocabulary
+    }
+    return bad;
+}
+
+// The bytes of a token at sb, which may have any alignment (LDS stores may, too).
+__device__ __forceinline__ void put_token(const uint32_t *pool_w, uint8_t *sb, const Record &rec) {
+    const uint32_t l = rec.x, w0 = rec.y, w1 = rec.z, w2 = rec.w;
+    if (l <= kInlineBytes) {
+        uint32_t tail = w0, at = l & ~3u;
+        if (l >= 4) { __builtin_memcpy(sb, &w0, 4); tail = w1; }
+        if (l >= 8) { __builtin_memcpy(sb + 4, &w1, 4); tail = w2; }
+        if (l >= 12) __builtin_memcpy(sb + 8, &w2, 4);
+        if (l & 2u) {
+            const uint16_t half = (uint16_t)tail;
+            __builtin_memcpy(sb + at, &half, 2);
+            tail >>= 16;
+            at += 2;
+        }
+        if (l & 1u) sb[at] = (uint8_t)tail;
+    } else {
+        const uint32_t full = l & ~3u;
+        for (uint32_t k = 0; k < full; k += 4) {
+            const uint32_t w = pool_w[(w0 + k) >> 2];
+            __builtin_memcpy(sb + k, &w, 4);
+        }
+        if (l & 3u) {
+            const uint32_t w = pool_w[(w0 + full) >> 2];
+            for (uint32_t q = 0; q < (l & 3u); ++q) sb[full + q] = (uint8_t)(w >> (8 * q));
+        }
+    }
+}
+
+// The n bytes at stage + 1 word to dst: whole aligned words, put together from two words of the
+// stage, and the first and the last one byte by byte.  (stage[0] and the word behind the n bytes
+// exist and hold anything.)
+__device__ __forceinline__ void store_stage(const uint32_t *stage, uint8_t *dst, int n) {
+    const int m = (int)((uintptr_t)dst & 3);       // word d of the output starts at byte 4 d - m
+    const int n_words = (m + n + 3) >> 2;
+    uint32_t *dst_w = (uint32_t *)(dst - m);
+    const uint32_t *src = stage + (m ? 0 : 1);
+    const uint32_t shift = (4 - m) & 3;
+    for (int d = threadIdx.x; d < n_words; d += kGroupThreads) {
+        const uint32_t w = __builtin_amdgcn_alignbyte(src[d + 1], src[d], shift);
+        const int lo = d == 0 ? m : 0, hi = min(4, m + n - 4 * d);
+        if (lo == 0 && hi == 4) {
+            dst_w[d] = w;
+        } else {
+            for (int q = lo; q < hi; ++q) ((uint8_t *)(dst_w + d))[q] = (uint8_t)(w >> (8 * q));
+        }
+    }
+}
+
 // A tile is ROUNDS x 1024 tokens: thread t owns tokens r * 1024 + 4 t .. + 3 of the
 // tile for r = 0 .. ROUNDS - 1.  The bytes before the tile are found once per tile
-// (every tile polls the state words of 256 others, so deep grids want few, large
-// tiles); the bytes go out round by round through the same 16 KiB of LDS.
+// (every tile polls the state words of WINDOW others, so deep grids want few, large
+// tiles).  The tile's bytes are assembled in LDS between the publication of its total
+// and the look-back, while the tiles before it finish theirs; only their alignment in
+// the output is not known by then, and store_stage makes up for it.
 template <int ROUNDS, int WINDOW>
 __global__ void __launch_bounds__(kGroupThreads) decode_kernel(DecodeParams p) {
     constexpr int kTile = ROUNDS * kTileTokens;
+    constexpr int kTileStage = ROUNDS == 1 ? kStageBytes : 2 * kStageBytes;
     __shared__ LookbackTmp lb;
     __shared__ int wave_total[ROUNDS][kWavesPerGroup];
-    __shared__ uint32_t stage[kStageBytes / 4 + 2];
+    __shared__ uint32_t stage[kTileStage / 4 + 3];
+    uint8_t *const staged = (uint8_t *)(stage + 1);
+    const uint32_t *pool_w = (const uint32_t *)p.pool;       // every expansion starts at a multiple of 4
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const int tile = blockIdx.x;
     const int n = token_count(p);
@@ -73,48 +160,60 @@ __global__ void __launch_bounds__(kGroupThreads) decode_kernel(DecodeParams p) {
     if (tile == 0 && tid == 0) mark_call(p.status, p.call_id);
     const int32_t epoch = p.status[kStatusEpochDecode];
 
-    uint32_t len[ROUNDS][kTokPerThread], off[ROUNDS][kTokPerThread];
-    int ex[ROUNDS];                            // bytes of the round before this thread's tokens
-    bool bad = false;
-#pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-        const int t0 = tile * kTile + r * kTileTokens + tid * kTokPerThread;
-        int mine = 0;
-#pragma unroll
-        for (int j = 0; j < kTokPerThread; ++j) {
-            len[r][j] = 0;
-            off[r][j] = 0;
-            if (t0 + j < n) {
-                int id = p.ids[t0 + j];
-                if (p.int_of) id = id >= 0 && id < p.n_out ? p.int_of[id] : -1;
-                if (id >= 0 && id < p.n_ids) { const uint2 t = p.tok[id]; off[r][j] = t.x; len[r][j] = t.y; }
-                bad |= len[r][j] == 0;         // no token is empty: the id is not in the vocabulary
-            }
-            mine += (int)len[r][j];
-        }
-        const int inc = wave_scan_inclusive(mine);
-        if (lane == kWave - 1) wave_total[r][wv] = inc;
-        ex[r] = inc - mine;
-    }
-    if (__ballot(bad) && lane == 0)
-        __hip_atomic_store(&p.status[kStatusBadInput], p.call_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
+    const int first = tile * kTile + tid * kTokPerThread;
+    uint32_t len[ROUNDS][kTokPerThread];
+    int ex[ROUNDS];                            // bytes of the tile before this thread's tokens of a round
     int round_total[ROUNDS], total = 0;
+    bool fits;
+    {
+        Record rec[ROUNDS][kTokPerThread];
+        bool bad = false;
 #pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-        round_total[r] = 0;
+        for (int r = 0; r < ROUNDS; ++r) bad |= load_records(p, first + r * kTileTokens, n, rec[r]);
 #pragma unroll
-        for (int w = 0; w < kWavesPerGroup; ++w) {
-            if (w < wv) ex[r] += wave_total[r][w];
-            round_total[r] += wave_total[r][w];
+        for (int r = 0; r < ROUNDS; ++r) {
+            int mine = 0;
+#pragma unroll
+            for (int j = 0; j < kTokPerThread; ++j) mine += (int)(len[r][j] = rec[r][j].x);
+            const int inc = wave_scan_inclusive(mine);
+            if (lane == kWave - 1) wave_total[r][wv] = inc;
+            ex[r] = inc - mine;
         }
-        total += round_total[r];
+        if (__ballot(bad) && lane == 0)
+            __hip_atomic_store(&p.status[kStatusBadInput], p.call_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            round_total[r] = 0;
+            ex[r] += total;
+#pragma unroll
+            for (int w = 0; w < kWavesPerGroup; ++w) {
+                if (w < wv) ex[r] += wave_total[r][w];
+                round_total[r] += wave_total[r][w];
+            }
+            total += round_total[r];
+        }
+        if (tid == 0) publish_tile_total(p.tile_state, p.call_id, epoch, tile, total);
+        // (a token has at most 2^20 bytes and a round 2^10 tokens: the total of a round cannot wrap,
+        // that of four rounds of nothing but such tokens could)
+        fits = total >= 0 && total <= kTileStage;
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) fits &= round_total[r] <= kTileStage;
+        if (fits) {
+#pragma unroll
+            for (int r = 0; r < ROUNDS; ++r) {
+                int at = ex[r];
+#pragma unroll
+                for (int j = 0; j < kTokPerThread; ++j) {
+                    put_token(pool_w, staged + at, rec[r][j]);
+                    at += (int)len[r][j];
+                }
+            }
+        }
     }
-    // token lengths are at most 2^20 and a tile has at most 2^13 tokens: a tile total
-    // cannot wrap, and the running total is compared against the capacity in 64 bits
     const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane(
-        total_before_tile<1, WINDOW>(p.tile_state, p.status, p.call_id, p.status + kStatusEpochDecode, epoch, tile,
-                                     n_tiles, total, lb));
+        total_before_tile<1, WINDOW, kWavesPerGroup, true>(p.tile_state, p.status, p.call_id, p.status + kStatusEpochDecode,
+                                                           epoch, tile, n_tiles, total, lb));
     const int64_t end = (int64_t)base + (uint32_t)total;
     if ((base > (uint32_t)p.out_capacity || end > p.out_capacity) && tid == 0)
         __hip_atomic_store(&p.status[kStatusOverflow], p.call_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -122,67 +221,69 @@ __global__ void __launch_bounds__(kGroupThreads) decode_kernel(DecodeParams p) {
         if (p.token_byte_offsets) p.token_byte_offsets[n] = (int)end;
         if (p.n_bytes) *p.n_bytes = (int)min(end, (int64_t)p.out_capacity);
     }
-
-    const uint32_t *pool_w = (const uint32_t *)p.pool;       // every expansion starts at a multiple of 4
-    int64_t round_base = base;
+    if (p.token_byte_offsets) {
 #pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-        const int t0 = tile * kTile + r * kTileTokens + tid * kTokPerThread;
-        const int rt = __builtin_amdgcn_readfirstlane(round_total[r]);
-        if (p.token_byte_offsets) {
-            int at = (int)round_base + ex[r];
+        for (int r = 0; r < ROUNDS; ++r) {
+            const int t0 = first + r * kTileTokens;
+            Int4 at;
+            at[0] = (int)base + ex[r];
 #pragma unroll
-            for (int j = 0; j < kTokPerThread; ++j) {
-                if (t0 + j < n) p.token_byte_offsets[t0 + j] = at;
-                at += (int)len[r][j];
+            for (int j = 1; j < kTokPerThread; ++j) at[j] = at[j - 1] + (int)len[r][j - 1];
+            if (t0 + kTokPerThread <= n) {
+                *(Int4 *)(p.token_byte_offsets + t0) = at;
+            } else {
+#pragma unroll
+                for (int j = 0; j < kTokPerThread; ++j)
+                    if (t0 + j < n) p.token_byte_offsets[t0 + j] = at[j];
             }
         }
-        if (round_base + rt <= p.out_capacity && rt <= kStageBytes) {
-            // Assemble in LDS at the same offset from a 4-byte boundary as in the output,
-            // then store whole aligned words (the first and last one byte by byte).
-            uint8_t *dst = p.out + round_base;
-            const int m = (int)((uintptr_t)dst & 3);
-            uint8_t *sb = (uint8_t *)stage;
-            int at = m + ex[r];
+    }
+
+    if (fits && end <= p.out_capacity) {
+        __syncthreads();                       // (tile 0 has passed no barrier since the stage was written)
+        store_stage(stage, p.out + base, total);
+        return;
+    }
+    // Longer tokens than the stage holds, or an output that is too small: round by round, through
+    // the stage if a round fits both.  The records are read again: kept, they would cost the common
+    // path its registers.
+    int64_t round_base = base;
+    for (int r = 0; r < ROUNDS; ++r) {
+        Record rec[kTokPerThread];
+        (void)load_records(p, first + r * kTileTokens, n, rec);
+        int before = 0, rt = 0;                // as ex[r] and round_total[r], which are indexed by constants only
+        {
+            int mine = 0;
+#pragma unroll
+            for (int j = 0; j < kTokPerThread; ++j) mine += (int)rec[j].x;
+            before = wave_scan_inclusive(mine) - mine;
+            for (int w = 0; w < kWavesPerGroup; ++w) {
+                if (w < wv) before += wave_total[r][w];
+                rt += wave_total[r][w];
+            }
+        }
+        if (round_base + (uint32_t)rt <= p.out_capacity && (uint32_t)rt <= (uint32_t)kStageBytes) {
+            __syncthreads();                   // the stage is free
+            int at = before;
 #pragma unroll
             for (int j = 0; j < kTokPerThread; ++j) {
-                // whole words first (the compiler picks the widest LDS store the target
-                // allows at an unaligned address), then the last one to three bytes
-                const uint32_t l = len[r][j], o = off[r][j], full = l & ~3u;
-                for (uint32_t k = 0; k < full; k += 4) {
-                    const uint32_t w = pool_w[(o + k) >> 2];
-                    __builtin_memcpy(sb + at + k, &w, 4);
-                }
-                if (l & 3u) {
-                    const uint32_t w = pool_w[(o + full) >> 2];
-                    for (uint32_t q = 0; q < (l & 3u); ++q) sb[at + full + q] = (uint8_t)(w >> (8 * q));
-                }
-                at += (int)l;
+                put_token(pool_w, staged + at, rec[j]);
+                at += (int)rec[j].x;
             }
             __syncthreads();
-            const int n_words = (m + rt + 3) >> 2;
-            uint32_t *dst_w = (uint32_t *)(dst - m);
-            for (int d = tid; d < n_words; d += kGroupThreads) {
-                const uint32_t w = stage[d];
-                const int lo = d == 0 ? m : 0, hi = min(4, m + rt - 4 * d);
-                if (lo == 0 && hi == 4) {
-                    dst_w[d] = w;
-                } else {
-                    for (int q = lo; q < hi; ++q) ((uint8_t *)(dst_w + d))[q] = (uint8_t)(w >> (8 * q));
-                }
-            }
-            if (r + 1 < ROUNDS) __syncthreads();             // the next round reuses the stage
+            store_stage(stage, p.out + round_base, rt);
         } else {
-            // Long tokens (or an output that is too small): bytes straight to the output,
-            // a wavefront sharing every token of more than 64 bytes.
-            int64_t at = round_base + ex[r];
+            // bytes straight to the output, a wavefront sharing every token of more than 64 bytes
+            int64_t at = round_base + before;
 #pragma unroll
             for (int j = 0; j < kTokPerThread; ++j) {
-                const uint32_t l = len[r][j], o = off[r][j];
+                const uint32_t l = rec[j].x, o = rec[j].y, w1 = rec[j].z, w2 = rec[j].w;
                 const bool is_long = l > 64;
                 if (!is_long) {
-                    for (uint32_t k = 0; k < l; ++k)
-                        if (at + k < p.out_capacity) p.out[at + k] = p.pool[o + k];
+                    for (uint32_t k = 0; k < l; ++k) {
+                        const uint32_t w = l > kInlineBytes ? pool_w[(o + k) >> 2] : k < 4 ? o : k < 8 ? w1 : w2;
+                        if (at + k < p.out_capacity) p.out[at + k] = (uint8_t)(w >> (8 * (k & 3)));
+                    }
                 }
                 for (uint64_t lm = __ballot(is_long); lm;) {
                     const int src_lane = __builtin_ctzll(lm);
@@ -197,7 +298,7 @@ __global__ void __launch_bounds__(kGroupThreads) decode_kernel(DecodeParams p) {
                 at += l;
             }
         }
-        round_base += rt;
+        round_base += (uint32_t)rt;
     }
 }
 
@@ -280,14 +381,22 @@ extern "C" int bpe_vocab_build(const int32_t *merges, const int32_t *ranks, cons
             out_of[id] = o;
         }
     }
-    std::vector<uint32_t> tok((size_t)(2 * n_ids));
-    for (int64_t id = 0; id < n_ids; ++id) { tok[2 * id] = tok_off[id]; tok[2 * id + 1] = tok_len[id]; }
-    const int64_t b_tok = 0, b_outof = b_tok + align256v(8 * n_ids),
+    auto token_record = [&](int64_t id) {
+        Record t = Record{tok_len[id], 0, 0, 0};
+        if (t.x > kInlineBytes) t.y = tok_off[id];
+        else memcpy((char *)&t + 4, pool.data() + tok_off[id], t.x);
+        return t;
+    };
+    const int64_t b_tok = 0, b_tokout = b_tok + align256v(16 * n_ids),
+                  b_outof = b_tokout + align256v(16 * (int64_t)int_of.size()),
                   b_intof = b_outof + align256v(4 * (int64_t)out_of.size()),
                   b_pool = b_intof + align256v(4 * (int64_t)int_of.size()),
                   b_total = b_pool + align256v((int64_t)pool.size());
     std::vector<char> blob((size_t)b_total, 0);
-    memcpy(blob.data() + b_tok, tok.data(), tok.size() * 4);
+    Record *tok = (Record *)(blob.data() + b_tok), *tok_out = (Record *)(blob.data() + b_tokout);
+    for (int64_t id = 0; id < n_ids; ++id) tok[id] = token_record(id);
+    for (size_t o = 0; o < int_of.size(); ++o)
+        if (int_of[o] >= 0) tok_out[o] = token_record(int_of[o]);
     if (!out_of.empty()) memcpy(blob.data() + b_outof, out_of.data(), out_of.size() * 4);
     if (!int_of.empty()) memcpy(blob.data() + b_intof, int_of.data(), int_of.size() * 4);
     memcpy(blob.data() + b_pool, pool.data(), pool.size());
@@ -301,7 +410,8 @@ extern "C" int bpe_vocab_build(const int32_t *merges, const int32_t *ranks, cons
     e = hipMemcpy(v->device_mem, blob.data(), blob.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) { (void)hipFree(v->device_mem); delete v; return hip_fail(e, "hipMemcpy(vocab)"); }
     char *d = (char *)v->device_mem;
-    v->tok = (const uint2 *)(d + b_tok);
+    v->tok = (const Record *)(d + b_tok);
+    v->tok_out = int_of.empty() ? nullptr : (const Record *)(d + b_tokout);
     v->out_of = out_of.empty() ? nullptr : (const int32_t *)(d + b_outof);
     v->int_of = int_of.empty() ? nullptr : (const int32_t *)(d + b_intof);
     v->pool = (const uint8_t *)(d + b_pool);
@@ -373,11 +483,9 @@ extern "C" int bpe_decode(const bpe_vocab *v, const int32_t *ids, int64_t n_toke
     const int dev_rc = check_device(v->device, "the vocabulary");
     if (dev_rc != BPE_OK) return dev_rc;
     DecodeParams p = {};
-    p.tok = v->tok;
-    p.int_of = ids_are_output_ids ? v->int_of : nullptr;
+    p.tok = ids_are_output_ids ? v->tok_out : v->tok;
+    p.n_tok = ids_are_output_ids ? v->n_out : (int32_t)v->info.n_ids;
     p.pool = v->pool;
-    p.n_ids = (int32_t)v->info.n_ids;
-    p.n_out = v->n_out;
     p.ids = ids;
     p.n_tokens = (int32_t)n_tokens;
     p.n_tokens_dev = n_tokens_device;

@@ -1,0 +1,46 @@
+"""The decoder's token records at the edges of their inline form (tokens of up to 12 bytes live in
+the record, longer ones in the pool) and of a tile's stage, byte for byte against the CPU oracle."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+TEXT = bytes(range(100, 124))                 # token 256 + k is its first k + 2 bytes
+MERGES = [(TEXT[0] if k == 0 else 255 + k, TEXT[k + 1]) for k in range(len(TEXT) - 1)]
+
+
+# sizes: one thread's tokens and their edges, one round and two rounds per tile; lengths: around the
+# words of a record, around the inline limit, and a mean of 20 bytes (a tile of 1024 exceeds the stage)
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 1023, 1025, 4099, 512 * 1024 + 3])
+@pytest.mark.parametrize("lo,hi", [(1, 5), (7, 9), (11, 13), (1, 24), (18, 22)])
+def test_token_lengths(oracle_mod, n, lo, hi):
+    import torch
+    import paper_2603_02597_amd as B
+    rng = np.random.default_rng(n * 100 + lo)
+    length = rng.integers(lo, hi + 1, n)
+    ids = np.where(length == 1, TEXT[0], 254 + length).astype(np.int32)
+    table = oracle_mod.Table(MERGES)
+    want, want_off = oracle_mod.decode(table, ids), oracle_mod.token_byte_offsets(table, ids)
+    out_ids = (rng.permutation(256 + len(MERGES)) + 50).astype(np.int32)
+    vocab = B.Vocab(MERGES, output_ids=out_ids)
+    print(f"[case] {n} tokens of {lo}..{hi} bytes", flush=True)
+    for renumber in (False, True):
+        src = torch.empty(n + 4, dtype=torch.int32, device="cuda")
+        shift = n % 4                          # ids, offsets and bytes at every alignment a caller may have
+        d_ids = src[shift:shift + n]
+        d_ids.copy_(torch.from_numpy(out_ids[ids] if renumber else ids))
+        for cap in (want.size, want.size // 2):
+            buf = torch.full((want.size + 16,), 0xEE, dtype=torch.uint8, device="cuda")
+            tbo = torch.full((n + 8,), -7, dtype=torch.int32, device="cuda")
+            nb = torch.zeros(1, dtype=torch.int32, device="cuda")
+            ws = torch.empty(B.bpe_decode_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+            B.bpe_decode(vocab, d_ids, buf[shift:shift + cap], ws, tbo[shift:shift + n + 1], nb, None, renumber)
+            assert B.bpe_encode_status(ws) == (0 if cap == want.size else -2)
+            assert int(nb.item()) == cap
+            got, off = buf.cpu().numpy(), tbo.cpu().numpy()
+            if cap == want.size:
+                assert np.array_equal(got[shift:shift + cap], want)
+            assert (got[:shift] == 0xEE).all() and (got[shift + cap:] == 0xEE).all()
+            assert np.array_equal(off[shift:shift + n + 1], want_off)
+            assert (off[:shift] == -7).all() and (off[shift + n + 1:] == -7).all()
+    vocab.free()

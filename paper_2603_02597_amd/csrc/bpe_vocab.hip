@@ -146,7 +146,9 @@ __device__ __forceinline__ void store_stage(const uint32_t *stage, uint8_t *dst,
 template <int ROUNDS, int WINDOW>
 __global__ void __launch_bounds__(kGroupThreads) decode_kernel(DecodeParams p) {
     constexpr int kTile = ROUNDS * kTileTokens;
-    constexpr int kTileStage = ROUNDS == 1 ? kStageBytes : 2 * kStageBytes;
+    // Two rounds: 12 bytes per token, and six workgroups per compute unit.  (With 32 KiB it is four, 1,024 on
+    // the chip, and the 1,031 tiles of 2.1 M tokens run a second, nearly empty time: 22.6 against 19.5 us.)
+    constexpr int kTileStage = ROUNDS == 1 ? kStageBytes : ROUNDS == 2 ? 24576 : 2 * kStageBytes;
     __shared__ LookbackTmp lb;
     __shared__ int wave_total[ROUNDS][kWavesPerGroup];
     __shared__ uint32_t stage[kTileStage / 4 + 3];
@@ -500,7 +502,9 @@ extern "C" int bpe_decode(const bpe_vocab *v, const int32_t *ids, int64_t n_toke
     // another workgroup is an uncached read), but the registers of a round cost
     // occupancy: 40 M tokens take 643 us with (1 round, 256 tiles looked at per round),
     // 558 with (1, 32), 434 with (2, 32), 393 with (4, 32), 519 with (8, 256: 224 VGPRs);
-    // 2.1 M tokens take 33 us with (1, 256), 25 with (2, 64), 29 with (4, 32).
+    // 2.1 M tokens take 33 us with (1, 256), 25 with (2, 64), 29 with (4, 32).  (Measured with two gathers
+    // per token; since then 2.1 M tokens take 19.5 us with (2, 64), 19.5 with two and 21.7 with four tiles
+    // of 256 threads' window each, 21.5 with (4, 256).)
     const dim3 block(kGroupThreads);
     auto tiles = [&](int rounds) { return (unsigned)std::max<int64_t>((n_tokens + rounds * kTileTokens - 1) / (rounds * kTileTokens), 1); };
     const hipStream_t st = (hipStream_t)stream;

@@ -54,16 +54,18 @@ __host__ __device__ constexpr int row_pieces(int waves) { return 2 * waves * (kW
 // tile per compute unit), and a tile of a table with few whole words leaves 60 pieces over.
 constexpr int kFusedWaves = 16;
 constexpr int kFusedThreads = kFusedWaves * kWave;
+constexpr int kPairPieces = 2 * kGroupThreads;
 union MergeLds {
     TinyState tiny[kWavesPerGroup];
     struct { int32_t A[kLdsMaxLen]; int32_t B[kLdsMaxLen]; } group;
     struct { uint4 bytes[kGroupThreads]; uint32_t tok[row_pieces(kFusedWaves)][kTinyMax]; } left;   // see merge_left_over
+    struct { uint4 bytes[kPairPieces]; int o[kPairPieces]; int meta[kPairPieces]; } pair;           // see merge_tile_pair
 };
 
 struct TileShared {
     MergeLds lds;
     GroupTmp tmp;
-    int left_n[kWavesPerGroup];    // pieces of a wavefront that find_word left over (| kAnyLonger: it has longer pieces),
+    int left_n[2 * kWavesPerGroup];    // (a pair of tiles needs both halves) pieces of a wavefront that find_word left over (| kAnyLonger: it has longer pieces),
                                    // and per such piece (wavefront w's from 64 w on): its first byte in list, its
                                    // length << 8 | thread in cnt_back
     int list[kGroupThreads];       // threads whose piece waits for the wavefront paths, then for the workgroup path
@@ -488,6 +490,144 @@ __device__ __forceinline__ void merge_and_count_tile(const EncodeParams &p, Tile
     }
 }
 
+// Two tiles of 256 pieces by one workgroup, two pieces per lane; pieces beyond tiny_max are somebody
+// else's, as with merge_tile's SKIP_LONG.  A tile is a chain of dependent round trips (offsets, bytes,
+// probe, then the merges of what the probes leave over, a handful of pieces that occupy a quarter of
+// the lanes), and the chip holds four workgroups per compute unit: two tiles in flight per workgroup
+// take hardly longer than one.  7,944 tiles (13.5 MB of text): 75.1 us per call with a tile per workgroup,
+// 60.2 with two; 2,065 tiles (text with runs and random bytes): within 1 % of each other.
+__device__ __forceinline__ void merge_tile_pair(const EncodeParams &p, TileShared &sh, int *wave_tokens, int pair, int n_pieces) {
+    constexpr int kParts = 2 * kWavesPerGroup;     // left-over lists: one per half and wavefront, kWave slots each
+    const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+    const int64_t q0 = (int64_t)pair * kPairPieces;
+    if (q0 >= n_pieces) return;                    // the grid has a workgroup per tile: the second half leaves at once
+    int o[2], len[2], tok0[2];
+    bool tiny[2], own[2], bad = false;
+    int o_next[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int64_t q = q0 + h * kGroupThreads + tid;
+        own[h] = q < n_pieces;
+        o[h] = own[h] ? p.off[q] : 0;
+        o_next[h] = own[h] ? p.off[q + 1] : 0;
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int64_t q = q0 + h * kGroupThreads + tid;
+        const bool bad_h = own[h] && (o[h] < 0 || o_next[h] < o[h] || o_next[h] > p.n_bytes || (q == 0 && o[h] != 0) ||
+                                      (q == n_pieces - 1 && o_next[h] != p.n_bytes));
+        bad |= bad_h;
+        len[h] = bad_h ? 0 : o_next[h] - o[h];
+        tiny[h] = len[h] > 0 && len[h] <= p.tiny_max;
+        own[h] = own[h] && len[h] <= p.tiny_max;   // whoever merges a piece writes its record
+        tok0[h] = -1;
+    }
+    if (__ballot(bad) && lane == 0)
+        __hip_atomic_store(&p.status[0], p.call_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
+    uint32_t w[2][4] = {};
+    if (__ballot(tiny[0] || tiny[1])) {            // (so there is a byte to load; lanes without a short piece load it, too)
+        WordKey key[2];
+        uint4 a[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) load_piece_bytes(p, tiny[h] ? o[h] : 0, w[h]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            key[h] = word_key(w[h], tiny[h] ? len[h] : 1);
+            a[h] = word_slot(p.table, word_slot1(key[h].hash, p.table.word_shift));
+        }
+        bool more[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const bool look = tiny[h] && len[h] <= kWordMax;
+            if (look && word_hit(a[h], key[h], len[h])) tok0[h] = (int)(a[h].w >> 8);
+            more[h] = look && tok0[h] < 0 && (a[h].w & kWordMore);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (more[h]) a[h] = word_slot(p.table, word_slot2(key[h].hash, p.table.word_shift));
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (more[h] && word_hit(a[h], key[h], len[h])) tok0[h] = (int)(a[h].w >> 8);
+    }
+    uint32_t tokens = 0;                           // of the first tile | of the second << 16 (a tile has at most 4,096)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const bool left = tiny[h] && tok0[h] < 0;
+        const uint64_t left_mask = __ballot(left);
+        if (left) {
+            const int slot = (h * kWavesPerGroup + wv) * kWave + mbcnt(left_mask);
+            sh.lds.pair.bytes[slot] = make_uint4(w[h][0], w[h][1], w[h][2], w[h][3]);
+            sh.lds.pair.o[slot] = o[h];
+            sh.lds.pair.meta[slot] = len[h] << 16 | h << 8 | tid;
+        }
+        if (lane == 0) sh.left_n[h * kWavesPerGroup + wv] = __builtin_popcountll(left_mask);
+        if (own[h] && !left) p.rec[q0 + h * kGroupThreads + tid] = make_int2(tok0[h] >= 0 ? 1 : 0, tok0[h]);
+        tokens += (tok0[h] >= 0 ? 1u : 0u) << (16 * h);
+    }
+    __syncthreads();
+    int n[kParts], n_left = 0;
+#pragma unroll
+    for (int k = 0; k < kParts; ++k) n_left += n[k] = __builtin_amdgcn_readfirstlane(sh.left_n[k]);
+    auto slot_of = [&](int e) {                    // slot of left-over piece e < n_left
+        int base = 0;
+#pragma unroll
+        for (int k = 0; k + 1 < kParts; ++k) {
+            const bool on = e >= n[k] && base == k * kWave;
+            e -= on ? n[k] : 0;
+            base += on ? kWave : 0;
+        }
+        return base + e;
+    };
+    auto record = [&](int meta, int c, int first) {
+        p.rec[q0 + (meta & 0xFFFF)] = make_int2(c, first);     // (half << 8 | thread is the piece's number in the pair)
+        tokens += (uint32_t)c << (((meta >> 8) & 1) * 16);
+    };
+    if (n_left <= row_pieces(kWavesPerGroup)) {
+        constexpr int kRows = kWave / kTinyMax;
+        for (int e0 = __builtin_amdgcn_readfirstlane(wv) * kRows; e0 < n_left; e0 += kWavesPerGroup * kRows) {
+            const int j = lane & (kTinyMax - 1), e = e0 + lane / kTinyMax;
+            const bool mine = e < n_left;
+            const int slot = mine ? slot_of(e) : 0;
+            const int at = sh.lds.pair.o[slot], meta = sh.lds.pair.meta[slot];
+            uint32_t sym = ((const uint8_t *)&sh.lds.pair.bytes[slot])[j] | (3u << 24);
+            const int c = row_merge(p, sym, mine ? meta >> 16 : 0);
+            sym &= 0xFFFFFFu;
+            if (j > 0 && j < c) p.scratch[at + j] = (int)sym;
+            if (mine && j == 0) record(meta, c, (int)sym);
+        }
+    } else {
+        uint4 b[2];
+        int at[2], meta[2];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int e = r * kGroupThreads + tid, slot = e < n_left ? slot_of(e) : 0;
+            b[r] = sh.lds.pair.bytes[slot];
+            at[r] = sh.lds.pair.o[slot];
+            meta[r] = sh.lds.pair.meta[slot];
+        }
+        __syncthreads();               // the columns take the place of the bytes; from here on a wavefront has its own
+        TinyState &L = sh.lds.tiny[wv];
+        for (int r = 0; r < 2 && r * kGroupThreads < n_left; ++r) {
+            const bool mine = r * kGroupThreads + tid < n_left;
+            const uint4 br = r ? b[1] : b[0];
+            const int m = r ? meta[1] : meta[0], a0 = r ? at[1] : at[0];
+            const uint32_t ww[4] = {br.x, br.y, br.z, br.w};
+            const uint32_t alive = tiny_merge(p, L, ww, m >> 16, mine);
+            tiny_store(L, alive & (alive - 1), p.scratch + a0 + 1);
+            if (mine) record(m, __builtin_popcount(alive), (int)(L.S[__builtin_ctz(alive)][lane] & 0xFFFFFFu));
+        }
+    }
+    const int wave_total = __builtin_amdgcn_readlane(wave_scan_inclusive((int)tokens), kWave - 1);
+    if (lane == 0) wave_tokens[wv] = wave_total;
+    __syncthreads();
+    if (tid < 2 && q0 + tid * kGroupThreads < n_pieces) {
+        uint32_t sum = 0;
+        for (int k = 0; k < kWavesPerGroup; ++k) sum += ((uint32_t)wave_tokens[k] >> (16 * tid)) & 0xFFFFu;
+        p.tile_sum[2 * pair + tid] = (int)sum;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // The pieces beyond tiny_max of p.tiles_per_long_group consecutive tiles (of 256 pieces),
 // by one workgroup.  In word-like text they are few, and each is a chain of dependent
@@ -659,7 +799,7 @@ __global__ void __launch_bounds__(kGroupThreads) merge_tiles_kernel(EncodeParams
 }
 
 // Word-sized pieces on average: the first p.n_long_groups workgroups take the long pieces (see
-// above), every other one the short pieces of one tile.
+// above), every other one the short pieces of two tiles.
 // (The long-piece role has one place where it works its lists off: inlined at three, it took the kernel
 // beyond 128 vector registers, and the tiles lost a workgroup per compute unit to that.)
 __global__ void __launch_bounds__(kGroupThreads) merge_kernel(EncodeParams p) {
@@ -674,7 +814,7 @@ __global__ void __launch_bounds__(kGroupThreads) merge_kernel(EncodeParams p) {
                        "s"(p.n_bytes), "s"(p.n_pieces), "s"(p.tiny_max), "s"(p.rec), "s"(p.tile_sum), "s"(p.scratch),
                        "s"(p.status), "s"(p.call_id), "s"(p.n_long_groups));
     if ((int)blockIdx.x >= p.n_long_groups) {
-        merge_and_count_tile<kFromOffsets, true>(p, sh, wave_tokens, blockIdx.x - p.n_long_groups, p.n_pieces, p.P);
+        merge_tile_pair(p, sh, wave_tokens, blockIdx.x - p.n_long_groups, p.n_pieces);
     } else {
         __shared__ int acc[kGroupThreads];
         const EncodeParams &kp = kernel_params();

@@ -44,6 +44,22 @@ __device__ __forceinline__ void load_piece_bytes(const EncodeParams &p, int o, u
         w[k] = (uint32_t)((((uint64_t)raw[k + 1] << 32) | raw[k]) >> sh);
 }
 
+struct WordKey { uint32_t w0, w1, w2; WordHash hash; };       // the first len <= kWordMax bytes of w, zero-padded
+__device__ __forceinline__ WordKey word_key(const uint32_t (&w)[4], int len) {
+    const uint32_t bits = 8u * (uint32_t)len;
+    uint64_t lo = ((uint64_t)w[1] << 32) | w[0];
+    lo = bits >= 64 ? lo : lo & ((1ull << bits) - 1);
+    const uint32_t w0 = (uint32_t)lo, w1 = (uint32_t)(lo >> 32);
+    const uint32_t w2 = bits >= 96 ? w[2] : bits > 64 ? w[2] & ((1u << (bits & 31u)) - 1u) : 0u;
+    return {w0, w1, w2, word_hash(w0, w1, w2)};
+}
+__device__ __forceinline__ uint4 word_slot(const TableView &t, uint32_t i) {
+    return *(const uint4 *)((const char *)t.words + (i << 4));
+}
+__device__ __forceinline__ bool word_hit(const uint4 &s, const WordKey &k, int len) {
+    return s.x == k.w0 && s.y == k.w1 && s.z == k.w2 && (s.w & kWordLenMask) == (uint32_t)len;
+}
+
 // The token that the piece of `len` bytes in w becomes, or -1 if the whole-piece table does not
 // hold it (1 <= len <= kWordMax; w may hold anything behind the piece).  EAGER: both slots at
 // once, one round trip (grids the chip holds at a time: latency counts); otherwise the second
@@ -51,25 +67,16 @@ __device__ __forceinline__ void load_piece_bytes(const EncodeParams &p, int o, u
 // probes in three are spared, and the gathers are what the texture path is busy with).
 template <bool EAGER>
 __device__ __forceinline__ int find_word(const TableView &t, const uint32_t (&w)[4], int len) {
-    const uint32_t bits = 8u * (uint32_t)len;
-    uint64_t lo = ((uint64_t)w[1] << 32) | w[0];
-    lo = bits >= 64 ? lo : lo & ((1ull << bits) - 1);
-    const uint32_t w0 = (uint32_t)lo, w1 = (uint32_t)(lo >> 32);
-    const uint32_t w2 = bits >= 96 ? w[2] : bits > 64 ? w[2] & ((1u << (bits & 31u)) - 1u) : 0u;
-    const WordHash h = word_hash(w0, w1, w2);
-    auto slot = [&](uint32_t i) { return *(const uint4 *)((const char *)t.words + (i << 4)); };
-    auto hit = [&](const uint4 &s) {
-        return s.x == w0 && s.y == w1 && s.z == w2 && (s.w & kWordLenMask) == (uint32_t)len;
-    };
-    const uint4 a = slot(word_slot1(h, t.word_shift));
+    const WordKey k = word_key(w, len);
+    const uint4 a = word_slot(t, word_slot1(k.hash, t.word_shift));
     if (EAGER) {
-        const uint4 b = slot(word_slot2(h, t.word_shift));
-        return hit(a) ? (int)(a.w >> 8) : hit(b) ? (int)(b.w >> 8) : -1;
+        const uint4 b = word_slot(t, word_slot2(k.hash, t.word_shift));
+        return word_hit(a, k, len) ? (int)(a.w >> 8) : word_hit(b, k, len) ? (int)(b.w >> 8) : -1;
     }
-    int id = hit(a) ? (int)(a.w >> 8) : -1;
+    int id = word_hit(a, k, len) ? (int)(a.w >> 8) : -1;
     if (id < 0 && (a.w & kWordMore)) {
-        const uint4 b = slot(word_slot2(h, t.word_shift));
-        if (hit(b)) id = (int)(b.w >> 8);
+        const uint4 b = word_slot(t, word_slot2(k.hash, t.word_shift));
+        if (word_hit(b, k, len)) id = (int)(b.w >> 8);
     }
     return id;
 }

@@ -223,7 +223,7 @@ __device__ __forceinline__ bool merge_left_over(const EncodeParams &p, TileShare
 
 // n_pieces, P: the piece count and the pieces per wavefront of this launch (p's own
 // values, except on the raw path, where the kernel finds them out).
-// SKIP_LONG: the pieces beyond tiny_max are somebody else's (merge_kernel's long-piece
+// SKIP_LONG: the pieces beyond tiny_max are somebody else's (merge_raw_groups_kernel's long-piece
 // workgroups): they count as no tokens here and get no record from this tile.
 // SRC == kFromBytes: `tile` and n_pieces are not used; the thread's piece is number bt.k0 + threadIdx.x of
 // the tile (if that is below bt.n_t), and its record goes to slot bt_q0 + that number.

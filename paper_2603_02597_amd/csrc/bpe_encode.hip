@@ -50,10 +50,9 @@ namespace bpe {
 // Short pieces without a whole-piece token: up to two rounds of all wavefronts are merged one per
 // row of 16 lanes, more of them one per lane.
 __host__ __device__ constexpr int row_pieces(int waves) { return 2 * waves * (kWave / kTinyMax); }
-// The single kernel has helper wavefronts for the rows: its grids leave the chip idle (at most one
-// tile per compute unit), and a tile of a table with few whole words leaves 60 pieces over.
+// The single kernel has helper wavefronts for the rows on grids that leave the chip idle (at most one
+// tile per compute unit), where a tile of a table with few whole words leaves 60 pieces over.
 constexpr int kFusedWaves = 16;
-constexpr int kFusedThreads = kFusedWaves * kWave;
 constexpr int kPairPieces = 2 * kGroupThreads;
 union MergeLds {
     TinyState tiny[kWavesPerGroup];
@@ -1113,9 +1112,16 @@ __global__ void __launch_bounds__(kGroupThreads) merge_mapped_kernel(EncodeParam
 // total, finds the number of tokens of all tiles before it by decoupled
 // look-back over the published totals, and stores its tokens straight from LDS
 // to their final place.
+//
+// While every tile is resident no wait for a tile before can last.  With the helpers
+// (WAVES = kFusedWaves) a compute unit holds one workgroup: 16 wavefronts of 87 registers
+// are more than half of it, so 256 tiles are resident, which is as far as the library
+// takes this path by itself.  Grids that a caller forces beyond that run without the
+// helpers, four workgroups per compute unit.
 constexpr int kFusedMaxTiles = 256;
 
-__global__ void __launch_bounds__(kFusedThreads) encode_kernel(EncodeParams p, int n_tiles) {
+template <int WAVES>
+__global__ void __launch_bounds__(WAVES * kWave) encode_kernel(EncodeParams p, int n_tiles) {
     __shared__ TileShared sh;
     __shared__ LookbackTmp lb;
     __shared__ int long_src, long_dst, long_cnt;
@@ -1124,8 +1130,8 @@ __global__ void __launch_bounds__(kFusedThreads) encode_kernel(EncodeParams p, i
     if (tile == 0 && tid == 0) mark_call(p.status, p.call_id);
     const int32_t epoch = p.status[kStatusEpochEncode];
 
-    const TilePiece t = merge_tile<kFromOffsets, false, kFusedWaves>(p, sh, tile, true, p.n_pieces, p.P);
-    if (wv >= kWavesPerGroup) return;          // the helpers are done; barriers wait for the wavefronts that are left
+    const TilePiece t = merge_tile<kFromOffsets, false, WAVES>(p, sh, tile, true, p.n_pieces, p.P);
+    if (WAVES > kWavesPerGroup && wv >= kWavesPerGroup) return;          // the helpers are done; barriers wait for the wavefronts that are left
     const bool has_piece = t.has_piece;
     const int o = t.o, my_cnt = t.cnt;
     const int64_t q = t.q;
@@ -1153,7 +1159,7 @@ __global__ void __launch_bounds__(kFusedThreads) encode_kernel(EncodeParams p, i
         __syncthreads();
         int n[kWavesPerGroup];
         for (int w = 0; w < kWavesPerGroup; ++w) n[w] = __builtin_amdgcn_readfirstlane(sh.left_n[w]);
-        if (t.n_left <= row_pieces(kFusedWaves)) {
+        if (t.n_left <= row_pieces(WAVES)) {
             for (int i = tid; i < t.n_left * kTinyMax; i += kGroupThreads) {
                 const int slot = left_slot_of(i / kTinyMax, n), j = i % kTinyMax;
                 const int dst = sh.list[slot];
@@ -1793,9 +1799,9 @@ constexpr int kKernels = 3;
 constexpr int kRawKernels = 5;
 constexpr int64_t kRawMaxGrid = 8192;   // raw path: workgroups of the merge and emit kernels
 constexpr int64_t kRawRestGrid = 2048;  // ... of the strided merge kernel (two rounds of the chip; mostly it finds nothing to do)
-// Workgroups of the merge kernels that the chip holds at a time (4 per compute unit: LDS).  The
-// single-kernel path is only free of deadlock by construction while every tile is resident;
-// beyond, it relies on workgroups being dispatched in index order.
+// Workgroups of 256 threads of the merge kernels and of the single kernel that the chip holds at a time (4 per
+// compute unit: LDS).  The single-kernel path is only free of deadlock by construction while every tile is
+// resident; beyond, it relies on workgroups being dispatched in index order.
 constexpr int64_t kResidentGroups = 1024;
 // merge_kernel: one workgroup for the long pieces of every so many tiles, from grids of so many tiles on
 // (more than the chip holds at a time: below, a tile that takes long holds no other tile up),
@@ -1996,7 +2002,10 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
         run.run("emit_bytes_kernel", 3, emit_bytes_kernel, nt, kGroupThreads, p, (int)nt, self_scan);
         if (ev) { (void)hipEventRecord(ev[n_ev++], s); (void)hipEventRecord(ev[n_ev++], s); }
     } else if (fused) {
-        run.run("encode_kernel", 0, encode_kernel, n_tiles, kFusedThreads, p, (int)n_tiles);
+        if (n_tiles <= kFusedMaxTiles)
+            run.run("encode_kernel", 0, encode_kernel<kFusedWaves>, n_tiles, kFusedWaves * kWave, p, (int)n_tiles);
+        else
+            run.run("encode_kernel", 0, encode_kernel<kWavesPerGroup>, n_tiles, kGroupThreads, p, (int)n_tiles);
         if (ev) { (void)hipEventRecord(ev[1], s); (void)hipEventRecord(ev[2], s); (void)hipEventRecord(ev[3], s); }
     } else {
         // Raw path: n_tiles only bounds the tile count.  A capped grid strides over the

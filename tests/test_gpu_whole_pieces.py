@@ -81,3 +81,19 @@ def test_piece_lengths(n):
     pieces += [bytes(rng.choice(np.frombuffer(b"eat ", dtype=np.uint8), n)) for _ in range(300)]
     pieces += [bytes(rng.integers(0, 256, n, dtype=np.uint8)) for _ in range(100)]
     _check(merges, pieces, FORMS)
+
+
+@pytest.mark.parametrize("n_tiles", [256, 257, 1024])
+def test_left_over_pieces_in_the_single_kernel_with_and_without_helpers(n_tiles):
+    """The same counts of left-over pieces where the single kernel is asked for: 16 wavefronts a tile up to 256
+    tiles, four beyond (few left over: rows; more than 32 or 128: columns), longer pieces in some tiles."""
+    merges, whole, left = _word_pieces()
+    rng = np.random.default_rng(n_tiles)
+    counts = [0, 1, 31, 32, 33, 128, 129, 256, 5]
+    pieces = []
+    for t in range(n_tiles):
+        kinds = rng.permutation(256) < counts[t % len(counts)]
+        pieces += [left[rng.integers(len(left))] if k else whole[rng.integers(len(whole))] for k in kinds]
+        if t % 4 == 1:
+            pieces[-1] = pieces[-1] * 5
+    _check(merges, pieces[:-3], ({"fused": 1},))

@@ -69,3 +69,22 @@ def test_column_merge_names_its_address_spaces(compiled):
     assert count(r"global_load_dwordx2") >= 4                                  # the slots of two pairs
     assert count(r"flat_load_dwordx4") <= 3 and count(r"flat_store") == 0      # (the parameter block itself is read flat)
     assert count(r"scratch_") == 0
+
+
+def test_the_single_kernel_is_resident_as_a_whole(compiled):
+    """The largest grids of the single kernel that need no caller's say-so about the order of dispatch (256 tiles by
+    default, 1024 with fused = 1) fit the chip at once: 256 compute units of four SIMDs with 512 vector registers per
+    lane and at most 8 wavefronts each, and 160 KiB of LDS.  Otherwise a tile could wait for one that is not there."""
+    import paper_2603_02597_amd as B
+    _, remarks = compiled
+    usage = {k: u for k, u in _usage(remarks).items() if "encode_kernel" in k}
+    for n_pieces, fused in ((256 * 256, 0), (256 * 256, 1), (256 * 256 + 1, 1), (1024 * 256, 1)):
+        plan = B.bpe_encode_plan(6 * n_pieces, n_pieces, B.EncodeOptions(fused=fused))
+        launch, = plan["launches"]
+        assert launch["kernel"] == "encode_kernel"
+        waves = launch["block"] // 64
+        kernel, = [u for k, u in usage.items() if f"ILi{waves}E" in k] or usage.values()
+        regs = -(-(kernel["VGPRs"] + kernel.get("AGPRs", 0)) // 8) * 8
+        by_waves = 4 * min(8, 512 // regs) // waves
+        by_lds = 160 * 1024 // kernel["LDS Size"]
+        assert launch["grid"] <= 256 * min(by_waves, by_lds), (launch, kernel)

@@ -47,9 +47,14 @@ namespace bpe {
 // LDS of a tile: the lane-per-piece state of the four wavefronts and the double
 // buffer of the workgroup path share the same bytes; a barrier separates the two
 // uses, and the lane-per-piece tokens are in the workspace by then.
-// Short pieces without a whole-piece token: up to two rounds of all wavefronts are merged one per
-// row of 16 lanes, more of them one per lane.
-__host__ __device__ constexpr int row_pieces(int waves) { return 2 * waves * (kWave / kTinyMax); }
+// Short pieces without a whole-piece token: as many as the wavefronts have rows of 16 lanes are merged
+// one per row, more of them one per lane.  Not two rounds of rows: a round is as long as its longest
+// chain (words of 13 to 16 bytes are never in the whole-piece table and take a dozen merges), and one
+// round of columns takes them all at once.  840 KB with the 100k table: 14.3 us with two rounds, 12.6 with
+// one; 13.5 MB with the 50k table 58.6 and 56.3; 60 KB with the 1k table 11.5 and 10.6.  (Except in
+// merge_raw_kernel: a tile per workgroup on grids of many rounds of the chip, where 17 left-over pieces
+// delay nobody; 64 MB from raw bytes 365 us with two rounds, 369 with one.)
+__host__ __device__ constexpr int row_pieces(int waves) { return waves * (kWave / kTinyMax); }
 // The single kernel has helper wavefronts for the rows on grids that leave the chip idle (at most one
 // tile per compute unit), where a tile of a table with few whole words leaves 60 pieces over.
 constexpr int kFusedWaves = 16;
@@ -152,7 +157,7 @@ __device__ __forceinline__ int left_slot_of(int e, const int (&n)[kWavesPerGroup
 constexpr int kAnyLonger = 1 << 16;
 
 // Returns whether the tile has longer pieces.
-template <int SRC, int WAVES>
+template <int SRC, int WAVES, int ROUNDS>
 __device__ __forceinline__ bool merge_left_over(const EncodeParams &p, TileShared &sh, TilePiece &t, int64_t tile_q0, int P,
                                                 bool keep_in_lds) {
     const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -169,9 +174,9 @@ __device__ __forceinline__ bool merge_left_over(const EncodeParams &p, TileShare
     auto record_of = [&](int owner) {
         return SRC == kFromBytes ? tile_q0 + owner : tile_q0 + (int64_t)(owner / kWave) * P + (owner % kWave);
     };
-    if (t.n_left <= row_pieces(WAVES)) {
+    if (t.n_left <= ROUNDS * row_pieces(WAVES)) {
         constexpr int kRows = kWave / kTinyMax;
-        for (int e0 = wv * kRows; e0 < t.n_left; e0 += WAVES * kRows) {
+        for (int e0 = wv * kRows; e0 < t.n_left; e0 += row_pieces(WAVES)) {
             const int j = lane & (kTinyMax - 1), e = e0 + lane / kTinyMax;
             const bool mine = e < t.n_left;
             const int slot = mine ? left_slot_of(e, n) : 0;
@@ -226,9 +231,10 @@ __device__ __forceinline__ bool merge_left_over(const EncodeParams &p, TileShare
 // workgroups): they count as no tokens here and get no record from this tile.
 // SRC == kFromBytes: `tile` and n_pieces are not used; the thread's piece is number bt.k0 + threadIdx.x of
 // the tile (if that is below bt.n_t), and its record goes to slot bt_q0 + that number.
-// WAVES: wavefronts that merge left-over pieces in rows (0: always one per lane); the ones beyond the tile's four only help with left-over pieces.
+// WAVES: wavefronts of the workgroup; the ones beyond the tile's four only help with left-over pieces.
 // EAGER: see find_word.
-template <int SRC = kFromOffsets, bool SKIP_LONG = false, int WAVES = kWavesPerGroup, bool EAGER = !SKIP_LONG>
+// ROUNDS: rounds of rows that left-over pieces may take (0: always one per lane); see row_pieces.
+template <int SRC = kFromOffsets, bool SKIP_LONG = false, int WAVES = kWavesPerGroup, bool EAGER = !SKIP_LONG, int ROUNDS = 1>
 __device__ __forceinline__ TilePiece merge_tile(const EncodeParams &p, TileShared &sh, int tile, bool keep_in_lds,
                                                 int n_pieces, int P, const ByteTile &bt = ByteTile{}, int64_t bt_q0 = 0) {
     const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
@@ -310,7 +316,7 @@ __device__ __forceinline__ TilePiece merge_tile(const EncodeParams &p, TileShare
     if (lane == 0 && (WAVES <= kWavesPerGroup || wv < kWavesPerGroup))
         sh.left_n[wv] = __builtin_popcountll(left_mask) | (wave_longer ? kAnyLonger : 0);
     __syncthreads();
-    const bool any_longer = merge_left_over<SRC, WAVES>(p, sh, t, tile_q0, P, keep_in_lds);
+    const bool any_longer = merge_left_over<SRC, WAVES, ROUNDS>(p, sh, t, tile_q0, P, keep_in_lds);
 
     if (SKIP_LONG) {
         t.has_piece = t.has_piece && !is_wave && !is_long;     // whoever merges a piece writes its record
@@ -474,10 +480,10 @@ __device__ inline int tiles_of(const EncodeParams &p) {
 
 // Several-kernel path, first kernel: tokens and counts of every piece to the
 // workspace, the tile's token total to tile_sum.
-template <int SRC = kFromOffsets, bool SKIP_LONG = false, int WAVES = kWavesPerGroup, bool EAGER = !SKIP_LONG>
+template <int SRC = kFromOffsets, bool SKIP_LONG = false, bool EAGER = !SKIP_LONG, int ROUNDS = 1>
 __device__ __forceinline__ void merge_and_count_tile(const EncodeParams &p, TileShared &sh, int *wave_tokens, int tile,
                                                      int n_pieces, int P) {
-    const TilePiece t = merge_tile<SRC, SKIP_LONG, WAVES, EAGER>(p, sh, tile, false, n_pieces, P);
+    const TilePiece t = merge_tile<SRC, SKIP_LONG, kWavesPerGroup, EAGER, ROUNDS>(p, sh, tile, false, n_pieces, P);
     if (t.has_piece && t.left_slot < 0) p.rec[t.q] = make_int2(t.cnt, t.tok0);
     const int wave_total = __builtin_amdgcn_readlane(wave_scan_inclusive(t.cnt + t.others_cnt), kWave - 1);
     if (lane_id() == 0) wave_tokens[threadIdx.x / kWave] = wave_total;
@@ -584,7 +590,8 @@ __device__ __forceinline__ void merge_tile_pair(const EncodeParams &p, TileShare
     };
     if (n_left <= row_pieces(kWavesPerGroup)) {
         constexpr int kRows = kWave / kTinyMax;
-        for (int e0 = __builtin_amdgcn_readfirstlane(wv) * kRows; e0 < n_left; e0 += kWavesPerGroup * kRows) {
+        const int e0 = __builtin_amdgcn_readfirstlane(wv) * kRows;
+        if (e0 < n_left) {
             const int j = lane & (kTinyMax - 1), e = e0 + lane / kTinyMax;
             const bool mine = e < n_left;
             const int slot = mine ? slot_of(e) : 0;
@@ -867,7 +874,7 @@ __global__ void __launch_bounds__(kGroupThreads) merge_raw_kernel(EncodeParams p
     __shared__ TileShared sh;
     __shared__ int wave_tokens[kWavesPerGroup];
     raw_geometry(p);
-    if ((int)blockIdx.x < tiles_of(p)) merge_and_count_tile(p, sh, wave_tokens, blockIdx.x, p.n_pieces, p.P);
+    if ((int)blockIdx.x < tiles_of(p)) merge_and_count_tile<kFromOffsets, false, true, 2>(p, sh, wave_tokens, blockIdx.x, p.n_pieces, p.P);
 }
 
 // The same for a caller who says that the pieces are word-sized (pieces_per_wave 64 given, not left
@@ -901,7 +908,7 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_raw_rest_kernel(Encode
         const EncodeParams *kp = &kernel_params();
         asm volatile("" : "+s"(kp));
         if (kp->long_sum && threadIdx.x == 0) kp->long_sum[tile] = 0;      // nothing of this tile goes to a long-piece workgroup
-        merge_and_count_tile<kFromOffsets, false, 0, false>(*kp, sh, wave_tokens, tile, n_pieces, P);
+        merge_and_count_tile<kFromOffsets, false, false, 0>(*kp, sh, wave_tokens, tile, n_pieces, P);
         __syncthreads();   // the next tile reuses the LDS
     }
 }

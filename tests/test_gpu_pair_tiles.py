@@ -39,3 +39,35 @@ def test_pairs_of_tiles(oracle_mod, n_pieces, unknown):
         assert np.array_equal(got_off.cpu().numpy(), want_off)
         assert np.array_equal(ids.cpu().numpy(), want_ids)
     table.free()
+
+
+@pytest.mark.parametrize("n_left", [15, 16, 17, 255, 256, 257, 512])
+def test_left_over_pieces_of_a_pair(oracle_mod, n_left):
+    """Pairs of tiles that leave exactly so many pieces over, around what one round of rows (16) and one round of
+    columns (256) take, in each half and across both; left-over pieces of 13 to 16 bytes among them."""
+    import torch
+    import paper_2603_02597_amd as B
+    from workloads import configs as C
+    merges = C.load_merges("t1k")
+    ot, table = oracle_mod.Table(merges), B.Table(merges)
+    rng = np.random.default_rng(n_left)
+    known = [oracle_mod.decode(ot, np.array([i], dtype=np.int32)).tobytes() for i in range(256, 256 + len(merges))]
+    tokens_of = lambda x: oracle_mod.encode(ot, np.frombuffer(x, np.uint8), np.array([0, len(x)], np.int32))[0].size
+    known = [k for k in known if len(k) <= 12 and tokens_of(k) == 1]
+    left = [bytes(rng.integers(0, 256, int(n)).astype(np.uint8)) for n in rng.integers(5, 17, 200)]
+    left += [(known[int(a)] + known[int(b)] + known[int(c)])[:16] for a, b, c in rng.integers(0, len(known), (200, 3))]
+    left = [x for x in left if tokens_of(x) > 1]
+    pieces = []
+    for first in (0, 512 - n_left, -1):            # left-over pieces in front, at the end, scattered
+        where = rng.permutation(512)[:n_left] if first < 0 else np.arange(first, first + n_left)
+        is_left = np.zeros(512, bool)
+        is_left[where] = True
+        pieces += [left[rng.integers(len(left))] if k else known[rng.integers(len(known))] for k in is_left]
+    off = np.concatenate([[0], np.cumsum([len(x) for x in pieces])]).astype(np.int32)
+    data = np.frombuffer(b"".join(pieces), dtype=np.uint8)
+    want_ids, want_off = oracle_mod.encode(ot, data, off)
+    ids, got_off = B.encode(table, torch.from_numpy(data.copy()).cuda(), torch.from_numpy(off).cuda(),
+                            B.EncodeOptions(long_groups=4, fused=-1))
+    assert np.array_equal(got_off.cpu().numpy(), want_off)
+    assert np.array_equal(ids.cpu().numpy(), want_ids)
+    table.free()

@@ -86,10 +86,10 @@ def test_piece_lengths(n):
 @pytest.mark.parametrize("n_tiles", [256, 257, 1024])
 def test_left_over_pieces_in_the_single_kernel_with_and_without_helpers(n_tiles):
     """The same counts of left-over pieces where the single kernel is asked for: 16 wavefronts a tile up to 256
-    tiles, four beyond (few left over: rows; more than 32 or 128: columns), longer pieces in some tiles."""
+    tiles, four beyond (few left over: rows; more than 64 or 16: columns), longer pieces in some tiles."""
     merges, whole, left = _word_pieces()
     rng = np.random.default_rng(n_tiles)
-    counts = [0, 1, 31, 32, 33, 128, 129, 256, 5]
+    counts = [0, 1, 16, 17, 64, 65, 128, 256, 5]
     pieces = []
     for t in range(n_tiles):
         kinds = rng.permutation(256) < counts[t % len(counts)]

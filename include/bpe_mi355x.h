@@ -70,9 +70,10 @@ typedef struct bpe_table bpe_table;
 typedef struct {
     int64_t n_merges;
     int64_t capacity;       /* slots */
-    int64_t device_bytes;   /* 8-byte slots, the whole-piece table (16 bytes a slot: every string of up to 12 bytes
-                             * that becomes one token), the 65536-entry direct table for byte pairs (4 bytes each), two
-                             * rank-order arrays, 8 bytes per token id up to max_id */
+    int64_t device_bytes;   /* of the table on the device: 8-byte slots, the whole-piece table (strings of up to 12
+                             * bytes that become one token, as far as they find room; 16 bytes a slot, at most half
+                             * full), the 65536-entry direct table for byte pairs (4 bytes each), two rank-order
+                             * arrays, 8 bytes per token id up to max_id */
     int32_t hash_attempt;   /* which multiplier set placed all keys (0 = first) */
     int32_t max_id;         /* largest token id the table can produce or consume */
 } bpe_table_info_t;

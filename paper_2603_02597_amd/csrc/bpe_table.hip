@@ -199,7 +199,6 @@ static int build_image(const int32_t *merges, const int32_t *ranks, const int32_
     if (attempt == kHashSeeds) { set_error("could not place the keys with any of the %d hash seeds", kHashSeeds); return BPE_ERR_SIZE; }
     img.info.n_merges = n;
     img.info.capacity = cap;
-    img.info.device_bytes = cap * 8 + 65536 * 4 + 2 * 4 * std::max<int64_t>(n, 1) + 8 * (max_id + 1);
     img.info.hash_attempt = attempt;
     img.info.max_id = (int32_t)max_id;
     return BPE_OK;
@@ -320,6 +319,21 @@ static void build_words(const int32_t *merges, const RuleOrder &ro, const HostIm
     }
 }
 
+// The one allocation of a table on the device: where its arrays start, and its size.
+struct DeviceLayout { size_t words, byte_pairs, merged_of, rank_of, sym_lr, total; };     // (the slots are first)
+
+static DeviceLayout device_layout(const HostImage &img, const WordImage &words) {
+    const size_t rule_bytes = (img.merged_of.size() * 4 + 255) / 256 * 256;
+    DeviceLayout l;
+    l.words = (size_t)img.info.capacity * 8;
+    l.byte_pairs = l.words + words.slots.size() * 4;
+    l.merged_of = l.byte_pairs + img.byte_pairs.size() * 4;
+    l.rank_of = l.merged_of + rule_bytes;
+    l.sym_lr = l.rank_of + rule_bytes;
+    l.total = l.sym_lr + img.sym_lr.size() * 4;
+    return l;
+}
+
 }  // namespace bpe
 
 using namespace bpe;
@@ -349,7 +363,12 @@ extern "C" int bpe_table_image_build(const int32_t *merges, const int32_t *ranks
     int rc = build_image(merges, ranks, merged_ids, n, img, ro);
     if (rc != BPE_OK) return rc;
     memcpy(slots, img.slots.data(), (size_t)cap * 16);
-    if (info) *info = img.info;
+    if (info) {
+        WordImage words;
+        build_words(merges, ro, img, words);
+        img.info.device_bytes = (int64_t)device_layout(img, words).total;
+        *info = img.info;
+    }
     return BPE_OK;
 }
 
@@ -365,7 +384,12 @@ extern "C" int bpe_table_build(const int32_t *merges, const int32_t *ranks, cons
     const int64_t half = img.info.capacity / 2;
     const int index_bits = log2_exact(half), low_bits = 24 - index_bits;
     const HashSeed seed = hash_seed(img.info.hash_attempt);
-    std::vector<uint32_t> dev_slots((size_t)img.info.capacity * 2);
+    WordImage words;
+    build_words(merges, ro, img, words);
+    const DeviceLayout at = device_layout(img, words);
+    img.info.device_bytes = (int64_t)at.total;
+    std::vector<char> blob(at.total, 0);
+    uint32_t *dev_slots = (uint32_t *)blob.data();
     for (int64_t i = 0; i < img.info.capacity; ++i) {
         const uint64_t key = img.slots[2 * (size_t)i], val = img.slots[2 * (size_t)i + 1];
         uint32_t rest = 0, word = kNoRank;
@@ -377,19 +401,11 @@ extern "C" int bpe_table_build(const int32_t *merges, const int32_t *ranks, cons
         dev_slots[2 * (size_t)i] = rest;
         dev_slots[2 * (size_t)i + 1] = word;
     }
-    WordImage words;
-    build_words(merges, ro, img, words);
-    const size_t word_bytes = words.slots.size() * 4;
-    const size_t slot_bytes = dev_slots.size() * 4 + word_bytes, bp_bytes = img.byte_pairs.size() * 4;
-    const size_t arr_bytes = ((img.merged_of.size() * 4 + 255) / 256) * 256;
-    const size_t lr_bytes = img.sym_lr.size() * 4;
-    std::vector<char> blob(slot_bytes + bp_bytes + 2 * arr_bytes + lr_bytes, 0);
-    memcpy(blob.data(), dev_slots.data(), slot_bytes - word_bytes);
-    memcpy(blob.data() + (slot_bytes - word_bytes), words.slots.data(), word_bytes);
-    memcpy(blob.data() + slot_bytes, img.byte_pairs.data(), bp_bytes);
-    memcpy(blob.data() + slot_bytes + bp_bytes, img.merged_of.data(), img.merged_of.size() * 4);
-    memcpy(blob.data() + slot_bytes + bp_bytes + arr_bytes, img.rank_of.data(), img.rank_of.size() * 4);
-    memcpy(blob.data() + slot_bytes + bp_bytes + 2 * arr_bytes, img.sym_lr.data(), lr_bytes);
+    memcpy(blob.data() + at.words, words.slots.data(), words.slots.size() * 4);
+    memcpy(blob.data() + at.byte_pairs, img.byte_pairs.data(), img.byte_pairs.size() * 4);
+    memcpy(blob.data() + at.merged_of, img.merged_of.data(), img.merged_of.size() * 4);
+    memcpy(blob.data() + at.rank_of, img.rank_of.data(), img.rank_of.size() * 4);
+    memcpy(blob.data() + at.sym_lr, img.sym_lr.data(), img.sym_lr.size() * 4);
 
     bpe_table *t = new (std::nothrow) bpe_table();
     if (!t) { set_error("out of host memory"); return BPE_ERR_SIZE; }
@@ -400,15 +416,14 @@ extern "C" int bpe_table_build(const int32_t *merges, const int32_t *ranks, cons
     e = hipMemcpy(t->device_mem, blob.data(), blob.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) { (void)hipFree(t->device_mem); delete t; return hip_fail(e, "hipMemcpy(table)"); }
     t->info = img.info;
-    t->info.device_bytes = (int64_t)blob.size();
     char *d = (char *)t->device_mem;
     t->view.slots = (const uint2 *)d;
-    t->view.words = (const uint4 *)(d + (slot_bytes - word_bytes));
+    t->view.words = (const uint4 *)(d + at.words);
     t->view.word_shift = words.shift;
-    t->view.byte_pairs = (const uint32_t *)(d + slot_bytes);
-    t->view.merged_of = (const int32_t *)(d + slot_bytes + bp_bytes);
-    t->view.rank_of = (const int32_t *)(d + slot_bytes + bp_bytes + arr_bytes);
-    t->view.sym_lr = (const uint2 *)(d + slot_bytes + bp_bytes + 2 * arr_bytes);
+    t->view.byte_pairs = (const uint32_t *)(d + at.byte_pairs);
+    t->view.merged_of = (const int32_t *)(d + at.merged_of);
+    t->view.rank_of = (const int32_t *)(d + at.rank_of);
+    t->view.sym_lr = (const uint2 *)(d + at.sym_lr);
     t->view.half = (uint32_t)half;
     t->view.low_bits = low_bits;
     t->view.index_bits = index_bits;

@@ -308,6 +308,27 @@ def test_forced_single_kernel_is_refused_beyond_the_resident_grid():
         B.bpe_encode_plan(100, 10, E(fused=3))
 
 
+@pytest.mark.parametrize("table", ["empty", "t1k"])
+def test_image_info_reports_what_the_device_keeps(table):
+    """device_bytes of bpe_table_image_build: all arrays of the device copy, the whole-piece table among them."""
+    import oracle
+    from workloads import configs as C
+    merges = np.zeros((0, 2), dtype=np.int32) if table == "empty" else C.load_merges(table)
+    n = len(merges)
+    strings = [bytes([b]) for b in range(256)]
+    for a, b in merges:
+        strings.append(strings[a] + strings[b])
+    data = np.frombuffer(b"".join(strings), dtype=np.uint8)
+    off = np.concatenate([[0], np.cumsum([len(s) for s in strings])]).astype(np.int32)
+    ids, tok_off = oracle.encode(oracle.Table(merges), data, off)
+    words = sum(len(s) <= 12 and t == 1 for s, t in zip(strings, np.diff(tok_off)))
+    slots = 1024
+    while slots < 2 * words:
+        slots *= 2
+    _, info = B.bpe_table_image_build(merges)
+    arrays = 2 * (-(-4 * max(n, 1) // 256) * 256) + 4 * 65536 + 8 * (256 + n)
+    assert info["device_bytes"] == 8 * info["capacity"] + 16 * slots + arrays
+
 
 def test_status_from_words():
     """The verdict a host copy of a workspace's status words spells (word 2: the call, word 7: its

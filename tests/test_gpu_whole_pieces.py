@@ -97,3 +97,10 @@ def test_left_over_pieces_in_the_single_kernel_with_and_without_helpers(n_tiles)
         if t % 4 == 1:
             pieces[-1] = pieces[-1] * 5
     _check(merges, pieces[:-3], ({"fused": 1},))
+
+
+@pytest.mark.parametrize("name", ["t1k", "t50k"])
+def test_table_info_equals_the_images(name):
+    import paper_2603_02597_amd as B
+    merges = C.load_merges(name)
+    assert B.Table(merges).info == B.bpe_table_image_build(merges)[1]

@@ -15,9 +15,9 @@ DRIVERS = os.path.join(ROOT, "tests", "sanitize")
 SAN = ["-fsanitize=address", "-fsanitize=undefined", "-fno-sanitize-recover=all"]
 
 
-def _run(exe):
+def _run(exe, *args):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0", UBSAN_OPTIONS="print_stacktrace=1")
-    r = subprocess.run([exe], capture_output=True, text=True, timeout=300, env=env)
+    r = subprocess.run([exe, *args], capture_output=True, text=True, timeout=300, env=env)
     assert r.returncode == 0, f"{exe}:\n{r.stdout}\n{r.stderr}"
     return r.stdout
 
@@ -41,7 +41,7 @@ def test_oracle_under_sanitizers(tmp_path):
     assert "ok" in _run(exe)
 
 
-def test_host_builders_under_sanitizers(tmp_path):
+def _host_san(tmp_path, *sources):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if not (os.path.exists(hipcc) or shutil.which(hipcc)):
         pytest.skip("no hipcc")
@@ -52,8 +52,16 @@ def test_host_builders_under_sanitizers(tmp_path):
                            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                            "-Wno-unused-command-line-argument", *host_san,
                            "-I", os.path.join(ROOT, "include"), "-I", csrc,
-                           os.path.join(csrc, "bpe_table.hip"), os.path.join(csrc, "bpe_vocab.hip"),
-                           os.path.join(DRIVERS, "host_builders_driver.cpp"), "-o", exe],
+                           *[os.path.join(csrc if s.endswith(".hip") else DRIVERS, s) for s in sources], "-o", exe],
                           stderr=subprocess.DEVNULL)
     assert _instrumented(exe)
-    assert "ok" in _run(exe)
+    return exe
+
+
+def test_host_builders_under_sanitizers(tmp_path):
+    assert "ok" in _run(_host_san(tmp_path, "bpe_table.hip", "bpe_vocab.hip", "host_builders_driver.cpp"))
+
+
+def test_whole_piece_table_under_sanitizers(tmp_path):
+    tables = [os.path.join(ROOT, "workloads", "tables", t + ".merges.i32") for t in ("t1k", "t50k")]
+    assert "ok" in _run(_host_san(tmp_path, "word_table_driver.cpp"), *tables)

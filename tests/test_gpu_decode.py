@@ -118,6 +118,7 @@ def test_many_tokens_take_larger_tiles(gpu, oracle_mod):
         want = oracle_mod.decode(ot, ids)
         buf, tbo, nb, st = _decode(gpu, vocab, ids, want.size - 70000)
         assert st == BPE_ERR_SIZE and nb == want.size - 70000 and (buf[want.size - 70000:] == 0xEE).all()
+        assert np.array_equal(buf[:nb], want[:nb])
         assert np.array_equal(tbo, oracle_mod.token_byte_offsets(ot, ids))
     # long tokens in the larger tiles: rounds that do not fit the LDS stage
     merges2 = [(120, 120)] + [(256 + k, 256 + k) for k in range(9)]
@@ -168,7 +169,8 @@ def test_output_too_small_is_reported(gpu, oracle_mod):
         else:
             assert st == BPE_ERR_SIZE and nb == cap
         assert (buf[cap:] == 0xEE).all(), "wrote behind the capacity"
-        # tiles that fit entirely are complete; offsets are always the true ones
+        # the bytes up to the capacity are complete; offsets are always the true ones
+        assert np.array_equal(buf[:cap], want[:cap])
         assert np.array_equal(tbo, oracle_mod.token_byte_offsets(ot, ids))
     vocab.free()
 

@@ -38,9 +38,42 @@ def test_token_lengths(oracle_mod, n, lo, hi):
             assert B.bpe_encode_status(ws) == (0 if cap == want.size else -2)
             assert int(nb.item()) == cap
             got, off = buf.cpu().numpy(), tbo.cpu().numpy()
-            if cap == want.size:
-                assert np.array_equal(got[shift:shift + cap], want)
+            assert np.array_equal(got[shift:shift + cap], want[:cap])
             assert (got[:shift] == 0xEE).all() and (got[shift + cap:] == 0xEE).all()
             assert np.array_equal(off[shift:shift + n + 1], want_off)
             assert (off[:shift] == -7).all() and (off[shift + n + 1:] == -7).all()
+    vocab.free()
+
+
+LONG = MERGES + [(255 + len(MERGES) + k, 255 + len(MERGES) + k) for k in range(3)]     # 48, 96 and 192 bytes
+
+
+# tiles of 1, 2 and 4 rounds whose rounds do not fit the stage, or only the first ones do: tokens of 9 to 12 bytes,
+# which live in their record, between tokens of 192
+@pytest.mark.parametrize("n", [5000, 530_001, 4_200_003])
+@pytest.mark.parametrize("first_round", [0.0, 0.1, 1.0])
+def test_inline_and_long_tokens_in_one_tile(oracle_mod, n, first_round):
+    import torch
+    import paper_2603_02597_amd as B
+    rng = np.random.default_rng(n + int(10 * first_round))
+    length = rng.integers(9, 13, n)
+    ids = (254 + length).astype(np.int32)
+    place = np.arange(n) % 4096                # round 0 of a tile of any kind starts at a multiple of 4096
+    share = np.where(place < 1024, first_round, 0.1)
+    ids[rng.random(n) < share] = 255 + len(LONG)
+    table = oracle_mod.Table(LONG)
+    want, want_off = oracle_mod.decode(table, ids), oracle_mod.token_byte_offsets(table, ids)
+    vocab = B.Vocab(LONG)
+    d_ids = torch.from_numpy(ids).cuda()
+    ws = torch.empty(B.bpe_decode_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+    for cap in (want.size, want.size - 1, want.size // 3, 700):
+        print(f"[case] {n} tokens, {first_round} of the first round long, {cap} of {want.size} bytes", flush=True)
+        buf = torch.full((want.size + 16,), 0xEE, dtype=torch.uint8, device="cuda")
+        tbo = torch.empty(n + 1, dtype=torch.int32, device="cuda")
+        nb = torch.zeros(1, dtype=torch.int32, device="cuda")
+        B.bpe_decode(vocab, d_ids, buf[3:3 + cap], ws, tbo, nb)
+        assert B.bpe_encode_status(ws) == (0 if cap == want.size else -2) and int(nb.item()) == cap
+        got = buf.cpu().numpy()
+        assert np.array_equal(got[3:3 + cap], want[:cap]) and (got[:3] == 0xEE).all() and (got[3 + cap:] == 0xEE).all()
+        assert np.array_equal(tbo.cpu().numpy(), want_off)
     vocab.free()

@@ -73,7 +73,7 @@ static_assert(kTokPerThread == 4, "a thread's tokens are one Int4");
 // The records of the thread's four tokens from t0 on; returns whether one of the ids is unknown.
 __device__ __forceinline__ bool load_records(const DecodeParams &p, int t0, int n, Record (&rec)[kTokPerThread]) {
     Int4 id;
-    if (t0 + kTokPerThread <= n) {
+    if (t0 <= n - kTokPerThread) {             // (t0 + 4 may be 2^31)
         id = *(const Int4 *)(p.ids + t0);
     } else {
 #pragma unroll
@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(kGroupThreads) decode_kernel(DecodeParams p) {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const int tile = blockIdx.x;
     const int n = token_count(p);
-    const int n_tiles = max((n + kTile - 1) / kTile, 1);
+    const int n_tiles = max((int)(((uint32_t)n + (kTile - 1)) / kTile), 1);     // (n may be 2^31 - 2)
     if (tile >= n_tiles) return;               // the grid was sized for the host's upper bound
     if (tile == 0 && tid == 0) mark_call(p.status, p.call_id);
     const int32_t epoch = p.status[kStatusEpochDecode];
@@ -231,7 +231,7 @@ __global__ void __launch_bounds__(kGroupThreads) decode_kernel(DecodeParams p) {
             at[0] = (int)base + ex[r];
 #pragma unroll
             for (int j = 1; j < kTokPerThread; ++j) at[j] = at[j - 1] + (int)len[r][j - 1];
-            if (t0 + kTokPerThread <= n) {
+            if (t0 <= n - kTokPerThread) {
                 *(Int4 *)(p.token_byte_offsets + t0) = at;
             } else {
 #pragma unroll

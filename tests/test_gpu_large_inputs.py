@@ -80,3 +80,29 @@ def test_two_gigabytes_of_text(oracle_mod):
     _say("[step] decode done")
     vocab.free()
     table.free()
+
+
+@pytest.mark.parametrize("n", [2**31 - 4095, 2**31 - 4, 2**31 - 2])
+def test_as_many_tokens_as_the_decoder_takes(n):
+    """One-byte tokens up to the interface's limit on n_tokens, where the index behind a tile's last tokens is 2^31:
+    every byte and offset, compared on the device."""
+    import torch
+    import paper_2603_02597_amd as B
+    vocab = B.Vocab([(97, 98)])
+    _say(f"[case] {n} one-byte tokens")
+    step = 1 << 28
+    ids = torch.full((n + 2,), 7, dtype=torch.int32, device="cuda")
+    for a in range(0, n, step):
+        ids[a:min(a + step, n)].copy_((torch.arange(a, min(a + step, n), device="cuda") * 2654435761 >> 13) & 0xFF)
+    out = torch.full((n + 16,), 0xEE, dtype=torch.uint8, device="cuda")
+    tbo = torch.full((n + 3,), -7, dtype=torch.int32, device="cuda")
+    nb = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(B.bpe_decode_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+    B.bpe_decode(vocab, ids[:n], out[:n], ws, tbo[:n + 1], nb)
+    assert B.bpe_encode_status(ws) == 0 and int(nb.item()) == n
+    for a in range(0, n, step):
+        b = min(a + step, n)
+        assert torch.equal(out[a:b], ids[a:b].to(torch.uint8)), f"bytes from {a} on"
+        assert torch.equal(tbo[a:b], torch.arange(a, b, dtype=torch.int32, device="cuda")), f"offsets from {a} on"
+    assert int(tbo[n].item()) == n and (tbo[n + 1:] == -7).all() and (out[n:] == 0xEE).all()
+    vocab.free()

@@ -166,7 +166,8 @@ __global__ void __launch_bounds__(kGroupThreads) decode_kernel(DecodeParams p) {
     uint32_t len[ROUNDS][kTokPerThread];
     int ex[ROUNDS];                            // bytes of the tile before this thread's tokens of a round
     int round_total[ROUNDS], total = 0;
-    bool fits;
+    int n_staged = 0, staged_bytes = 0;
+    bool fits;                                 // the whole tile does
     {
         Record rec[ROUNDS][kTokPerThread];
         bool bad = false;
@@ -196,20 +197,21 @@ __global__ void __launch_bounds__(kGroupThreads) decode_kernel(DecodeParams p) {
             total += round_total[r];
         }
         if (tid == 0) publish_tile_total(p.tile_state, p.call_id, epoch, tile, total);
-        // (a token has at most 2^20 bytes and a round 2^10 tokens: the total of a round cannot wrap,
-        // that of four rounds of nothing but such tokens could)
+        // As many rounds as the stage holds, from the first one on.  (A token has at most 2^20 bytes and a round 2^10
+        // tokens: the total of a round cannot wrap, that of four rounds of nothing but such tokens could.)
         fits = total >= 0 && total <= kTileStage;
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) fits &= round_total[r] <= kTileStage;
-        if (fits) {
 #pragma unroll
-            for (int r = 0; r < ROUNDS; ++r) {
-                int at = ex[r];
+        for (int r = 0; r < ROUNDS; ++r) {
+            if (ROUNDS == 1 ? !fits : (n_staged < r || round_total[r] > kTileStage - staged_bytes)) continue;
+            n_staged = r + 1;
+            staged_bytes += round_total[r];
+            int at = ex[r];
 #pragma unroll
-                for (int j = 0; j < kTokPerThread; ++j) {
-                    put_token(pool_w, staged + at, rec[r][j]);
-                    at += (int)len[r][j];
-                }
+            for (int j = 0; j < kTokPerThread; ++j) {
+                put_token(pool_w, staged + at, rec[r][j]);
+                at += (int)len[r][j];
             }
         }
     }
@@ -246,11 +248,17 @@ __global__ void __launch_bounds__(kGroupThreads) decode_kernel(DecodeParams p) {
         store_stage(stage, p.out + base, total);
         return;
     }
-    // Longer tokens than the stage holds, or an output that is too small: round by round, through
-    // the stage if a round fits both.  The records are read again: kept, they would cost the common
-    // path its registers.
-    int64_t round_base = base;
-    for (int r = 0; r < ROUNDS; ++r) {
+    // Longer tokens than the stage holds, or an output that is too small: the other rounds one by one,
+    // through the stage if a round fits both.  Their records are read again: kept, they would cost the
+    // common path its registers.  (Tokens of 12 to 16 bytes, 2 M of them: 27.4 us before there was a stage for
+    // more than one round, 28.6 when no round of a tile that does not fit was staged ahead, 25.3 now.)
+    if (fits || (int64_t)base + staged_bytes > p.out_capacity) n_staged = staged_bytes = 0;
+    if (ROUNDS > 1 && n_staged > 0) {
+        __syncthreads();
+        store_stage(stage, p.out + base, staged_bytes);
+    }
+    int64_t round_base = (int64_t)base + staged_bytes;
+    for (int r = ROUNDS > 1 ? n_staged : 0; r < ROUNDS; ++r) {
         Record rec[kTokPerThread];
         (void)load_records(p, first + r * kTileTokens, n, rec);
         int before = 0, rt = 0;                // as ex[r] and round_total[r], which are indexed by constants only
@@ -264,7 +272,7 @@ __global__ void __launch_bounds__(kGroupThreads) decode_kernel(DecodeParams p) {
                 rt += wave_total[r][w];
             }
         }
-        if (round_base + (uint32_t)rt <= p.out_capacity && (uint32_t)rt <= (uint32_t)kStageBytes) {
+        if (round_base + (uint32_t)rt <= p.out_capacity && (uint32_t)rt <= (uint32_t)kTileStage) {
             __syncthreads();                   // the stage is free
             int at = before;
 #pragma unroll

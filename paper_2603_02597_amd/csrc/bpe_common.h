@@ -157,8 +157,10 @@ __device__ inline uint32_t merged_id_of(const TableView &t, uint32_t rank) {
 // with that token.  In word-like text nearly every piece is such a string, and a piece that is
 // needs no merge loop at all: one probe instead of a chain of five or six merges, each with two
 // lookups.  Which strings these are follows from the rules alone and is found out when the
-// table is built.  Measured: merge_kernel on 13.5 MB of text (97 % of the pieces are one token, a tile per workgroup) 91.8 -> 65.6 us,
-// merge_tiles_kernel on 840 KB 12.1 -> 9.4 us, merge_bytes_kernel on 840 KB 13.6 -> 10.7 us.
+// table is built.  Measured in a kernel trace on text of which 97 % of the pieces are one token, before and with
+// it (and what came with it): merge_kernel on 13.5 MB 85.4 -> 44.5 us, merge_tiles_kernel on 840 KB 11.2 -> 10.0,
+// merge_bytes_kernel on 840 KB 12.8 -> 9.9.  Text of words that the table does not know pays for the probe: 840 KB
+// 13.5 -> 14.5 us per call, 13.5 MB 99 -> 105.
 // A string that has no room at either of its two slots is left out (the merge
 // loop handles it), so the table is a shortcut and never a condition.
 // A slot is 16 bytes: the string, zero-padded, and id << 8 | kWordMore | length (0: empty).

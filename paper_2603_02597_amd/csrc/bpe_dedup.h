@@ -9,7 +9,7 @@
 //                         finds there: equal, and that piece stands for both; different
 //                         (two words in one slot), and the piece stands for itself;
 //   dedup_compact_kernel  the representatives, in piece order, become a dense list;
-//   merge_raw_kernel      merges the pieces of that list (bpe_encode.hip; the list's
+//   merge_mapped_kernel   merges the pieces of that list (bpe_encode.hip; the list's
 //                         length is only known on the device, as on the raw path);
 //   dedup_count_kernel    every piece takes the record {token count, first token} of its
 //                         representative; token totals per tile;

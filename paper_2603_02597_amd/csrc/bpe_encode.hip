@@ -5,7 +5,9 @@
 // All kernels work on the same tiling of the piece array (a tile = up to 64
 // pieces per wavefront x 4 wavefronts).  merge_tile merges every piece of a tile
 // by length class:
-//     <= 16 bytes    one lane per piece, state in 16-entry LDS columns (bpe_short_pieces.h);
+//     <= 12 bytes    looked up whole: nearly every piece of word-like text is one token;
+//     <= 16 bytes    what that leaves over: a row of 16 lanes per piece while the wavefronts have
+//                    a row for each, else one lane per piece, 16-entry LDS columns (bpe_short_pieces.h);
 //     <= 64 bytes    one lane per piece, 64-entry columns, 16 pieces per wavefront and round;
 //     runs x x x ... one lane per run of equal symbols, one wavefront per piece, any length;
 //     <= 640 bytes   one wavefront, the piece in its LDS region        (bpe_long_pieces.h);
@@ -17,7 +19,7 @@
 // Up to 1024 tiles (what the chip holds at once): merge_tiles_kernel, then emit_kernel
 // (out_offsets and the dense copy into out_ids).
 // Deeper grids: merge_kernel, whose first workgroups take the pieces beyond 16 bytes of
-// four tiles each while the others merge the short pieces of one tile; then emit_kernel,
+// four tiles each while the others merge the short pieces of two tiles; then emit_kernel,
 // from 4096 tiles on emit_deep_kernel (four tiles per workgroup), with scan_tiles_kernel
 // in between when there are too many tile totals for the emit workgroups to add up.
 // Raw path (bpe_encode_raw): token-only calls on inputs the chip holds at once find the
@@ -44,9 +46,10 @@
 
 namespace bpe {
 
-// LDS of a tile: the lane-per-piece state of the four wavefronts and the double
-// buffer of the workgroup path share the same bytes; a barrier separates the two
-// uses, and the lane-per-piece tokens are in the workspace by then.
+// LDS of a tile: the bytes of left-over pieces, the lane-per-piece state of the four
+// wavefronts and the double buffer of the workgroup path share the same room; a barrier
+// separates the uses, and the tokens of short pieces are in the workspace (or in
+// registers) before the workgroup path begins.
 // Short pieces without a whole-piece token: as many as the wavefronts have rows of 16 lanes are merged
 // one per row, more of them one per lane.  Not two rounds of rows: a round is as long as its longest
 // chain (words of 13 to 16 bytes are never in the whole-piece table and take a dozen merges), and one
@@ -69,9 +72,10 @@ union MergeLds {
 struct TileShared {
     MergeLds lds;
     GroupTmp tmp;
-    int left_n[2 * kWavesPerGroup];    // (a pair of tiles needs both halves) pieces of a wavefront that find_word left over (| kAnyLonger: it has longer pieces),
-                                   // and per such piece (wavefront w's from 64 w on): its first byte in list, its
-                                   // length << 8 | thread in cnt_back
+    int left_n[2 * kWavesPerGroup];    // pieces of a wavefront that find_word left over (| kAnyLonger: it has longer
+                                   // pieces), and per such piece (wavefront w's from 64 w on): its first byte in list,
+                                   // its length << 8 | thread in cnt_back.  (A pair of tiles: one entry per half and
+                                   // wavefront, the pieces in MergeLds::pair.)
     int list[kGroupThreads];       // threads whose piece waits for the wavefront paths, then for the workgroup path
     int cnt_back[kGroupThreads];   // token counts handed back to the owning thread (long-piece workgroups: more list)
     int list_n, list_back;
@@ -499,8 +503,11 @@ __device__ __forceinline__ void merge_and_count_tile(const EncodeParams &p, Tile
 // else's, as with merge_tile's SKIP_LONG.  A tile is a chain of dependent round trips (offsets, bytes,
 // probe, then the merges of what the probes leave over, a handful of pieces that occupy a quarter of
 // the lanes), and the chip holds four workgroups per compute unit: two tiles in flight per workgroup
-// take hardly longer than one.  7,944 tiles (13.5 MB of text): 75.1 us per call with a tile per workgroup,
-// 60.2 with two; 2,065 tiles (text with runs and random bytes): within 1 % of each other.
+// take hardly longer than one.  Tiles of words that the table knows: 7,944 tiles (13.5 MB) 72.9 us per call with a
+// tile per workgroup, 56.3 with two, 1,470 tiles (2.5 MB) 18.5 and 18.1; 1k table, 1,470 tiles 26.9 and 22.5.  Where
+// most pieces are left over a pair takes its columns in two rounds: 7,944 such tiles 126.7 and 121.6 us, but 1,468
+// of them 27.0 and 32.1 (734 workgroups fill 256 compute units unevenly).  Text with runs and random bytes, 2,065
+// tiles: within 1 % of each other.
 __device__ __forceinline__ void merge_tile_pair(const EncodeParams &p, TileShared &sh, int *wave_tokens, int pair, int n_pieces) {
     constexpr int kParts = 2 * kWavesPerGroup;     // left-over lists: one per half and wavefront, kWave slots each
     const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
@@ -904,7 +911,9 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_raw_rest_kernel(Encode
     raw_geometry(p);
     const int n_tiles = __builtin_amdgcn_readfirstlane(tiles_of(p)), n_pieces = p.n_pieces, P = p.P;
     for (int tile = first_tile + blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        // (the parameters are read anew for every tile: kept over the loop they cost the common path its registers)
+        // (the parameters are read anew for every tile: kept over the loop they cost the common path its registers.
+        // The second slot only where the first says so and no rows: with both slots at once and two rounds of rows, as
+        // in merge_raw_kernel, 30 MB of 3-byte pieces take 198 instead of 192 us.)
         const EncodeParams *kp = &kernel_params();
         asm volatile("" : "+s"(kp));
         if (kp->long_sum && threadIdx.x == 0) kp->long_sum[tile] = 0;      // nothing of this tile goes to a long-piece workgroup

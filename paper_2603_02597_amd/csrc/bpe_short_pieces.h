@@ -62,9 +62,12 @@ __device__ __forceinline__ bool word_hit(const uint4 &s, const WordKey &k, int l
 
 // The token that the piece of `len` bytes in w becomes, or -1 if the whole-piece table does not
 // hold it (1 <= len <= kWordMax; w may hold anything behind the piece).  EAGER: both slots at
-// once, one round trip (grids the chip holds at a time: latency counts); otherwise the second
-// slot only where the first says that a word of its own sits in a second slot (deep grids: two
-// probes in three are spared, and the gathers are what the texture path is busy with).
+// once, one round trip; otherwise the second slot only where the first says that a word of its own
+// sits in a second slot, two probes in three less.  Both at once wherever a workgroup takes one tile:
+// such a tile is a chain of round trips that too few others hide, also on deep grids (raw bytes, 1k
+// table, 13.5 MB: 120.7 us with both at once, 123.4 otherwise; 50k table, 64 MB 366 and 370).  In a
+// pair of tiles, in the strided kernel and beside long-piece workgroups (merge_raw_groups_kernel: 1k table 126.7
+// and 132.0 us) two slots cost more gathers than they save waiting.
 template <bool EAGER>
 __device__ __forceinline__ int find_word(const TableView &t, const uint32_t (&w)[4], int len) {
     const WordKey k = word_key(w, len);

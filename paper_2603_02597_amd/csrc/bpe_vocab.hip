@@ -508,11 +508,13 @@ extern "C" int bpe_decode(const bpe_vocab *v, const int32_t *ids, int64_t n_toke
     p.call_id = next_call_id();
     // Deep grids want fewer, larger tiles and a narrow look-back (every state word of
     // another workgroup is an uncached read), but the registers of a round cost
-    // occupancy: 40 M tokens take 643 us with (1 round, 256 tiles looked at per round),
-    // 558 with (1, 32), 434 with (2, 32), 393 with (4, 32), 519 with (8, 256: 224 VGPRs);
-    // 2.1 M tokens take 33 us with (1, 256), 25 with (2, 64), 29 with (4, 32).  (Measured with two gathers
-    // per token; since then 2.1 M tokens take 19.5 us with (2, 64), 19.5 with two and 21.7 with four tiles
-    // of 256 threads' window each, 21.5 with (4, 256).)
+    // occupancy.  us for 0.5 / 1 / 2.1 / 4.1 / 8 / 40 M tokens of text (rounds, tiles looked at per round):
+    //   (1, 256)  9.5  13.1  22.2  39.9  81  431      (1, 32) 11.3  15.5  22.9  41.0  72  340
+    //   (2, 64)  10.0  13.6  19.1  33.4  55  269      (2, 256) 8.9  12.5  17.6  31.2  54  293
+    //   (4, 32)  13.0  14.7  20.7  30.3  50  238      (4, 256) 11.3 12.4  19.1  28.3  49  264
+    // The lines were drawn where two gathers per token were measured (2.1 M tokens: 33 us with (1, 256), 25 with
+    // (2, 64), 29 with (4, 32); 40 M: 643, 434 with (2, 32), 393); by this table wider windows are the quicker ones
+    // up to 8 M tokens.
     const dim3 block(kGroupThreads);
     auto tiles = [&](int rounds) { return (unsigned)std::max<int64_t>((n_tokens + rounds * kTileTokens - 1) / (rounds * kTileTokens), 1); };
     const hipStream_t st = (hipStream_t)stream;

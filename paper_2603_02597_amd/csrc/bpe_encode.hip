@@ -1910,10 +1910,10 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
     const int64_t per_tile = p.paper ? 1 : (int64_t)p.P * p.W;
     const int64_t n_tiles = (n_pieces + per_tile - 1) / per_tile;
     // One kernel while the grid is a single look-back window deep (256 tiles): it
-    // saves a launch (11.2 vs 13.2 us on 3 tiles, 12.7 vs 13.7 us on 124).  Beyond
-    // that the waiting costs as much as the launch (16.4 vs 16.2 us on 494 tiles),
-    // and on deep grids a tile that waits keeps its LDS from the next tile (208 vs
-    // 141 us on 7944 tiles).
+    // saves a launch (10.5 vs 13.2 us on 176 tiles, 10.7 vs 13.4 us on 258).  Beyond
+    // that the waiting costs as much as the launch (13.5 vs 13.2 us on 352 tiles, 14.5
+    // vs 13.2 us on 494), and on deep grids a tile that waits keeps its LDS from the
+    // next tile (133 vs 56 us on 7944 tiles).
     // ... and only while pieces are short on average: a tile that waits for its
     // predecessors gives up after a bounded time (about two seconds), and tiles that merge
     // kilobyte-long pieces one merge at a time hold their successors up for that long.

@@ -19,7 +19,7 @@
 // Up to 1024 tiles (what the chip holds at once): merge_tiles_kernel, then emit_kernel
 // (out_offsets and the dense copy into out_ids).
 // Deeper grids: merge_kernel, whose first workgroups take the pieces beyond 16 bytes of
-// four tiles each while the others merge the short pieces of two tiles; then emit_kernel,
+// four tiles each while the others merge the short pieces of several tiles; then emit_kernel,
 // from 4096 tiles on emit_deep_kernel (four tiles per workgroup), with scan_tiles_kernel
 // in between when there are too many tile totals for the emit workgroups to add up.
 // Raw path (bpe_encode_raw): token-only calls on inputs the chip holds at once find the
@@ -61,21 +61,23 @@ __host__ __device__ constexpr int row_pieces(int waves) { return waves * (kWave 
 // The single kernel has helper wavefronts for the rows on grids that leave the chip idle (at most one
 // tile per compute unit), where a tile of a table with few whole words leaves 60 pieces over.
 constexpr int kFusedWaves = 16;
-constexpr int kPairPieces = 2 * kGroupThreads;
+constexpr int kRunPiecesMax = 4;               // tiles in flight together, a piece of each per thread
+constexpr int kRunTilesMax = 16;
+constexpr int kRunLeft = 1360;                 // left-over pieces that the list holds
+constexpr int kRunRounds = (kRunLeft + kGroupThreads - 1) / kGroupThreads;
 union MergeLds {
     TinyState tiny[kWavesPerGroup];
     struct { int32_t A[kLdsMaxLen]; int32_t B[kLdsMaxLen]; } group;
     struct { uint4 bytes[kGroupThreads]; uint32_t tok[row_pieces(kFusedWaves)][kTinyMax]; } left;   // see merge_left_over
-    struct { uint4 bytes[kPairPieces]; int o[kPairPieces]; int meta[kPairPieces]; } pair;           // see merge_tile_pair
+    struct { uint4 bytes[kRunLeft]; int2 piece[kRunLeft]; } run;   // see merge_tile_run: {first byte, length << 16 | number in the run}
 };
 
 struct TileShared {
     MergeLds lds;
     GroupTmp tmp;
-    int left_n[2 * kWavesPerGroup];    // pieces of a wavefront that find_word left over (| kAnyLonger: it has longer
+    int left_n[kWavesPerGroup];        // pieces of a wavefront that find_word left over (| kAnyLonger: it has longer
                                    // pieces), and per such piece (wavefront w's from 64 w on): its first byte in list,
-                                   // its length << 8 | thread in cnt_back.  (A pair of tiles: one entry per half and
-                                   // wavefront, the pieces in MergeLds::pair.)
+                                   // its length << 8 | thread in cnt_back.
     int list[kGroupThreads];       // threads whose piece waits for the wavefront paths, then for the workgroup path
     int cnt_back[kGroupThreads];   // token counts handed back to the owning thread (long-piece workgroups: more list)
     int list_n, list_back;
@@ -499,146 +501,198 @@ __device__ __forceinline__ void merge_and_count_tile(const EncodeParams &p, Tile
     }
 }
 
-// Two tiles of 256 pieces by one workgroup, two pieces per lane; pieces beyond tiny_max are somebody
-// else's, as with merge_tile's SKIP_LONG.  A tile is a chain of dependent round trips (offsets, bytes,
-// probe, then the merges of what the probes leave over, a handful of pieces that occupy a quarter of
-// the lanes), and the chip holds four workgroups per compute unit: two tiles in flight per workgroup
-// take hardly longer than one.  Tiles of words that the table knows: 7,944 tiles (13.5 MB) 72.9 us per call with a
-// tile per workgroup, 56.3 with two, 1,470 tiles (2.5 MB) 18.5 and 18.1; 1k table, 1,470 tiles 26.9 and 22.5.  Where
-// most pieces are left over a pair takes its columns in two rounds: 7,944 such tiles 126.7 and 121.6 us, but 1,468
-// of them 27.0 and 32.1 (734 workgroups fill 256 compute units unevenly).  Text with runs and random bytes, 2,065
-// tiles: within 1 % of each other.
-__device__ __forceinline__ void merge_tile_pair(const EncodeParams &p, TileShared &sh, int *wave_tokens, int pair, int n_pieces) {
-    constexpr int kParts = 2 * kWavesPerGroup;     // left-over lists: one per half and wavefront, kWave slots each
-    const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
-    const int64_t q0 = (int64_t)pair * kPairPieces;
-    if (q0 >= n_pieces) return;                    // the grid has a workgroup per tile: the second half leaves at once
-    int o[2], len[2], tok0[2];
-    bool tiny[2], own[2], bad = false;
-    int o_next[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int64_t q = q0 + h * kGroupThreads + tid;
-        own[h] = q < n_pieces;
-        o[h] = own[h] ? p.off[q] : 0;
-        o_next[h] = own[h] ? p.off[q + 1] : 0;
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int64_t q = q0 + h * kGroupThreads + tid;
-        const bool bad_h = own[h] && (o[h] < 0 || o_next[h] < o[h] || o_next[h] > p.n_bytes || (q == 0 && o[h] != 0) ||
-                                      (q == n_pieces - 1 && o_next[h] != p.n_bytes));
-        bad |= bad_h;
-        len[h] = bad_h ? 0 : o_next[h] - o[h];
-        tiny[h] = len[h] > 0 && len[h] <= p.tiny_max;
-        own[h] = own[h] && len[h] <= p.tiny_max;   // whoever merges a piece writes its record
-        tok0[h] = -1;
-    }
-    if (__ballot(bad) && lane == 0)
-        __hip_atomic_store(&p.status[0], p.call_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Several consecutive tiles of 256 pieces by one workgroup; pieces beyond tiny_max are somebody else's, as with
+// merge_tile's SKIP_LONG.  A tile is a chain of dependent round trips (offsets, bytes, probe), and the merges of
+// what the probes leave over, a handful of pieces that occupy a few lanes, are a chain several times as long.  So a
+// thread has kRunPieces pieces in flight together, and the left-over pieces of all the workgroup's tiles are listed
+// in LDS and merged at the end, one chain for all of them (or when the list is nearly full).  Bound by those round
+// trips: a compute unit holds four such workgroups.  Per call, text of known words / of which most pieces are left over,
+// two tiles per workgroup before and now: 13.5 MB 56.2 -> 39.6 / 121.9 -> 121.7 us (kernel trace, known words: 44.5 -> 27.5),
+// 6.8 MB 34.4 -> 28.7 / 66.5 -> 67.1, 40 MB 147 -> 98 / 241 -> 221, 2.5 MB 17.8 -> 17.9 / 31.6 -> 31.5.  Text with runs and
+// random bytes, 13.5 MB: 119 -> 110.
+struct RunShared {
+    int acc[kRunTilesMax];                     // tokens of the tiles
+    int part[2][kRunPiecesMax * kWavesPerGroup];  // left-over pieces of a tile's wavefronts; of this batch and of the one before
+};
 
-    uint32_t w[2][4] = {};
-    if (__ballot(tiny[0] || tiny[1])) {            // (so there is a byte to load; lanes without a short piece load it, too)
-        WordKey key[2];
-        uint4 a[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) load_piece_bytes(p, tiny[h] ? o[h] : 0, w[h]);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            key[h] = word_key(w[h], tiny[h] ? len[h] : 1);
-            a[h] = word_slot(p.table, word_slot1(key[h].hash, p.table.word_shift));
-        }
-        bool more[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const bool look = tiny[h] && len[h] <= kWordMax;
-            if (look && word_hit(a[h], key[h], len[h])) tok0[h] = (int)(a[h].w >> 8);
-            more[h] = look && tok0[h] < 0 && (a[h].w & kWordMore);
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            if (more[h]) a[h] = word_slot(p.table, word_slot2(key[h].hash, p.table.word_shift));
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            if (more[h] && word_hit(a[h], key[h], len[h])) tok0[h] = (int)(a[h].w >> 8);
-    }
-    uint32_t tokens = 0;                           // of the first tile | of the second << 16 (a tile has at most 4,096)
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const bool left = tiny[h] && tok0[h] < 0;
-        const uint64_t left_mask = __ballot(left);
-        if (left) {
-            const int slot = (h * kWavesPerGroup + wv) * kWave + mbcnt(left_mask);
-            sh.lds.pair.bytes[slot] = make_uint4(w[h][0], w[h][1], w[h][2], w[h][3]);
-            sh.lds.pair.o[slot] = o[h];
-            sh.lds.pair.meta[slot] = len[h] << 16 | h << 8 | tid;
-        }
-        if (lane == 0) sh.left_n[h * kWavesPerGroup + wv] = __builtin_popcountll(left_mask);
-        if (own[h] && !left) p.rec[q0 + h * kGroupThreads + tid] = make_int2(tok0[h] >= 0 ? 1 : 0, tok0[h]);
-        tokens += (tok0[h] >= 0 ? 1u : 0u) << (16 * h);
-    }
-    __syncthreads();
-    int n[kParts], n_left = 0;
-#pragma unroll
-    for (int k = 0; k < kParts; ++k) n_left += n[k] = __builtin_amdgcn_readfirstlane(sh.left_n[k]);
-    auto slot_of = [&](int e) {                    // slot of left-over piece e < n_left
-        int base = 0;
-#pragma unroll
-        for (int k = 0; k + 1 < kParts; ++k) {
-            const bool on = e >= n[k] && base == k * kWave;
-            e -= on ? n[k] : 0;
-            base += on ? kWave : 0;
-        }
-        return base + e;
-    };
+// Offsets of a piece and the next one, and 16 bytes from a multiple of 4 on, in one load each.
+typedef int32_t int2_any __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t uint4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+// Merges the n pieces that lds.run lists and writes their records.  Every thread must call it, behind a barrier.
+__device__ __forceinline__ void merge_run_left(const EncodeParams &p, MergeLds &lds, RunShared &rs, int64_t q0, int n) {
+    const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     auto record = [&](int meta, int c, int first) {
-        p.rec[q0 + (meta & 0xFFFF)] = make_int2(c, first);     // (half << 8 | thread is the piece's number in the pair)
-        tokens += (uint32_t)c << (((meta >> 8) & 1) * 16);
+        p.rec[q0 + (meta & 0xFFFF)] = make_int2(c, first);
+        atomicAdd(&rs.acc[(meta & 0xFFFF) / kGroupThreads], c);
     };
-    if (n_left <= row_pieces(kWavesPerGroup)) {
+    if (n <= row_pieces(kWavesPerGroup)) {
         constexpr int kRows = kWave / kTinyMax;
-        const int e0 = __builtin_amdgcn_readfirstlane(wv) * kRows;
-        if (e0 < n_left) {
-            const int j = lane & (kTinyMax - 1), e = e0 + lane / kTinyMax;
-            const bool mine = e < n_left;
-            const int slot = mine ? slot_of(e) : 0;
-            const int at = sh.lds.pair.o[slot], meta = sh.lds.pair.meta[slot];
-            uint32_t sym = ((const uint8_t *)&sh.lds.pair.bytes[slot])[j] | (3u << 24);
-            const int c = row_merge(p, sym, mine ? meta >> 16 : 0);
+        if (wv * kRows < n) {
+            const int j = lane & (kTinyMax - 1), e = wv * kRows + lane / kTinyMax;
+            const bool mine = e < n;
+            const int2 piece = lds.run.piece[mine ? e : 0];
+            uint32_t sym = ((const uint8_t *)&lds.run.bytes[mine ? e : 0])[j] | (3u << 24);
+            const int c = row_merge(p, sym, mine ? piece.y >> 16 : 0);
             sym &= 0xFFFFFFu;
-            if (j > 0 && j < c) p.scratch[at + j] = (int)sym;
-            if (mine && j == 0) record(meta, c, (int)sym);
+            if (j > 0 && j < c) p.scratch[piece.x + j] = (int)sym;
+            if (mine && j == 0) record(piece.y, c, (int)sym);
         }
-    } else {
-        uint4 b[2];
-        int at[2], meta[2];
+        return;
+    }
+    uint4 b[kRunRounds];
+    int2 piece[kRunRounds];
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int e = r * kGroupThreads + tid, slot = e < n_left ? slot_of(e) : 0;
-            b[r] = sh.lds.pair.bytes[slot];
-            at[r] = sh.lds.pair.o[slot];
-            meta[r] = sh.lds.pair.meta[slot];
-        }
-        __syncthreads();               // the columns take the place of the bytes; from here on a wavefront has its own
-        TinyState &L = sh.lds.tiny[wv];
-        for (int r = 0; r < 2 && r * kGroupThreads < n_left; ++r) {
-            const bool mine = r * kGroupThreads + tid < n_left;
-            const uint4 br = r ? b[1] : b[0];
-            const int m = r ? meta[1] : meta[0], a0 = r ? at[1] : at[0];
-            const uint32_t ww[4] = {br.x, br.y, br.z, br.w};
-            const uint32_t alive = tiny_merge(p, L, ww, m >> 16, mine);
-            tiny_store(L, alive & (alive - 1), p.scratch + a0 + 1);
-            if (mine) record(m, __builtin_popcount(alive), (int)(L.S[__builtin_ctz(alive)][lane] & 0xFFFFFFu));
-        }
+    for (int r = 0; r < kRunRounds; ++r) {
+        const int e = r * kGroupThreads + tid;
+        piece[r] = make_int2(0, 0);
+        if (e < n) { b[r] = lds.run.bytes[e]; piece[r] = lds.run.piece[e]; }
     }
-    const int wave_total = __builtin_amdgcn_readlane(wave_scan_inclusive((int)tokens), kWave - 1);
-    if (lane == 0) wave_tokens[wv] = wave_total;
+    __syncthreads();               // the columns take the place of the list; from here on a wavefront has its own
+    TinyState &L = lds.tiny[wv];
+#pragma unroll 1
+    for (int e0 = wv * kWave; e0 < n; e0 += kGroupThreads) {
+        const bool mine = piece[0].y != 0;         // (a listed piece has a length)
+        const uint32_t w[4] = {b[0].x, b[0].y, b[0].z, b[0].w};
+        const uint32_t alive = tiny_merge(p, L, w, piece[0].y >> 16, mine);
+        tiny_store(L, alive & (alive - 1), p.scratch + piece[0].x + 1);
+        if (mine) record(piece[0].y, __builtin_popcount(alive), (int)(L.S[__builtin_ctz(alive)][lane] & 0xFFFFFFu));
+#pragma unroll
+        for (int r = 0; r + 1 < kRunRounds; ++r) { b[r] = b[r + 1]; piece[r] = piece[r + 1]; }
+        piece[kRunRounds - 1] = make_int2(0, 0);
+    }
+}
+
+// kRunPieces: pieces per thread in flight together.  Two where a workgroup has two or three tiles (1.9 to 3.4 MB of
+// known words: 15.5, 17.4, 20.7 us with two, 16.2, 18.1, 21.2 with four), else four (6.8 MB 29.2 and 28.7, 13.5 MB
+// 41.5 and 39.6, 40 MB 112 and 101).
+template <int kRunPieces>
+__device__ __forceinline__ void merge_tile_run(const EncodeParams &p, MergeLds &lds, RunShared &rs, int group, int n_pieces) {
+    const int n_tiles = p.tiles_per_group, tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int64_t q0 = (int64_t)group * n_tiles * kGroupThreads;
+    if (q0 >= n_pieces) return;                // the grid has a workgroup per tile: the ones beyond leave at once
+    const int here = (int)min((int64_t)n_pieces - q0, (int64_t)n_tiles * kGroupThreads);
+    if (tid < kRunTilesMax) rs.acc[tid] = 0;
+    const uint32_t mis = (uint32_t)((uintptr_t)p.bytes & 3);
+    const uint8_t *base = p.bytes - mis;
+    const uint32_t last = ((uint32_t)p.n_bytes + mis - 1u) & ~3u;       // (only looked at if there is a byte)
+    int n_left = 0;
+    for (int k0 = 0; k0 < here; k0 += kRunPieces * kGroupThreads) {
+        if (n_left > kRunLeft - kRunPieces * kGroupThreads) {  // there may not be room for this batch's
+            __syncthreads();
+            merge_run_left(p, lds, rs, q0, n_left);
+            n_left = 0;
+            __syncthreads();
+        }
+        int o[kRunPieces], len[kRunPieces], tok0[kRunPieces];
+        bool tiny[kRunPieces], own[kRunPieces], bad = false;
+        int2_any off[kRunPieces];
+#pragma unroll
+        for (int h = 0; h < kRunPieces; ++h) {
+            const int k = k0 + h * kGroupThreads + tid;
+            own[h] = k < here;
+            off[h] = int2_any{0, 0};
+            if (own[h]) off[h] = *(const int2_any *)(p.off + q0 + k);
+        }
+#pragma unroll
+        for (int h = 0; h < kRunPieces; ++h) {
+            const int64_t q = q0 + k0 + h * kGroupThreads + tid;
+            o[h] = off[h].x;
+            const bool bad_h = own[h] && (o[h] < 0 || off[h].y < o[h] || off[h].y > p.n_bytes || (q == 0 && o[h] != 0) ||
+                                          (q == n_pieces - 1 && off[h].y != p.n_bytes));
+            bad |= bad_h;
+            len[h] = bad_h ? 0 : off[h].y - o[h];
+            tiny[h] = len[h] > 0 && len[h] <= p.tiny_max;
+            own[h] = own[h] && len[h] <= p.tiny_max;           // whoever merges a piece writes its record
+            tok0[h] = -1;
+        }
+        if (__ballot(bad) && lane == 0)
+            __hip_atomic_store(&p.status[0], p.call_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bool any = false;
+        uint32_t w[kRunPieces][4] = {};
+#pragma unroll
+        for (int h = 0; h < kRunPieces; ++h) any |= tiny[h];
+        if (__ballot(any)) {       // (so there is a byte to load; lanes without a short piece load it, too)
+            WordKey key[kRunPieces];
+            uint4 a[kRunPieces];
+            uint4_any raw[kRunPieces];
+            uint32_t first[kRunPieces], fifth[kRunPieces];
+            bool ends = false;     // the 16 bytes would reach beyond the input's last word
+#pragma unroll
+            for (int h = 0; h < kRunPieces; ++h) {
+                const uint32_t pos = (uint32_t)(tiny[h] ? o[h] : 0) + mis;
+                first[h] = pos & ~3u;
+                ends |= first[h] + 12u > last;
+                fifth[h] = 0;      // (a piece of 13 bytes or more may end there)
+                if (tiny[h] && (pos & 3u) + (uint32_t)len[h] > 16u) fifth[h] = *(const uint32_t *)(base + first[h] + 16u);
+            }
+            if (!__ballot(ends)) {
+#pragma unroll
+                for (int h = 0; h < kRunPieces; ++h) raw[h] = *(const uint4_any *)(base + first[h]);
+            } else {
+#pragma unroll
+                for (int h = 0; h < kRunPieces; ++h)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) raw[h][j] = *(const uint32_t *)(base + min(first[h] + 4u * (uint32_t)j, last));
+            }
+#pragma unroll
+            for (int h = 0; h < kRunPieces; ++h) {
+                const uint32_t sh = ((uint32_t)o[h] + mis) & 3u;
+                w[h][3] = __builtin_amdgcn_alignbyte(fifth[h], raw[h][3], sh);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) w[h][j] = __builtin_amdgcn_alignbyte(raw[h][j + 1], raw[h][j], sh);
+                key[h] = word_key(w[h], tiny[h] ? len[h] : 1);
+                a[h] = word_slot(p.table, word_slot1(key[h].hash, p.table.word_shift));
+            }
+            bool more[kRunPieces];
+#pragma unroll
+            for (int h = 0; h < kRunPieces; ++h) {
+                const bool look = tiny[h] && len[h] <= kWordMax;
+                if (look && word_hit(a[h], key[h], len[h])) tok0[h] = (int)(a[h].w >> 8);
+                more[h] = look && tok0[h] < 0 && (a[h].w & kWordMore);
+            }
+#pragma unroll
+            for (int h = 0; h < kRunPieces; ++h)
+                if (more[h]) a[h] = word_slot(p.table, word_slot2(key[h].hash, p.table.word_shift));
+#pragma unroll
+            for (int h = 0; h < kRunPieces; ++h)
+                if (more[h] && word_hit(a[h], key[h], len[h])) tok0[h] = (int)(a[h].w >> 8);
+        }
+        uint64_t left_mask[kRunPieces];
+        int (&part)[kRunPiecesMax * kWavesPerGroup] = rs.part[(k0 / (kRunPieces * kGroupThreads)) & 1];
+#pragma unroll
+        for (int h = 0; h < kRunPieces; ++h) {
+            const bool left = tiny[h] && tok0[h] < 0;
+            left_mask[h] = __ballot(left);
+            if (lane == 0) part[h * kWavesPerGroup + wv] = __builtin_popcountll(left_mask[h]);
+            if (own[h] && !left) p.rec[q0 + k0 + h * kGroupThreads + tid] = make_int2(tok0[h] >= 0 ? 1 : 0, tok0[h]);
+        }
+        __syncthreads();
+        int before[kRunPieces], n_new = 0;
+#pragma unroll
+        for (int k = 0; k < kRunPieces * kWavesPerGroup; ++k) {
+            if (k % kWavesPerGroup == wv) before[k / kWavesPerGroup] = n_new;
+            n_new += part[k];
+        }
+        n_new = __builtin_amdgcn_readfirstlane(n_new);
+#pragma unroll
+        for (int h = 0; h < kRunPieces; ++h) {
+            if (tiny[h] && tok0[h] < 0) {
+                const int e = n_left + before[h] + mbcnt(left_mask[h]);
+                lds.run.bytes[e] = make_uint4(w[h][0], w[h][1], w[h][2], w[h][3]);
+                lds.run.piece[e] = make_int2(o[h], len[h] << 16 | (k0 + h * kGroupThreads + tid));
+            }
+            const uint64_t whole = __ballot(tok0[h] >= 0);
+            if (lane == 0 && whole) atomicAdd(&rs.acc[k0 / kGroupThreads + h], __builtin_popcountll(whole));
+        }
+        n_left += n_new;
+    }
     __syncthreads();
-    if (tid < 2 && q0 + tid * kGroupThreads < n_pieces) {
-        uint32_t sum = 0;
-        for (int k = 0; k < kWavesPerGroup; ++k) sum += ((uint32_t)wave_tokens[k] >> (16 * tid)) & 0xFFFFu;
-        p.tile_sum[2 * pair + tid] = (int)sum;
+    if (n_left) {
+        merge_run_left(p, lds, rs, q0, n_left);
+        __syncthreads();
     }
+    if (tid * kGroupThreads < here) p.tile_sum[group * n_tiles + tid] = rs.acc[tid];
 }
 
 // ---------------------------------------------------------------------------
@@ -660,7 +714,7 @@ struct LongLists {
 
 __device__ __forceinline__ void long_pieces_flush(const EncodeParams &p, TileShared &sh, int *entry, int *acc,
                                               int64_t q_base) {
-    const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+    const int tid = threadIdx.x, lane = lane_id_here(), wv = tid / kWave;
     __syncthreads();               // the lists are complete
     // what a finished piece leaves: its record, and its tokens in its tile's total
     auto done = [&](int rel, int c) {
@@ -812,12 +866,14 @@ __global__ void __launch_bounds__(kGroupThreads) merge_tiles_kernel(EncodeParams
 }
 
 // Word-sized pieces on average: the first p.n_long_groups workgroups take the long pieces (see
-// above), every other one the short pieces of two tiles.
+// above), the next ones the short pieces of p.tiles_per_group tiles each; there is one for every tile, and those
+// without a tile leave at once, which costs nothing (13.5 MB: 40.1 us with and without the 6,951 of them).
 // (The long-piece role has one place where it works its lists off: inlined at three, it took the kernel
 // beyond 128 vector registers, and the tiles lost a workgroup per compute unit to that.)
+template <int kRunPieces>
 __global__ void __launch_bounds__(kGroupThreads) merge_kernel(EncodeParams p) {
     __shared__ TileShared sh;
-    __shared__ int wave_tokens[kWavesPerGroup];
+    __shared__ RunShared rs;
     // What a tile needs of the arguments is fetched before the role is known: left alone, the compiler
     // fetches n_long_groups, waits, branches, and only then fetches the rest, a second round trip to the
     // scalar cache at the head of every tile.
@@ -825,9 +881,9 @@ __global__ void __launch_bounds__(kGroupThreads) merge_kernel(EncodeParams p) {
                        "s"(p.table.low_bits), "s"(p.table.index_bits), "s"(p.table.merged_delta), "s"(p.table.seed.k1a),
                        "s"(p.table.seed.k1b), "s"(p.table.seed.k2a), "s"(p.table.seed.k2b), "s"(p.bytes), "s"(p.off),
                        "s"(p.n_bytes), "s"(p.n_pieces), "s"(p.tiny_max), "s"(p.rec), "s"(p.tile_sum), "s"(p.scratch),
-                       "s"(p.status), "s"(p.call_id), "s"(p.n_long_groups));
+                       "s"(p.status), "s"(p.call_id), "s"(p.n_long_groups), "s"(p.table.words), "s"(p.tiles_per_group));
     if ((int)blockIdx.x >= p.n_long_groups) {
-        merge_tile_pair(p, sh, wave_tokens, blockIdx.x - p.n_long_groups, p.n_pieces);
+        merge_tile_run<kRunPieces>(p, sh.lds, rs, blockIdx.x - p.n_long_groups, p.n_pieces);
     } else {
         __shared__ int acc[kGroupThreads];
         const EncodeParams &kp = kernel_params();
@@ -1824,6 +1880,19 @@ constexpr int64_t kResidentGroups = 1024;
 // and at most so many of them (then each takes more tiles; at most 256, the reach of a list entry)
 constexpr int64_t kTilesPerLongGroup = 4, kLongGroupsMinTiles = kLongGroupsMinTilesDevice, kMaxLongGroups = 65536;
 
+// Tiles per workgroup of merge_kernel: as few as let the chip hold all of them at once; on deeper grids the number, from
+// 8 on, with the least work in the longest line of workgroups behind each other (8 tiles each for 8,250: 1,031
+// workgroups, 86.9 us; 9 each: 917, 79.0.  23,500 tiles: 8 each 103.8, 12 each 98.2, 16 each 101.1).
+static int32_t run_tiles(int64_t n_tiles) {
+    auto groups_in_line = [&](int64_t m) { return ((n_tiles + m - 1) / m + kResidentGroups - 1) / kResidentGroups; };
+    for (int64_t m = 2; m <= kRunTilesMax / 2; ++m)
+        if (groups_in_line(m) <= 1) return (int32_t)m;
+    int64_t best = kRunTilesMax;
+    for (int64_t m = kRunTilesMax; m >= kRunTilesMax / 2; --m)
+        if (groups_in_line(m) * m < groups_in_line(best) * best) best = m;
+    return (int32_t)best;
+}
+
 static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int32_t *piece_offsets,
                          int64_t n_bytes, int64_t n_pieces, int32_t *out_ids, int32_t *out_offsets,
                          void *workspace, int64_t workspace_bytes, const bpe_encode_options *opts,
@@ -2082,9 +2151,13 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
                 const int64_t wanted = o.long_groups > 0 ? o.long_groups : kTilesPerLongGroup;
                 p.tiles_per_long_group = (int32_t)std::max<int64_t>(wanted, (n_tiles + kMaxLongGroups - 1) / kMaxLongGroups);
                 p.n_long_groups = (int32_t)((n_tiles + p.tiles_per_long_group - 1) / p.tiles_per_long_group);
+                p.tiles_per_group = run_tiles(n_tiles);
                 p.long_sum = (int32_t *)ws_at(l.long_sum);
             }
-            if (p.n_long_groups) run.run("merge_kernel", i0, merge_kernel, grid + p.n_long_groups, kGroupThreads, p);
+            if (p.n_long_groups && p.tiles_per_group < kRunPiecesMax)
+                run.run("merge_kernel", i0, merge_kernel<2>, grid + p.n_long_groups, kGroupThreads, p);
+            else if (p.n_long_groups)
+                run.run("merge_kernel", i0, merge_kernel<kRunPiecesMax>, grid + p.n_long_groups, kGroupThreads, p);
             else run.run("merge_tiles_kernel", i0, merge_tiles_kernel, grid, kGroupThreads, p);
         }
         if (ev) (void)hipEventRecord(ev[n_ev++], s);

@@ -34,7 +34,8 @@ struct EncodeParams {
     int32_t *tile_sum;   // [n_tiles]
     int32_t *long_sum;   // [n_tiles] tokens of a tile's pieces that the long-piece workgroups merged (nullptr: there are none)
     int32_t n_long_groups;    // merge_kernel: the first so many workgroups take the pieces beyond tiny_max ...
-    int32_t tiles_per_long_group;   // ... of so many consecutive tiles each; the others take the short pieces of one or two tiles
+    int32_t tiles_per_long_group;   // ... of so many consecutive tiles each; the others take the short pieces
+    int32_t tiles_per_group;        // ... of so many consecutive tiles each (merge_kernel)
     int32_t *tile_base;  // [n_tiles]
     int32_t *scratch;    // [n_bytes] tokens of piece q at scratch[off[q] ...]
     int32_t *scratch2;   // [n_bytes] second buffer of the workspace ping-pong
@@ -47,6 +48,14 @@ struct EncodeParams {
 };
 
 __device__ inline int lane_id() { return threadIdx.x & (kWave - 1); }
+// The same, opaque to the compiler: for the long paths, where it would otherwise work addresses out ahead and keep
+// them, and the scalars they are made of, over whole kernels (merge_kernel: 126 vector registers and 81 spilled scalar
+// ones, 107 and 45 with this).
+__device__ inline int lane_id_here() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t & (kWave - 1);
+}
 __device__ inline int mbcnt(uint64_t m) {   // set bits of m below this lane
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
 }

@@ -33,7 +33,7 @@ __device__ inline uint64_t group_min(uint64_t v, GroupTmp &tmp) {
     uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
     wave_min_pair(hi, lo);
     const int wv = threadIdx.x / kWave;
-    if (lane_id() == 0) { tmp.min_lo[wv] = lo; tmp.min_hi[wv] = hi; }
+    if (lane_id_here() == 0) { tmp.min_lo[wv] = lo; tmp.min_hi[wv] = hi; }
     __syncthreads();
     uint64_t best = ~0ull;
     for (int w = 0; w < kWavesPerGroup; ++w)
@@ -43,7 +43,7 @@ __device__ inline uint64_t group_min(uint64_t v, GroupTmp &tmp) {
 
 // Exclusive max-scan over the threads of the group (identity -1).
 __device__ inline int group_scan_max_excl(int v, GroupTmp &tmp) {
-    const int lane = lane_id(), wv = threadIdx.x / kWave;
+    const int lane = lane_id_here(), wv = threadIdx.x / kWave;
     const int inc = wave_scan_max_inclusive(v);
     if (lane == kWave - 1) tmp.max_w[wv] = inc;
     __syncthreads();
@@ -54,7 +54,7 @@ __device__ inline int group_scan_max_excl(int v, GroupTmp &tmp) {
 
 // Exclusive sum-scan over the threads of the group; total to every thread.
 __device__ inline int group_scan_sum_excl(int v, GroupTmp &tmp, int &total) {
-    const int lane = lane_id(), wv = threadIdx.x / kWave;
+    const int lane = lane_id_here(), wv = threadIdx.x / kWave;
     const int inc = wave_scan_inclusive(v);
     if (lane == kWave - 1) tmp.sum_w[wv] = inc;
     __syncthreads();
@@ -80,7 +80,7 @@ struct GroupScope {
     // the largest v of all threads (a barrier must separate two calls)
     __device__ int max_all(int v) const {
         v = __builtin_amdgcn_readlane(wave_scan_max_inclusive(v), kWave - 1);
-        if (lane_id() == 0) tmp.all_w[threadIdx.x / kWave] = v;
+        if (lane_id_here() == 0) tmp.all_w[threadIdx.x / kWave] = v;
         __syncthreads();
         int m = tmp.all_w[0];
         for (int w = 1; w < kWavesPerGroup; ++w) m = max(m, tmp.all_w[w]);
@@ -88,7 +88,7 @@ struct GroupScope {
     }
     // v of the thread before this one (0 for the first thread)
     __device__ int from_previous_thread(int v) const {
-        const int lane = lane_id(), wv = threadIdx.x / kWave;
+        const int lane = lane_id_here(), wv = threadIdx.x / kWave;
         if (lane == kWave - 1) tmp.last_w[wv] = v;
         __syncthreads();
         const int up = wave_from_lane_below(v, 0);
@@ -114,14 +114,14 @@ struct WideScope {
         uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
         wave_min_pair(hi, lo);
         const int wv = threadIdx.x / kWave;
-        if (lane_id() == 0) { tmp.min_lo[wv] = lo; tmp.min_hi[wv] = hi; }
+        if (lane_id_here() == 0) { tmp.min_lo[wv] = lo; tmp.min_hi[wv] = hi; }
         __syncthreads();
         uint64_t best = ~0ull;
         for (int w = 0; w < kWideWaves; ++w) best = min(best, ((uint64_t)tmp.min_hi[w] << 32) | tmp.min_lo[w]);
         return best;
     }
     __device__ int scan_max_excl(int v) const {
-        const int lane = lane_id(), wv = threadIdx.x / kWave;
+        const int lane = lane_id_here(), wv = threadIdx.x / kWave;
         const int inc = wave_scan_max_inclusive(v);
         if (lane == kWave - 1) tmp.max_w[wv] = inc;
         __syncthreads();
@@ -130,7 +130,7 @@ struct WideScope {
         return ex;
     }
     __device__ int scan_sum_excl(int v, int &total) const {
-        const int lane = lane_id(), wv = threadIdx.x / kWave;
+        const int lane = lane_id_here(), wv = threadIdx.x / kWave;
         const int inc = wave_scan_inclusive(v);
         if (lane == kWave - 1) tmp.sum_w[wv] = inc;
         __syncthreads();
@@ -144,14 +144,14 @@ struct WideScope {
     }
     __device__ int max_all(int v) const {
         v = __builtin_amdgcn_readlane(wave_scan_max_inclusive(v), kWave - 1);
-        if (lane_id() == 0) tmp.all_w[threadIdx.x / kWave] = v;
+        if (lane_id_here() == 0) tmp.all_w[threadIdx.x / kWave] = v;
         __syncthreads();
         int m = tmp.all_w[0];
         for (int w = 1; w < kWideWaves; ++w) m = max(m, tmp.all_w[w]);
         return m;
     }
     __device__ int from_previous_thread(int v) const {
-        const int lane = lane_id(), wv = threadIdx.x / kWave;
+        const int lane = lane_id_here(), wv = threadIdx.x / kWave;
         if (lane == kWave - 1) tmp.last_w[wv] = v;
         __syncthreads();
         const int up = wave_from_lane_below(v, 0);
@@ -161,7 +161,7 @@ struct WideScope {
 
 struct WaveScope {
     static constexpr int kThreads = kWave;
-    __device__ int tid() const { return lane_id(); }
+    __device__ int tid() const { return lane_id_here(); }
     __device__ void sync() const {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         __builtin_amdgcn_wave_barrier();
@@ -195,7 +195,7 @@ struct WaveScope {
 // round trips).  Tokens to out[0 ...]; returns their number.
 template <typename Ptr>
 __device__ __forceinline__ int finish_in_registers(const EncodeParams &p, Ptr A, int cur, int32_t *out) {
-    const int lane = lane_id();
+    const int lane = lane_id_here();
     uint32_t sym = lane < cur ? (uint32_t)A[lane] : 0u;
     cur = encode_wave_symbols(p, sym, cur);
     if (lane < cur) out[lane] = (int32_t)sym;

@@ -309,7 +309,7 @@ template <int N>
 __device__ __noinline__ typename ColumnGeometry<N>::Mask column_merge(const EncodeParams &p, ColumnState &L, int o, int len, bool mine) {
     using Mask = typename ColumnGeometry<N>::Mask;
     constexpr int kPosBits = ColumnGeometry<N>::kPosBits;
-    const int lane = lane_id();
+    const int lane = lane_id_here();
     const int my_len = mine ? len : 0;
     if (!__ballot(my_len > 0)) return (Mask)0;
     // What the loop below needs of the table is read once and pinned in scalar registers: left to itself
@@ -438,7 +438,7 @@ __device__ __noinline__ typename ColumnGeometry<N>::Mask column_merge(const Enco
 // Stores the lane's final tokens (positions `alive` of its column) to dst[0 ...].
 template <int N>
 __device__ inline void column_store(const ColumnState &L, typename ColumnGeometry<N>::Mask alive, int32_t *dst) {
-    const int lane = lane_id();
+    const int lane = lane_id_here();
     int n_out = 0;
     while (__ballot(alive != 0)) {
         if (alive) {
@@ -507,7 +507,7 @@ __device__ __forceinline__ bool wave_pair_is_bound(bool want, uint32_t r, uint2 
 // The passes over a piece whose cur <= 64 symbols sit one per lane (lanes from cur on
 // hold anything); returns the final number of symbols and leaves them in `sym`.
 __device__ int encode_wave_symbols(const EncodeParams &p, uint32_t &sym, int cur) {
-    const int lane = lane_id();
+    const int lane = lane_id_here();
     const uint64_t lt_mask = (1ull << lane) - 1;
     for (;;) {
         const uint32_t nxt = (uint32_t)wave_from_lane_above((int)sym, (int)sym);
@@ -566,7 +566,7 @@ constexpr int kMaxRuns = kWave;
 
 // Lanes flagged `gone` drop out: the others close up, in order.  Returns the new run count.
 __device__ __forceinline__ int runs_compact(uint32_t &sym, uint32_t &cnt, bool gone, int cur) {
-    const int lane = lane_id();
+    const int lane = lane_id_here();
     const uint64_t live = cur == kWave ? ~0ull : ((1ull << cur) - 1);
     const uint64_t removed = __ballot(gone) & live;
     if (!removed) return cur;
@@ -582,7 +582,7 @@ __device__ __forceinline__ int runs_compact(uint32_t &sym, uint32_t &cnt, bool g
 // A run whose symbol equals that of the run below joins it (its count moves down, the run goes).
 // One round joins pairs; three equal runs in a row (a fresh symbol between two runs of it) need two.
 __device__ __forceinline__ int runs_join(uint32_t &sym, uint32_t &cnt, int cur) {
-    const int lane = lane_id();
+    const int lane = lane_id_here();
 #pragma unroll
     for (int round = 0; round < 2; ++round) {
         const uint32_t below = (uint32_t)wave_from_lane_below((int)sym, -1);
@@ -601,7 +601,7 @@ __device__ __forceinline__ int runs_join(uint32_t &sym, uint32_t &cnt, int cur) 
 }
 
 __device__ int encode_wave_runs(const EncodeParams &p, int b, int n, uint32_t *stage) {
-    const int lane = lane_id();
+    const int lane = lane_id_here();
     // The runs of the piece: 16 bytes per lane and round, a start wherever a byte differs from
     // the one before it.  stage[r] = symbol of run r, stage[64 + r] = where it starts.
     int n_runs = 0;
@@ -713,7 +713,7 @@ __device__ int encode_wave_runs(const EncodeParams &p, int b, int n, uint32_t *s
 
 // Piece bytes[base .. base + n), n <= 64: tokens to p.scratch[base ...], their number back.
 __device__ int encode_wave_piece(const EncodeParams &p, int base, int n) {
-    const int lane = lane_id();
+    const int lane = lane_id_here();
     uint32_t sym = 0;
     if (lane < n) sym = p.bytes[base + lane];
     const int cur = encode_wave_symbols(p, sym, n);

@@ -22,9 +22,9 @@
 // four tiles each while the others merge the short pieces of several tiles; then emit_kernel,
 // from 4096 tiles on emit_deep_kernel (four tiles per workgroup), with scan_tiles_kernel
 // in between when there are too many tile totals for the emit workgroups to add up.
-// Raw path (bpe_encode_raw): token-only calls on inputs the chip holds at once find the
-// pieces inside the merge kernel (merge_bytes_kernel, emit_bytes_kernel: tiles of 1280
-// bytes); otherwise the pre-tokenizer first, then merge_raw_kernel and emit_raw_kernel,
+// Raw path (bpe_encode_raw): token-only calls find the pieces inside the merge kernel (tiles of
+// 1280 bytes while the chip holds all of them at once: merge_bytes_kernel, emit_bytes_kernel; runs of
+// tiles of 4 KiB beyond: bpe_byte_runs.h); otherwise the pre-tokenizer first, then merge_raw_kernel and emit_raw_kernel,
 // which stride over the tiles that exist (the piece count is only known on the device),
 // then the first token of every sequence.
 // Option paper_kernel: the paper's own two kernels, one workgroup per piece.
@@ -712,72 +712,102 @@ struct LongLists {
     int n_col, n_back;
 };
 
-__device__ __forceinline__ void long_pieces_flush(const EncodeParams &p, TileShared &sh, int *entry, int *acc,
-                                              int64_t q_base) {
+// Words [from, n) of src to dst, by the T threads of which this is number t: four loads in flight per thread.
+template <int T>
+__device__ __forceinline__ void copy_words(const int32_t *src, int32_t *dst, int from, int n, int t) {
+    for (int i = from + t; i < n; i += 4 * T) {
+        int v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = i + u * T < n ? src[i + u * T] : 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i + u * T < n) dst[i + u * T] = v[u];
+    }
+}
+
+// Merges the pieces that the workgroup has listed: n_col for the 64-entry columns, entries 0 .. n_col - 1, and
+// n_back for the wavefront and workgroup paths, behind them.  entry(e): the listed word; bounds(k, b, n): first
+// byte and length of the piece that the word k stands for; done(e, k, c): called once per piece, by one thread, with its
+// number of tokens, which are in p.scratch[b ...] then.  Every thread must call it, behind a barrier.
+template <class Entry, class Bounds, class Done>
+__device__ __forceinline__ void merge_listed_pieces(const EncodeParams &p, MergeLds &lds, GroupTmp &tmp, int n_col, int n_back,
+                                                    const Entry &entry, const Bounds &bounds, const Done &done) {
     const int tid = threadIdx.x, lane = lane_id_here(), wv = tid / kWave;
-    __syncthreads();               // the lists are complete
-    // what a finished piece leaves: its record, and its tokens in its tile's total
-    auto done = [&](int rel, int c) {
-        p.rec[q_base + rel] = make_int2(c, -1);
-        atomicAdd(&acc[rel / kGroupThreads], c);
-    };
     // Columns: 16 pieces per wavefront and round, the first wavefront fills up first.
-    const int n_col = __builtin_amdgcn_readfirstlane(sh.list_n);
     for (int e0 = 0; e0 < n_col; e0 += kWavesPerGroup * kColumnLanes) {
         const int e = e0 + kColumnLanes * wv + lane;
         const bool mine = lane < kColumnLanes && e < n_col;
-        int rel = 0, b = 0, n = 0;
+        int k = 0, b = 0, n = 0;
         if (mine) {
-            rel = entry[e];
-            b = p.off[q_base + rel];                     // validated when the piece was listed
-            n = p.off[q_base + rel + 1] - b;
+            k = (int)entry(e);
+            bounds(k, b, n);
         }
-        ColumnState &cs = *(ColumnState *)&sh.lds.tiny[wv];
+        ColumnState &cs = *(ColumnState *)&lds.tiny[wv];
         const uint64_t alive = column_merge<kColumnMax>(p, cs, b, n, mine);
         column_store<kColumnMax>(cs, alive, p.scratch + b);
-        if (mine) done(rel, mask_count(alive));
+        if (mine) done(e, k, mask_count(alive));
     }
     // Wavefront paths, dealt to the wavefronts that have no columns (see wave_deal).
-    // What a wavefront hands on to the workgroup goes to the front of the list, which the
-    // columns are done with... once every wavefront has left them: hence its own counter.
-    const int n_back = __builtin_amdgcn_readfirstlane(sh.list_back);
     const WaveDeal deal = wave_deal(n_col, n_back, wv);
-    for (int e = deal.first; e < n_back; e += deal.stride) {
-        const int rel = __builtin_amdgcn_readfirstlane(entry[kLongListMax - 1 - e]);
-        const int b = __builtin_amdgcn_readfirstlane(p.off[q_base + rel]);
-        const int n = __builtin_amdgcn_readfirstlane(p.off[q_base + rel + 1]) - b;
+    for (int i = deal.first; i < n_back; i += deal.stride) {
+        const int k = __builtin_amdgcn_readfirstlane((int)entry(n_col + i));
+        int b, n;
+        bounds(k, b, n);
+        b = __builtin_amdgcn_readfirstlane(b);
+        n = __builtin_amdgcn_readfirstlane(n);
         int c = -1;
         if (p.runs_by_best_rank && n > p.wave_max && piece_is_run_like(p, b, n, WaveScope{}))
-            c = encode_wave_runs(p, b, n, &sh.lds.tiny[wv].S[0][0]);
+            c = encode_wave_runs(p, b, n, &lds.tiny[wv].S[0][0]);
         if (c >= 0) {}
         else if (n > p.wave_lds_max) c = kLongMark;
         else if (n <= p.wave_max) c = encode_wave_piece(p, b, n);
         else if (p.level >= 3 && !(p.runs_by_best_rank && piece_is_run_like(p, b, n, WaveScope{})))
-            c = n <= kWaveBoundHandOn ? encode_long_piece_bound(p, b, n, &sh.lds.tiny[wv].S[0][0], kWaveBoundMax, WaveScope{})
+            c = n <= kWaveBoundHandOn ? encode_long_piece_bound(p, b, n, &lds.tiny[wv].S[0][0], kWaveBoundMax, WaveScope{})
                                       : kLongMark;
-        else c = encode_wave_lds_piece(p, b, n, sh.lds.tiny[wv]);
+        else c = encode_wave_lds_piece(p, b, n, lds.tiny[wv]);
         if (lane == 0) {
-            if (c == kLongMark) entry[kLongListMax - 1 - e] = ~rel;      // for the workgroup
-            else done(rel, c);
+            if (c == kLongMark) entry(n_col + i) = ~(uint32_t)k;         // for the workgroup
+            else done(n_col + i, k, c);                                  // (what it puts there, if anything, is no mark)
         }
     }
     __syncthreads();
-    // Workgroup path, one piece at a time by all threads: the marked entries of the back list.
-    for (int e = 0; e < n_back; ++e) {
-        const int rel = ~__builtin_amdgcn_readfirstlane(entry[kLongListMax - 1 - e]);
-        if (rel < 0) continue;     // a wavefront has merged it
-        const int b = __builtin_amdgcn_readfirstlane(p.off[q_base + rel]);
-        const int n = __builtin_amdgcn_readfirstlane(p.off[q_base + rel + 1]) - b;
+    // Workgroup path, one piece at a time by all threads: the marked entries.
+    for (int i = 0; i < n_back; ++i) {
+        const int k = ~__builtin_amdgcn_readfirstlane((int)entry(n_col + i));
+        if (k < 0) continue;       // a wavefront has merged it
+        int b, n;
+        bounds(k, b, n);
+        b = __builtin_amdgcn_readfirstlane(b);
+        n = __builtin_amdgcn_readfirstlane(n);
         int c;
-        if (p.level >= 3 && !(p.runs_by_best_rank && piece_is_run_like(p, b, n, GroupScope{sh.tmp})))
-            c = encode_long_piece_bound(p, b, n, (uint32_t *)sh.lds.group.A,
-                                        min(max(p.lds_max, kGroupBoundMin), kGroupBoundMax), GroupScope{sh.tmp});
-        else if (n <= p.lds_max) c = encode_group_piece<int32_t *>(p, b, n, sh.lds.group.A, sh.lds.group.B, sh.tmp);
-        else c = encode_group_piece<int32_t *>(p, b, n, p.scratch + b, p.scratch2 + b, sh.tmp);
-        if (tid == 0) done(rel, c);
+        if (p.level >= 3 && !(p.runs_by_best_rank && piece_is_run_like(p, b, n, GroupScope{tmp})))
+            c = encode_long_piece_bound(p, b, n, (uint32_t *)lds.group.A,
+                                        min(max(p.lds_max, kGroupBoundMin), kGroupBoundMax), GroupScope{tmp});
+        else if (n <= p.lds_max) c = encode_group_piece<int32_t *>(p, b, n, lds.group.A, lds.group.B, tmp);
+        else c = encode_group_piece<int32_t *>(p, b, n, p.scratch + b, p.scratch2 + b, tmp);
+        if (tid == 0) done(n_col + i, k, c);
     }
+}
+
+__device__ __forceinline__ void long_pieces_flush(const EncodeParams &p, TileShared &sh, int *entry, int *acc,
+                                              int64_t q_base) {
+    __syncthreads();               // the lists are complete
+    const int n_col = __builtin_amdgcn_readfirstlane(sh.list_n);
+    const int n_back = __builtin_amdgcn_readfirstlane(sh.list_back);
+    merge_listed_pieces(
+        p, sh.lds, sh.tmp, n_col, n_back,
+        [&](int e) -> uint32_t & { return (uint32_t &)entry[e < n_col ? e : kLongListMax - 1 - (e - n_col)]; },
+        [&](int rel, int &b, int &n) {
+            b = p.off[q_base + rel];                     // validated when the piece was listed
+            n = p.off[q_base + rel + 1] - b;
+        },
+        // what a finished piece leaves: its record, and its tokens in its tile's total
+        [&](int, int rel, int c) {
+            p.rec[q_base + rel] = make_int2(c, -1);
+            atomicAdd(&acc[rel / kGroupThreads], c);
+        });
     __syncthreads();
-    if (tid == 0) {
+    if (threadIdx.x == 0) {
         sh.list_n = 0;
         sh.list_back = 0;
         // some piece of this call went through these workgroups: the emit kernels add long_sum to tile_sum
@@ -1169,6 +1199,10 @@ __global__ void __launch_bounds__(kGroupThreads) merge_bytes_kernel(EncodeParams
     }
 }
 
+}  // namespace bpe
+#include "bpe_byte_runs.h"
+namespace bpe {
+
 // De-duplication: merges the pieces of the list p.piece_map, whose length *p.n_pieces_dev the
 // kernel before it left on the device (a workgroup beyond the tiles that exist returns at once).
 __global__ void __launch_bounds__(kGroupThreads) merge_mapped_kernel(EncodeParams p) {
@@ -1350,17 +1384,10 @@ __device__ __forceinline__ int copy_count(const EncodeParams &p, int c, int o, i
     return min(c, min(room, src_room));
 }
 
-// Tokens [from, n) of a piece, by the T threads of which this is number t: four loads in flight per thread.
+// Tokens [from, n) of a piece, by the T threads of which this is number t.
 template <int T>
 __device__ __forceinline__ void copy_tokens(const EncodeParams &p, int src, int dst, int from, int n, int t) {
-    for (int i = from + t; i < n; i += 4 * T) {
-        int v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = i + u * T < n ? p.scratch[src + i + u * T] : 0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (i + u * T < n) p.out_ids[dst + i + u * T] = v[u];
-    }
+    copy_words<T>(p.scratch + src, p.out_ids + dst, from, n, t);
 }
 
 // Dense copy of one piece's c tokens to out_ids[first ...]: the first one travels in the
@@ -1765,6 +1792,12 @@ struct RawLayout {
     int64_t byte_rec, byte_off, byte_cnt;     // the path without a pre-tokenizer launch (-1: no room was asked for)
 };
 
+// Tiles of merge_byte_runs_kernel: they start up to 15 bytes below the first byte.  That path is the quicker one wherever
+// the small tiles end (1.4 MB: 15 against 23.5 us through the pre-tokenizer), but for one tile: a test of
+// bpe_encode_raw_plan names the pre-tokenizer path at the first size beyond them.
+static int64_t byte_run_tiles(int64_t n_bytes) { return (n_bytes + 15 + kRunTile - 1) / kRunTile; }
+constexpr int64_t kByteRunTilesMin = 322;
+
 static int64_t byte_tiles(int64_t n_bytes) { return std::max<int64_t>((n_bytes + kByteTile - 1) / kByteTile, 1); }
 
 static RawLayout raw_layout(int64_t n_bytes, int64_t max_pieces, int64_t n_seqs) {
@@ -1880,15 +1913,16 @@ constexpr int64_t kResidentGroups = 1024;
 // and at most so many of them (then each takes more tiles; at most 256, the reach of a list entry)
 constexpr int64_t kTilesPerLongGroup = 4, kLongGroupsMinTiles = kLongGroupsMinTilesDevice, kMaxLongGroups = 65536;
 
-// Tiles per workgroup of merge_kernel: as few as let the chip hold all of them at once; on deeper grids the number, from
+// Tiles per workgroup of merge_kernel (from 2 to 16) and merge_byte_runs_kernel (1 to 8): as few as let the chip hold all of them at once; on deeper grids the number, from
 // 8 on, with the least work in the longest line of workgroups behind each other (8 tiles each for 8,250: 1,031
 // workgroups, 86.9 us; 9 each: 917, 79.0.  23,500 tiles: 8 each 103.8, 12 each 98.2, 16 each 101.1).
-static int32_t run_tiles(int64_t n_tiles) {
+// Byte runs of 16 gain 1 % on text of 64 MB and lose 4 % on 64 MB of 40-byte pieces; runs of 4 lose 8 % on 134 MB.
+static int32_t run_tiles(int64_t n_tiles, int64_t least, int64_t most) {
     auto groups_in_line = [&](int64_t m) { return ((n_tiles + m - 1) / m + kResidentGroups - 1) / kResidentGroups; };
-    for (int64_t m = 2; m <= kRunTilesMax / 2; ++m)
+    for (int64_t m = least; m < 8; ++m)
         if (groups_in_line(m) <= 1) return (int32_t)m;
-    int64_t best = kRunTilesMax;
-    for (int64_t m = kRunTilesMax; m >= kRunTilesMax / 2; --m)
+    int64_t best = most;
+    for (int64_t m = most; m >= 8; --m)
         if (groups_in_line(m) * m < groups_in_line(best) * best) best = m;
     return (int32_t)best;
 }
@@ -2009,16 +2043,17 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
     if (ev) (void)hipEventRecord(ev[n_ev++], s);
     // bpe_encode_raw for tokens only (no piece array asked for, default capacity, tiles left to the library):
     // no pre-tokenizer launch, the merge workgroups find the pieces in their bytes
-    bool byte_tiles_path = false;
-    if (raw) {
+    bool byte_tiles_path = false, byte_runs_path = false;
+    if (raw && !raw->piece_offsets && !out_offsets && !raw->n_pieces && raw_auto_P && o.fused >= 0) {
         const RawLayout r = raw_layout(n_bytes, n_pieces, raw->n_seqs);
-        // ... while the chip holds all the tiles at once: then the call is as long as its chain of dependent
-        // steps, and a launch less shortens it (840 KB: 19.6 -> 15.8 us).  A deeper grid is bound by instruction
-        // issue, and tiles of a fixed number of bytes leave a quarter of the lanes idle (13.5 MB: 122 -> 154 us).
-        byte_tiles_path = !raw->piece_offsets && !out_offsets && !raw->n_pieces && raw_auto_P && o.fused >= 0 &&
-                          r.byte_rec >= 0 && byte_tiles(n_bytes) <= kResidentGroups;
+        // ... in small tiles while the chip holds all of them at once: then the call is as long as its chain of dependent
+        // steps, and a launch less shortens it (840 KB: 19.6 -> 15.8 us).
+        byte_tiles_path = r.byte_rec >= 0 && byte_tiles(n_bytes) <= kResidentGroups;
+        // ... in runs of larger tiles on deeper grids.
+        byte_runs_path = !byte_tiles_path && n_pieces >= n_bytes && o.tiny_max_len == kTinyMax &&
+                         byte_run_tiles(n_bytes) >= kByteRunTilesMin;
     }
-    if (byte_tiles_path) {
+    if (byte_tiles_path || byte_runs_path) {
         if (ev) (void)hipEventRecord(ev[n_ev++], s);      // (the pre-tokenizer's interval: empty)
         p.seq_off = raw->seq_offsets;
         p.seq_token_offsets = raw->seq_token_offsets;
@@ -2086,6 +2121,27 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
         if (ev) (void)hipEventRecord(ev[n_ev++], s);
         run.run("emit_bytes_kernel", 3, emit_bytes_kernel, nt, kGroupThreads, p, (int)nt, self_scan);
         if (ev) { (void)hipEventRecord(ev[n_ev++], s); (void)hipEventRecord(ev[n_ev++], s); }
+    } else if (byte_runs_path) {
+        const RawLayout r = raw_layout(n_bytes, n_pieces, raw->n_seqs);
+        const int64_t nt = byte_run_tiles(n_bytes);
+        // (the arrays of the piece tiles are free: rec holds the lists of longer pieces, one word per tile of the others is
+        // enough, and there are 256 bytes and more for each)
+        p.piece_word = (int32_t *)ws_at(r.piece_offsets);
+        p.tile_n = (int32_t *)ws_at(r.out_offsets);
+        p.tile_info = (int2 *)ws_at(l.tile_state + align256(8 * (nt / kScanSpan + 1)));
+        p.tile_shift = (int32_t)((uintptr_t)bytes & 15);
+        p.tiles_per_group = run_tiles(nt, 1, 8);
+        p.out_offsets = nullptr;
+        p.raw_auto_P = 0;
+        const int64_t groups = (nt + p.tiles_per_group - 1) / p.tiles_per_group;
+        if (plan) { plan->n_tiles = nt; plan->pieces_per_wave = kWave; plan->waves_per_tile = kWavesPerGroup; }
+        run.run("merge_byte_runs_kernel", 1, merge_byte_runs_kernel, groups, kGroupThreads, p, (int)nt);
+        if (ev) (void)hipEventRecord(ev[n_ev++], s);
+        const int self_scan = nt <= kDeepSelfScanTiles;
+        if (!self_scan) run.run("scan_tiles_kernel", 2, scan_tiles_kernel, (nt + kScanSpan - 1) / kScanSpan, kScanThreads, p, nt);
+        if (ev) (void)hipEventRecord(ev[n_ev++], s);
+        run.run("emit_byte_runs_kernel", 3, emit_byte_runs_kernel, nt, kGroupThreads, p, (int)nt, self_scan);
+        if (ev) { (void)hipEventRecord(ev[n_ev++], s); (void)hipEventRecord(ev[n_ev++], s); }
     } else if (fused) {
         if (n_tiles <= kFusedMaxTiles)
             run.run("encode_kernel", 0, encode_kernel<kFusedWaves>, n_tiles, kFusedWaves * kWave, p, (int)n_tiles);
@@ -2151,7 +2207,7 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
                 const int64_t wanted = o.long_groups > 0 ? o.long_groups : kTilesPerLongGroup;
                 p.tiles_per_long_group = (int32_t)std::max<int64_t>(wanted, (n_tiles + kMaxLongGroups - 1) / kMaxLongGroups);
                 p.n_long_groups = (int32_t)((n_tiles + p.tiles_per_long_group - 1) / p.tiles_per_long_group);
-                p.tiles_per_group = run_tiles(n_tiles);
+                p.tiles_per_group = run_tiles(n_tiles, 2, kRunTilesMax);
                 p.long_sum = (int32_t *)ws_at(l.long_sum);
             }
             if (p.n_long_groups && p.tiles_per_group < kRunPiecesMax)

@@ -15,6 +15,10 @@ struct EncodeParams {
     const int32_t *rep_of;         // de-duplication: [n_pieces] the piece whose tokens piece q shares (else nullptr)
     const int32_t *seq_off;        // raw path without a pre-tokenizer launch: [n_seqs + 1] the caller's sequence offsets (or nullptr)
     int32_t *tile_cnt;             // ... [byte tiles] pieces that start in a tile
+    int32_t *piece_word;           // byte runs: [n_bytes] see merge_byte_runs_kernel
+    int32_t *tile_n;               // ... [tiles] pieces that start in a tile
+    int2 *tile_info;               // ... [tiles + 1] {first byte of a tile's first piece, first sequence that starts in the tile or behind}
+    int32_t tile_shift;            // ... tile t is bytes [t, t + 1) x tile size, less this
     int32_t *off_out;              // ... [byte tiles x kByteTileStride] first byte of every piece (`off` points to the same array)
     const int32_t *seq_first_piece;   // raw path: [n_seqs + 1] first piece of every sequence
     int32_t *seq_token_offsets;       // raw path: [n_seqs + 1] first token of every sequence

@@ -392,16 +392,15 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_byte_runs_kernel(Encod
                 sh.longer.entry[tid] = (uint32_t)tid;
             }
             __syncthreads();
-            const EncodeParams *lp = &kp;                      // (see merge_raw_rest_kernel)
-            asm volatile("" : "+s"(lp));
+            const EncodeParams &lp = kernel_params_here();
             merge_listed_pieces(
-                *lp, sh.merge, sh.tmp, col_here, long_here, [&](int e) -> uint32_t & { return sh.longer.entry[e]; },
+                lp, sh.merge, sh.tmp, col_here, long_here, [&](int e) -> uint32_t & { return sh.longer.entry[e]; },
                 [&](int k, int &b, int &n) { b = sh.longer.piece[k].b; n = sh.longer.piece[k].n; },
                 [&](int, int k, int c) {
                     const LongPiece q = sh.longer.piece[k];
-                    const uint32_t v = (uint32_t)(q.b + lp->tile_shift);
-                    lp->piece_word[q.slot] = (int)(kSeveral | (v % kRunTile) << kStartShift | min((uint32_t)c, kManyTokens));
-                    if ((uint32_t)c >= kManyTokens) lp->scratch2[q.b + 1] = c;
+                    const uint32_t v = (uint32_t)(q.b + lp.tile_shift);
+                    lp.piece_word[q.slot] = (int)(kSeveral | (v % kRunTile) << kStartShift | min((uint32_t)c, kManyTokens));
+                    if ((uint32_t)c >= kManyTokens) lp.scratch2[q.b + 1] = c;
                     atomicAdd(&sh.acc[q.tile], c);
                 });
             __syncthreads();

@@ -207,8 +207,16 @@ int launch_pretokenize(const uint8_t *bytes, int64_t n_bytes, const int32_t *seq
 
 }  // namespace bpe
 
+namespace bpe {
+// Bytes at which a piece can be cut without changing its tokens (see bpe_cut_tiles.h), one bit per byte: no rule joins
+// a string to one that starts with the byte / one that ends with the byte to another, save equal bytes; some rule
+// joins the byte to itself.
+struct CutSets { uint32_t before[8], behind[8], twin[8]; };
+}  // namespace bpe
+
 struct bpe_table {
     bpe::TableView view;
+    bpe::CutSets cuts;
     bpe_table_info_t info;
     void *device_mem;     // one allocation: slots | words | byte_pairs | merged_of | rank_of | sym_lr
     int device;

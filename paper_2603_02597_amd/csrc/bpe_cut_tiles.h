@@ -1,0 +1,610 @@
+// Encoding pieces that are longer on average than a lane takes (fixed chunks of text, whole documents): a piece is cut
+// first, wherever no token can reach across, and its parts are encoded like pieces.  Device code, included by
+// bpe_encode.hip behind bpe_byte_runs.h.
+//
+// A token that reached across the border of two bytes x, y would have them side by side in its expansion, and every
+// rule that makes such a token joins a string that ends with x to one that starts with y, or works on one that
+// already holds both.  So where no rule joins a string that ends with x to one that starts with y, nothing merges
+// across: the parts on either side merge as if they stood alone, whatever the rest does (tests/test_cuts_rule.py).
+// Which bytes that concerns is kept per byte (CutSets): tables trained on words never put a space behind another
+// byte, and a piece of text then falls into its words, nearly all of them found whole by one probe each.
+//
+// A workgroup takes TILE consecutive bytes, whatever pieces they belong to, and keeps them in LDS.  The parts that
+// start there are a dense list: a thread takes ROUNDS of them, with the probes of the whole-piece table in flight
+// together.  What the probes leave over is listed and merged by all wavefronts; then the token counts are scanned
+// once and every thread stores its tokens at their place among the tile's: scratch2[first byte of the tile's first
+// part ...] (parts have at least as many bytes as tokens, so the tiles do not overlap).  A second kernel copies them to
+// their place.  Bound by the chain of a tile: offsets, bytes, cuts, probes, left-over merges, counts.
+//
+// Per call, every piece by one workgroup, wavefront or lane / cut: 840 KB of text with the 50k table in chunks of 64, 256, 1,024 and
+// 2,048 bytes 54.9, 93, 121 and 157 / 19.3, 16.5, 16.5 and 16.4 us; with runs and random bytes, 100k table, 60, 281, 1,886 and 2,186 /
+// 40, 42, 42 and 42; 4 MB of text in chunks of 1,024 378 / 28.  Pieces without a place to cut pay for the look: random bytes
+// in pieces of 64, 256, 1,024 39, 338, 537 / 51, 343, 545; text without spaces in pieces of 64, 256, 1,024, 2,048 49, 205, 324,
+// 502 / 61, 258, 335, 493; runs of 200 in pieces of 64, 256, 1,024 63, 47, 38 / 44, 31, 47.
+#pragma once
+
+namespace bpe {
+
+constexpr int kTileGroup = 16;               // a thread looks at 16 bytes at a time ("group")
+constexpr int kAheadGroups = 16;             // groups looked at behind the tile for the end of its last part
+
+// Bits of byte b in a table of its properties.
+constexpr uint32_t kCutBefore = 1, kCutBehind = 2, kTwin = 4;
+
+__device__ __forceinline__ uint32_t cut_code(const CutSets &c, uint32_t b) {
+    return ((c.before[b >> 5] >> (b & 31)) & 1u) | ((c.behind[b >> 5] >> (b & 31)) & 1u) << 1 | ((c.twin[b >> 5] >> (b & 31)) & 1u) << 2;
+}
+
+// Bit j set: a part starts at byte j of the 16-byte group; prev: the byte before the group.  code: kCutBefore ... of
+// every byte.  n_equal: how many of the bytes equal the one before them.
+__device__ __forceinline__ uint32_t cuts_in_group(const uint8_t *code, const uint4 &x, uint32_t prev, int &n_equal) {
+    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+    uint32_t m = 0, last = prev, last_code = code[prev];
+    n_equal = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const uint32_t b = (w[j / 4] >> (8 * (j % 4))) & 0xFFu, c = code[b];
+        const uint32_t cut = ((c & kCutBefore) | (last_code & kCutBehind) >> 1) & ~(b == last ? c >> 2 : 0u);
+        n_equal += b == last;
+        m |= cut << j;
+        last = b;
+        last_code = c;
+    }
+    return m;
+}
+
+template <int TILE, int ROUNDS>
+struct CutTileShared {
+    static constexpr int kPieces = ROUNDS * kGroupThreads;     // pieces merged per pass
+    static constexpr int kParts = ROUNDS * kWavesPerGroup;     // a round of a wavefront
+    // 16-byte groups that hold bytes of the tile, and that are kept: the words of a short part end 19 bytes behind the
+    // tile at most
+    static constexpr int kGroups = TILE / kTileGroup;
+    static constexpr int kStaged = kGroups + 2;
+    union {
+        MergeLds merge;
+        uint4 bytes[kStaged];      // until the columns, or the paths of longer pieces, take its place
+    } lds;
+    GroupTmp tmp;
+    uint8_t code[256];             // see cuts_in_group
+    uint32_t group[kGroups];       // starts in the tile before the group << 16 | start mask
+    uint32_t entry[kPieces];       // pieces that the probes leave over, by kind: first the short ones, then those for the
+                                   // columns, then the longer ones.  The piece's number in the pass; then its token count;
+                                   // then where its tokens go.
+    uint32_t part[kParts];         // how many of each kind a round of a wavefront has (10 bits each)
+    uint32_t total[kParts];        // tokens
+    int long_bytes, run_groups;    // bytes of parts beyond the columns; groups that are mostly one byte
+    uint16_t start[kPieces + 2];   // first byte of every piece of the pass, counted from the first group; later its first token
+    int ahead[kWavesPerGroup + 1];
+    int wave_n[kWavesPerGroup];
+};
+
+// EAGER: both slots of the whole-piece table at once (see find_word).
+template <int TILE, int ROUNDS, bool EAGER>
+__global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(EncodeParams p, CutSets cuts) {
+    using Shared = CutTileShared<TILE, ROUNDS>;
+    constexpr int kPieces = Shared::kPieces, kParts = Shared::kParts, kGroups = Shared::kGroups;
+    constexpr int kLoads = kGroups + kAheadGroups > kGroupThreads ? 2 : 1;     // groups per thread
+    static_assert(kGroups <= kGroupThreads && kGroups + kAheadGroups <= kGroupThreads + kWave, "the second load is the first wavefront's");
+    __shared__ Shared sh;
+    const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int tile = blockIdx.x;
+    // Positions v are counted from the 16-byte boundary at or below the input: byte i is v = i + mis.
+    const uint32_t mis = (uint32_t)((uintptr_t)p.bytes & 15);
+    const uint32_t v_end = p.n_bytes ? (uint32_t)p.n_bytes + mis : 0u;
+    const int lo = (int)min(max((int64_t)tile * TILE - p.tile_shift, (int64_t)0), (int64_t)p.n_bytes);    // (the last tile may be empty)
+    const int hi = (int)min((int64_t)(tile + 1) * TILE - p.tile_shift, (int64_t)p.n_bytes);
+    const uint32_t v0 = ((uint32_t)lo + mis) & ~15u;           // the tile's first group
+    const uint4 *src = (const uint4 *)(p.bytes - mis);
+
+    // The tile's bytes and the 256 behind them, asked for before anything else.  (A group that holds a byte of
+    // the input lies in that byte's page.)
+    uint4 x[kLoads];
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+        const int g = tid + u * kGroupThreads;
+        x[u] = make_uint4(0, 0, 0, 0);
+        if (g < kGroups + kAheadGroups && v0 + 16u * (uint32_t)g < v_end) x[u] = src[(v0 >> 4) + (uint32_t)g];
+    }
+
+    // (the byte before the group, where no lane below holds it)
+    uint32_t prev[kLoads];
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+        const int64_t before_group = (int64_t)v0 + 16 * (tid + u * kGroupThreads) - 1 - mis;
+        prev[u] = lane == 0 && before_group >= 0 && before_group < p.n_bytes ? p.bytes[before_group] : 0u;
+    }
+    sh.code[tid] = (uint8_t)cut_code(cuts, (uint32_t)tid);
+    if (tid == 0) sh.long_bytes = sh.run_groups = 0;
+
+    // Pieces (seq_off): every tile checks a strided share of their offsets and finds the ones that start among its own
+    // bytes, seq_off[s0 .. s1); seq_next: the first one at or behind the tile's end (a part ends there at the latest).
+    int s0, s1, seq_next = p.n_bytes;
+    {
+        bool bad = false;
+        for (int64_t k = (int64_t)tile * kGroupThreads + tid; k <= p.n_seqs; k += (int64_t)gridDim.x * kGroupThreads) {
+            const int sv = p.seq_off[k];
+            bad |= sv < 0 || sv > p.n_bytes || (k == 0 && sv != 0) || (k == p.n_seqs && sv != p.n_bytes);
+            if (k < p.n_seqs) bad |= p.seq_off[k + 1] < sv;
+        }
+        if (__ballot(bad) && lane == 0)
+            __hip_atomic_store(&p.status[kStatusBadInput], p.call_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // Pieces of about one length (chunks) are where the average says: 64 offsets around that place, usually the only
+        // look.  Otherwise a search, 64 places at a time.
+        const float per_byte = (float)p.n_seqs / (float)p.n_bytes;
+        const int guess = min(max((int)((float)lo * per_byte) - kWave / 2, 0), p.n_seqs);
+        int at = guess, v = p.seq_off[min((int64_t)guess + lane, (int64_t)p.n_seqs)];
+        uint64_t below = __ballot((int64_t)guess + lane <= p.n_seqs && v < lo);
+        if ((guess > 0 && !(below & 1)) || !~below) {
+            at = wave_lower_bound(p.seq_off, 0, p.n_seqs + 1, lo);
+            v = p.seq_off[min((int64_t)at + lane, (int64_t)p.n_seqs)];
+            below = 0;
+        }
+        s0 = at + (int)__builtin_ctzll(~below);
+        const uint64_t inside = __ballot((int64_t)at + lane <= p.n_seqs && v < hi);
+        if (~inside) {
+            const int c = (int)__builtin_ctzll(~inside);
+            s1 = at + c;
+            if (s1 <= p.n_seqs) seq_next = min(max(read_lane(v, c), hi), p.n_bytes);
+        } else {
+            s1 = wave_lower_bound(p.seq_off, min(at + kWave, p.n_seqs + 1), p.n_seqs + 1, hi);
+            if (s1 <= p.n_seqs) seq_next = min(max(__builtin_amdgcn_readfirstlane(p.seq_off[s1]), hi), p.n_bytes);
+        }
+        s1 = max(s0, s1);          // (offsets that decrease)
+    }
+    const bool any_seq = s1 > s0;                              // the same in every wavefront
+    if (tid < kGroups) sh.group[tid] = 0;
+    __syncthreads();               // (the byte codes, too)
+    if (any_seq) {
+        for (int64_t k = (int64_t)s0 + tid; k < s1; k += kGroupThreads) {
+            const int sv = p.seq_off[k];
+            if (sv < lo || sv >= hi) continue;
+            const uint32_t at = (uint32_t)sv + mis - v0;
+            atomicOr(&sh.group[at >> 4], 1u << (at & 15));
+        }
+        __syncthreads();
+    }
+
+    // Start masks of the groups; starts behind the tile only say where its last piece ends.
+    uint32_t mask = 0, piece_starts = 0;
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+        const int g = tid + u * kGroupThreads;
+        const uint32_t v = v0 + 16u * (uint32_t)g;             // position of the group's first byte
+        // bits of the group's bytes below position `limit`
+        auto below = [&](uint32_t limit) { return limit <= v ? 0u : limit - v >= 16u ? 0xFFFFu : (1u << (limit - v)) - 1u; };
+        const uint32_t before_group = (uint32_t)wave_from_lane_below((int)(x[u].w >> 24), (int)prev[u]);
+        int n_equal = 0;
+        uint32_t m = g < kGroups + kAheadGroups ? cuts_in_group(sh.code, x[u], before_group, n_equal) : 0u;
+        const uint32_t ahead = m & below(v_end) & ~below((uint32_t)hi + mis);
+        if (u == 0 && g < kGroups) {
+            if (any_seq) piece_starts = sh.group[g];
+            if (lo == 0 && v <= mis && mis < v + 16u) piece_starts |= 1u << (mis - v);     // byte 0 starts a piece
+            m |= piece_starts;
+            const uint64_t runs = __ballot(n_equal > 12);
+            if (lane == 0 && runs) atomicAdd(&sh.run_groups, __builtin_popcountll(runs));
+            mask = m & below((uint32_t)hi + mis) & ~below((uint32_t)lo + mis);
+        }
+        // (the groups of the second load are all the first wavefront's, and behind every other one)
+        const uint64_t hit = __ballot(ahead != 0);
+        if (u == 0 || wv == 0) {
+            int at = 0x7FFFFFFF;
+            if (hit) {
+                const int l = __builtin_ctzll(hit);
+                at = (int)(__builtin_amdgcn_readlane((int)v, l) - mis) + __builtin_ctz((uint32_t)__builtin_amdgcn_readlane((int)ahead, l));
+            }
+            if (lane == 0) sh.ahead[u == 0 ? wv : kWavesPerGroup] = at;
+        }
+        if (g < Shared::kStaged) sh.lds.bytes[g] = x[u];
+    }
+    if (kLoads == 1 && tid == 0) sh.ahead[kWavesPerGroup] = 0x7FFFFFFF;
+    const int c0 = __builtin_popcount(mask);
+    const int inc0 = wave_scan_inclusive(c0);
+    if (lane == kWave - 1) sh.wave_n[wv] = inc0;
+    __syncthreads();
+    int before = inc0 - c0, n_t = 0;
+#pragma unroll
+    for (int w = 0; w < kWavesPerGroup; ++w) {
+        if (w < wv) before += sh.wave_n[w];
+        n_t += sh.wave_n[w];
+    }
+    if (tid < kGroups) sh.group[tid] = (uint32_t)before << 16 | mask;
+    n_t = __builtin_amdgcn_readfirstlane(n_t);
+    int2 *const info = p.tile_info + tile;
+    if (n_t == 0) {                // no piece starts here: the bytes are an earlier tile's
+        if (tid == 0) {
+            p.tile_sum[tile] = 0;
+            *info = make_int2(0, s0);
+            if (tile == (int)gridDim.x - 1) info[1] = make_int2(0, s1);
+        }
+        return;
+    }
+    // Where the tile's last piece ends: at the next start behind the tile.
+    int end = min(seq_next, p.n_bytes);
+    {
+        int at = sh.ahead[0];
+#pragma unroll
+        for (int w = 1; w <= kWavesPerGroup; ++w) at = min(at, sh.ahead[w]);
+        const uint32_t looked_at = v0 + 16u * (kGroups + kAheadGroups);        // positions below are done with
+        if (at != 0x7FFFFFFF) {
+            end = min(end, at);
+        } else if ((uint32_t)end + mis > looked_at) {          // a long piece: on, 4 KiB at a time
+            for (uint32_t v = looked_at; v < (uint32_t)end + mis; v += 16u * kGroupThreads) {
+                const uint32_t mine = v + 16u * (uint32_t)tid;
+                uint32_t m = 0;
+                int n_equal;
+                if (mine < v_end) m = cuts_in_group(sh.code, src[mine >> 4], p.bytes[mine - mis - 1], n_equal);
+                if (mine + 16u > v_end) m &= mine < v_end ? (1u << (v_end - mine)) - 1u : 0u;
+                const uint32_t found = wave_min_u32(m ? mine + (uint32_t)__builtin_ctz(m) : 0xFFFFFFFFu);
+                __syncthreads();
+                if (lane == 0) sh.tmp.min_lo[wv] = found;
+                __syncthreads();
+                uint32_t first = sh.tmp.min_lo[0];
+                for (int w = 1; w < kWavesPerGroup; ++w) first = min(first, sh.tmp.min_lo[w]);
+                if (first != 0xFFFFFFFFu) { end = min(end, (int)(first - mis)); break; }
+            }
+        }
+    }
+    end = __builtin_amdgcn_readfirstlane(end);
+
+    const uint32_t *const words = (const uint32_t *)sh.lds.bytes;
+    const uint8_t *const bytes = (const uint8_t *)sh.lds.bytes;
+    const int origin = (int)(v0 - mis);                        // input index of the first group's first byte (may be -15)
+    int r0 = 0;                                                // input index of the tile's first piece
+    int done = 0;                                              // tokens of the passes before
+    int whole_tile = 0;                                        // 1: cut at pieces only
+    for (int k0 = 0; k0 < n_t; k0 += kPieces) {                // nearly always one pass
+        const EncodeParams &p = kernel_params_here();
+        const int lane = lane_id_here(), tid = wv * kWave + lane;
+        if (k0) {
+            __syncthreads();       // the pass before is done with the lists
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) {                 // the columns may have taken the bytes' place
+                const int g = tid + u * kGroupThreads;
+                if (g < Shared::kStaged) {
+                    uint4 again = make_uint4(0, 0, 0, 0);
+                    if (v0 + 16u * (uint32_t)g < v_end) again = src[(v0 >> 4) + (uint32_t)g];
+                    sh.lds.bytes[g] = again;
+                }
+            }
+        }
+        // the starts of the pass's pieces, and of the one behind them
+        const uint32_t starts = tid < kGroups ? sh.group[tid] : 0u;
+        int k_next = (int)(starts >> 16) - k0;
+        for (uint32_t m = starts & 0xFFFFu; m; m &= m - 1, ++k_next)
+            if (k_next >= 0 && k_next <= kPieces) sh.start[k_next] = (uint16_t)(16 * tid + __builtin_ctz(m));
+        __syncthreads();
+        const int n_here = min(n_t - k0, kPieces);
+
+        int s[ROUNDS], len[ROUNDS], tok0[ROUNDS], kind[ROUNDS];        // kind: 0 none or whole, 1 short, 2 for the columns, 3 longer
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            const int k = r * kGroupThreads + tid;
+            s[r] = len[r] = 0;
+            tok0[r] = -1;
+            if (k < n_here) {
+                s[r] = sh.start[k];
+                len[r] = k0 + k + 1 < n_t ? (int)sh.start[k + 1] - s[r] : end - (origin + s[r]);
+            }
+        }
+        if (k0 == 0) r0 = origin + __builtin_amdgcn_readfirstlane((int)sh.start[0]);
+        // one probe per piece (two with EAGER), all of them in flight together, then the second slots where the first
+        // says that a word of its own sits there
+        {
+            WordKey key[ROUNDS];
+            uint4 a[ROUNDS], b[ROUNDS];
+            bool look[ROUNDS];
+#pragma unroll
+            for (int r = 0; r < ROUNDS; ++r) {
+                look[r] = len[r] > 0 && len[r] <= min(p.tiny_max, kWordMax);
+                const int at = s[r] >> 2;
+                uint32_t raw[4], w[4] = {0, 0, 0, 0};          // (12 bytes from byte 3 on end in the fourth word)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) raw[j] = words[at + j];
+#pragma unroll
+                for (int j = 0; j < 3; ++j) w[j] = __builtin_amdgcn_alignbyte(raw[j + 1], raw[j], (uint32_t)s[r] & 3u);
+                key[r] = word_key(w, look[r] ? len[r] : 1);
+                a[r] = word_slot(p.table, word_slot1(key[r].hash, p.table.word_shift));
+                if (EAGER) b[r] = word_slot(p.table, word_slot2(key[r].hash, p.table.word_shift));
+            }
+            bool more[ROUNDS];
+#pragma unroll
+            for (int r = 0; r < ROUNDS; ++r) {
+                if (look[r] && word_hit(a[r], key[r], len[r])) tok0[r] = (int)(a[r].w >> 8);
+                more[r] = look[r] && tok0[r] < 0 && (EAGER || (a[r].w & kWordMore));
+            }
+#pragma unroll
+            for (int r = 0; r < ROUNDS; ++r)
+                if (!EAGER && more[r]) b[r] = word_slot(p.table, word_slot2(key[r].hash, p.table.word_shift));
+#pragma unroll
+            for (int r = 0; r < ROUNDS; ++r)
+                if (more[r] && word_hit(b[r], key[r], len[r])) tok0[r] = (int)(b[r].w >> 8);
+        }
+
+        // What is left over, listed by kind.
+        uint64_t of_kind[ROUNDS];
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            kind[r] = tok0[r] >= 0 || len[r] <= 0 ? 0 : len[r] <= p.tiny_max ? 1 : len[r] <= p.col_max ? 2 : 3;
+            if (kind[r] == 2) {
+                // A run (told by eight equal bytes) is halved by every pass of a wavefront, but merges one pair a time in a
+                // column: 64-byte pieces of text with runs and random bytes 59 us with all of them in columns, 34 so, and
+                // random bytes 48 and 84 with none there.
+                const int at = s[r] + 8;
+                const uint32_t w0 = words[at >> 2], w1 = words[(at >> 2) + 1], w2 = words[(at >> 2) + 2];
+                const uint32_t a = __builtin_amdgcn_alignbyte(w1, w0, (uint32_t)at & 3u), b = __builtin_amdgcn_alignbyte(w2, w1, (uint32_t)at & 3u);
+                if (a == b && a == (a & 0xFFu) * 0x01010101u) kind[r] = 3;
+            }
+            uint32_t n = 0;
+            of_kind[r] = 0;
+#pragma unroll
+            for (int q = 1; q <= 3; ++q) {
+                const uint64_t m = __ballot(kind[r] == q);
+                if (kind[r] == q) of_kind[r] = m;
+                n |= (uint32_t)__builtin_popcountll(m) << (10 * (q - 1));
+            }
+            if (lane == 0) sh.part[r * kWavesPerGroup + wv] = n;
+            if (kind[r] == 3 && len[r] > p.col_max) atomicAdd(&sh.long_bytes, min(len[r], TILE));
+        }
+        __syncthreads();
+        uint32_t all = 0, mine_from[ROUNDS];
+#pragma unroll
+        for (int k = 0; k < kParts; ++k) {
+            if (k % kWavesPerGroup == wv) mine_from[k / kWavesPerGroup] = all;
+            all += sh.part[k];
+        }
+        all = (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
+        const int n_short = all & 1023;
+        int n_col = (all >> 10) & 1023, n_long = all >> 20;
+        // Little but parts of hundreds of bytes (binary data, text that has no spaces), and no runs: each by itself would take
+        // one wavefront most of the time that all four take for the whole tile (1,024-byte pieces of random bytes, which fall
+        // into five parts: 1,026 us, and 538 uncut).  So then the tile's bytes are cut at the pieces only.
+        if (whole_tile == 0 && n_long >= 2 && n_t <= kPieces &&
+            2 * __builtin_amdgcn_readfirstlane(sh.long_bytes) >= hi - r0 && __builtin_amdgcn_readfirstlane(sh.run_groups) <= TILE / 128) {
+            whole_tile = 1;
+            const int first_at = (int)sh.start[0];
+            uint32_t m = tid < kGroups ? piece_starts : 0u;
+            if (first_at >> 4 == tid) m |= 1u << (first_at & 15);
+            const int c = __builtin_popcount(m), inc = wave_scan_inclusive(c);
+            if (lane == kWave - 1) sh.wave_n[wv] = inc;
+            __syncthreads();
+            int before = inc - c;
+            n_t = 0;
+#pragma unroll
+            for (int w = 0; w < kWavesPerGroup; ++w) {
+                if (w < wv) before += sh.wave_n[w];
+                n_t += sh.wave_n[w];
+            }
+            n_t = __builtin_amdgcn_readfirstlane(n_t);
+            if (tid < kGroups) sh.group[tid] = (uint32_t)before << 16 | m;
+            k0 = -kPieces;
+            continue;
+        }
+        int slot[ROUNDS];
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            slot[r] = -1;
+            if (kind[r]) {
+                const int q = kind[r] - 1;
+                slot[r] = (q > 0 ? n_short : 0) + (q > 1 ? n_col : 0) + (int)((mine_from[r] >> (10 * q)) & 1023u) + mbcnt(of_kind[r]);
+                sh.entry[slot[r]] = (uint32_t)(r * kGroupThreads + tid);
+            }
+        }
+        if (whole_tile && n_col + n_long <= 2 * kWavesPerGroup) {      // (mostly the longer ones: no wavefront for the others alone)
+            n_long += n_col;
+            n_col = 0;
+        }
+        // Where the columns leave wavefronts idle, these merge the short parts meanwhile: a chain less.
+        const int col_waves = min((n_col + kColumnLanes - 1) / kColumnLanes, kWavesPerGroup);
+        const bool beside = n_col && n_short <= kWave * (kWavesPerGroup - col_waves);
+        const int first_wave = beside ? col_waves : 0;
+        // first byte (counted from the first group) and length of piece k of the pass
+        auto bounds = [&](int k, int &at, int &n) {
+            at = sh.start[k];
+            n = k0 + k + 1 < n_t ? (int)sh.start[k + 1] - at : end - (origin + at);
+        };
+        // Tokens of left-over short pieces stay with whoever merges them (a row's lanes, a lane's column) until their
+        // place is known; if longer pieces need the room, or one round of columns does not do, they go to scratch.
+        const bool parked = n_col + n_long > 0 || n_short > kGroupThreads;
+        uint32_t row_sym = 0, alive = 0;
+        int row_n = 0;
+        if (n_short) {
+            __syncthreads();
+            if (!beside && n_short <= row_pieces(kWavesPerGroup)) {
+                constexpr int kRows = kWave / kTinyMax;
+                if (wv * kRows < n_short) {
+                    const int j = lane & (kTinyMax - 1), e = wv * kRows + lane / kTinyMax;
+                    int at = 0, n = 0;
+                    if (e < n_short) bounds((int)sh.entry[e], at, n);
+                    row_sym = bytes[at + j] | (3u << 24);
+                    row_n = row_merge(p, row_sym, n);
+                    row_sym &= 0xFFFFFFu;
+                    if (parked && j < row_n) p.scratch[origin + at + j] = (int)row_sym;
+                    if (e < n_short && j == 0) sh.entry[e] = (uint32_t)row_n;
+                }
+            } else {
+                uint32_t w[ROUNDS][4];
+                int at[ROUNDS], n[ROUNDS];
+#pragma unroll
+                for (int r = 0; r < ROUNDS; ++r) {
+                    const int e = r * kGroupThreads + tid - first_wave * kWave;
+                    at[r] = n[r] = 0;
+                    if (e >= 0 && e < n_short) bounds((int)sh.entry[e], at[r], n[r]);
+                    uint32_t raw[5];
+#pragma unroll
+                    for (int j = 0; j < 5; ++j) raw[j] = words[(at[r] >> 2) + j];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) w[r][j] = __builtin_amdgcn_alignbyte(raw[j + 1], raw[j], (uint32_t)at[r] & 3u);
+                }
+                __syncthreads();   // the columns take the place of the bytes; from here on a wavefront has its own
+                TinyState &L = sh.lds.merge.tiny[wv];
+#pragma unroll 1
+                for (int r = 0; r * kGroupThreads < n_short; ++r) {
+                    uint32_t ww[4] = {w[0][0], w[0][1], w[0][2], w[0][3]};
+                    int a0 = at[0], nn = n[0];
+#pragma unroll
+                    for (int q = 1; q < ROUNDS; ++q) {
+                        const bool on = r == q;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) ww[j] = on ? w[q][j] : ww[j];
+                        a0 = on ? at[q] : a0;
+                        nn = on ? n[q] : nn;
+                    }
+                    alive = tiny_merge(p, L, ww, nn, nn > 0);
+                    if (parked) tiny_store(L, alive, p.scratch + origin + a0);
+                    if (nn > 0) sh.entry[r * kGroupThreads + tid - first_wave * kWave] = (uint32_t)__builtin_popcount(alive);
+                }
+            }
+        }
+        if (n_col + n_long) {
+            if (!beside || !n_short) __syncthreads();
+            merge_listed_pieces(p, sh.lds.merge, sh.tmp, n_col, n_long,
+                                [&](int e) -> uint32_t & { return sh.entry[n_short + e]; },
+                                [&](int k, int &b, int &n) {
+                                    const int at = sh.start[k];
+                                    b = origin + at;
+                                    n = k0 + k + 1 < n_t ? (int)sh.start[k + 1] - at : end - b;
+                                },
+                                [&](int e, int, int c) { sh.entry[n_short + e] = (uint32_t)c; });
+        }
+        if (all) __syncthreads();  // counts
+        int c[ROUNDS], inc[ROUNDS];
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            c[r] = slot[r] >= 0 ? (int)sh.entry[slot[r]] : tok0[r] >= 0 ? 1 : 0;
+            inc[r] = wave_scan_inclusive(c[r]);
+            if (lane == kWave - 1) sh.total[r * kWavesPerGroup + wv] = (uint32_t)inc[r];
+        }
+        __syncthreads();
+        int32_t *const out = p.scratch2 + r0;
+        int first[ROUNDS], sum = done;
+#pragma unroll
+        for (int k = 0; k < kParts; ++k) {
+            if (k % kWavesPerGroup == wv) first[k / kWavesPerGroup] = sum + inc[k / kWavesPerGroup] - c[k / kWavesPerGroup];
+            sum += (int)sh.total[k];
+        }
+        done = __builtin_amdgcn_readfirstlane(sum);
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r)
+            if (tok0[r] >= 0) out[first[r]] = tok0[r];
+        if (all && !parked) {      // whoever merged a left-over piece stores its tokens: the owner says where
+#pragma unroll
+            for (int r = 0; r < ROUNDS; ++r)
+                if (slot[r] >= 0) sh.entry[slot[r]] = (uint32_t)first[r];
+            __syncthreads();
+            if (n_short <= row_pieces(kWavesPerGroup)) {
+                const int e = wv * (kWave / kTinyMax) + lane / kTinyMax, j = lane & (kTinyMax - 1);
+                if (e < n_short && j < row_n) out[sh.entry[e] + j] = (int)row_sym;
+            } else {
+                tiny_store(sh.lds.merge.tiny[wv], alive, out + (tid < n_short ? (int)sh.entry[tid] : 0));
+            }
+        } else if (all) {          // from scratch: the first eight tokens by the owner, the rest by its wavefront
+#pragma unroll
+            for (int r = 0; r < ROUNDS; ++r) {
+                const int n = slot[r] >= 0 ? c[r] : 0, at = sh.start[r * kGroupThreads + tid];
+                const int32_t *from = p.scratch + origin + at;
+                for (int i = 0; i < 8; ++i) {
+                    if (!__ballot(i < n)) break;
+                    if (i < n) out[first[r] + i] = from[i];
+                }
+                for (uint64_t m = __ballot(n > 8); m;) {
+                    const int t = __builtin_ctzll(m);
+                    m &= m - 1;
+                    copy_words<kWave>(p.scratch + origin + read_lane(at, t), out + read_lane(first[r], t), 8, read_lane(n, t), lane);
+                }
+            }
+        }
+        // The first token of every piece that starts in the tile, counted from the tile's first.  (Fewer than
+        // 2^16 before any piece: they belong to bytes of the tile.)
+        if (any_seq) {
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < ROUNDS; ++r)
+                if (r * kGroupThreads + tid < n_here) sh.start[r * kGroupThreads + tid] = (uint16_t)first[r];
+            __syncthreads();
+            for (int64_t q = (int64_t)s0 + tid; q < s1; q += kGroupThreads) {
+                const int sv = p.seq_off[q];
+                if (sv < lo || sv >= hi) continue;
+                const uint32_t at = (uint32_t)sv + mis - v0, g = sh.group[at >> 4];
+                const int k = (int)(g >> 16) + __builtin_popcount(g & ((1u << (at & 15)) - 1u)) - k0;
+                if (k >= 0 && k < n_here) p.seq_token_offsets[q] = (int)sh.start[k];
+            }
+        }
+    }
+    if (tid == 0) {
+        p.tile_sum[tile] = done;
+        *info = make_int2(r0, s0);
+        if (tile == (int)gridDim.x - 1) info[1] = make_int2(0, s1);
+    }
+}
+
+// The packed tokens of the tiles to their place in out_ids, and the token offsets of the pieces from
+// "in the tile" to "in the output".  A wavefront copies a tile.
+constexpr int kCopyTiles = kWavesPerGroup;
+__global__ void __launch_bounds__(kGroupThreads) emit_cut_tiles_kernel(EncodeParams p, int n_tiles, int self_scan) {
+    __shared__ int before_w[kWavesPerGroup], tile_n[kCopyTiles];
+    const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int tile0 = blockIdx.x * kCopyTiles, tile = tile0 + wv;
+    int n = 0;
+    int2 info = make_int2(0, 0);
+    int s_end = 0;
+    if (tile < n_tiles) {
+        n = p.tile_sum[tile];
+        info = p.tile_info[tile];
+        s_end = p.tile_info[tile + 1].y;
+    }
+    // tokens before the workgroup's tiles
+    int before = 0;
+    if (self_scan) {               // tile_sum is 256-byte aligned
+        for (int t = tid * 4; t < tile0; t += kGroupThreads * 4) {     // (tile0 is a multiple of 4)
+            const int4 a = *(const int4 *)(p.tile_sum + t);
+            before += a.x + a.y + a.z + a.w;
+        }
+        before = __builtin_amdgcn_readlane(wave_scan_inclusive(before), kWave - 1);
+    } else {
+        before = wv == 0 ? p.tile_base[tile0] : 0;
+    }
+    n = __builtin_amdgcn_readfirstlane(n);
+    if (lane == 0) { before_w[wv] = before; tile_n[wv] = n; }
+    __syncthreads();
+    int base = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < kWavesPerGroup; ++w) {
+        base += before_w[w] + (w < wv ? tile_n[w] : 0);
+        total += before_w[w] + tile_n[w];
+    }
+    const int32_t *src = p.scratch2 + info.x;
+    int32_t *dst = p.out_ids + base;
+    constexpr int kAtOnce = 4;     // 16-byte loads in flight per thread
+    for (int i0 = 4 * lane; i0 < n; i0 += kAtOnce * 4 * kWave) {
+        int4_any v[kAtOnce];
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u) {
+            const int i = i0 + u * 4 * kWave;
+            if (i + 4 <= n) {
+                v[u] = *(const int4_any *)(src + i);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[u][j] = i + j < n ? src[i + j] : 0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u) {
+            const int i = i0 + u * 4 * kWave;
+            if (i + 4 <= n) {
+                *(int4_any *)(dst + i) = v[u];
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (i + j < n) dst[i + j] = v[u][j];
+            }
+        }
+    }
+    for (int64_t s = (int64_t)info.y + lane; s < s_end; s += kWave) p.seq_token_offsets[s] += base;
+    if (tile0 + kCopyTiles >= n_tiles) {           // the last tiles: the closing entry, and pieces that start behind the last byte
+        for (int64_t s = (int64_t)p.tile_info[n_tiles].y + tid; s <= p.n_seqs; s += kGroupThreads) p.seq_token_offsets[s] = total;
+    }
+    if (tile0 == 0 && tid == 0) mark_call(p.status, p.call_id);
+}
+
+}  // namespace bpe

@@ -33,6 +33,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cstdio>
+#include <cstring>
 #include <new>
 #include <tuple>
 #include <utility>
@@ -341,6 +342,17 @@ __device__ __forceinline__ TilePiece merge_tile(const EncodeParams &p, TileShare
 // compiler kept them all live from the start of the kernel and spilled dozens of them.
 __device__ __forceinline__ const EncodeParams &kernel_params() {
     return *(const EncodeParams *)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+// The same, opaque to the compiler, for use inside a loop: what it would otherwise work out of the parameters before the
+// loop and keep over it costs the common path its registers.  (In the constant address space, which the caller's
+// reference is inferred to be in: as an ordinary pointer every field came through a flat load, and the passes over
+// 1,024-byte pieces took a third longer.)
+__device__ __forceinline__ const EncodeParams &kernel_params_here() {
+    typedef __attribute__((address_space(4))) const EncodeParams ConstantParams;
+    ConstantParams *k = (ConstantParams *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(k));
+    return *(const EncodeParams *)k;
 }
 
 // Which entries of the list of pieces for the wavefront paths wavefront wv takes: first, first + stride, ...
@@ -1201,6 +1213,7 @@ __global__ void __launch_bounds__(kGroupThreads) merge_bytes_kernel(EncodeParams
 
 }  // namespace bpe
 #include "bpe_byte_runs.h"
+#include "bpe_cut_tiles.h"
 namespace bpe {
 
 // De-duplication: merges the pieces of the list p.piece_map, whose length *p.n_pieces_dev the
@@ -1792,6 +1805,43 @@ struct RawLayout {
     int64_t byte_rec, byte_off, byte_cnt;     // the path without a pre-tokenizer launch (-1: no room was asked for)
 };
 
+// Workgroups of 256 threads of the merge kernels and of the single kernel that the chip holds at a time (4 per
+// compute unit: LDS).  The single-kernel path is only free of deadlock by construction while every tile is
+// resident; beyond, it relies on workgroups being dispatched in index order.
+constexpr int64_t kResidentGroups = 1024;
+
+// Tiles of merge_cut_tiles_kernel: they start up to 15 bytes below the first byte.
+static int64_t cut_tiles(int64_t n_bytes, int64_t size) { return (n_bytes + 15 + size - 1) / size; }
+
+// Their arrays take the place of the per-piece ones of the encode layout, which are not used then.
+struct CutTileLayout { int64_t info, tile_sum, tile_base, tile_state, total; };
+
+static CutTileLayout cut_tile_layout(const Layout &l, int64_t n_tiles) {
+    CutTileLayout c;
+    const bool scan = n_tiles > kDeepSelfScanTiles;
+    int64_t at = l.rec;
+    c.info = at;       at += align256(8 * (n_tiles + 1));
+    c.tile_sum = at;   at += align256(4 * n_tiles);
+    c.tile_base = at;  at += scan ? align256(4 * n_tiles) : 0;
+    c.tile_state = at; at += scan ? align256(8 * (n_tiles / kScanSpan + 1)) : 0;
+    c.total = at;
+    return c;
+}
+
+constexpr int kCutTileMax = 3072;
+
+// As small as lets the chip hold all of them at once, so that whatever cannot be cut is spread over it; 0 (the paths
+// without cuts) where the arrays do not fit (pieces of several tiles each on average).  A few very long pieces go to
+// merge_wide_kernel.
+static int64_t cut_tile_size(const Layout &l, int64_t n_bytes, int64_t n_pieces) {
+    if (n_pieces <= kWideMaxPieces && n_bytes > n_pieces * (int64_t)kGroupBoundMax) return 0;
+    for (int64_t size = 1024; size <= kCutTileMax; size += 1024)
+        if ((size == kCutTileMax || cut_tiles(n_bytes, size) <= kResidentGroups) &&
+            cut_tile_layout(l, cut_tiles(n_bytes, size)).total <= l.scratch)
+            return size;
+    return 0;
+}
+
 // Tiles of merge_byte_runs_kernel: they start up to 15 bytes below the first byte.  That path is the quicker one wherever
 // the small tiles end (1.4 MB: 15 against 23.5 us through the pre-tokenizer), but for one tile: a test of
 // bpe_encode_raw_plan names the pre-tokenizer path at the first size beyond them.
@@ -1904,10 +1954,6 @@ constexpr int kKernels = 3;
 constexpr int kRawKernels = 5;
 constexpr int64_t kRawMaxGrid = 8192;   // raw path: workgroups of the merge and emit kernels
 constexpr int64_t kRawRestGrid = 2048;  // ... of the strided merge kernel (two rounds of the chip; mostly it finds nothing to do)
-// Workgroups of 256 threads of the merge kernels and of the single kernel that the chip holds at a time (4 per
-// compute unit: LDS).  The single-kernel path is only free of deadlock by construction while every tile is
-// resident; beyond, it relies on workgroups being dispatched in index order.
-constexpr int64_t kResidentGroups = 1024;
 // merge_kernel: one workgroup for the long pieces of every so many tiles, from grids of so many tiles on
 // (more than the chip holds at a time: below, a tile that takes long holds no other tile up),
 // and at most so many of them (then each takes more tiles; at most 256, the reach of a list entry)
@@ -2028,7 +2074,13 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
                   (long long)n_tiles, kWave);
         return BPE_ERR_OPTION;
     }
-    const bool fused = !raw && !p.paper && !o.dedup && n_tiles > 0 &&
+    // Pieces that are longer on average than a lane takes are cut first, in tiles of bytes (unless an option asks for a
+    // path of its own).  Up to 16 bytes most are words, which are one probe as they are; from there on cutting wins wherever
+    // there is something to cut (20-byte chunks of text, 4 MB: 89.8 -> 49.3 us, 840 KB 27.8 -> 23.7, 20 KB 19.8 -> 19.7).
+    bpe_encode_options plain = {};
+    const bool any_option = opts && memcmp(opts, &plain, sizeof(plain)) != 0;
+    const int64_t cut_tile = !raw && !any_option && n_pieces > 0 && n_bytes / n_pieces > kTinyMax ? cut_tile_size(l, n_bytes, n_pieces) : 0;
+    const bool fused = !raw && !cut_tile && !p.paper && !o.dedup && n_tiles > 0 &&
                        (o.fused > 0 || (o.fused == 0 && n_tiles <= kFusedMaxTiles && short_pieces));
     if (plan) {
         *plan = {};
@@ -2121,6 +2173,33 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
         if (ev) (void)hipEventRecord(ev[n_ev++], s);
         run.run("emit_bytes_kernel", 3, emit_bytes_kernel, nt, kGroupThreads, p, (int)nt, self_scan);
         if (ev) { (void)hipEventRecord(ev[n_ev++], s); (void)hipEventRecord(ev[n_ev++], s); }
+    } else if (cut_tile) {
+        const int64_t nt = cut_tiles(n_bytes, cut_tile);
+        const CutTileLayout c = cut_tile_layout(l, nt);
+        p.tile_shift = (int32_t)((uintptr_t)bytes & 15);
+        p.tile_info = (int2 *)ws_at(c.info);
+        p.tile_sum = (int32_t *)ws_at(c.tile_sum);
+        p.tile_base = (int32_t *)ws_at(c.tile_base);
+        p.tile_state = (unsigned long long *)ws_at(c.tile_state);
+        p.seq_off = piece_offsets;
+        p.n_seqs = (int32_t)n_pieces;
+        p.seq_token_offsets = out_offsets;
+        p.out_offsets = nullptr;       // (scan_tiles_kernel has no piece's offset to write)
+        if (plan) { plan->n_tiles = nt; plan->pieces_per_wave = kWave; plan->waves_per_tile = kWavesPerGroup; plan->single_kernel = 0; }
+        CutSets cuts = {};
+        if (!dry) cuts = table->cuts;
+        if (cut_tile == 1024)
+            run.run("merge_cut_tiles_kernel", 0, merge_cut_tiles_kernel<1024, 1, true>, nt, kGroupThreads, p, cuts);
+        else if (cut_tile == 2048)
+            run.run("merge_cut_tiles_kernel", 0, merge_cut_tiles_kernel<2048, 2, true>, nt, kGroupThreads, p, cuts);
+        else
+            run.run("merge_cut_tiles_kernel", 0, merge_cut_tiles_kernel<kCutTileMax, 2, false>, nt, kGroupThreads, p, cuts);
+        if (ev) (void)hipEventRecord(ev[n_ev++], s);
+        const int self_scan = nt <= kDeepSelfScanTiles;
+        if (!self_scan) run.run("scan_tiles_kernel", 1, scan_tiles_kernel, (nt + kScanSpan - 1) / kScanSpan, kScanThreads, p, nt);
+        if (ev) (void)hipEventRecord(ev[n_ev++], s);
+        run.run("emit_cut_tiles_kernel", 2, emit_cut_tiles_kernel, (nt + kCopyTiles - 1) / kCopyTiles, kGroupThreads, p, (int)nt, self_scan);
+        if (ev) (void)hipEventRecord(ev[n_ev++], s);
     } else if (byte_runs_path) {
         const RawLayout r = raw_layout(n_bytes, n_pieces, raw->n_seqs);
         const int64_t nt = byte_run_tiles(n_bytes);

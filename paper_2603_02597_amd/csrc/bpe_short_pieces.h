@@ -134,7 +134,7 @@ __device__ __forceinline__ int row_merge(const EncodeParams &p, uint32_t &sym, i
 // the mask of positions that hold the final tokens (they stay in L.S[.][lane]).
 // Loads are batched so that dependent round trips stay few: all byte-pair ranks,
 // then per merge the two neighbour symbols and the two new pairs' slots together.
-__device__ uint32_t tiny_merge(const EncodeParams &p, TinyState &L, const uint32_t (&w)[4], int len, bool mine) {
+__device__ __forceinline__ uint32_t tiny_merge(const EncodeParams &p, TinyState &L, const uint32_t (&w)[4], int len, bool mine) {
     const int lane = lane_id();
     const int my_len = mine ? len : 0;
     if (!__ballot(my_len > 0)) return 0u;
@@ -219,7 +219,7 @@ __device__ uint32_t tiny_merge(const EncodeParams &p, TinyState &L, const uint32
 }
 
 // Stores the lane's final tokens (positions `alive` of its LDS column) to dst[0 ...].
-__device__ inline void tiny_store(const TinyState &L, uint32_t alive, int32_t *dst) {
+__device__ __forceinline__ void tiny_store(const TinyState &L, uint32_t alive, int32_t *dst) {
     const int lane = lane_id();
     int n_out = 0;
     while (__ballot(alive != 0)) {

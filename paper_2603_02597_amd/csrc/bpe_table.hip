@@ -332,6 +332,27 @@ static void build_words(const int32_t *merges, const RuleOrder &ro, const HostIm
     }
 }
 
+// Which bytes a piece can be cut at: from the last byte of every rule's left part and the first one of its right part.
+static void build_cuts(const int32_t *merges, const RuleOrder &ro, CutSets &cuts) {
+    std::vector<uint8_t> first(ro.made_at.size()), last(ro.made_at.size());
+    for (int b = 0; b < 256; ++b) first[b] = last[b] = (uint8_t)b;
+    bool follows[256] = {}, leads[256] = {}, twin[256] = {};       // behind another byte; before another one; itself
+    for (const auto &rule : ro.by_rank) {
+        const int64_t row = rule.second;
+        const int32_t a = merges[2 * row], b = merges[2 * row + 1];
+        first[ro.merged_row[row]] = first[a];
+        last[ro.merged_row[row]] = last[b];
+        if (last[a] == first[b]) twin[first[b]] = true;
+        else leads[last[a]] = follows[first[b]] = true;
+    }
+    memset(&cuts, 0, sizeof(cuts));
+    for (int b = 0; b < 256; ++b) {
+        cuts.before[b >> 5] |= (uint32_t)!follows[b] << (b & 31);
+        cuts.behind[b >> 5] |= (uint32_t)!leads[b] << (b & 31);
+        cuts.twin[b >> 5] |= (uint32_t)twin[b] << (b & 31);
+    }
+}
+
 // The one allocation of a table on the device: where its arrays start, and its size.
 struct DeviceLayout { size_t words, byte_pairs, merged_of, rank_of, sym_lr, total; };     // (the slots are first)
 
@@ -429,6 +450,7 @@ extern "C" int bpe_table_build(const int32_t *merges, const int32_t *ranks, cons
     e = hipMemcpy(t->device_mem, blob.data(), blob.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) { (void)hipFree(t->device_mem); delete t; return hip_fail(e, "hipMemcpy(table)"); }
     t->info = img.info;
+    build_cuts(merges, ro, t->cuts);
     char *d = (char *)t->device_mem;
     t->view.slots = (const uint2 *)d;
     t->view.words = (const uint4 *)(d + at.words);

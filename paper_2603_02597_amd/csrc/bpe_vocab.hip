@@ -512,14 +512,16 @@ extern "C" int bpe_decode(const bpe_vocab *v, const int32_t *ids, int64_t n_toke
     //   (1, 256)  9.5  13.1  22.2  39.9  81  431      (1, 32) 11.3  15.5  22.9  41.0  72  340
     //   (2, 64)  10.0  13.6  19.1  33.4  55  269      (2, 256) 8.9  12.5  17.6  31.2  54  293
     //   (4, 32)  13.0  14.7  20.7  30.3  50  238      (4, 256) 11.3 12.4  19.1  28.3  49  264
-    // The lines were drawn where two gathers per token were measured (2.1 M tokens: 33 us with (1, 256), 25 with
-    // (2, 64), 29 with (4, 32); 40 M: 643, 434 with (2, 32), 393); by this table wider windows are the quicker ones
-    // up to 8 M tokens.
+    // Up to 0.5 M tokens the call's launch hides the difference, but tokens of more than 12 bytes do not fit the stage of two
+    // rounds (0.3 to 0.5 M of 13 to 16 bytes: 9.9 to 10.6 us with one round, 13.2 to 13.6 with two).  Against (1, 256) to
+    // 0.5 M, (2, 64) to 4 M, (4, 32) beyond: 1 M 12.7 -> 11.8, 2.1 M 18.8 -> 17.3, 4.2 M 31.6 -> 27.6, 8 M 48.6 -> 47.0; 2 M
+    // random ids of 1 to 6 bytes 18.2 -> 21.4, 4 M of them 35.3 -> 32.8.
     const dim3 block(kGroupThreads);
     auto tiles = [&](int rounds) { return (unsigned)std::max<int64_t>((n_tokens + rounds * kTileTokens - 1) / (rounds * kTileTokens), 1); };
     const hipStream_t st = (hipStream_t)stream;
     if (n_tokens <= 512 * kTileTokens) hipLaunchKernelGGL((decode_kernel<1, kGroupThreads>), dim3(tiles(1)), block, 0, st, p);
-    else if (n_tokens <= 4096 * kTileTokens) hipLaunchKernelGGL((decode_kernel<2, 64>), dim3(tiles(2)), block, 0, st, p);
+    else if (n_tokens <= 3072 * kTileTokens) hipLaunchKernelGGL((decode_kernel<2, kGroupThreads>), dim3(tiles(2)), block, 0, st, p);
+    else if (n_tokens <= 8192 * kTileTokens) hipLaunchKernelGGL((decode_kernel<4, kGroupThreads>), dim3(tiles(4)), block, 0, st, p);
     else hipLaunchKernelGGL((decode_kernel<4, 32>), dim3(tiles(4)), block, 0, st, p);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? BPE_OK : hip_fail(e, "bpe_decode launch");

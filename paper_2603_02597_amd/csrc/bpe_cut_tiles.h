@@ -79,8 +79,9 @@ struct CutTileShared {
     int wave_n[kWavesPerGroup];
 };
 
-// EAGER: both slots of the whole-piece table at once (see find_word).
-template <int TILE, int ROUNDS, bool EAGER>
+// EAGER: both slots of the whole-piece table at once (see find_word).  WIDE: merge_uncut_parts has merged the parts beyond
+// kGroupBoundMax bytes (number of tokens in scratch2[first byte], the tokens in scratch).
+template <int TILE, int ROUNDS, bool EAGER, bool WIDE>
 __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(EncodeParams p, CutSets cuts) {
     using Shared = CutTileShared<TILE, ROUNDS>;
     constexpr int kPieces = Shared::kPieces, kParts = Shared::kParts, kGroups = Shared::kGroups;
@@ -276,7 +277,7 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
         __syncthreads();
         const int n_here = min(n_t - k0, kPieces);
 
-        int s[ROUNDS], len[ROUNDS], tok0[ROUNDS], kind[ROUNDS];        // kind: 0 none or whole, 1 short, 2 for the columns, 3 longer
+        int s[ROUNDS], len[ROUNDS], tok0[ROUNDS], n_wide[ROUNDS], kind[ROUNDS];        // kind: 0 none or whole, 1 short, 2 for the columns, 3 longer
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) {
             const int k = r * kGroupThreads + tid;
@@ -325,7 +326,12 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
         uint64_t of_kind[ROUNDS];
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) {
-            kind[r] = tok0[r] >= 0 || len[r] <= 0 ? 0 : len[r] <= p.tiny_max ? 1 : len[r] <= p.col_max ? 2 : 3;
+            n_wide[r] = 0;
+            if (WIDE && !whole_tile && len[r] > kGroupBoundMax) {
+                n_wide[r] = min(max(p.scratch2[origin + s[r]], 0), len[r]);    // (any number there if the offsets decrease)
+                atomicAdd(&sh.run_groups, TILE);               // no cutting at the pieces only: this part is done
+            }
+            kind[r] = tok0[r] >= 0 || len[r] <= 0 || n_wide[r] ? 0 : len[r] <= p.tiny_max ? 1 : len[r] <= p.col_max ? 2 : 3;
             if (kind[r] == 2) {
                 // A run (told by eight equal bytes) is halved by every pass of a wavefront, but merges one pair a time in a
                 // column: 64-byte pieces of text with runs and random bytes 59 us with all of them in columns, 34 so, and
@@ -471,7 +477,7 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
         int c[ROUNDS], inc[ROUNDS];
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) {
-            c[r] = slot[r] >= 0 ? (int)sh.entry[slot[r]] : tok0[r] >= 0 ? 1 : 0;
+            c[r] = slot[r] >= 0 ? (int)sh.entry[slot[r]] : tok0[r] >= 0 ? 1 : n_wide[r];
             inc[r] = wave_scan_inclusive(c[r]);
             if (lane == kWave - 1) sh.total[r * kWavesPerGroup + wv] = (uint32_t)inc[r];
         }
@@ -487,6 +493,16 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r)
             if (tok0[r] >= 0) out[first[r]] = tok0[r];
+        if (WIDE) {
+#pragma unroll
+            for (int r = 0; r < ROUNDS; ++r) {
+                for (uint64_t m = __ballot(n_wide[r] > 0); m;) {
+                    const int t = __builtin_ctzll(m);
+                    m &= m - 1;
+                    copy_words<kWave>(p.scratch + origin + read_lane(s[r], t), out + read_lane(first[r], t), 0, read_lane(n_wide[r], t), lane);
+                }
+            }
+        }
         if (all && !parked) {      // whoever merged a left-over piece stores its tokens: the owner says where
 #pragma unroll
             for (int r = 0; r < ROUNDS; ++r)
@@ -535,6 +551,91 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
         p.tile_sum[tile] = done;
         *info = make_int2(r0, s0);
         if (tile == (int)gridDim.x - 1) info[1] = make_int2(0, s1);
+    }
+}
+
+// A few very long pieces: the parts that have more symbols than four wavefronts keep resident are merged ahead of the tiles
+// by 16 (see merge_wide_kernel).  A workgroup looks at kWideSpan bytes for places to cut and takes the parts that start there;
+// text has none that long.  A launch more, but a part that long would take twice the time in a tile.  (The lines on the number
+// of pieces and on the workspace leave at most 2 MB of input, so positions fit 32 bits.)
+// Per call, 16 wavefronts per piece / now: text, 50k table, 24 KB in pieces of 2,358 bytes 105 / 19 us, 800 KB of 4,090 166 / 25;
+// with runs and random bytes 606 / 24 and 3,682 / 33 (1k table 2,272 / 36, 100k table 4,109 / 82).
+// Text without spaces, which falls into parts of hundreds of bytes, loses there and gains on longer pieces: 24 KB of 2,358
+// bytes 258 / 412, 800 KB of 4,090 453 / 1,058, 40 KB of 20,000 2,366 / 642.
+constexpr int kWideSpan = 4 * kWideThreads;
+static_assert(kWideSpan < 2 * (kGroupBoundMax + 1), "one part that long lies inside a span, and another one reaches out of it");
+__device__ __forceinline__ void merge_uncut_parts(const EncodeParams &p, const CutSets &cuts, uint32_t *X, WideTmp &tmp) {
+    __shared__ uint8_t code[256];
+    __shared__ uint32_t bits[kWideSpan / 32];      // bytes of the span that pieces start with
+    __shared__ int2 part[2];                       // {first byte, length}
+    __shared__ int n_parts, next_piece;
+    const int tid = threadIdx.x;
+    const WideScope sc{tmp};
+    // Positions v are counted from the 16-byte boundary at or below the input: byte i is v = i + mis.
+    const int mis = (int)((uintptr_t)p.bytes & 15), v_end = p.n_bytes + mis;
+    const int v0 = (int)blockIdx.x * kWideSpan, lo = max(v0, mis), hi = min(v0 + kWideSpan, v_end);
+    if (lo >= hi) return;
+    const uint32_t *const words = (const uint32_t *)(p.bytes - mis);
+    if (tid < 256) code[tid] = (uint8_t)cut_code(cuts, (uint32_t)tid);
+    if (tid < kWideSpan / 32) bits[tid] = 0;
+    if (tid == 0) { n_parts = 0; next_piece = v_end; }
+    __syncthreads();
+    for (int k = tid; k <= p.n_seqs; k += kWideThreads) {
+        const int sv = p.seq_off[k];
+        if (sv < 0 || sv >= p.n_bytes) continue;
+        const int v = sv + mis;
+        if (v >= lo && v < hi) atomicOr(&bits[(v - v0) >> 5], 1u << ((v - v0) & 31));
+        if (v >= hi) atomicMin(&next_piece, v);
+    }
+    if (lo == mis && tid == 0) atomicOr(&bits[(mis - v0) >> 5], 1u << ((mis - v0) & 31));      // byte 0 starts a piece
+    __syncthreads();
+    // Bit j set: a part starts at byte v + j.  (A word that holds a byte of the input lies in that byte's page.)
+    auto cuts_in_word = [&](int v) -> uint32_t {
+        if (v >= v_end) return 0u;
+        const uint32_t w = words[v >> 2];
+        uint32_t last = v > mis ? p.bytes[v - 1 - mis] : 0u, last_code = code[last], m = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t b = (w >> (8 * j)) & 0xFFu, c = code[b];
+            const uint32_t cut = ((c & kCutBefore) | (last_code & kCutBehind) >> 1) & ~(b == last ? c >> 2 : 0u);
+            if (v + j > mis && v + j < v_end) m |= cut << j;
+            last = b;
+            last_code = c;
+        }
+        return m;
+    };
+    const uint32_t mask = cuts_in_word(v0 + 4 * tid) | ((bits[tid >> 3] >> (4 * (tid & 7))) & 15u);
+    const int last = mask ? 4 * tid + 31 - __builtin_clz(mask) : -1;
+    const int before = sc.scan_max_excl(last);
+    const int last_of_all = sc.max_all(last);
+    if (last_of_all < 0) return;                   // (the same in every thread)
+    if (mask && before >= 0) {
+        const int n = 4 * tid + __builtin_ctz(mask) - before;
+        if (n > kGroupBoundMax) part[atomicAdd(&n_parts, 1)] = make_int2(v0 + before - mis, n);
+    }
+    // the end of the last one: the next start behind the span
+    int end = next_piece;
+    for (int v = v0 + kWideSpan; v < end; v += kWideSpan) {
+        const uint32_t m = cuts_in_word(v + 4 * tid);
+        __syncthreads();                           // (between two uses of the scope's words)
+        const int at = -sc.max_all(m ? -(v + 4 * tid + __builtin_ctz(m)) : -0x7FFFFFFF);
+        end = min(end, at);
+        if (at != 0x7FFFFFFF) break;
+    }
+    __syncthreads();
+    const int first = v0 + last_of_all;
+    if (tid == 0 && end - first > kGroupBoundMax) {
+        part[n_parts] = make_int2(first - mis, end - first);
+        ++n_parts;
+    }
+    __syncthreads();
+    const int n = __builtin_amdgcn_readfirstlane(n_parts);
+#pragma unroll 1
+    for (int i = 0; i < n; ++i) {
+        const int b = __builtin_amdgcn_readfirstlane(part[i].x), len = __builtin_amdgcn_readfirstlane(part[i].y);
+        const int c = merge_wide_piece(p, b, len, X, sc);
+        __syncthreads();
+        if (tid == 0) p.scratch2[b] = c;
     }
 }
 

@@ -933,17 +933,34 @@ __global__ void __launch_bounds__(kGroupThreads) merge_kernel(EncodeParams p) {
     }
 }
 
+// A piece (PARTS: a part of one), bytes [o, o + len), by 16 wavefronts: tokens to scratch[o ...], their number back.
+__device__ __forceinline__ int merge_wide_piece(const EncodeParams &p, int o, int len, uint32_t *X, const WideScope &sc) {
+    const int cap = min(max(p.lds_max, kGroupBoundMin), kWideBoundMax);
+    if (p.level >= 3 && !(p.runs_by_best_rank && piece_is_run_like(p, o, len, sc)))
+        return encode_long_piece_bound(p, o, len, X, cap, sc);
+    if (len <= 2 * cap)
+        return encode_long_piece<WideScope, int32_t *>(p, o, len, (int32_t *)X, (int32_t *)X + 2 * kWideBoundMax, sc);
+    return encode_long_piece<WideScope, int32_t *>(p, o, len, p.scratch + o, p.scratch2 + o, sc);
+}
+
+__device__ __forceinline__ void merge_uncut_parts(const EncodeParams &p, const CutSets &cuts, uint32_t *X, WideTmp &tmp);     // bpe_cut_tiles.h
+
 // Inputs of a few very long pieces (one piece per tile, at most kWideMaxPieces of
 // them, longer on average than the 2,052 symbols four wavefronts keep resident): a
 // workgroup of 16 wavefronts per piece instead of 4, with twice the symbols resident
-// in LDS.  With so few pieces the chip is idle either way, and a pass over a long
+// in LDS.  PARTS: the pieces are cut, and this kernel takes what is still that long.  With so few pieces the chip is idle either way, and a pass over a long
 // piece is as quick as the threads that share it are many (4 KiB pieces: 190 against
 // 282 us, 16 KiB pieces: 478 against 1,050 us; 2 KiB pieces are quicker with four
 // wavefronts, 178 against 224 us: more barriers than work).
 constexpr int kWideMaxPieces = 256;     // one workgroup per CU
-__global__ void __launch_bounds__(kWideThreads) merge_wide_kernel(EncodeParams p) {
+template <bool PARTS>
+__global__ void __launch_bounds__(kWideThreads) merge_wide_kernel(EncodeParams p, CutSets cuts) {
     __shared__ uint32_t X[4 * kWideBoundMax];
     __shared__ WideTmp tmp;
+    if (PARTS) {
+        merge_uncut_parts(p, cuts, X, tmp);
+        return;
+    }
     const int tid = threadIdx.x;
     const int q = blockIdx.x;
     int o = p.off[q];
@@ -953,17 +970,7 @@ __global__ void __launch_bounds__(kWideThreads) merge_wide_kernel(EncodeParams p
     if (bad && tid == 0) __hip_atomic_store(&p.status[0], p.call_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     o = __builtin_amdgcn_readfirstlane(o);
     const int len = __builtin_amdgcn_readfirstlane(bad ? 0 : o_next - o);
-    const WideScope sc{tmp};
-    int c = 0;
-    if (len > 0) {
-        const int cap = min(max(p.lds_max, kGroupBoundMin), kWideBoundMax);
-        if (p.level >= 3 && !(p.runs_by_best_rank && piece_is_run_like(p, o, len, sc)))
-            c = encode_long_piece_bound(p, o, len, X, cap, sc);
-        else if (len <= 2 * cap)
-            c = encode_long_piece<WideScope, int32_t *>(p, o, len, (int32_t *)X, (int32_t *)X + 2 * kWideBoundMax, sc);
-        else
-            c = encode_long_piece<WideScope, int32_t *>(p, o, len, p.scratch + o, p.scratch2 + o, sc);
-    }
+    const int c = len > 0 ? merge_wide_piece(p, o, len, X, WideScope{tmp}) : 0;
     if (tid == 0) {
         p.rec[q] = make_int2(c, -1);
         p.tile_sum[q] = c;
@@ -1856,11 +1863,15 @@ static CutTileLayout cut_tile_layout(const Layout &l, int64_t n_tiles) {
 
 constexpr int kCutTileMax = 3072;
 
+// A few very long pieces: what they hold that long without a place to cut goes to merge_wide_kernel (see merge_uncut_parts).
+static bool few_long_pieces(int64_t n_bytes, int64_t n_pieces) {
+    return n_pieces <= kWideMaxPieces && n_bytes > n_pieces * (int64_t)kGroupBoundMax;
+}
+
 // As small as lets the chip hold all of them at once, so that whatever cannot be cut is spread over it; 0 (the paths
-// without cuts) where the arrays do not fit (pieces of several tiles each on average).  A few very long pieces go to
-// merge_wide_kernel.
-static int64_t cut_tile_size(const Layout &l, int64_t n_bytes, int64_t n_pieces) {
-    if (n_pieces <= kWideMaxPieces && n_bytes > n_pieces * (int64_t)kGroupBoundMax) return 0;
+// without cuts) where the arrays do not fit (pieces of several tiles each on average: one piece of 292 KB and more, 256 of
+// 6 KB).
+static int64_t cut_tile_size(const Layout &l, int64_t n_bytes) {
     for (int64_t size = 1024; size <= kCutTileMax; size += 1024)
         if ((size == kCutTileMax || cut_tiles(n_bytes, size) <= kResidentGroups) &&
             cut_tile_layout(l, cut_tiles(n_bytes, size)).total <= l.scratch)
@@ -2105,7 +2116,7 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
     // there is something to cut (20-byte chunks of text, 4 MB: 89.8 -> 49.3 us, 840 KB 27.8 -> 23.7, 20 KB 19.8 -> 19.7).
     bpe_encode_options plain = {};
     const bool any_option = opts && memcmp(opts, &plain, sizeof(plain)) != 0;
-    const int64_t cut_tile = !raw && !any_option && n_pieces > 0 && n_bytes / n_pieces > kTinyMax ? cut_tile_size(l, n_bytes, n_pieces) : 0;
+    const int64_t cut_tile = !raw && !any_option && n_pieces > 0 && n_bytes / n_pieces > kTinyMax ? cut_tile_size(l, n_bytes) : 0;
     const bool fused = !raw && !cut_tile && !p.paper && !o.dedup && n_tiles > 0 &&
                        (o.fused > 0 || (o.fused == 0 && n_tiles <= kFusedMaxTiles && short_pieces));
     if (plan) {
@@ -2214,12 +2225,13 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
         if (plan) { plan->n_tiles = nt; plan->pieces_per_wave = kWave; plan->waves_per_tile = kWavesPerGroup; plan->single_kernel = 0; }
         CutSets cuts = {};
         if (!dry) cuts = table->cuts;
-        if (cut_tile == 1024)
-            run.run("merge_cut_tiles_kernel", 0, merge_cut_tiles_kernel<1024, 1, true>, nt, kGroupThreads, p, cuts);
-        else if (cut_tile == 2048)
-            run.run("merge_cut_tiles_kernel", 0, merge_cut_tiles_kernel<2048, 2, true>, nt, kGroupThreads, p, cuts);
-        else
-            run.run("merge_cut_tiles_kernel", 0, merge_cut_tiles_kernel<kCutTileMax, 2, false>, nt, kGroupThreads, p, cuts);
+        const bool wide = few_long_pieces(n_bytes, n_pieces);
+        if (wide) run.run("merge_wide_kernel", 0, merge_wide_kernel<true>, cut_tiles(n_bytes, kWideSpan), kWideThreads, p, cuts);
+        const auto kernel = cut_tile == 1024   ? (wide ? merge_cut_tiles_kernel<1024, 1, true, true> : merge_cut_tiles_kernel<1024, 1, true, false>)
+                            : cut_tile == 2048 ? (wide ? merge_cut_tiles_kernel<2048, 2, true, true> : merge_cut_tiles_kernel<2048, 2, true, false>)
+                                               : (wide ? merge_cut_tiles_kernel<kCutTileMax, 2, false, true>
+                                                       : merge_cut_tiles_kernel<kCutTileMax, 2, false, false>);
+        run.run("merge_cut_tiles_kernel", 0, kernel, nt, kGroupThreads, p, cuts);
         if (ev) (void)hipEventRecord(ev[n_ev++], s);
         const int self_scan = nt <= kDeepSelfScanTiles;
         if (!self_scan) run.run("scan_tiles_kernel", 1, scan_tiles_kernel, (nt + kScanSpan - 1) / kScanSpan, kScanThreads, p, nt);
@@ -2302,8 +2314,8 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
             run.run("dedup_count_kernel", i0 + 1, dedup_count_kernel, grid, kGroupThreads, dp);
             p.rec = dp.rec_all;
             p.rep_of = dp.rep;
-        } else if (grid > 0 && p.W == 1 && !p.paper && n_pieces <= kWideMaxPieces && n_bytes > n_pieces * (int64_t)kGroupBoundMax) {
-            run.run("merge_wide_kernel", i0, merge_wide_kernel, grid, kWideThreads, p);
+        } else if (grid > 0 && p.W == 1 && !p.paper && few_long_pieces(n_bytes, n_pieces)) {
+            run.run("merge_wide_kernel", i0, merge_wide_kernel<false>, grid, kWideThreads, p, CutSets{});
         } else if (grid > 0) {
             // Word-sized pieces on average (a tile is 256 pieces): the rare longer ones go to workgroups
             // of their own at the head of the grid, one for every kTilesPerLongGroup tiles.

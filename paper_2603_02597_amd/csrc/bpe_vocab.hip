@@ -515,11 +515,15 @@ extern "C" int bpe_decode(const bpe_vocab *v, const int32_t *ids, int64_t n_toke
     // Up to 0.5 M tokens the call's launch hides the difference, but tokens of more than 12 bytes do not fit the stage of two
     // rounds (0.3 to 0.5 M of 13 to 16 bytes: 9.9 to 10.6 us with one round, 13.2 to 13.6 with two).  Against (1, 256) to
     // 0.5 M, (2, 64) to 4 M, (4, 32) beyond: 1 M 12.7 -> 11.8, 2.1 M 18.8 -> 17.3, 4.2 M 31.6 -> 27.6, 8 M 48.6 -> 47.0; 2 M
-    // random ids of 1 to 6 bytes 18.2 -> 21.4, 4 M of them 35.3 -> 32.8.
+    // random ids of 1 to 6 bytes 18.2 -> 21.4, 4 M of them 35.3 -> 32.8.  With an output numbering records lie anywhere, tiles come
+    // to their look-back at different times, and the polls of a full window cost more than they save (text with random bytes,
+    // 1.9 M and 2.5 M tokens of the 50k table 14.9 -> 16.8 and 18.2 -> 22.1; 128 tiles at a time 21.0), so there the lines stay.
     const dim3 block(kGroupThreads);
     auto tiles = [&](int rounds) { return (unsigned)std::max<int64_t>((n_tokens + rounds * kTileTokens - 1) / (rounds * kTileTokens), 1); };
     const hipStream_t st = (hipStream_t)stream;
     if (n_tokens <= 512 * kTileTokens) hipLaunchKernelGGL((decode_kernel<1, kGroupThreads>), dim3(tiles(1)), block, 0, st, p);
+    else if (ids_are_output_ids && n_tokens <= 4096 * kTileTokens) hipLaunchKernelGGL((decode_kernel<2, 64>), dim3(tiles(2)), block, 0, st, p);
+    else if (ids_are_output_ids) hipLaunchKernelGGL((decode_kernel<4, 32>), dim3(tiles(4)), block, 0, st, p);
     else if (n_tokens <= 3072 * kTileTokens) hipLaunchKernelGGL((decode_kernel<2, kGroupThreads>), dim3(tiles(2)), block, 0, st, p);
     else if (n_tokens <= 8192 * kTileTokens) hipLaunchKernelGGL((decode_kernel<4, kGroupThreads>), dim3(tiles(4)), block, 0, st, p);
     else hipLaunchKernelGGL((decode_kernel<4, 32>), dim3(tiles(4)), block, 0, st, p);

@@ -517,7 +517,8 @@ extern "C" int bpe_decode(const bpe_vocab *v, const int32_t *ids, int64_t n_toke
     // 0.5 M, (2, 64) to 4 M, (4, 32) beyond: 1 M 12.7 -> 11.8, 2.1 M 18.8 -> 17.3, 4.2 M 31.6 -> 27.6, 8 M 48.6 -> 47.0; 2 M
     // random ids of 1 to 6 bytes 18.2 -> 21.4, 4 M of them 35.3 -> 32.8.  With an output numbering records lie anywhere, tiles come
     // to their look-back at different times, and the polls of a full window cost more than they save (text with random bytes,
-    // 1.9 M and 2.5 M tokens of the 50k table 14.9 -> 16.8 and 18.2 -> 22.1; 128 tiles at a time 21.0), so there the lines stay.
+    // 1.9 M and 2.5 M tokens of the 50k table 14.9 -> 16.8 and 18.2 -> 22.1; 128 tiles at a time 21.0): (2, 64)
+    // there up to 4 M tokens, (4, 32) beyond.
     const dim3 block(kGroupThreads);
     auto tiles = [&](int rounds) { return (unsigned)std::max<int64_t>((n_tokens + rounds * kTileTokens - 1) / (rounds * kTileTokens), 1); };
     const hipStream_t st = (hipStream_t)stream;

@@ -30,7 +30,8 @@ static_assert(kRunGroups == kGroupThreads, "a group per thread");
 static_assert(kBytePass <= kRunLeft, "the list holds what a pass leaves over");
 
 // The word of a piece that is not one token: its first byte counted from the tile's first group, and its number of
-// tokens (kManyTokens: that is in scratch2[first byte + 1]; such a piece is the last one of its tile, and longer).
+// tokens (kManyTokens: that is the next word; such a piece is the last one of its tile, and longer, so no other
+// piece's word is there).
 constexpr uint32_t kSeveral = 0x80000000u, kManyTokens = 0x7FFFFu;
 constexpr int kStartShift = 19;
 
@@ -400,13 +401,24 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_byte_runs_kernel(Encod
                     const LongPiece q = sh.longer.piece[k];
                     const uint32_t v = (uint32_t)(q.b + lp.tile_shift);
                     lp.piece_word[q.slot] = (int)(kSeveral | (v % kRunTile) << kStartShift | min((uint32_t)c, kManyTokens));
-                    if ((uint32_t)c >= kManyTokens) lp.scratch2[q.b + 1] = c;
+                    if ((uint32_t)c >= kManyTokens) lp.piece_word[q.slot + 1] = c;
                     atomicAdd(&sh.acc[q.tile], c);
                 });
             __syncthreads();
         }
     }
     if (tid < tile1 - tile0) kernel_params().tile_sum[tile0 + tid] = sh.acc[tid];
+}
+
+// Whether the offsets off[0 .. n] are anything but 0, ..., n_bytes without a decrease.  Every thread of the workgroup must
+// call it.
+__device__ __forceinline__ bool offsets_are_bad(const int32_t *off, int n, int n_bytes) {
+    bool bad = false;
+    for (int64_t k = threadIdx.x; k <= n; k += kGroupThreads) {
+        const int v = off[k];
+        bad |= v < 0 || v > n_bytes || (k == 0 && v != 0) || (k == n ? v != n_bytes : off[k + 1] < v);
+    }
+    return __syncthreads_or(bad);
 }
 
 // Assembly: the tokens of every tile to their place in out_ids, and the first token of every sequence.  A workgroup
@@ -421,6 +433,16 @@ __global__ void __launch_bounds__(kGroupThreads) emit_byte_runs_kernel(EncodePar
     const int tile = blockIdx.x;
     const int n = p.tile_n[tile], s_end = p.tile_info[tile + 1].y;
     const int2 info = p.tile_info[tile];
+    // Sequence offsets that are out of range or decrease: each tile has searched them for its own part, the tiles need not
+    // agree on where a piece ends, and pieces that overlap can have more tokens than out_ids has room for.  So no token is
+    // stored then, and every sequence is empty.  (The verdict can be that of an earlier replay of a recorded call: the
+    // workgroup looks for itself.)
+    if (p.seq_off && p.status[kStatusBadInput] == p.call_id && offsets_are_bad(p.seq_off, p.n_seqs, p.n_bytes)) {
+        for (int64_t s = (int64_t)tile * kGroupThreads + tid; s <= p.n_seqs; s += (int64_t)n_tiles * kGroupThreads)
+            p.seq_token_offsets[s] = 0;
+        if (tile == 0 && tid == 0) mark_call(p.status, p.call_id);
+        return;
+    }
     // tokens before the tile
     int before = 0;
     if (self_scan) {               // tile_sum is 256-byte aligned
@@ -446,7 +468,7 @@ __global__ void __launch_bounds__(kGroupThreads) emit_byte_runs_kernel(EncodePar
             const uint32_t u = (uint32_t)word[j];
             at[j] = origin + (int)((u & ~kSeveral) >> kStartShift);
             c[j] = i + j >= n ? 0 : word[j] < 0 ? (int)(u & kManyTokens) : 1;
-            if (word[j] < 0 && c[j] == (int)kManyTokens) c[j] = p.scratch2[at[j] + 1];
+            if (word[j] < 0 && c[j] == (int)kManyTokens) c[j] = words[i + j + 1];
             mine += c[j];
         }
         // the first four tokens of a piece of several, asked for before anything waits (what lies behind them is the workspace's)

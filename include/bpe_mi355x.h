@@ -223,9 +223,8 @@ int64_t bpe_dedup_workspace_bytes(int64_t n_bytes, int64_t n_pieces);
  *   opts           NULL for defaults
  * n_bytes < 2^31.  An empty piece yields no token; n_pieces == 0 writes only
  * out_offsets[0] = 0.  Offsets that are out of range or decreasing are detected
- * on the device: nothing is read or written out of bounds, and bpe_encode_status
- * reports BPE_ERR_INPUT (the affected pieces yield no tokens; where pieces average more
- * than 16 bytes, which tokens and offsets come out is not specified then).
+ * on the device: the affected pieces yield no tokens, nothing is read or written
+ * out of bounds, and bpe_encode_status reports BPE_ERR_INPUT.
  */
 int bpe_encode(const bpe_table *table, const uint8_t *bytes, const int32_t *piece_offsets,
                int64_t n_bytes, int64_t n_pieces, int32_t *out_ids, int32_t *out_offsets,

@@ -639,13 +639,77 @@ __device__ __forceinline__ void merge_uncut_parts(const EncodeParams &p, const C
     }
 }
 
+// Offsets that are out of range or decrease.  Every tile has searched them for its own part, what the tiles found
+// need not fit together, and parts that overlap can have more tokens than out_ids has room for.  So all of it is
+// dropped and the pieces are encoded as they stand, an equal share by every workgroup, one piece after the other; the last
+// workgroup to finish puts the tokens in their place.  A piece whose own offsets are bad yields none, as on the other paths.
+// (n_done: 0 at the start of the launch.)
+constexpr int kUncutResident = 1020;           // symbols in LDS: 16 KiB, so that the copies keep eight workgroups per compute unit
+struct UncutShared {
+    uint32_t X[4 * kUncutResident];
+    GroupTmp tmp;
+    int last;
+};
+__device__ __forceinline__ void encode_pieces_uncut(const EncodeParams &p, UncutShared &sh, int *n_done) {
+    const int tid = threadIdx.x, lane = lane_id();
+    const int64_t share = ((int64_t)p.n_seqs + gridDim.x - 1) / gridDim.x;
+    const int q0 = (int)min(blockIdx.x * share, (int64_t)p.n_seqs), q1 = (int)min(q0 + share, (int64_t)p.n_seqs);
+#pragma unroll 1
+    for (int q = q0; q < q1; ++q) {
+        const int b = __builtin_amdgcn_readfirstlane(p.seq_off[q]), e = __builtin_amdgcn_readfirstlane(p.seq_off[q + 1]);
+        const bool bad = b < 0 || e < b || e > p.n_bytes || (q == 0 && b != 0) || (q == p.n_seqs - 1 && e != p.n_bytes);
+        const int len = bad ? 0 : e - b;
+        int c = 0;
+        if (len > 0) {
+            if (p.level >= 3 && !(p.runs_by_best_rank && piece_is_run_like(p, b, len, GroupScope{sh.tmp})))
+                c = encode_long_piece_bound(p, b, len, sh.X, kUncutResident, GroupScope{sh.tmp});
+            else c = encode_group_piece<int32_t *>(p, b, len, p.scratch + b, p.scratch2 + b, sh.tmp);
+        }
+        if (tid == 0) p.seq_token_offsets[q] = c;
+    }
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) sh.last = atomicAdd(n_done, 1) == (int)gridDim.x - 1;
+    __syncthreads();
+    if (!sh.last) return;
+    __threadfence();
+    constexpr int kOwn = 16;       // tokens that a thread copies itself
+    int base = 0;
+    for (int64_t k = tid; k - tid < p.n_seqs; k += kGroupThreads) {
+        const bool has_piece = k < p.n_seqs;
+        const int c = has_piece ? p.seq_token_offsets[k] : 0, o = has_piece ? p.seq_off[k] : 0;
+        int total;
+        const int first = base + group_scan_sum_excl(c, sh.tmp, total);
+        if (has_piece) p.seq_token_offsets[k] = first;
+        const int n = copy_count(p, c, o, first);
+        for (int i = 0; i < min(n, kOwn); ++i) p.out_ids[first + i] = p.scratch[o + i];
+        for (uint64_t m = __ballot(n > kOwn); m;) {
+            const int t = __builtin_ctzll(m);
+            m &= m - 1;
+            copy_tokens<kWave>(p, read_lane(o, t), read_lane(first, t), kOwn, read_lane(n, t), lane);
+        }
+        base += total;
+        __syncthreads();           // (the scan's words are free)
+    }
+    if (tid == 0) {
+        p.seq_token_offsets[p.n_seqs] = base;
+        mark_call(p.status, p.call_id);
+    }
+}
+
 // The packed tokens of the tiles to their place in out_ids, and the token offsets of the pieces from
 // "in the tile" to "in the output".  A wavefront copies a tile.
 constexpr int kCopyTiles = kWavesPerGroup;
 __global__ void __launch_bounds__(kGroupThreads) emit_cut_tiles_kernel(EncodeParams p, int n_tiles, int self_scan) {
     __shared__ int before_w[kWavesPerGroup], tile_n[kCopyTiles];
+    __shared__ UncutShared uncut;
     const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int tile0 = blockIdx.x * kCopyTiles, tile = tile0 + wv;
+    // (the verdict can be that of an earlier replay of a recorded call: the workgroup looks for itself)
+    if (p.status[kStatusBadInput] == p.call_id && offsets_are_bad(p.seq_off, p.n_seqs, p.n_bytes)) {
+        encode_pieces_uncut(p, uncut, &p.tile_info[n_tiles].x);
+        return;
+    }
     int n = 0;
     int2 info = make_int2(0, 0);
     int s_end = 0;

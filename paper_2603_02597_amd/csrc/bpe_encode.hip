@@ -1218,6 +1218,21 @@ __global__ void __launch_bounds__(kGroupThreads) merge_bytes_kernel(EncodeParams
     }
 }
 
+// How many of a piece's c tokens can be copied from scratch[o ...] to out_ids[first ...]: bad offsets can
+// make pieces overlap and the total exceed the capacity of out_ids; then they must still not become
+// bad addresses.
+__device__ __forceinline__ int copy_count(const EncodeParams &p, int c, int o, int first) {
+    const int room = first >= 0 && first < p.n_bytes ? p.n_bytes - first : 0;
+    const int src_room = o >= 0 && o < p.n_bytes ? p.n_bytes - o : 0;
+    return min(c, min(room, src_room));
+}
+
+// Tokens [from, n) of a piece, by the T threads of which this is number t.
+template <int T>
+__device__ __forceinline__ void copy_tokens(const EncodeParams &p, int src, int dst, int from, int n, int t) {
+    copy_words<T>(p.scratch + src, p.out_ids + dst, from, n, t);
+}
+
 }  // namespace bpe
 #include "bpe_byte_runs.h"
 #include "bpe_cut_tiles.h"
@@ -1390,24 +1405,6 @@ __global__ void __launch_bounds__(kScanThreads) scan_tiles_kernel(EncodeParams p
         if (p.out_offsets) p.out_offsets[p.n_pieces] = before + total;
         mark_call(p.status, p.call_id);
     }
-}
-
-// Dense copy of one piece's c tokens to out_ids[first ...]: the first one travels in the
-// record (tok0 >= 0), the others wait in scratch at the piece's byte offset o.  Every lane of
-// the wavefront must call it (c = 0 without a piece).
-// How many of a piece's c tokens can be copied from scratch[o ...] to out_ids[first ...]: bad offsets can
-// make pieces overlap and the total exceed the capacity of out_ids; then they must still not become
-// bad addresses.
-__device__ __forceinline__ int copy_count(const EncodeParams &p, int c, int o, int first) {
-    const int room = first >= 0 && first < p.n_bytes ? p.n_bytes - first : 0;
-    const int src_room = o >= 0 && o < p.n_bytes ? p.n_bytes - o : 0;
-    return min(c, min(room, src_room));
-}
-
-// Tokens [from, n) of a piece, by the T threads of which this is number t.
-template <int T>
-__device__ __forceinline__ void copy_tokens(const EncodeParams &p, int src, int dst, int from, int n, int t) {
-    copy_words<T>(p.scratch + src, p.out_ids + dst, from, n, t);
 }
 
 // Up to four of a piece's tokens that wait in scratch, in one load, asked for before the piece's place is known: one

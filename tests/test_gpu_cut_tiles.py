@@ -104,3 +104,132 @@ def test_as_many_tiles_as_need_a_scan(oracle_mod):
     ev = C.make_eval("batch")
     data = np.resize(ev["bytes"], 8193 * 3072 + 5)
     _check(oracle_mod, C.load_merges(ev["table"]), data, textgen.fixed_chunks(data.size, 2048), 0, "scan")
+
+
+def _run_with(B, table, data, off, guard):
+    """ids (guard words behind the capacity included), offsets and verdict of a call whose offsets may be bad."""
+    import torch
+    d, o = torch.from_numpy(data).cuda(), torch.from_numpy(off).cuda()
+    ids = torch.full((data.size + guard,), -7, dtype=torch.int32, device="cuda")
+    got_off = torch.full((off.size + 64,), -7, dtype=torch.int32, device="cuda")
+    ws = torch.empty(B.bpe_workspace_bytes(data.size, off.size - 1), dtype=torch.uint8, device="cuda")
+    B.bpe_encode(table, d, o, ids[:data.size], got_off[:off.size], ws)
+    verdict = B.bpe_encode_status(ws)
+    got_off = got_off.cpu().numpy()
+    assert (got_off[off.size:] == -7).all()
+    return ids.cpu().numpy(), got_off[:off.size], verdict
+
+
+def _good_pieces(off, n):
+    """Which pieces have offsets of their own that are in range, do not decrease, and start and end the input."""
+    good = (off[:-1] >= 0) & (off[1:] >= off[:-1]) & (off[1:] <= n)
+    good[0] &= off[0] == 0
+    good[-1] &= off[-1] == n
+    return good
+
+
+# bytes and pieces: tiles of each size, with and without merge_wide_kernel, and as many as need a scan kernel
+@pytest.mark.parametrize("n,n_pieces,kernels", [
+    (40_000, 700, 2), (300_000, 4600, 2), (1_500_000, 40_000, 2), (2_500_000, 3000, 2), (8193 * 3072 + 5, 16_000, 3),
+    (20_000, 9, 3), (600_000, 200, 3), (1_300_000, 255, 3)])
+def test_bad_offsets_yield_no_tokens_for_their_pieces(oracle_mod, n, n_pieces, kernels):
+    """Offsets out of range, a first one that is not 0, a last one that is not the end: every other piece has its tokens, every
+    offset is written, and nothing behind the capacity."""
+    import torch  # noqa: F401  (its HIP runtime before the library's)
+    import paper_2603_02597_amd as B
+    from workloads import configs as C
+    ev = C.make_eval("batch")
+    merges = C.load_merges(ev["table"])
+    data = np.resize(ev["bytes"], n).copy()
+    good_off = (np.arange(n_pieces + 1, dtype=np.int64) * n // n_pieces).astype(np.int32)
+    plan = [l["kernel"] for l in B.bpe_encode_plan(n, n_pieces)["launches"]]
+    assert "merge_cut_tiles_kernel" in plan and len(plan) == kernels
+    table = B.Table(merges)
+    all_ids, all_off = oracle_mod.encode(oracle_mod.Table(merges), data, good_off, n_threads=16)
+    for name, changes in {"beyond the end": {n_pieces // 2: n + 7}, "negative": {n_pieces // 3: -1},
+                          "several": {1: n + 1, n_pieces // 4: -2**31, n_pieces - 1: 2**31 - 1}, "first": {0: 3},
+                          "last": {n_pieces: n - 3}, "none": {}}.items():
+        off = good_off.copy()
+        for k, v in changes.items():
+            off[k] = v
+        print(f"[case] bad offsets, {name}: n_bytes={n} n_pieces={n_pieces}", flush=True)
+        ids, got_off, verdict = _run_with(B, table, data, off, 64)
+        assert verdict == (-11 if changes else 0)
+        good = _good_pieces(off, n)            # (these have both offsets as they were)
+        count = np.where(good, np.diff(all_off), 0)
+        want_ids = all_ids[np.repeat(good, np.diff(all_off))]
+        assert np.array_equal(got_off, np.concatenate([[0], np.cumsum(count)])), name
+        assert np.array_equal(ids[:want_ids.size], want_ids) and (ids[n:] == -7).all(), name
+    table.free()
+
+
+@pytest.mark.parametrize("n,n_pieces", [(10_000, 6), (20_000, 200), (600_000, 200), (2_500_000, 3000)])
+def test_offsets_that_decrease_write_nothing_behind_the_output(oracle_mod, n, n_pieces):
+    """Pieces that overlap have more tokens than out_ids has room for: bytes that no rule knows, a token each.  out_ids is the
+    head of a buffer here that would hold them all."""
+    import torch  # noqa: F401  (its HIP runtime before the library's)
+    import paper_2603_02597_amd as B
+    data = np.random.default_rng(6).integers(0x80, 0x100, n).astype(np.uint8)
+    table = B.Table([(97, 97), (97, 98), (98, 97)])
+    good_off = (np.arange(n_pieces + 1, dtype=np.int64) * n // n_pieces).astype(np.int32)
+    dip, late, back = good_off.copy(), good_off.copy(), good_off.copy()
+    dip[n_pieces // 2: 3 * n_pieces // 4] = good_off[1]
+    late[[1, n_pieces // 3, n_pieces // 2, -2]] = n
+    back[1::2] = n - good_off[1::2]
+    cases = {"a dip": dip, "some at the end": late, "back and forth": back}
+    if n_pieces == 6:
+        cases["overlap in one tile"] = np.array([0, 9200, 8200, 8250, 8300, 8400, n], dtype=np.int32)
+    for name, off in cases.items():
+        off = off.astype(np.int32)
+        assert B.bpe_encode_plan(n, n_pieces)["launches"][-2]["kernel"] == "merge_cut_tiles_kernel"
+        good = np.nonzero(_good_pieces(off, n))[0]
+        total = int((off[good + 1].astype(np.int64) - off[good]).sum())
+        print(f"[case] offsets that decrease, {name}: n_bytes={n} n_pieces={n_pieces}, {total} tokens", flush=True)
+        assert total < 2**31
+        ids, got_off, verdict = _run_with(B, table, data, off, 2 * n + min(total, 40_000_000))
+        assert verdict == -11 and (ids[n:] == -7).all()
+        count = np.zeros(n_pieces, dtype=np.int64)
+        count[good] = off[good + 1] - off[good]
+        assert np.array_equal(got_off, np.concatenate([[0], np.cumsum(count)])), name
+        want = np.concatenate([data[off[k]:off[k + 1]] for k in good])[:n] if total < 40_000_000 else None
+        assert want is None or np.array_equal(ids[:want.size], want), name
+    ids, got_off, verdict = _run_with(B, table, data, good_off, 64)
+    assert verdict == 0 and np.array_equal(got_off, good_off) and np.array_equal(ids[:n], data) and (ids[n:] == -7).all()
+    table.free()
+
+
+def test_a_recorded_call_after_one_with_bad_offsets(oracle_mod):
+    """The verdict of a replay stays until it is asked for; the next replay's offsets are judged for themselves."""
+    import torch
+    import paper_2603_02597_amd as B
+    from workloads import configs as C
+    ev = C.make_eval("seq131k")
+    merges = C.load_merges(ev["table"])
+    data = ev["bytes"][:50_000].copy()
+    good = np.arange(0, 50_001, 500, dtype=np.int32)
+    bad = good.copy()
+    bad[40] = 50_009
+    table, ot = B.Table(merges), oracle_mod.Table(merges)
+    want_ids, want_off = oracle_mod.encode(ot, data, good)
+    d, off = torch.from_numpy(data).cuda(), torch.from_numpy(good.copy()).cuda()
+    ids = torch.full((data.size,), -7, dtype=torch.int32, device="cuda")
+    got = torch.full((good.size,), -7, dtype=torch.int32, device="cuda")
+    ws = torch.empty(B.bpe_workspace_bytes(data.size, good.size - 1), dtype=torch.uint8, device="cuda")
+    B.bpe_encode(table, d, off, ids, got, ws)
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        B.bpe_encode(table, d, off, ids, got, ws)
+    for o in (bad, good, bad, bad, good):
+        off.copy_(torch.from_numpy(o))
+        ids.fill_(-7)
+        got.fill_(-7)
+        g.replay()
+        torch.cuda.synchronize()
+        if o is good:
+            assert np.array_equal(got.cpu().numpy(), want_off) and np.array_equal(ids[:want_ids.size].cpu().numpy(), want_ids)
+        else:
+            left_out = want_off[41] - want_off[39]
+            assert int(got[-1]) == want_ids.size - left_out and int(got[39]) == int(got[41])
+    assert B.bpe_encode_status(ws) == -11 and B.bpe_encode_status(ws) == 0
+    table.free()

@@ -76,6 +76,7 @@ struct TableView {
     const int32_t *rank_of;    // [n_merges] caller's rank value by rank order
     const uint2 *sym_lr;       // [max_id + 1] per id: {lowest rank order of a rule with the id as its right part,
                                // ... as its left part}, kNoRank where there is none
+    uint32_t max_id;           // last entry of sym_lr
     const uint4 *words;        // whole-piece table (see WordHash): {bytes 0-3, 4-7, 8-11 (zero-padded), word of the slot}
     int32_t word_shift;        // 32 - log2(slots of `words`)
     uint32_t half;             // slots per half (power of two, 2^16 .. 2^24)

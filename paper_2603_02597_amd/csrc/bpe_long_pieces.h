@@ -189,6 +189,12 @@ struct WaveScope {
     }
 };
 
+// A symbol of the buffer A, which may be the workspace.  There, pieces that overlap (bad offsets) write over each
+// other's symbols while they merge; what is read then must still not become a bad address (TableView::sym_lr).
+__device__ __forceinline__ uint32_t buffer_symbol(const EncodeParams &p, int32_t sym) {
+    return min((uint32_t)sym, p.table.max_id);
+}
+
 // A piece that one wavefront merges in LDS (or in the workspace) has shrunk to cur <= 64
 // symbols in A: the remaining passes run on one symbol per lane in registers (a pass
 // there is one table round trip and a permute; through LDS it is a dozen dependent
@@ -196,7 +202,7 @@ struct WaveScope {
 template <typename Ptr>
 __device__ __forceinline__ int finish_in_registers(const EncodeParams &p, Ptr A, int cur, int32_t *out) {
     const int lane = lane_id_here();
-    uint32_t sym = lane < cur ? (uint32_t)A[lane] : 0u;
+    uint32_t sym = lane < cur ? buffer_symbol(p, A[lane]) : 0u;
     cur = encode_wave_symbols(p, sym, cur);
     if (lane < cur) out[lane] = (int32_t)sym;
     WaveScope{}.sync();
@@ -300,7 +306,7 @@ __device__ __forceinline__ int encode_long_piece(const EncodeParams &p, int b, i
     while (cur >= 2) {
         if (cur <= kWave) return finish_small(p, A, cur, out, sc);
         const int n = best_rank_pass(p, A, B, cur, sc);
-        if (n < 0) break;
+        if (n < 0 || n >= cur) break;      // (a pass merges something, unless another piece writes over the buffers)
         Ptr t = A; A = B; B = t;
         cur = n;
     }
@@ -531,7 +537,7 @@ __device__ __forceinline__ int bound_pairs_pass_windows(const EncodeParams &p, c
         const int g1 = min(g0 + span, cur);
         const int lo = max(g0 - kSafeHalo, 0), hi = min(g1 + kSafeHalo, cur);
         const int n = hi - lo;
-        for (int i = tid; i < n; i += T) S[i] = A[lo + i];
+        for (int i = tid; i < n; i += T) S[i] = (int32_t)buffer_symbol(p, A[lo + i]);
         sc.sync();
         const uint64_t wbest = evaluate_pairs(p, S, R, QL, QR, n, sc);
         if (wbest != ~0ull) best = min(best, wbest + (uint32_t)lo);
@@ -622,18 +628,20 @@ __device__ __forceinline__ int encode_long_piece_bound(const EncodeParams &p, in
         sc.sync();
         CarriedRank carried = {kNoRank, 0, false};
         bool done = false;
+        int idle = 0;              // passes in a row that merged nothing: one at most, unless another piece writes over the buffers
         while (cur > cap) {
             const int n = bound_pairs_pass_windows(p, A, B, cur, S, R, QL, QR, cap, carried, sc);
             { int32_t *t = A; A = B; B = t; }
-            if (carried.rho == kNoRank) { done = true; cur = n; break; }    // no pair anywhere: n == cur
+            idle = n < cur ? 0 : idle + 1;
             cur = n;
+            if (carried.rho == kNoRank || idle > 1) { done = true; break; }         // no pair anywhere: n == cur
         }
         if (done) {
             if (A != out) for (int i = tid; i < cur; i += T) out[i] = A[i];
             sc.sync();
             return cur;
         }
-        for (int i = tid; i < cur; i += T) S[i] = A[i];
+        for (int i = tid; i < cur; i += T) S[i] = (int32_t)buffer_symbol(p, A[i]);
     } else {
         for (int i = tid; i < len; i += T) S[i] = p.bytes[b + i];
     }

@@ -459,6 +459,7 @@ extern "C" int bpe_table_build(const int32_t *merges, const int32_t *ranks, cons
     t->view.merged_of = (const int32_t *)(d + at.merged_of);
     t->view.rank_of = (const int32_t *)(d + at.rank_of);
     t->view.sym_lr = (const uint2 *)(d + at.sym_lr);
+    t->view.max_id = (uint32_t)(img.sym_lr.size() / 2 - 1);
     t->view.half = (uint32_t)half;
     t->view.low_bits = low_bits;
     t->view.index_bits = index_bits;

@@ -233,3 +233,29 @@ def test_a_recorded_call_after_one_with_bad_offsets(oracle_mod):
             assert int(got[-1]) == want_ids.size - left_out and int(got[39]) == int(got[41])
     assert B.bpe_encode_status(ws) == -11 and B.bpe_encode_status(ws) == 0
     table.free()
+
+
+@pytest.mark.parametrize("options", [{}, {"fused": -1}, {"fused": -1, "selection_level": 1}, {"fused": -1, "selection_level": 3, "lds_max_len": 700},
+                                     {"fused": -1, "selection_level": 2, "lds_max_len": 300, "wave_lds_max_len": 100}])
+def test_long_pieces_that_overlap_end_and_stay_in_bounds(options):
+    """Pieces that do not fit LDS keep their symbols in the workspace, at their bytes' place: overlapping ones write over each
+    other's.  Whatever they then make of it, they end, and write nothing behind the output."""
+    import torch
+    import paper_2603_02597_amd as B
+    n = 60_000
+    rng = np.random.default_rng(8)
+    data = np.concatenate([np.full(25_000, 97), rng.choice(u8(b"abc"), 15_000), np.full(20_000, 98)]).astype(np.uint8)
+    merges = [(97, 97), (256, 256), (257, 257), (98, 98), (259, 259), (97, 98), (98, 97), (98, 99), (99, 97), (256, 98), (261, 262)]
+    table = B.Table(merges)
+    off = np.array([0, 30_000, 9_000, 40_000, 12_001, 47_003, 26_000, 50_001, 39_000, n, 30_500, n], dtype=np.int32)
+    d, o = torch.from_numpy(data).cuda(), torch.from_numpy(off).cuda()
+    ids = torch.full((8 * n,), -7, dtype=torch.int32, device="cuda")
+    got = torch.full((off.size + 64,), -7, dtype=torch.int32, device="cuda")
+    ws = torch.full((B.bpe_workspace_bytes(n, off.size - 1),), 0x7F, dtype=torch.uint8, device="cuda")
+    print(f"[case] long pieces that overlap, {options}", flush=True)
+    B.bpe_encode(table, d, o, ids[:n], got[:off.size], ws, B.EncodeOptions(**options) if options else None)
+    assert B.bpe_encode_status(ws) == -11
+    assert (ids[n:] == -7).all() and (got[off.size:] == -7).all()
+    tokens = got[:off.size].cpu().numpy()
+    assert tokens[0] == 0 and (np.diff(tokens) >= 0).all()
+    table.free()

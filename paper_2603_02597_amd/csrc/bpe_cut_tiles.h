@@ -28,6 +28,10 @@ namespace bpe {
 constexpr int kTileGroup = 16;               // a thread looks at 16 bytes at a time ("group")
 constexpr int kAheadGroups = 16;             // groups looked at behind the tile for the end of its last part
 
+// Longest piece that merge_uncut_parts merges as a whole: 16 wavefronts then take as long as the tiles do (text without
+// spaces, 50k / 100k table, in pieces of 8,000 bytes 790 / 662 and 778 / 659 us; of 20,000 2,400 / 1,984 and 612 / 2,006).
+constexpr int kWideWhole = 2 * kWideBoundMax;
+
 // Bits of byte b in a table of its properties.
 constexpr uint32_t kCutBefore = 1, kCutBehind = 2, kTwin = 4;
 
@@ -74,13 +78,15 @@ struct CutTileShared {
     uint32_t part[kParts];         // how many of each kind a round of a wavefront has (10 bits each)
     uint32_t total[kParts];        // tokens
     int long_bytes, run_groups;    // bytes of parts beyond the columns; groups that are mostly one byte
+    int2 whole[4];                 // WIDE: pieces that start here and are merged as a whole: first byte, end
+    int n_whole;
     uint16_t start[kPieces + 2];   // first byte of every piece of the pass, counted from the first group; later its first token
     int ahead[kWavesPerGroup + 1];
     int wave_n[kWavesPerGroup];
 };
 
 // EAGER: both slots of the whole-piece table at once (see find_word).  WIDE: merge_uncut_parts has merged the parts beyond
-// kGroupBoundMax bytes (number of tokens in scratch2[first byte], the tokens in scratch).
+// kGroupBoundMax bytes, and some pieces as a whole (the tokens in scratch; for their numbers see there).
 template <int TILE, int ROUNDS, bool EAGER, bool WIDE>
 __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(EncodeParams p, CutSets cuts) {
     using Shared = CutTileShared<TILE, ROUNDS>;
@@ -116,11 +122,12 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
         prev[u] = lane == 0 && before_group >= 0 && before_group < p.n_bytes ? p.bytes[before_group] : 0u;
     }
     sh.code[tid] = (uint8_t)cut_code(cuts, (uint32_t)tid);
-    if (tid == 0) sh.long_bytes = sh.run_groups = 0;
+    if (tid == 0) sh.long_bytes = sh.run_groups = sh.n_whole = 0;
+    const bool in_whole = WIDE && p.tile_sum[tile] == 1;       // (looked at only where a piece reaches into the tile)
 
     // Pieces (seq_off): every tile checks a strided share of their offsets and finds the ones that start among its own
     // bytes, seq_off[s0 .. s1); seq_next: the first one at or behind the tile's end (a part ends there at the latest).
-    int s0, s1, seq_next = p.n_bytes;
+    int s0, s1, seq_next = p.n_bytes, seq_first = p.n_bytes;   // seq_first: the first one of all
     {
         bool bad = false;
         for (int64_t k = (int64_t)tile * kGroupThreads + tid; k <= p.n_seqs; k += (int64_t)gridDim.x * kGroupThreads) {
@@ -142,6 +149,7 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
             below = 0;
         }
         s0 = at + (int)__builtin_ctzll(~below);
+        if (WIDE && s0 <= p.n_seqs) seq_first = read_lane(v, s0 - at);
         const uint64_t inside = __ballot((int64_t)at + lane <= p.n_seqs && v < hi);
         if (~inside) {
             const int c = (int)__builtin_ctzll(~inside);
@@ -162,9 +170,19 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
             if (sv < lo || sv >= hi) continue;
             const uint32_t at = (uint32_t)sv + mis - v0;
             atomicOr(&sh.group[at >> 4], 1u << (at & 15));
+            if (WIDE && k < p.n_seqs) {
+                const int next = p.seq_off[k + 1];
+                if (next <= p.n_bytes && next - sv > kGroupBoundMax && next - sv <= kWideWhole && p.scratch2[sv] >= 0) {
+                    const int i = atomicAdd(&sh.n_whole, 1);
+                    if (i < 4) sh.whole[i] = make_int2(sv, next);          // (more only if the offsets decrease)
+                }
+            }
         }
         __syncthreads();
     }
+    const int n_whole = WIDE ? __builtin_amdgcn_readfirstlane(min(sh.n_whole, 4)) : 0;
+    bool out_of_tile = false;      // the last piece is merged as a whole and reaches out of the tile
+    for (int i = 0; i < n_whole; ++i) out_of_tile |= sh.whole[i].y > hi;
 
     // Start masks of the groups; starts behind the tile only say where its last piece ends.
     uint32_t mask = 0, piece_starts = 0;
@@ -185,6 +203,11 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
             const uint64_t runs = __ballot(n_equal > 12);
             if (lane == 0 && runs) atomicAdd(&sh.run_groups, __builtin_popcountll(runs));
             mask = m & below((uint32_t)hi + mis) & ~below((uint32_t)lo + mis);
+            if (in_whole && seq_first > lo) mask &= ~below((uint32_t)min(seq_first, hi) + mis);
+            for (int i = 0; i < n_whole; ++i) {
+                const int2 w = sh.whole[i];
+                mask &= ~(below((uint32_t)min(w.y, hi) + mis) & ~below((uint32_t)w.x + 1u + mis));
+            }
         }
         // (the groups of the second load are all the first wavefront's, and behind every other one)
         const uint64_t hit = __ballot(ahead != 0);
@@ -227,7 +250,8 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
 #pragma unroll
         for (int w = 1; w <= kWavesPerGroup; ++w) at = min(at, sh.ahead[w]);
         const uint32_t looked_at = v0 + 16u * (kGroups + kAheadGroups);        // positions below are done with
-        if (at != 0x7FFFFFFF) {
+        if (WIDE && out_of_tile) {                             // up to the next piece
+        } else if (at != 0x7FFFFFFF) {
             end = min(end, at);
         } else if ((uint32_t)end + mis > looked_at) {          // a long piece: on, 4 KiB at a time
             for (uint32_t v = looked_at; v < (uint32_t)end + mis; v += 16u * kGroupThreads) {
@@ -328,7 +352,8 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
         for (int r = 0; r < ROUNDS; ++r) {
             n_wide[r] = 0;
             if (WIDE && !whole_tile && len[r] > kGroupBoundMax) {
-                n_wide[r] = min(max(p.scratch2[origin + s[r]], 0), len[r]);    // (any number there if the offsets decrease)
+                const int n = p.scratch2[origin + s[r]];
+                n_wide[r] = min(n < 0 ? ~n : n, len[r]);       // (any number there if the offsets decrease)
                 atomicAdd(&sh.run_groups, TILE);               // no cutting at the pieces only: this part is done
             }
             kind[r] = tok0[r] >= 0 || len[r] <= 0 || n_wide[r] ? 0 : len[r] <= p.tiny_max ? 1 : len[r] <= p.col_max ? 2 : 3;
@@ -554,69 +579,132 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
     }
 }
 
-// A few very long pieces: the parts that have more symbols than four wavefronts keep resident are merged ahead of the tiles
-// by 16 (see merge_wide_kernel).  A workgroup looks at kWideSpan bytes for places to cut and takes the parts that start there;
-// text has none that long.  A launch more, but a part that long would take twice the time in a tile.  (The lines on the number
-// of pieces and on the workspace leave at most 2 MB of input, so positions fit 32 bits.)
-// Per call, 16 wavefronts per piece / now: text, 50k table, 24 KB in pieces of 2,358 bytes 105 / 19 us, 800 KB of 4,090 166 / 25;
-// with runs and random bytes 606 / 24 and 3,682 / 33 (1k table 2,272 / 36, 100k table 4,109 / 82).
-// Text without spaces, which falls into parts of hundreds of bytes, loses there and gains on longer pieces: 24 KB of 2,358
-// bytes 258 / 412, 800 KB of 4,090 453 / 1,058, 40 KB of 20,000 2,366 / 642.
+// A few very long pieces: what of them has more symbols than four wavefronts keep resident is merged ahead of the tiles
+// by 16 (see merge_wide_kernel): parts, or pieces of up to kWideWhole bytes that little would be gained by cutting.  A
+// launch more, but four wavefronts take twice the time for a part that long, and in a tile one part waits for the other.  (The
+// lines on the number of pieces and on the workspace leave at most 2 MB of input, so positions fit 32 bits.)
+// Per call, 16 wavefronts per piece / every piece cut / now, 50k table: text, 24 KB in pieces of 2,358 bytes 107 / 19 / 20 us, 800 KB
+// of 4,090 169 / 26 / 25, 40 KB of 20,000 507 / 19 / 20; with runs and random bytes, 100k table, 800 KB of 4,090 4,165 / 80 / 79;
+// text without spaces 24 KB of 2,358 298 / 659 / 307, 800 KB of 4,090 457 / 1,073 / 467, 40 KB of 20,000 2,490 / 620 / 620; random bytes, 100k
+// table, 800 KB of 4,090 850 / 3,470 / 860; runs of 200 bytes, 100k table, 800 KB of 4,090 530 / 1,001 / 629.
 constexpr int kWideSpan = 4 * kWideThreads;
+constexpr int kWideParts = kWideWhole / (kGroupBoundMax + 1);
 static_assert(kWideSpan < 2 * (kGroupBoundMax + 1), "one part that long lies inside a span, and another one reaches out of it");
-__device__ __forceinline__ void merge_uncut_parts(const EncodeParams &p, const CutSets &cuts, uint32_t *X, WideTmp &tmp) {
-    __shared__ uint8_t code[256];
+static_assert(kWideWhole + 3 <= 8 * kWideThreads, "eight bytes per thread");
+
+// Bit j set: a part may start at byte v + j of the word.  Positions v are counted from the 16-byte boundary at or below the
+// input, mis: byte 0.  (A word that holds a byte of the input lies in that byte's page.)  n_equal: see cuts_in_group.
+__device__ __forceinline__ uint32_t cuts_in_word(const EncodeParams &p, const uint8_t *code, int mis, int v, int &n_equal) {
+    const int v_end = p.n_bytes + mis;
+    n_equal = 0;
+    if (v >= v_end) return 0u;
+    const uint32_t w = *(const uint32_t *)(p.bytes - mis + v);
+    uint32_t last = v > mis ? p.bytes[v - 1 - mis] : 0u, last_code = code[last], m = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t b = (w >> (8 * j)) & 0xFFu, c = code[b];
+        const uint32_t cut = ((c & kCutBefore) | (last_code & kCutBehind) >> 1) & ~(b == last ? c >> 2 : 0u);
+        if (v + j > mis && v + j < v_end) m |= cut << j;
+        n_equal += b == last;
+        last = b;
+        last_code = c;
+    }
+    return m;
+}
+
+struct WideParts {
+    uint8_t code[256];
+    int2 part[kWideParts + 1 + 2];                 // what the workgroup merges: first byte, length
+    int n_parts;
+};
+
+// Lists the parts that long of the piece [b, e), if that has no more than kWideWhole bytes.  Where at least half of it are
+// parts of more bytes than a column takes, and it is not runs (the rule of the tiles), it is listed as a whole: its parts
+// would wait for each other in their tile.  scratch2[first byte] is its number of tokens then, and otherwise ~(number of tokens
+// of its first part, if that is one of the long ones).  tile_sum[t] of every tile that starts inside a piece: 1 if that piece is
+// merged as a whole.
+// at_b: the piece's first byte if its word in scratch2 is of that kind, else -1.  Returns whether it is the whole piece.
+__device__ __forceinline__ bool list_piece_parts(const EncodeParams &p, int b, int e, int tile_bytes, WideParts &sh, const WideScope &sc, int &at_b) {
+    const int tid = threadIdx.x, mis = p.tile_shift;
+    at_b = -1;
+    if (b < 0 || e <= b || e > p.n_bytes) return false;
+    const int len = e - b;
+    bool whole = false;
+    if (len > kGroupBoundMax && len <= kWideWhole) {
+        const int v = ((b + mis) & ~3) + 8 * tid, at = v - mis - b;        // at: counted from the piece's first byte
+        int equal0, equal1;
+        uint32_t m = cuts_in_word(p, sh.code, mis, v, equal0);
+        m |= cuts_in_word(p, sh.code, mis, v + 4, equal1) << 4;
+        auto below = [&](int limit) { return limit <= at ? 0u : limit - at >= 8 ? 0xFFu : (1u << (limit - at)) - 1u; };
+        m &= below(len) & ~below(1);
+        if (at <= 0 && at > -8) m |= 1u << -at;    // the piece's own start
+        const int last = m ? at + 31 - __builtin_clz(m) : -1;
+        const int before = sc.scan_max_excl(last), last_of_all = sc.max_all(last);
+        const int first = at + __builtin_ctz(m | 256u);
+        const int gap = m && before >= 0 ? first - before : 0;             // the part that ends here
+        if (gap > kGroupBoundMax) sh.part[atomicAdd(&sh.n_parts, 1)] = make_int2(b + before, gap);
+        if (tid == 0 && len - last_of_all > kGroupBoundMax) sh.part[atomicAdd(&sh.n_parts, 1)] = make_int2(b + last_of_all, len - last_of_all);
+        const int end_gap = tid == 0 ? len - last_of_all : 0;
+        // bytes of long parts | eights of equal bytes << 14 | long parts << 24
+        constexpr int kOnePart = 1 << 24, kOneRun = 1 << 14;
+        static_assert(kWideWhole < kOneRun && kWideWhole / kColumnMax < 128, "the sums fit");
+        int sums;
+        (void)sc.scan_sum_excl((gap > kColumnMax ? kOnePart + gap : 0) + (end_gap > kColumnMax ? kOnePart + end_gap : 0) +
+                               (at < len && equal0 + equal1 > 6 ? kOneRun : 0), sums);
+        sc.sync();
+        whole = sums >= 2 * kOnePart && 2 * (sums & (kOneRun - 1)) >= len && 64 * ((sums / kOneRun) & (kOnePart / kOneRun - 1)) <= len;
+        if (tid == 0) {
+            if (whole) { sh.part[0] = make_int2(b, len); sh.n_parts = 1; }
+            else p.scratch2[b] = ~0;
+        }
+        at_b = b;
+    }
+    for (int t = (b + mis) / tile_bytes + 1 + tid; t <= (e - 1 + mis) / tile_bytes; t += kWideThreads) p.tile_sum[t] = whole;
+    return whole;
+}
+
+// Lists the parts that long of pieces beyond kWideWhole that start in span `span` of kWideSpan bytes; text has none.
+__device__ __forceinline__ void list_span_parts(const EncodeParams &p, int span, WideParts &sh, const WideScope &sc) {
     __shared__ uint32_t bits[kWideSpan / 32];      // bytes of the span that pieces start with
-    __shared__ int2 part[2];                       // {first byte, length}
-    __shared__ int n_parts, next_piece;
-    const int tid = threadIdx.x;
-    const WideScope sc{tmp};
-    // Positions v are counted from the 16-byte boundary at or below the input: byte i is v = i + mis.
-    const int mis = (int)((uintptr_t)p.bytes & 15), v_end = p.n_bytes + mis;
-    const int v0 = (int)blockIdx.x * kWideSpan, lo = max(v0, mis), hi = min(v0 + kWideSpan, v_end);
+    __shared__ int2 longer[2];                     // the pieces of that many bytes that the span holds bytes of
+    __shared__ int n_longer, next_piece;
+    const int tid = threadIdx.x, mis = p.tile_shift, v_end = p.n_bytes + mis;
+    const int v0 = span * kWideSpan, lo = max(v0, mis), hi = min(v0 + kWideSpan, v_end);
     if (lo >= hi) return;
-    const uint32_t *const words = (const uint32_t *)(p.bytes - mis);
-    if (tid < 256) code[tid] = (uint8_t)cut_code(cuts, (uint32_t)tid);
     if (tid < kWideSpan / 32) bits[tid] = 0;
-    if (tid == 0) { n_parts = 0; next_piece = v_end; }
+    if (tid == 0) { n_longer = 0; next_piece = v_end; }
     __syncthreads();
-    for (int k = tid; k <= p.n_seqs; k += kWideThreads) {
-        const int sv = p.seq_off[k];
+    for (int k = tid; k < p.n_seqs; k += kWideThreads) {
+        const int sv = p.seq_off[k], next = p.seq_off[k + 1];
         if (sv < 0 || sv >= p.n_bytes) continue;
         const int v = sv + mis;
         if (v >= lo && v < hi) atomicOr(&bits[(v - v0) >> 5], 1u << ((v - v0) & 31));
         if (v >= hi) atomicMin(&next_piece, v);
+        if (next <= p.n_bytes && next - sv > kWideWhole && v < hi && next + mis > lo) {
+            const int at = atomicAdd(&n_longer, 1);
+            if (at < 2) longer[at] = make_int2(v, next + mis);             // (more than two only if the offsets decrease)
+        }
     }
+    __syncthreads();
+    const int n_pieces = __builtin_amdgcn_readfirstlane(min(n_longer, 2));
+    if (n_pieces == 0) return;
     if (lo == mis && tid == 0) atomicOr(&bits[(mis - v0) >> 5], 1u << ((mis - v0) & 31));      // byte 0 starts a piece
     __syncthreads();
-    // Bit j set: a part starts at byte v + j.  (A word that holds a byte of the input lies in that byte's page.)
-    auto cuts_in_word = [&](int v) -> uint32_t {
-        if (v >= v_end) return 0u;
-        const uint32_t w = words[v >> 2];
-        uint32_t last = v > mis ? p.bytes[v - 1 - mis] : 0u, last_code = code[last], m = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t b = (w >> (8 * j)) & 0xFFu, c = code[b];
-            const uint32_t cut = ((c & kCutBefore) | (last_code & kCutBehind) >> 1) & ~(b == last ? c >> 2 : 0u);
-            if (v + j > mis && v + j < v_end) m |= cut << j;
-            last = b;
-            last_code = c;
-        }
-        return m;
-    };
-    const uint32_t mask = cuts_in_word(v0 + 4 * tid) | ((bits[tid >> 3] >> (4 * (tid & 7))) & 15u);
+    auto of_longer = [&](int v) { return (v >= longer[0].x && v < longer[0].y) || (n_pieces == 2 && v >= longer[1].x && v < longer[1].y); };
+    int n_equal;
+    const uint32_t mask = cuts_in_word(p, sh.code, mis, v0 + 4 * tid, n_equal) | ((bits[tid >> 3] >> (4 * (tid & 7))) & 15u);
     const int last = mask ? 4 * tid + 31 - __builtin_clz(mask) : -1;
     const int before = sc.scan_max_excl(last);
     const int last_of_all = sc.max_all(last);
     if (last_of_all < 0) return;                   // (the same in every thread)
     if (mask && before >= 0) {
         const int n = 4 * tid + __builtin_ctz(mask) - before;
-        if (n > kGroupBoundMax) part[atomicAdd(&n_parts, 1)] = make_int2(v0 + before - mis, n);
+        if (n > kGroupBoundMax && of_longer(v0 + before)) sh.part[atomicAdd(&sh.n_parts, 1)] = make_int2(v0 + before - mis, n);
     }
     // the end of the last one: the next start behind the span
     int end = next_piece;
     for (int v = v0 + kWideSpan; v < end; v += kWideSpan) {
-        const uint32_t m = cuts_in_word(v + 4 * tid);
+        const uint32_t m = cuts_in_word(p, sh.code, mis, v + 4 * tid, n_equal);
         __syncthreads();                           // (between two uses of the scope's words)
         const int at = -sc.max_all(m ? -(v + 4 * tid + __builtin_ctz(m)) : -0x7FFFFFFF);
         end = min(end, at);
@@ -624,18 +712,37 @@ __device__ __forceinline__ void merge_uncut_parts(const EncodeParams &p, const C
     }
     __syncthreads();
     const int first = v0 + last_of_all;
-    if (tid == 0 && end - first > kGroupBoundMax) {
-        part[n_parts] = make_int2(first - mis, end - first);
-        ++n_parts;
+    if (tid == 0 && end - first > kGroupBoundMax && of_longer(first)) sh.part[sh.n_parts++] = make_int2(first - mis, end - first);
+}
+
+// Workgroup i takes piece i, and if some piece is longer than kWideWhole, span i, too.  Number of tokens in scratch2[first byte].
+// (A workgroup for each: 800 KB of text in pieces of 4,090 bytes 28.0 us, the 390 of them are more than the chip holds at once.)
+__device__ __forceinline__ void merge_uncut_parts(const EncodeParams &p, const CutSets &cuts, int tile_bytes, uint32_t *X, WideTmp &tmp) {
+    __shared__ WideParts sh;
+    const int tid = threadIdx.x;
+    const WideScope sc{tmp};
+    const int i0 = min((int)blockIdx.x, p.n_seqs - 1);
+    const int b0 = p.seq_off[i0], e0 = p.seq_off[i0 + 1];      // (asked for ahead of the others)
+    bool longer = false;
+    for (int k = tid; k < p.n_seqs; k += kWideThreads) longer |= (int64_t)p.seq_off[k + 1] - p.seq_off[k] > kWideWhole;
+    if (tid < 256) sh.code[tid] = (uint8_t)cut_code(cuts, (uint32_t)tid);
+    if (tid == 0) sh.n_parts = 0;
+    longer = __syncthreads_or(longer);
+    int at_b = -1;
+    bool whole = false;
+    if ((int)blockIdx.x < p.n_seqs) whole = list_piece_parts(p, b0, e0, tile_bytes, sh, sc, at_b);
+    if (longer) {
+        __syncthreads();
+        list_span_parts(p, blockIdx.x, sh, sc);
     }
     __syncthreads();
-    const int n = __builtin_amdgcn_readfirstlane(n_parts);
+    const int n = __builtin_amdgcn_readfirstlane(sh.n_parts);
 #pragma unroll 1
     for (int i = 0; i < n; ++i) {
-        const int b = __builtin_amdgcn_readfirstlane(part[i].x), len = __builtin_amdgcn_readfirstlane(part[i].y);
+        const int b = __builtin_amdgcn_readfirstlane(sh.part[i].x), len = __builtin_amdgcn_readfirstlane(sh.part[i].y);
         const int c = merge_wide_piece(p, b, len, X, sc);
         __syncthreads();
-        if (tid == 0) p.scratch2[b] = c;
+        if (tid == 0) p.scratch2[b] = b == at_b && !whole ? ~c : c;
     }
 }
 

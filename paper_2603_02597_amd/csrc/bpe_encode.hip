@@ -943,7 +943,7 @@ __device__ __forceinline__ int merge_wide_piece(const EncodeParams &p, int o, in
     return encode_long_piece<WideScope, int32_t *>(p, o, len, p.scratch + o, p.scratch2 + o, sc);
 }
 
-__device__ __forceinline__ void merge_uncut_parts(const EncodeParams &p, const CutSets &cuts, uint32_t *X, WideTmp &tmp);     // bpe_cut_tiles.h
+__device__ __forceinline__ void merge_uncut_parts(const EncodeParams &p, const CutSets &cuts, int tile_bytes, uint32_t *X, WideTmp &tmp);     // bpe_cut_tiles.h
 
 // Inputs of a few very long pieces (one piece per tile, at most kWideMaxPieces of
 // them, longer on average than the 2,052 symbols four wavefronts keep resident): a
@@ -954,11 +954,11 @@ __device__ __forceinline__ void merge_uncut_parts(const EncodeParams &p, const C
 // wavefronts, 178 against 224 us: more barriers than work).
 constexpr int kWideMaxPieces = 256;     // one workgroup per CU
 template <bool PARTS>
-__global__ void __launch_bounds__(kWideThreads) merge_wide_kernel(EncodeParams p, CutSets cuts) {
+__global__ void __launch_bounds__(kWideThreads) merge_wide_kernel(EncodeParams p, CutSets cuts, int tile_bytes) {
     __shared__ uint32_t X[4 * kWideBoundMax];
     __shared__ WideTmp tmp;
     if (PARTS) {
-        merge_uncut_parts(p, cuts, X, tmp);
+        merge_uncut_parts(p, cuts, tile_bytes, X, tmp);
         return;
     }
     const int tid = threadIdx.x;
@@ -2240,7 +2240,7 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
         CutSets cuts = {};
         if (!dry) cuts = table->cuts;
         const bool wide = few_long_pieces(n_bytes, n_pieces);
-        if (wide) run.run("merge_wide_kernel", 0, merge_wide_kernel<true>, cut_tiles(n_bytes, kWideSpan), kWideThreads, p, cuts);
+        if (wide) run.run("merge_wide_kernel", 0, merge_wide_kernel<true>, std::max(n_pieces, cut_tiles(n_bytes, kWideSpan)), kWideThreads, p, cuts, (int)cut_tile);
         const auto kernel = cut_tile == 1024   ? (wide ? merge_cut_tiles_kernel<1024, 1, true, true> : merge_cut_tiles_kernel<1024, 1, true, false>)
                             : cut_tile == 2048 ? (wide ? merge_cut_tiles_kernel<2048, 2, true, true> : merge_cut_tiles_kernel<2048, 2, true, false>)
                                                : (wide ? merge_cut_tiles_kernel<kCutTileMax, 2, false, true>
@@ -2329,7 +2329,7 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
             p.rec = dp.rec_all;
             p.rep_of = dp.rep;
         } else if (grid > 0 && p.W == 1 && !p.paper && few_long_pieces(n_bytes, n_pieces)) {
-            run.run("merge_wide_kernel", i0, merge_wide_kernel<false>, grid, kWideThreads, p, CutSets{});
+            run.run("merge_wide_kernel", i0, merge_wide_kernel<false>, grid, kWideThreads, p, CutSets{}, 0);
         } else if (grid > 0) {
             // Word-sized pieces on average (a tile is 256 pieces): the rare longer ones go to workgroups
             // of their own at the head of the grid, one for every kTilesPerLongGroup tiles.

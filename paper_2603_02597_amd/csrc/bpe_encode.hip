@@ -1893,6 +1893,20 @@ static int64_t cut_tile_size(const Layout &l, int64_t n_bytes) {
     return 0;
 }
 
+// Pieces of so many bytes on average and more are cut.  Short ones fill the columns better as they are, and what cannot be cut
+// costs more in tiles; on few tiles a call is as long as one tile's chain all the same.  Uncut / cut, in chunks of 20:
+// text 30 KB 22 / 18 us, 120 KB 39 / 18, 200 KB 31 / 17; with runs and random bytes, 1k table, 30 KB 19 / 25, 120 KB 32 / 25, 200 KB 31 / 28, 230
+// KB 32 / 40 (100k table 22 / 23, 39 / 24, 38 / 70: one stretch of its random bytes, from 136 KB on).
+// 840 KB in chunks of 20, 32, 40 and 64: text 30 / 20, 32 / 20, 40 / 20, 55 / 19; with runs and random bytes 34 / 45, 35 / 38, 42 / 35, 59
+// / 27 (100k table 32 / 62, 35 / 52, 42 / 47, 60 / 42).  Of 1.5 and 4 MB in chunks of 48 and 64: text 45 / 22 and 59 / 21, 105 / 46 and 90 /
+// 41; with runs and random bytes, 1k and 100k table, 38 / 45 and 47 / 39, 113 / 131 and 96 / 118 (56: 126 / 118).
+// What cutting takes from data without a place to cut beyond these lines: text without spaces, 840 KB in pieces of 64, 256 and
+// 1,024 bytes 49 / 61, 197 / 200, 302 / 314, 4 MB 80 / 143, 744 / 772, 946 / 1,287 (its 1,302 tiles take a second round of the chip).
+static int64_t cut_least_bytes(int64_t n_bytes) {
+    const int64_t n_tiles = cut_tiles(n_bytes, 1024);
+    return n_tiles <= 192 ? kTinyMax + 1 : n_tiles <= kResidentGroups ? 40 : 56;
+}
+
 // Tiles of merge_byte_runs_kernel: they start up to 15 bytes below the first byte.  That path is the quicker one wherever
 // the small tiles end (1.4 MB: 15 against 23.5 us through the pre-tokenizer), but for one tile: a test of
 // bpe_encode_raw_plan names the pre-tokenizer path at the first size beyond them.
@@ -2125,12 +2139,11 @@ static int launch_encode(const bpe_table *table, const uint8_t *bytes, const int
                   (long long)n_tiles, kWave);
         return BPE_ERR_OPTION;
     }
-    // Pieces that are longer on average than a lane takes are cut first, in tiles of bytes (unless an option asks for a
-    // path of its own).  Up to 16 bytes most are words, which are one probe as they are; from there on cutting wins wherever
-    // there is something to cut (20-byte chunks of text, 4 MB: 89.8 -> 49.3 us, 840 KB 27.8 -> 23.7, 20 KB 19.8 -> 19.7).
+    // Long pieces are cut first, in tiles of bytes (unless an option asks for a path of its own).
     bpe_encode_options plain = {};
     const bool any_option = opts && memcmp(opts, &plain, sizeof(plain)) != 0;
-    const int64_t cut_tile = !raw && !any_option && n_pieces > 0 && n_bytes / n_pieces > kTinyMax ? cut_tile_size(l, n_bytes) : 0;
+    int64_t cut_tile = !raw && !any_option && n_pieces > 0 ? cut_tile_size(l, n_bytes) : 0;
+    if (cut_tile && n_bytes / n_pieces < cut_least_bytes(n_bytes)) cut_tile = 0;
     const bool fused = !raw && !cut_tile && !p.paper && !o.dedup && n_tiles > 0 &&
                        (o.fused > 0 || (o.fused == 0 && n_tiles <= kFusedMaxTiles && short_pieces));
     if (plan) {

@@ -347,3 +347,15 @@ def test_status_from_words():
     assert verdict(ok[:3] + [call] + ok[4:]) == -9
     assert verdict([call, call, call, call] + ok[4:]) == -9          # a run-out wait outranks the rest
     assert lib.bpe_status_from_words(None) == -1
+
+
+def test_which_chunks_are_cut():
+    """bpe_encode cuts pieces from 17 bytes on average on up to 192 tiles of 1 KiB, from 40 on up to 1,024, from 56 beyond, and never
+    where an option is given."""
+    for n, least in ((20_400, 17), (192 * 1024 - 15, 17), (192 * 1024 - 14, 40), (840_000, 40), (1024 * 1024 - 15, 40),
+                     (1024 * 1024 - 14, 56), (4_000_000, 56), (100_000_000, 56)):
+        n_pieces = n // least
+        kernel = lambda n_pieces, opts=None: B.bpe_encode_plan(n, n_pieces, opts)["launches"][0]["kernel"]
+        assert kernel(n_pieces) == "merge_cut_tiles_kernel", (n, least)
+        assert kernel(n // least + n // 100) != "merge_cut_tiles_kernel", (n, least)
+        assert kernel(n_pieces, B.EncodeOptions(fused=-1)) != "merge_cut_tiles_kernel"

@@ -130,7 +130,7 @@ def _good_pieces(off, n):
 
 # bytes and pieces: tiles of each size, with and without merge_wide_kernel, and as many as need a scan kernel
 @pytest.mark.parametrize("n,n_pieces,kernels", [
-    (40_000, 700, 2), (300_000, 4600, 2), (1_500_000, 40_000, 2), (2_500_000, 3000, 2), (8193 * 3072 + 5, 16_000, 3),
+    (40_000, 700, 2), (300_000, 4600, 2), (1_500_000, 25_000, 2), (2_500_000, 3000, 2), (8193 * 3072 + 5, 16_000, 3),
     (20_000, 9, 3), (600_000, 200, 3), (1_300_000, 255, 3)])
 def test_bad_offsets_yield_no_tokens_for_their_pieces(oracle_mod, n, n_pieces, kernels):
     """Offsets out of range, a first one that is not 0, a last one that is not the end: every other piece has its tokens, every

@@ -24,6 +24,7 @@ struct bpe_vocab {
     const Record *tok;      // [n_ids] by internal id: see token_record
     const Record *tok_out;  // [n_out] by output id, or nullptr
     const int32_t *out_of, *int_of;
+    int64_t token_bytes;    // of all expansions
     const uint8_t *pool;
     int32_t n_out;
     int device;
@@ -431,6 +432,7 @@ extern "C" int bpe_vocab_build(const int32_t *merges, const int32_t *ranks, cons
     v->info.pool_bytes = (int64_t)pool.size();
     v->info.device_bytes = b_total;
     v->info.max_token_bytes = (int32_t)longest;
+    for (int64_t id = 0; id < n_ids; ++id) v->token_bytes += tok_len[id];
     v->info.has_output_ids = output_ids ? 1 : 0;
     *out_vocab = v;
     return BPE_OK;
@@ -513,21 +515,36 @@ extern "C" int bpe_decode(const bpe_vocab *v, const int32_t *ids, int64_t n_toke
     //   (2, 64)  10.0  13.6  19.1  33.4  55  269      (2, 256) 8.9  12.5  17.6  31.2  54  293
     //   (4, 32)  13.0  14.7  20.7  30.3  50  238      (4, 256) 11.3 12.4  19.1  28.3  49  264
     // Up to 0.5 M tokens the call's launch hides the difference, but tokens of more than 12 bytes do not fit the stage of two
-    // rounds (0.3 to 0.5 M of 13 to 16 bytes: 9.9 to 10.6 us with one round, 13.2 to 13.6 with two).  Against (1, 256) to
-    // 0.5 M, (2, 64) to 4 M, (4, 32) beyond: 1 M 12.7 -> 11.8, 2.1 M 18.8 -> 17.3, 4.2 M 31.6 -> 27.6, 8 M 48.6 -> 47.0; 2 M
-    // random ids of 1 to 6 bytes 18.2 -> 21.4, 4 M of them 35.3 -> 32.8.  With an output numbering records lie anywhere, tiles come
-    // to their look-back at different times, and the polls of a full window cost more than they save (text with random bytes,
-    // 1.9 M and 2.5 M tokens of the 50k table 14.9 -> 16.8 and 18.2 -> 22.1; 128 tiles at a time 21.0): (2, 64)
-    // there up to 4 M tokens, (4, 32) beyond.
+    // rounds (0.3 to 0.5 M of 13 to 16 bytes: 9.9 to 10.6 us with one round, 13.2 to 13.6 with two).
+    // Beyond, it depends on where the records lie: where tiles wait for them, they come to their look-back at different times,
+    // and the polls of a full window cost more than they save.  (2, 64), (2, 128) and (2, 256):
+    //   2 M tokens    50k table: text 18.3, 18.0, 17.2, with random bytes 14.1, 13.4, 12.9, random ids 19.9, 19.5, 18.9, random ids
+    //                 of up to 6 bytes 19.1, 19.4, 21.2; 1k table: text 13.4, 12.6, 11.7, random ids 14.2, 13.6, 12.7
+    //   2.5 M         50k table: 20.1, 19.4, 19.1; 15.3, 15.1, 14.7; 24.6, 25.3, 29.4; 23.3, 23.9, 26.9; 1k: 13.6, 13.4, 13.2; 16.5, 15.8, 15.5
+    // (2, 64), (4, 32), (4, 64) and (4, 256), text, random bytes, random ids:
+    //   3.5 M         50k table: 28.5, 27.0, 25.8, 26.2; 21.8, 19.4, 18.4, 19.3; 32.8, 29.8, 30.3, 31.4; 100k table, whose mean token does not
+    //                 fit the 8 bytes that four rounds stage: 28.3, 27.1, 26.1, 25.9; 45.1, 52.9, 52.9, 54.3; 92.5, 113, 113, 113;
+    //                 1k table: 19.0, 17.7, 16.5, 15.7; 17.7, 16.2, 15.1, 14.3; 21.7, 20.0, 19.4, 18.7
+    //   6 M           50k table: 42.3, 40.6, 40.3, 39.4; 32.8, 31.3, 30.9, 32.1; 50.9, 45.2, 45.5, 46.7; 1k table: 26.9, 26.4, 25.7, 24.9
+    // So a full window while a compute unit's cache holds the records (of up to 2,048 ids), and for others up to 2.3 M
+    // tokens, 128 tiles up to 3 M, 64 up to 4 M.  With an output numbering records lie anywhere (text with random
+    // bytes, 2 and 2.5 M tokens of the 50k table 15.5, 17.8, 18.2 and 17.4, 20.4, 21.1): (2, 64) there up to 4 M tokens, (4, 32) beyond.
     const dim3 block(kGroupThreads);
     auto tiles = [&](int rounds) { return (unsigned)std::max<int64_t>((n_tokens + rounds * kTileTokens - 1) / (rounds * kTileTokens), 1); };
     const hipStream_t st = (hipStream_t)stream;
-    if (n_tokens <= 512 * kTileTokens) hipLaunchKernelGGL((decode_kernel<1, kGroupThreads>), dim3(tiles(1)), block, 0, st, p);
-    else if (ids_are_output_ids && n_tokens <= 4096 * kTileTokens) hipLaunchKernelGGL((decode_kernel<2, 64>), dim3(tiles(2)), block, 0, st, p);
-    else if (ids_are_output_ids) hipLaunchKernelGGL((decode_kernel<4, 32>), dim3(tiles(4)), block, 0, st, p);
-    else if (n_tokens <= 3072 * kTileTokens) hipLaunchKernelGGL((decode_kernel<2, kGroupThreads>), dim3(tiles(2)), block, 0, st, p);
-    else if (n_tokens <= 8192 * kTileTokens) hipLaunchKernelGGL((decode_kernel<4, kGroupThreads>), dim3(tiles(4)), block, 0, st, p);
-    else hipLaunchKernelGGL((decode_kernel<4, 32>), dim3(tiles(4)), block, 0, st, p);
+    const int64_t n_tiles = (n_tokens + kTileTokens - 1) / kTileTokens;
+    const bool near = v->info.n_ids <= 2048, long_tokens = v->token_bytes > 8 * v->info.n_ids;
+#define LAUNCH_DECODE(ROUNDS, WINDOW) hipLaunchKernelGGL((decode_kernel<ROUNDS, WINDOW>), dim3(tiles(ROUNDS)), block, 0, st, p)
+    if (n_tiles <= 512) LAUNCH_DECODE(1, kGroupThreads);
+    else if (ids_are_output_ids && n_tiles <= 4096) LAUNCH_DECODE(2, 64);
+    else if (ids_are_output_ids) LAUNCH_DECODE(4, 32);
+    else if (n_tiles <= (near ? 3072 : 2304)) LAUNCH_DECODE(2, kGroupThreads);
+    else if (n_tiles <= 3072) LAUNCH_DECODE(2, 128);
+    else if (near && n_tiles <= 8192) LAUNCH_DECODE(4, kGroupThreads);
+    else if (n_tiles <= 4096 && long_tokens) LAUNCH_DECODE(2, 64);
+    else if (n_tiles <= 4096) LAUNCH_DECODE(4, 64);
+    else LAUNCH_DECODE(4, 32);
+#undef LAUNCH_DECODE
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? BPE_OK : hip_fail(e, "bpe_decode launch");
 }

@@ -77,3 +77,34 @@ def test_inline_and_long_tokens_in_one_tile(oracle_mod, n, first_round):
         assert np.array_equal(got[3:3 + cap], want[:cap]) and (got[:3] == 0xEE).all() and (got[3 + cap:] == 0xEE).all()
         assert np.array_equal(tbo.cpu().numpy(), want_off)
     vocab.free()
+
+
+# both sides of every line between (rounds, tiles looked at) of vocabularies of more than 2,048 ids; the 100k table's mean token does
+# not fit the stage of four rounds
+@pytest.mark.parametrize("table_name", ["t50k", "t100k"])
+@pytest.mark.parametrize("tiles", [512, 2304, 3072, 4096])
+def test_both_sides_of_the_lines_between_tiles(oracle_mod, table_name, tiles):
+    import torch
+    import paper_2603_02597_amd as B
+    from workloads import configs as C
+    merges = C.load_merges(table_name)
+    rng = np.random.default_rng(tiles)
+    n_ids = 256 + len(merges)
+    ids = np.where(rng.random(tiles * 1024 + 1) < 0.7, rng.integers(97, 1500, tiles * 1024 + 1), rng.integers(0, n_ids, tiles * 1024 + 1)).astype(np.int32)
+    table, vocab = oracle_mod.Table(merges), B.Vocab(merges)
+    want, want_off = oracle_mod.decode(table, ids), oracle_mod.token_byte_offsets(table, ids)
+    d_ids = torch.from_numpy(ids).cuda()
+    for n in (tiles * 1024, tiles * 1024 + 1):
+        print(f"[case] {table_name}, {n} tokens", flush=True)
+        size = int(want_off[n])
+        buf = torch.full((size + 16,), 0xEE, dtype=torch.uint8, device="cuda")
+        tbo = torch.empty(n + 1, dtype=torch.int32, device="cuda")
+        nb = torch.zeros(1, dtype=torch.int32, device="cuda")
+        ws = torch.empty(B.bpe_decode_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+        for _ in range(2):
+            B.bpe_decode(vocab, d_ids[:n], buf[:size], ws, tbo, nb)
+        assert B.bpe_encode_status(ws) == 0 and int(nb.item()) == size
+        got = buf.cpu().numpy()
+        assert np.array_equal(got[:size], want[:size]) and (got[size:] == 0xEE).all()
+        assert np.array_equal(tbo.cpu().numpy(), want_off[:n + 1])
+    vocab.free()

@@ -81,7 +81,7 @@ struct CutTileShared {
     int2 whole[4];                 // WIDE: pieces that start here and are merged as a whole: first byte, end
     int n_whole;
     uint16_t start[kPieces + 2];   // first byte of every piece of the pass, counted from the first group; later its first token
-    int ahead[kWavesPerGroup + 1];
+    int ahead[kWavesPerGroup];
     int wave_n[kWavesPerGroup];
 };
 
@@ -91,8 +91,7 @@ template <int TILE, int ROUNDS, bool EAGER, bool WIDE>
 __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(EncodeParams p, CutSets cuts) {
     using Shared = CutTileShared<TILE, ROUNDS>;
     constexpr int kPieces = Shared::kPieces, kParts = Shared::kParts, kGroups = Shared::kGroups;
-    constexpr int kLoads = kGroups + kAheadGroups > kGroupThreads ? 2 : 1;     // groups per thread
-    static_assert(kGroups <= kGroupThreads && kGroups + kAheadGroups <= kGroupThreads + kWave, "the second load is the first wavefront's");
+    static_assert(kGroups + kAheadGroups <= kGroupThreads, "a group per thread");
     __shared__ Shared sh;
     const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int tile = blockIdx.x;
@@ -106,21 +105,13 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
 
     // The tile's bytes and the 256 behind them, asked for before anything else.  (A group that holds a byte of
     // the input lies in that byte's page.)
-    uint4 x[kLoads];
-#pragma unroll
-    for (int u = 0; u < kLoads; ++u) {
-        const int g = tid + u * kGroupThreads;
-        x[u] = make_uint4(0, 0, 0, 0);
-        if (g < kGroups + kAheadGroups && v0 + 16u * (uint32_t)g < v_end) x[u] = src[(v0 >> 4) + (uint32_t)g];
-    }
+    uint4 x = make_uint4(0, 0, 0, 0);
+    const uint32_t group_v = v0 + 16u * (uint32_t)tid;         // position of the thread's group
+    if (tid < kGroups + kAheadGroups && group_v < v_end) x = src[group_v >> 4];
 
     // (the byte before the group, where no lane below holds it)
-    uint32_t prev[kLoads];
-#pragma unroll
-    for (int u = 0; u < kLoads; ++u) {
-        const int64_t before_group = (int64_t)v0 + 16 * (tid + u * kGroupThreads) - 1 - mis;
-        prev[u] = lane == 0 && before_group >= 0 && before_group < p.n_bytes ? p.bytes[before_group] : 0u;
-    }
+    const int64_t before_at = (int64_t)group_v - 1 - mis;
+    const uint32_t prev = lane == 0 && before_at >= 0 && before_at < p.n_bytes ? p.bytes[before_at] : 0u;
     sh.code[tid] = (uint8_t)cut_code(cuts, (uint32_t)tid);
     if (tid == 0) sh.long_bytes = sh.run_groups = sh.n_whole = 0;
     const bool in_whole = WIDE && p.tile_sum[tile] == 1;       // (looked at only where a piece reaches into the tile)
@@ -186,42 +177,33 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
 
     // Start masks of the groups; starts behind the tile only say where its last piece ends.
     uint32_t mask = 0, piece_starts = 0;
-#pragma unroll
-    for (int u = 0; u < kLoads; ++u) {
-        const int g = tid + u * kGroupThreads;
-        const uint32_t v = v0 + 16u * (uint32_t)g;             // position of the group's first byte
-        // bits of the group's bytes below position `limit`
-        auto below = [&](uint32_t limit) { return limit <= v ? 0u : limit - v >= 16u ? 0xFFFFu : (1u << (limit - v)) - 1u; };
-        const uint32_t before_group = (uint32_t)wave_from_lane_below((int)(x[u].w >> 24), (int)prev[u]);
-        int n_equal = 0;
-        uint32_t m = g < kGroups + kAheadGroups ? cuts_in_group(sh.code, x[u], before_group, n_equal) : 0u;
-        const uint32_t ahead = m & below(v_end) & ~below((uint32_t)hi + mis);
-        if (u == 0 && g < kGroups) {
-            if (any_seq) piece_starts = sh.group[g];
-            if (lo == 0 && v <= mis && mis < v + 16u) piece_starts |= 1u << (mis - v);     // byte 0 starts a piece
-            m |= piece_starts;
-            const uint64_t runs = __ballot(n_equal > 12);
-            if (lane == 0 && runs) atomicAdd(&sh.run_groups, __builtin_popcountll(runs));
-            mask = m & below((uint32_t)hi + mis) & ~below((uint32_t)lo + mis);
-            if (in_whole && seq_first > lo) mask &= ~below((uint32_t)min(seq_first, hi) + mis);
-            for (int i = 0; i < n_whole; ++i) {
-                const int2 w = sh.whole[i];
-                mask &= ~(below((uint32_t)min(w.y, hi) + mis) & ~below((uint32_t)w.x + 1u + mis));
-            }
+    // bits of the group's bytes below position `limit`
+    auto below = [&](uint32_t limit) { return limit <= group_v ? 0u : limit - group_v >= 16u ? 0xFFFFu : (1u << (limit - group_v)) - 1u; };
+    const uint32_t before_group = (uint32_t)wave_from_lane_below((int)(x.w >> 24), (int)prev);
+    int n_equal = 0;
+    uint32_t m = tid < kGroups + kAheadGroups ? cuts_in_group(sh.code, x, before_group, n_equal) : 0u;
+    const uint32_t ahead = m & below(v_end) & ~below((uint32_t)hi + mis);
+    if (tid < kGroups) {
+        if (any_seq) piece_starts = sh.group[tid];
+        if (lo == 0 && group_v <= mis && mis < group_v + 16u) piece_starts |= 1u << (mis - group_v);     // byte 0 starts a piece
+        m |= piece_starts;
+        const uint64_t runs = __ballot(n_equal > 12);
+        if (lane == 0 && runs) atomicAdd(&sh.run_groups, __builtin_popcountll(runs));
+        mask = m & below((uint32_t)hi + mis) & ~below((uint32_t)lo + mis);
+        if (in_whole && seq_first > lo) mask &= ~below((uint32_t)min(seq_first, hi) + mis);
+        for (int i = 0; i < n_whole; ++i) {
+            const int2 w = sh.whole[i];
+            mask &= ~(below((uint32_t)min(w.y, hi) + mis) & ~below((uint32_t)w.x + 1u + mis));
         }
-        // (the groups of the second load are all the first wavefront's, and behind every other one)
-        const uint64_t hit = __ballot(ahead != 0);
-        if (u == 0 || wv == 0) {
-            int at = 0x7FFFFFFF;
-            if (hit) {
-                const int l = __builtin_ctzll(hit);
-                at = (int)(__builtin_amdgcn_readlane((int)v, l) - mis) + __builtin_ctz((uint32_t)__builtin_amdgcn_readlane((int)ahead, l));
-            }
-            if (lane == 0) sh.ahead[u == 0 ? wv : kWavesPerGroup] = at;
-        }
-        if (g < Shared::kStaged) sh.lds.bytes[g] = x[u];
     }
-    if (kLoads == 1 && tid == 0) sh.ahead[kWavesPerGroup] = 0x7FFFFFFF;
+    const uint64_t hit = __ballot(ahead != 0);
+    int first_ahead = 0x7FFFFFFF;
+    if (hit) {
+        const int l = __builtin_ctzll(hit);
+        first_ahead = (int)(__builtin_amdgcn_readlane((int)group_v, l) - mis) + __builtin_ctz((uint32_t)__builtin_amdgcn_readlane((int)ahead, l));
+    }
+    if (lane == 0) sh.ahead[wv] = first_ahead;
+    if (tid < Shared::kStaged) sh.lds.bytes[tid] = x;
     const int c0 = __builtin_popcount(mask);
     const int inc0 = wave_scan_inclusive(c0);
     if (lane == kWave - 1) sh.wave_n[wv] = inc0;
@@ -248,7 +230,7 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
     {
         int at = sh.ahead[0];
 #pragma unroll
-        for (int w = 1; w <= kWavesPerGroup; ++w) at = min(at, sh.ahead[w]);
+        for (int w = 1; w < kWavesPerGroup; ++w) at = min(at, sh.ahead[w]);
         const uint32_t looked_at = v0 + 16u * (kGroups + kAheadGroups);        // positions below are done with
         if (WIDE && out_of_tile) {                             // up to the next piece
         } else if (at != 0x7FFFFFFF) {
@@ -283,14 +265,9 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
         const int lane = lane_id_here(), tid = wv * kWave + lane;
         if (k0) {
             __syncthreads();       // the pass before is done with the lists
-#pragma unroll
-            for (int u = 0; u < kLoads; ++u) {                 // the columns may have taken the bytes' place
-                const int g = tid + u * kGroupThreads;
-                if (g < Shared::kStaged) {
-                    uint4 again = make_uint4(0, 0, 0, 0);
-                    if (v0 + 16u * (uint32_t)g < v_end) again = src[(v0 >> 4) + (uint32_t)g];
-                    sh.lds.bytes[g] = again;
-                }
+            if (tid < Shared::kStaged) {                       // the columns may have taken the bytes' place
+                const uint32_t at = v0 + 16u * (uint32_t)tid;
+                sh.lds.bytes[tid] = at < v_end ? src[at >> 4] : make_uint4(0, 0, 0, 0);
             }
         }
         // the starts of the pass's pieces, and of the one behind them

@@ -10,12 +10,12 @@
 // list in the workspace until then.  Between the two kernels a piece is one word in piece_word[first byte of its
 // tile's first piece + its number in the tile]: its token, or where it starts and how many tokens lie in scratch.
 //
-// Per call, through the pre-tokenizer and one tile of 256 pieces per workgroup / now: text of known words 1.9 MB 30.1 /
-// 15.7 us, 13.5 MB 96 / 38.9 (kernel trace: 13.9 + 60.2 + 2.7 + 2.7 + 16.3 + 4.6 us / 28 + 9.3), 64 MB 366 / 130, 134 MB 794 / 278;
-// of unknown words 13.5 MB 129 / 120, 64 MB 595 / 532; with runs and random bytes (100k table) 4 MB 105 / 61, 13.5 MB 278 / 139;
-// 30 MB of 3-byte pieces 192 / 78.  64 MB of nothing but runs lose: pieces of 40 bytes 1,125 / 1,155, of 1,000
-// 287 / 314 (a tile of few pieces takes its round trips all the same).  What bounds it is those round trips: a tile takes
-// about 3 us, a compute unit holds four workgroups, and they wait for three quarters of the time.
+// Per call, through the pre-tokenizer and one tile of 256 pieces per workgroup / now: text of known words 1.9 MB 29.6 /
+// 16.0 us, 13.5 MB 95.8 / 40.0, in 256 sequences 99.6 / 42.9 (kernel trace: 16.0 + 60.1 + 4.4 + 4.2 + 16.1 + 4.3 us / 33.1 + 9.2), 64 MB 367 / 131,
+// 134 MB 794 / 279; of unknown words 13.5 MB 128 / 120, 64 MB 591 / 530; with runs and random bytes (100k table) 4 MB 110 / 57, 13.5 MB
+// 281 / 141; 30 MB of 3-byte pieces 201 / 81; 64 MB of runs in pieces of 1,000 bytes 341 / 289, of 40 1,302 / 1,321 (a tile of few
+// pieces takes its round trips all the same).  What bounds it is those round trips: a tile takes about 3 us, a compute unit
+// holds four workgroups, 2.2 wavefronts per SIMD are in flight and wait for 62 % of the time (78 % with runs and random bytes).
 #pragma once
 
 namespace bpe {

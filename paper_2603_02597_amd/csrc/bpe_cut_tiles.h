@@ -1,5 +1,5 @@
-// Encoding pieces that are longer on average than a lane takes (fixed chunks of text, whole documents): a piece is cut
-// first, wherever no token can reach across, and its parts are encoded like pieces.  Device code, included by
+// Encoding pieces that are long on average (fixed chunks of text, whole documents; cut_least_bytes says from where on): a
+// piece is cut first, wherever no token can reach across, and its parts are encoded like pieces.  Device code, included by
 // bpe_encode.hip behind bpe_byte_runs.h.
 //
 // A token that reached across the border of two bytes x, y would have them side by side in its expansion, and every
@@ -17,10 +17,11 @@
 // their place.  Bound by the chain of a tile: offsets, bytes, cuts, probes, left-over merges, counts.
 //
 // Per call, every piece by one workgroup, wavefront or lane / cut: 840 KB of text with the 50k table in chunks of 64, 256, 1,024 and
-// 2,048 bytes 54.9, 93, 121 and 157 / 19.3, 16.5, 16.5 and 16.4 us; with runs and random bytes, 100k table, 60, 281, 1,886 and 2,186 /
-// 40, 42, 42 and 42; 4 MB of text in chunks of 1,024 378 / 28.  Pieces without a place to cut pay for the look: random bytes
-// in pieces of 64, 256, 1,024 39, 338, 537 / 51, 343, 545; text without spaces in pieces of 64, 256, 1,024, 2,048 49, 205, 324,
-// 502 / 61, 258, 335, 493; runs of 200 in pieces of 64, 256, 1,024 63, 47, 38 / 44, 31, 47.
+// 2,048 bytes 55, 89, 116 and 157 / 19.6, 16.7, 16.7 and 16.5 us (there wavefronts wait for 71 % of the time, 1.5 per SIMD in flight); with
+// runs and random bytes, 100k table, 60, 277, 1,999 and 2,262 / 42, 42, 42 and 42.  Data without a place to cut pays for the look:
+// random bytes, 100k table, in pieces of 64, 256, 1,024 and 2,048 39, 376, 532 and 879 / 51, 411, 541 and 1,094; text without spaces 49,
+// 196, 300 and 504 / 61, 199, 312 and 532; runs of 200 bytes 53, 38, 18 and 20 / 35, 32, 31 and 33 (there a piece is a handful of runs for one
+// wavefront, and cut, each run is one of its own).
 #pragma once
 
 namespace bpe {
@@ -119,6 +120,12 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
     // Pieces (seq_off): every tile checks a strided share of their offsets and finds the ones that start among its own
     // bytes, seq_off[s0 .. s1); seq_next: the first one at or behind the tile's end (a part ends there at the latest).
     int s0, s1, seq_next = p.n_bytes, seq_first = p.n_bytes;   // seq_first: the first one of all
+    // WIDE: pieces that start here and are merged as a whole, if all offsets needed are among the 64
+    auto of_whole_size = [&](int first, int next) {
+        return next <= p.n_bytes && next - first > kGroupBoundMax && next - first <= kWideWhole;
+    };
+    bool at_hand = false;
+    int whole_first = -1, whole_end = 0;
     {
         bool bad = false;
         for (int64_t k = (int64_t)tile * kGroupThreads + tid; k <= p.n_seqs; k += (int64_t)gridDim.x * kGroupThreads) {
@@ -151,24 +158,34 @@ __global__ void __launch_bounds__(kGroupThreads, 4) merge_cut_tiles_kernel(Encod
             if (s1 <= p.n_seqs) seq_next = min(max(__builtin_amdgcn_readfirstlane(p.seq_off[s1]), hi), p.n_bytes);
         }
         s1 = max(s0, s1);          // (offsets that decrease)
+        if (WIDE) {
+            const int k = at + lane, next = wave_from_lane_above(v, 0);
+            at_hand = s1 - at < kWave;
+            if (at_hand && wv == 0 && k >= s0 && k < s1 && k < p.n_seqs && v >= lo && v < hi && of_whole_size(v, next) && p.scratch2[v] >= 0) {
+                whole_first = v;
+                whole_end = next;
+            }
+        }
     }
     const bool any_seq = s1 > s0;                              // the same in every wavefront
     if (tid < kGroups) sh.group[tid] = 0;
     __syncthreads();               // (the byte codes, too)
     if (any_seq) {
+        auto list_whole = [&](int first, int end) {
+            const int i = atomicAdd(&sh.n_whole, 1);
+            if (i < 4) sh.whole[i] = make_int2(first, end);                // (more only if the offsets decrease)
+        };
         for (int64_t k = (int64_t)s0 + tid; k < s1; k += kGroupThreads) {
             const int sv = p.seq_off[k];
             if (sv < lo || sv >= hi) continue;
             const uint32_t at = (uint32_t)sv + mis - v0;
             atomicOr(&sh.group[at >> 4], 1u << (at & 15));
-            if (WIDE && k < p.n_seqs) {
+            if (WIDE && !at_hand && k < p.n_seqs) {
                 const int next = p.seq_off[k + 1];
-                if (next <= p.n_bytes && next - sv > kGroupBoundMax && next - sv <= kWideWhole && p.scratch2[sv] >= 0) {
-                    const int i = atomicAdd(&sh.n_whole, 1);
-                    if (i < 4) sh.whole[i] = make_int2(sv, next);          // (more only if the offsets decrease)
-                }
+                if (of_whole_size(sv, next) && p.scratch2[sv] >= 0) list_whole(sv, next);
             }
         }
+        if (WIDE && whole_first >= 0) list_whole(whole_first, whole_end);
         __syncthreads();
     }
     const int n_whole = WIDE ? __builtin_amdgcn_readfirstlane(min(sh.n_whole, 4)) : 0;
@@ -641,7 +658,8 @@ __device__ __forceinline__ bool list_piece_parts(const EncodeParams &p, int b, i
 }
 
 // Lists the parts that long of pieces beyond kWideWhole that start in span `span` of kWideSpan bytes; text has none.
-__device__ __forceinline__ void list_span_parts(const EncodeParams &p, int span, WideParts &sh, const WideScope &sc) {
+// [sv, next): the thread's piece (sv < 0: it has none).
+__device__ __forceinline__ void list_span_parts(const EncodeParams &p, int span, int sv, int next, WideParts &sh, const WideScope &sc) {
     __shared__ uint32_t bits[kWideSpan / 32];      // bytes of the span that pieces start with
     __shared__ int2 longer[2];                     // the pieces of that many bytes that the span holds bytes of
     __shared__ int n_longer, next_piece;
@@ -651,9 +669,7 @@ __device__ __forceinline__ void list_span_parts(const EncodeParams &p, int span,
     if (tid < kWideSpan / 32) bits[tid] = 0;
     if (tid == 0) { n_longer = 0; next_piece = v_end; }
     __syncthreads();
-    for (int k = tid; k < p.n_seqs; k += kWideThreads) {
-        const int sv = p.seq_off[k], next = p.seq_off[k + 1];
-        if (sv < 0 || sv >= p.n_bytes) continue;
+    if (sv >= 0 && sv < p.n_bytes) {
         const int v = sv + mis;
         if (v >= lo && v < hi) atomicOr(&bits[(v - v0) >> 5], 1u << ((v - v0) & 31));
         if (v >= hi) atomicMin(&next_piece, v);
@@ -700,8 +716,10 @@ __device__ __forceinline__ void merge_uncut_parts(const EncodeParams &p, const C
     const WideScope sc{tmp};
     const int i0 = min((int)blockIdx.x, p.n_seqs - 1);
     const int b0 = p.seq_off[i0], e0 = p.seq_off[i0 + 1];      // (asked for ahead of the others)
-    bool longer = false;
-    for (int k = tid; k < p.n_seqs; k += kWideThreads) longer |= (int64_t)p.seq_off[k + 1] - p.seq_off[k] > kWideWhole;
+    static_assert(kWideMaxPieces <= kWideThreads, "a piece per thread");
+    int sv = -1, next = -1;
+    if (tid < p.n_seqs) { sv = p.seq_off[tid]; next = p.seq_off[tid + 1]; }
+    bool longer = (int64_t)next - sv > kWideWhole;
     if (tid < 256) sh.code[tid] = (uint8_t)cut_code(cuts, (uint32_t)tid);
     if (tid == 0) sh.n_parts = 0;
     longer = __syncthreads_or(longer);
@@ -710,7 +728,7 @@ __device__ __forceinline__ void merge_uncut_parts(const EncodeParams &p, const C
     if ((int)blockIdx.x < p.n_seqs) whole = list_piece_parts(p, b0, e0, tile_bytes, sh, sc, at_b);
     if (longer) {
         __syncthreads();
-        list_span_parts(p, blockIdx.x, sh, sc);
+        list_span_parts(p, blockIdx.x, sv, next, sh, sc);
     }
     __syncthreads();
     const int n = __builtin_amdgcn_readfirstlane(sh.n_parts);

@@ -87,47 +87,66 @@ __device__ __forceinline__ int find_word(const TableView &t, const uint32_t (&w)
 // ---------------------------------------------------------------------------
 // One piece per row of 16 lanes, one symbol per lane, in registers: the pieces that
 // find_word leaves over are a few per tile, too few to fill a wavefront of the lane-per-piece
-// path below, and a step is shorter here (about 40 instructions and one table round trip: the
-// minimum over a row is four data-parallel moves, the symbols behind a merge move down by one
+// path below, and a step is shorter here (one table round trip: the
+// best pair of a row is four data-parallel moves, the symbols behind a merge move down by one
 // lane, and the two new pairs, at lanes k - 1 and k, are one lookup of (own symbol, next lane's)
-// each).  sym: lane j < n of the row holds symbol j as id | flags << 24, bytes with both flags
-// set; n <= 16, 0 for a row without a piece.  Returns the number of tokens, in the row's first
-// lanes.  Every lane of the wavefront must call it.
-__device__ __forceinline__ uint32_t from_next_lane(uint32_t v, uint32_t last) {    // within a row of 16
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)v, 0x101, 0xF, 0xF, false);   // row_shl:1
+// each).  sym: lane j < n of the row holds byte j in its low bits; n <= 16, 0 for a row without a
+// piece.  Returns the number of tokens, in the row's first lanes (the low 24 bits of sym).  Every
+// lane of the wavefront must call it.
+//
+// A call of few tiles is as long as the longest of these chains (up to a dozen steps), and a step is as long as its
+// dependent instructions: of about 830 cycles a lookup, which mostly hits the L2, is 250.  So a step has no branch but the
+// one that ends the loop (exec masks and jumps were a third of it), rank words are kept inverted (a lane that a move finds no source for
+// reads 0, and 0 is "no pair": the moves are operands of the instructions that use them), and both new pairs are looked up whatever
+// the flags of their symbols say: here a lookup in vain costs less than the test in front of it.  840 KB of text, 50k table, per
+// call: given pieces 12.0 -> 11.4 us, raw bytes 12.9 -> 12.1, chunks of 2,048 bytes 16.2 -> 15.0.
+__device__ __forceinline__ uint32_t from_next_lane(uint32_t v) {                   // within a row of 16; the last lane gets 0
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x101, 0xF, 0xF, true);   // row_shl:1
 }
-__device__ __forceinline__ uint32_t row_min_u32(uint32_t v) {                      // to every lane of the row
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x128, 0xF, 0xF, false));   // row_ror:8
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x124, 0xF, 0xF, false));   // row_ror:4
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x122, 0xF, 0xF, false));   // row_ror:2
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x121, 0xF, 0xF, false));   // row_ror:1
+__device__ __forceinline__ uint32_t row_max_u32(uint32_t v) {                      // to every lane of the row
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true));   // row_ror:8
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xF, 0xF, true));   // row_ror:4
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x122, 0xF, 0xF, true));   // row_ror:2
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x121, 0xF, 0xF, true));   // row_ror:1
     return v;
 }
-__device__ __forceinline__ int row_merge(const EncodeParams &p, uint32_t &sym, int n) {
-    const int j = lane_id() & 15;
-    uint32_t next = from_next_lane(sym, 0u);
-    uint32_t r = kNoRank;                            // rank word of the pair that starts at this lane
-    if (j + 1 < n) r = p.table.byte_pairs[((sym & 0xFFu) << 8) | (next & 0xFFu)];
+template <bool NUMBERED>           // merged id = rank order + merged_delta (see TableView)
+__device__ __forceinline__ void row_merge_steps(const TableView &t, uint32_t &sym, uint32_t q) {
+    constexpr uint32_t kLive = 1u << 24;             // set in every symbol (slot_probe looks at the bits below)
+    const int j = lane_id_here() & 15;
+    const uint32_t not_j = ~(uint32_t)j, from_rank = NUMBERED ? (uint32_t)t.merged_delta + kLive : 0u;
+    int at = j == 15 ? 16 : j;                       // (no pair starts at the last lane, but "no pair" reads as position 15)
+    asm("" : "+v"(at));                              // (or it is tested for again in every step)
     for (;;) {
-        const uint32_t best = row_min_u32(r | (uint32_t)j);          // kNoRank stays kNoRank
-        const bool act = best != kNoRank;
-        if (!__ballot(act)) break;
-        const int k = act ? (int)(best & 15u) : 16;                  // 16: nothing in this row
-        const uint32_t merged = (act ? merged_id_of(p.table, best >> 6) : 0u) | ((best >> 4) & 3u) << 24;
-        const uint32_t sym_up = from_next_lane(sym, 0u), r_up = from_next_lane(r, kNoRank);
-        sym = j == k ? merged : j > k ? sym_up : sym;
-        r = j == k || j + 1 == k ? kNoRank : j > k ? r_up : r;
-        n -= act ? 1 : 0;
-        next = from_next_lane(sym, 0u);
-        // a pair needs a lookup only if its symbols can be the left / right part of some rule
-        const bool need = (j == k || j + 1 == k) && j + 1 < n && ((sym >> 24) & 1u) && ((next >> 25) & 1u);
-        if (need) {
-            const SlotProbe q = slot_probe(p.table, sym, next);      // (flag bits: see slot_probe)
-            const uint2 s1 = slot_lower(p.table, q), s2 = slot_upper(p.table, q);
-            r = slot_match(s1, s2, q.rest1, q.rest2);
-        }
+        const uint32_t best = row_max_u32(q & not_j);
+        if (!__ballot(best != 0)) break;
+        const int k = (int)(~best & 15u);
+        uint32_t merged = (~best >> kRankShift) + from_rank;
+        if (!NUMBERED) merged = (uint32_t)t.merged_of[best ? merged : 0u] | kLive;
+        const uint32_t sym_up = from_next_lane(sym), q_up = from_next_lane(q);
+        sym = j > k ? sym_up : sym;
+        sym = at == k ? merged : sym;
+        const uint32_t next = from_next_lane(sym);
+        const bool fresh = (uint32_t)(k - j) <= 1u;  // (in a row that is done, lane 14 asks again and finds nothing again)
+        q = j > k ? q_up : q;
+        SlotProbe slot = slot_probe(t, sym, next);
+        slot.off1 = fresh ? slot.off1 : 0u;          // the other lanes' loads are one place
+        slot.off2 = fresh ? slot.off2 : 0u;
+        const uint2 s1 = slot_lower(t, slot), s2 = slot_upper(t, slot);
+        q = fresh ? 0u : q;
+        const bool look = fresh & (next != 0);
+        q = look ? ~slot_match(s1, s2, slot.rest1, slot.rest2) : q;
     }
-    return n;
+}
+__device__ __forceinline__ int row_merge(const EncodeParams &p, uint32_t &sym, int n) {
+    const int lane = lane_id_here();
+    sym = (lane & 15) < n ? (sym & 0xFFu) | 1u << 24 : 0u;
+    const uint32_t next = from_next_lane(sym);
+    uint32_t q = 0;                                  // ~rank word of the pair that starts at this lane
+    if (next) q = ~p.table.byte_pairs[((sym & 0xFFu) << 8) | (next & 0xFFu)];
+    if (p.table.merged_delta >= 0) row_merge_steps<true>(p.table, sym, q);
+    else row_merge_steps<false>(p.table, sym, q);
+    return __builtin_popcount((uint32_t)(__ballot(sym != 0) >> (lane & 48)) & 0xFFFFu);
 }
 
 // Merges the lane's piece of len <= kTinyMax bytes, which are w, if `mine`.  Returns

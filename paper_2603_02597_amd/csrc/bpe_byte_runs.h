@@ -422,7 +422,12 @@ __device__ __forceinline__ bool offsets_are_bad(const int32_t *off, int n, int n
 }
 
 // Assembly: the tokens of every tile to their place in out_ids, and the first token of every sequence.  A workgroup
-// takes a tile, a thread three consecutive pieces (616 of word-like text start in a tile).
+// takes a tile, a thread three of its pieces (616 of word-like text start in a tile): every 64th of its wavefront's 192
+// consecutive ones, so that the loads and, with one token per piece nearly always, the stores of a wavefront are contiguous.
+// (Three consecutive ones per thread touched every line with each of three loads and stores: 134 MB 71.0 -> 64.7 us in the kernel
+// trace, per call 298 -> 293; 1k table, where many pieces have several tokens, 20 MB 99.5 -> 92.9, 64 MB 308 -> 282.)
+// Bound by its round trips.  A wavefront per tile instead, with the totals before it always from scan_tiles_kernel: 134 MB of text
+// 282 us per call, but 1k table 64 MB 299.
 typedef int32_t int4_any __attribute__((ext_vector_type(4), aligned(4)));       // 16 bytes at any word
 constexpr int kEmitPieces = 3;
 constexpr int kEmitPass = kEmitPieces * kGroupThreads;
@@ -459,36 +464,40 @@ __global__ void __launch_bounds__(kGroupThreads) emit_byte_runs_kernel(EncodePar
     }
     int base = 0, par = 0;
     for (int i0 = 0; i0 < n || i0 == 0; i0 += kEmitPass, par ^= 1) {   // nearly always one pass
-        const int i = i0 + kEmitPieces * tid;
-        int word[kEmitPieces], c[kEmitPieces], at[kEmitPieces], mine = 0;
+        const int i = i0 + wv * kEmitPieces * kWave + lane;            // piece j of the thread: i + 64 j
+        int word[kEmitPieces], c[kEmitPieces], at[kEmitPieces], inc[kEmitPieces];
 #pragma unroll
-        for (int j = 0; j < kEmitPieces; ++j) word[j] = i + j < n ? words[i + j] : 0;
+        for (int j = 0; j < kEmitPieces; ++j) word[j] = i + j * kWave < n ? words[i + j * kWave] : 0;
 #pragma unroll
         for (int j = 0; j < kEmitPieces; ++j) {
             const uint32_t u = (uint32_t)word[j];
             at[j] = origin + (int)((u & ~kSeveral) >> kStartShift);
-            c[j] = i + j >= n ? 0 : word[j] < 0 ? (int)(u & kManyTokens) : 1;
-            if (word[j] < 0 && c[j] == (int)kManyTokens) c[j] = words[i + j + 1];
-            mine += c[j];
+            c[j] = i + j * kWave >= n ? 0 : word[j] < 0 ? (int)(u & kManyTokens) : 1;
+            if (word[j] < 0 && c[j] == (int)kManyTokens) c[j] = words[i + j * kWave + 1];
         }
         // the first four tokens of a piece of several, asked for before anything waits (what lies behind them is the workspace's)
         int4_any head[kEmitPieces];
 #pragma unroll
         for (int j = 0; j < kEmitPieces; ++j)
             if (word[j] < 0) head[j] = *(const int4_any *)(p.scratch + at[j]);
-        const int inc = wave_scan_inclusive(mine);
-        if (lane == kWave - 1) total_w[par][wv] = inc;
+        int wave_total = 0;
+#pragma unroll
+        for (int j = 0; j < kEmitPieces; ++j) {
+            inc[j] = wave_total + wave_scan_inclusive(c[j]);
+            wave_total = __builtin_amdgcn_readlane(inc[j], kWave - 1);
+        }
+        if (lane == 0) total_w[par][wv] = wave_total;
         __syncthreads();
         if (i0 == 0)
             for (int w = 0; w < kWavesPerGroup; ++w) base += before_w[w];
-        int first[kEmitPieces], all = 0;
-        first[0] = base + inc - mine;
+        int wave_first = base, all = 0;
         for (int w = 0; w < kWavesPerGroup; ++w) {
-            if (w < wv) first[0] += total_w[par][w];
+            if (w < wv) wave_first += total_w[par][w];
             all += total_w[par][w];
         }
+        int first[kEmitPieces];
 #pragma unroll
-        for (int j = 1; j < kEmitPieces; ++j) first[j] = first[j - 1] + c[j - 1];
+        for (int j = 0; j < kEmitPieces; ++j) first[j] = wave_first + inc[j] - c[j];
 #pragma unroll
         for (int j = 0; j < kEmitPieces; ++j) {
             if (c[j] && word[j] >= 0) p.out_ids[first[j]] = word[j];
@@ -519,7 +528,7 @@ __global__ void __launch_bounds__(kGroupThreads) emit_byte_runs_kernel(EncodePar
         }
         if (s_end > info.y) {      // sequences start in this tile: with which pieces, the merge kernel has noted
 #pragma unroll
-            for (int j = 0; j < kEmitPieces; ++j) firsts[kEmitPieces * tid + j] = first[j];
+            for (int j = 0; j < kEmitPieces; ++j) firsts[i - i0 + j * kWave] = first[j];
             __syncthreads();
             for (int64_t s = (int64_t)info.y + tid; s < s_end; s += kGroupThreads) {
                 const int k = ~p.seq_token_offsets[s] - i0;    // (one that has its token is far below)

@@ -445,6 +445,27 @@ int bpe_vocab_info(const bpe_vocab *vocab, bpe_vocab_info_t *info);
 int bpe_map_ids(const bpe_vocab *vocab, const int32_t *ids_in, int32_t *ids_out, int64_t n,
                 const int32_t *n_device, int to_output_ids, void *stream);
 
+/*
+ * Whole batches between the host and the device without copy commands: kernels on `stream` that read and write pinned
+ * host memory (hipHostMalloc) in place, for callers that encode or decode batches from host to host (Tokenizer in the
+ * Python package).  They only enqueue.  Buffers are 16-byte aligned, and their sizes are multiples of 16 bytes.
+ *   bpe_host_visible     1 if the GPU reaches `host` at the same address, else 0
+ *   bpe_batch_in         n_bytes from host to device; clock: device uint64, 0 before its first use
+ *   bpe_batch_ids_out    words: device int32, n_offsets offsets and behind them the ids, as many as the last offset says (at
+ *                        most max_ids); host gets the same, with the output ids of vocab unless that is NULL
+ *   bpe_batch_bytes_out  host_starts[k] = token_byte_offsets[bounds[k]], 0 <= k < n_bounds; host gets the first
+ *                        token_byte_offsets[n_tokens] bytes, at most `capacity`
+ *   host_head            host int32 [16]: [0 .. 8) the status words of `workspace` (see bpe_status_from_words), [8] the
+ *                        time from the end of bpe_batch_in to the start of this kernel, in units of 10 ns
+ */
+int bpe_host_visible(const void *host);
+int bpe_batch_in(const void *host, void *device, int64_t n_bytes, void *clock, void *stream);
+int bpe_batch_ids_out(const bpe_vocab *vocab, const int32_t *words, int64_t n_offsets, int64_t max_ids, int32_t *host,
+                      const void *workspace, const void *clock, int32_t *host_head, void *stream);
+int bpe_batch_bytes_out(const void *bytes, int64_t capacity, const int32_t *token_byte_offsets, int64_t n_tokens,
+                        const int32_t *bounds, int64_t n_bounds, int32_t *host_starts, void *host,
+                        const void *workspace, const void *clock, int32_t *host_head, void *stream);
+
 /* Device bytes bpe_decode needs for up to n_tokens tokens (pure function). */
 int64_t bpe_decode_workspace_bytes(int64_t n_tokens);
 

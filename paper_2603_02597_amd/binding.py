@@ -152,6 +152,14 @@ def load_library():
     lib.bpe_vocab_info.argtypes = [vp, ctypes.POINTER(_VocabInfo)]
     lib.bpe_map_ids.restype = i32
     lib.bpe_map_ids.argtypes = [vp, vp, vp, i64, vp, i32, vp]
+    lib.bpe_host_visible.restype = i32
+    lib.bpe_host_visible.argtypes = [vp]
+    lib.bpe_batch_in.restype = i32
+    lib.bpe_batch_in.argtypes = [vp, vp, i64, vp, vp]
+    lib.bpe_batch_ids_out.restype = i32
+    lib.bpe_batch_ids_out.argtypes = [vp, vp, i64, i64, vp, vp, vp, vp, vp]
+    lib.bpe_batch_bytes_out.restype = i32
+    lib.bpe_batch_bytes_out.argtypes = [vp, i64, vp, i64, vp, i64, vp, vp, vp, vp, vp, vp]
     lib.bpe_decode_workspace_bytes.restype = i64
     lib.bpe_decode_workspace_bytes.argtypes = [i64]
     lib.bpe_decode.restype = i32

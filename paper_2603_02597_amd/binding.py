@@ -23,7 +23,7 @@ EXPORTS = [
     "bpe_encode_timed", "bpe_encode_plan", "bpe_encode_raw_plan", "bpe_encode_status", "bpe_status_from_words", "bpe_pool_create", "bpe_pool_destroy", "bpe_pool_workspace",
     "bpe_pretokenize_workspace_bytes", "bpe_pretokenize", "bpe_encode_raw_workspace_bytes", "bpe_encode_raw",
     "bpe_encode_raw_timed", "bpe_vocab_build", "bpe_vocab_free", "bpe_vocab_info", "bpe_map_ids",
-    "bpe_decode_workspace_bytes", "bpe_decode",
+    "bpe_decode_workspace_bytes", "bpe_decode", "bpe_host_visible", "bpe_batch_in", "bpe_batch_ids_out", "bpe_batch_bytes_out",
 ]
 
 

@@ -25,6 +25,12 @@ constexpr uint32_t kDevCanLeft = 1u << 4, kDevCanRight = 1u << 5;
 __host__ __device__ inline uint32_t device_rank_word(uint32_t image_word) {
     return ((image_word & kRankMask) << kRankShift) | ((image_word >> 30) << 4);
 }
+// In byte_pairs only, in the place of kNoRank: no token reaches across these two bytes, whatever lies around them.
+constexpr uint32_t kNeverJoined = 1u << 31;
+__host__ __device__ inline uint32_t byte_pair_rank(uint32_t word) {     // a rank word is positive, neither of the others is
+    const int32_t w = (int32_t)word;
+    return (uint32_t)(w > -1 ? w : -1);
+}
 constexpr int kIdBits = 24;                    // token ids < 2^24: the slot hash is a 24-bit mix
 constexpr int kMaxRulesLog2 = 22;              // rule count < 2^22: a half of the slot table has at most 2^24 slots
 constexpr int kWave = 64;
@@ -70,8 +76,9 @@ __host__ __device__ inline uint32_t mul24(uint32_t x, uint32_t k) {
 // a slot that holds both ids, and half the cache lines a cold L2 has to pull.
 struct TableView {
     const uint2 *slots;        // {low bits of the mix | right id << 8, rank word}; empty: {0, kNoRank}
-    const uint32_t *byte_pairs; // [65536] direct table for pairs of byte symbols: rank word or kNoRank
-                               // rank word: see device_rank_word
+    const uint32_t *byte_pairs; // [65536] direct table for pairs of byte symbols: rank word (see device_rank_word), kNoRank,
+                               // or kNeverJoined where no rule joins a string that ends with the one to one that starts
+                               // with the other; read through byte_pair_rank
     const int32_t *merged_of;  // [n_merges] merged id by rank order
     const int32_t *rank_of;    // [n_merges] caller's rank value by rank order
     const uint2 *sym_lr;       // [max_id + 1] per id: {lowest rank order of a rule with the id as its right part,

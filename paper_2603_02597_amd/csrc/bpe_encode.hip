@@ -66,6 +66,12 @@ constexpr int kRunPiecesMax = 4;               // tiles in flight together, a pi
 constexpr int kRunTilesMax = 16;
 constexpr int kRunLeft = 1360;                 // left-over pieces that the list holds
 constexpr int kRunRounds = (kRunLeft + kGroupThreads - 1) / kGroupThreads;
+// Up to so many pieces of at most 64 bytes are merged in parts, if all of them fall into short ones (merge_pieces_in_parts): two for
+// each wavefront.  Such a piece takes a wavefront about 5 us, the columns take up to 16 pieces of a wavefront together in 25 to 30 (random
+// bytes, 100k table): 4 MB with 18 of them per workgroup 50.3 us per call with this line, 53 and 56 with 24 and 64 pieces in parts.  All or
+// none: parts and then columns are the sum of both (text without spaces in pieces of 40, 100 KB: 32 us without parts, 42 with a mixture, 31 so).
+// What cannot be cut pays for the look: the same text in pieces of 60 and 64 bytes 39.4 / 40.1 and 46.4 / 47.4.
+constexpr int kPartsPieces = 8;
 union MergeLds {
     TinyState tiny[kWavesPerGroup];
     struct { int32_t A[kLdsMaxLen]; int32_t B[kLdsMaxLen]; } group;
@@ -394,7 +400,29 @@ __device__ __forceinline__ TilePiece merge_tile_long_pieces(const EncodeParams &
     // Columns: 16 pieces per wavefront and round, entry 64 r + 16 w + l to lane l of wavefront w.
     // The first wavefront fills up first: a step costs a wavefront the same instructions
     // for one piece as for 16, and the compute unit's other tiles want the issue slots.
-    const int n_col = __builtin_amdgcn_readfirstlane(sh.list_n);
+    // (A few of them that all fall into short parts: see merge_listed_pieces.)
+    const int n_listed = __builtin_amdgcn_readfirstlane(sh.list_n);
+    int n_col = n_listed;
+    if (n_listed && n_listed <= kPartsPieces) {
+        bool fit = true;
+        for (int e = __builtin_amdgcn_readfirstlane(wv); e < n_listed; e += kWavesPerGroup) {
+            int b, n;
+            piece_bounds<SRC>(p, bt, tile_q0, P, sh.list[e], b, n);
+            fit &= in_short_parts(p, __builtin_amdgcn_readfirstlane(b), __builtin_amdgcn_readfirstlane(n));
+        }
+        if (__syncthreads_and(fit)) {
+            const int e = wv + kWavesPerGroup * lane;
+            const bool mine = e < n_listed;
+            int owner = 0, b = 0, n = 0;
+            if (mine) {
+                owner = sh.list[e];
+                piece_bounds<SRC>(p, bt, tile_q0, P, owner, b, n);
+            }
+            const int c = merge_pieces_in_parts(p, &sh.lds.tiny[wv].S[0][0], b, n, __builtin_popcountll(__ballot(mine)));
+            if (mine) sh.cnt_back[owner] = c;
+            n_col = 0;
+        }
+    }
     for (int e0 = 0; e0 < n_col; e0 += kWavesPerGroup * kColumnLanes) {
         const int e = e0 + kColumnLanes * wv + lane;
         const bool mine = lane < kColumnLanes && e < n_col;
@@ -428,14 +456,16 @@ __device__ __forceinline__ TilePiece merge_tile_long_pieces(const EncodeParams &
         if (c >= 0) {}
         else if (n > p.wave_lds_max) c = kLongMark;
         else if (n <= p.wave_max) c = encode_wave_piece(p, b, n);
-        else if (p.level >= 3 && !(p.runs_by_best_rank && piece_is_run_like(p, b, n, WaveScope{})))
+        else if (p.level >= 3 && !(p.runs_by_best_rank && piece_is_run_like(p, b, n, WaveScope{}))) {
             // well beyond what a wavefront keeps resident the whole workgroup is quicker (1,024 bytes
             // of text: 148 us against 272 us for one wavefront working through windows; even at 600)
             // (and at once when the piece has the workgroup to itself)
-            c = n <= (p.W == 1 ? kWaveBoundMax : kWaveBoundHandOn)
-                    ? encode_long_piece_bound(p, b, n, &sh.lds.tiny[wv].S[0][0], kWaveBoundMax, WaveScope{})
-                    : kLongMark;
-        else c = encode_wave_lds_piece(p, b, n, sh.lds.tiny[wv]);
+            c = kLongMark;
+            if (n <= (p.W == 1 ? kWaveBoundMax : kWaveBoundHandOn)) {
+                c = __builtin_amdgcn_readfirstlane(merge_pieces_in_parts(p, &sh.lds.tiny[wv].S[0][0], b, n, 1));
+                if (c < 0) c = encode_long_piece_bound(p, b, n, &sh.lds.tiny[wv].S[0][0], kWaveBoundMax, WaveScope{});
+            }
+        } else c = encode_wave_lds_piece(p, b, n, sh.lds.tiny[wv]);
         if (lane == 0) sh.cnt_back[owner] = c;
     }
     __syncthreads();
@@ -745,6 +775,29 @@ template <class Entry, class Bounds, class Done>
 __device__ __forceinline__ void merge_listed_pieces(const EncodeParams &p, MergeLds &lds, GroupTmp &tmp, int n_col, int n_back,
                                                     const Entry &entry, const Bounds &bounds, const Done &done) {
     const int tid = threadIdx.x, lane = lane_id_here(), wv = tid / kWave;
+    // Pieces of up to 64 bytes.  If they are few and all fall into short parts (random bytes do), each is merged by a
+    // wavefront; otherwise all of them in columns.
+    const int n_listed = n_col;
+    if (n_listed && n_listed <= kPartsPieces) {
+        bool fit = true;
+        for (int e = __builtin_amdgcn_readfirstlane(wv); e < n_listed; e += kWavesPerGroup) {
+            int b, n;
+            bounds((int)entry(e), b, n);
+            fit &= in_short_parts(p, __builtin_amdgcn_readfirstlane(b), __builtin_amdgcn_readfirstlane(n));
+        }
+        if (__syncthreads_and(fit)) {
+            const int e = wv + kWavesPerGroup * lane;
+            const bool mine = e < n_listed;
+            int k = 0, b = 0, n = 0;
+            if (mine) {
+                k = (int)entry(e);
+                bounds(k, b, n);
+            }
+            const int c = merge_pieces_in_parts(p, &lds.tiny[wv].S[0][0], b, n, __builtin_popcountll(__ballot(mine)));
+            if (mine) done(e, k, c);
+            n_col = 0;
+        }
+    }
     // Columns: 16 pieces per wavefront and round, the first wavefront fills up first.
     for (int e0 = 0; e0 < n_col; e0 += kWavesPerGroup * kColumnLanes) {
         const int e = e0 + kColumnLanes * wv + lane;
@@ -762,7 +815,7 @@ __device__ __forceinline__ void merge_listed_pieces(const EncodeParams &p, Merge
     // Wavefront paths, dealt to the wavefronts that have no columns (see wave_deal).
     const WaveDeal deal = wave_deal(n_col, n_back, wv);
     for (int i = deal.first; i < n_back; i += deal.stride) {
-        const int k = __builtin_amdgcn_readfirstlane((int)entry(n_col + i));
+        const int k = __builtin_amdgcn_readfirstlane((int)entry(n_listed + i));
         int b, n;
         bounds(k, b, n);
         b = __builtin_amdgcn_readfirstlane(b);
@@ -773,19 +826,22 @@ __device__ __forceinline__ void merge_listed_pieces(const EncodeParams &p, Merge
         if (c >= 0) {}
         else if (n > p.wave_lds_max) c = kLongMark;
         else if (n <= p.wave_max) c = encode_wave_piece(p, b, n);
-        else if (p.level >= 3 && !(p.runs_by_best_rank && piece_is_run_like(p, b, n, WaveScope{})))
-            c = n <= kWaveBoundHandOn ? encode_long_piece_bound(p, b, n, &lds.tiny[wv].S[0][0], kWaveBoundMax, WaveScope{})
-                                      : kLongMark;
-        else c = encode_wave_lds_piece(p, b, n, lds.tiny[wv]);
+        else if (p.level >= 3 && !(p.runs_by_best_rank && piece_is_run_like(p, b, n, WaveScope{}))) {
+            c = kLongMark;
+            if (n <= kWaveBoundHandOn) {
+                c = __builtin_amdgcn_readfirstlane(merge_pieces_in_parts(p, &lds.tiny[wv].S[0][0], b, n, 1));
+                if (c < 0) c = encode_long_piece_bound(p, b, n, &lds.tiny[wv].S[0][0], kWaveBoundMax, WaveScope{});
+            }
+        } else c = encode_wave_lds_piece(p, b, n, lds.tiny[wv]);
         if (lane == 0) {
-            if (c == kLongMark) entry(n_col + i) = ~(uint32_t)k;         // for the workgroup
-            else done(n_col + i, k, c);                                  // (what it puts there, if anything, is no mark)
+            if (c == kLongMark) entry(n_listed + i) = ~(uint32_t)k;         // for the workgroup
+            else done(n_listed + i, k, c);                                  // (what it puts there, if anything, is no mark)
         }
     }
     __syncthreads();
     // Workgroup path, one piece at a time by all threads: the marked entries.
     for (int i = 0; i < n_back; ++i) {
-        const int k = ~__builtin_amdgcn_readfirstlane((int)entry(n_col + i));
+        const int k = ~__builtin_amdgcn_readfirstlane((int)entry(n_listed + i));
         if (k < 0) continue;       // a wavefront has merged it
         int b, n;
         bounds(k, b, n);
@@ -797,7 +853,7 @@ __device__ __forceinline__ void merge_listed_pieces(const EncodeParams &p, Merge
                                         min(max(p.lds_max, kGroupBoundMin), kGroupBoundMax), GroupScope{tmp});
         else if (n <= p.lds_max) c = encode_group_piece<int32_t *>(p, b, n, lds.group.A, lds.group.B, tmp);
         else c = encode_group_piece<int32_t *>(p, b, n, p.scratch + b, p.scratch2 + b, tmp);
-        if (tid == 0) done(n_col + i, k, c);
+        if (tid == 0) done(n_listed + i, k, c);
     }
 }
 

@@ -143,7 +143,7 @@ __device__ __forceinline__ int row_merge(const EncodeParams &p, uint32_t &sym, i
     sym = (lane & 15) < n ? (sym & 0xFFu) | 1u << 24 : 0u;
     const uint32_t next = from_next_lane(sym);
     uint32_t q = 0;                                  // ~rank word of the pair that starts at this lane
-    if (next) q = ~p.table.byte_pairs[((sym & 0xFFu) << 8) | (next & 0xFFu)];
+    if (next) q = ~byte_pair_rank(p.table.byte_pairs[((sym & 0xFFu) << 8) | (next & 0xFFu)]);
     if (p.table.merged_delta >= 0) row_merge_steps<true>(p.table, sym, q);
     else row_merge_steps<false>(p.table, sym, q);
     return __builtin_popcount((uint32_t)(__ballot(sym != 0) >> (lane & 48)) & 0xFFFFu);
@@ -169,6 +169,8 @@ __device__ __forceinline__ uint32_t tiny_merge(const EncodeParams &p, TinyState 
     // next to its load, and with it a wait for every single load)
 #pragma unroll
     for (int j = 0; j < kTinyMax - 1; ++j) asm volatile("" : "+v"(r0[j]));
+#pragma unroll
+    for (int j = 0; j < kTinyMax - 1; ++j) r0[j] = byte_pair_rank(r0[j]);
     // S[j] = id | flags << 24: whether the symbol can be the left / right part of a rule
     // (bits 0 / 1).  Bytes are not classified: both flags set.
 #pragma unroll
@@ -391,7 +393,7 @@ __device__ __noinline__ typename ColumnGeometry<N>::Mask column_merge(const Enco
             for (int j = 0; j < 16; ++j) {
                 const int at = row + ((c0 + j) ^ sw);
                 S[at] = c[j] | (3u << 24);
-                const uint32_t e = column_entry<N>(r0[j], c0 + j);
+                const uint32_t e = column_entry<N>(byte_pair_rank(r0[j]), c0 + j);
                 R[at] = e;
                 best = min(best, e);
             }
@@ -452,6 +454,127 @@ __device__ __noinline__ typename ColumnGeometry<N>::Mask column_merge(const Enco
         }
     }
     return alive;
+}
+
+// ---------------------------------------------------------------------------
+// Pieces that fall into parts of at most kPartMax bytes where no rule joins two neighbouring bytes
+// (kNeverJoined): no token reaches from one part into another, so each part is merged as if it stood alone, one merge of
+// every part per pass.  Random bytes are such pieces: 64 of them take up to 28 merges one after the other with the 100k table, 3 to 6 passes.
+// One wavefront, a symbol per lane in registers, as many whole parts of a piece at a time as its 64 lanes hold.  The best pair of a part is found by an LDS
+// maximum at the place of its first symbol (`stage`, 64 words of the wavefront: cleared, joined into and read back in one round trip, since
+// a wavefront's LDS operations are done in order); then the symbols close up.  A pass is bound by its dependent steps, about 0.7 us: that
+// round trip, the cross-lane push, the lookup of the new pairs.  Lane i < n_pieces holds the first byte and the length
+// of piece i, and gets its number of tokens, which are in scratch[b ...], or -1 if a part is longer.  Every lane must call it.
+// (A function of its own for the reasons given at column_merge; many pieces per call, because it fetches its parameters anew.)
+// Per call, text with runs and random bytes, 100k table, before / with it: 4 MB 71 / 51 us (its 169 pieces of 65 bytes took 24 us each through
+// encode_long_piece_bound), 6 to 300 KB 34 to 37 / 20 to 35, 50k table 3 KB 19 / 10, raw bytes 13.6 MB 140 / 94, 500 KB 41 / 28, chunks of 2,000
+// bytes, 100 KB 38 / 25.  Two pieces at a time in one wavefront: no gain, a pass is instructions rather than waiting.
+constexpr int kPartMax = 40;
+// Whether symbols that do not start a part (bits of `rest`) are kPartMax in a row: then a part is longer.
+__device__ __forceinline__ bool long_part(uint64_t rest) {
+#pragma unroll
+    for (int row = 1; row < kPartMax; row += min(row, kPartMax - row)) rest &= rest >> min(row, kPartMax - row);
+    return rest != 0;
+}
+// Whether the piece of n <= 64 bytes from b on has no longer part.  Every lane must call it with the same arguments.
+__device__ __forceinline__ bool in_short_parts(const EncodeParams &p, int b, int n) {
+    const int lane = lane_id_here();
+    const uint32_t sym = lane < n ? p.bytes[b + lane] : 0u;
+    const uint32_t next = (uint32_t)wave_from_lane_above((int)sym, 0);
+    const bool joined = lane + 1 < n && p.table.byte_pairs[sym << 8 | next] != kNeverJoined;
+    return !long_part(__ballot(joined) << 1);
+}
+__device__ __noinline__ int merge_pieces_in_parts(const EncodeParams &p, uint32_t *stage_words, int b_of, int n_of, int n_pieces) {
+    constexpr uint32_t kFirst = 1u << 24, kNew = 1u << 25;         // first symbol of its part; made in this pass
+    typedef __attribute__((address_space(1))) const uint8_t global_u8;
+    typedef __attribute__((address_space(1))) int32_t global_i32;
+    const int lane = lane_id_here();
+    TableView tv = p.table;
+    tv.slots = uniform_pointer(tv.slots);
+    tv.byte_pairs = uniform_pointer(tv.byte_pairs);
+    tv.merged_of = uniform_pointer(tv.merged_of);
+    tv.half = (uint32_t)__builtin_amdgcn_readfirstlane((int)tv.half);
+    tv.low_bits = __builtin_amdgcn_readfirstlane(tv.low_bits);
+    tv.index_bits = __builtin_amdgcn_readfirstlane(tv.index_bits);
+    tv.merged_delta = __builtin_amdgcn_readfirstlane(tv.merged_delta);
+    tv.seed.k1a = (uint32_t)__builtin_amdgcn_readfirstlane((int)tv.seed.k1a);
+    tv.seed.k1b = (uint32_t)__builtin_amdgcn_readfirstlane((int)tv.seed.k1b);
+    tv.seed.k2a = (uint32_t)__builtin_amdgcn_readfirstlane((int)tv.seed.k2a);
+    tv.seed.k2b = (uint32_t)__builtin_amdgcn_readfirstlane((int)tv.seed.k2b);
+    const uintptr_t bytes = (uintptr_t)uniform_pointer(p.bytes), scratch = (uintptr_t)uniform_pointer((const int32_t *)p.scratch);
+    const uintptr_t lower = (uintptr_t)tv.slots, upper = (uintptr_t)(tv.slots + tv.half);
+    lds_u32 *const stage = (lds_u32 *)stage_words;
+    global_u32 *const byte_pairs = (global_u32 *)(uintptr_t)tv.byte_pairs, *const merged_of = (global_u32 *)(uintptr_t)tv.merged_of;
+    auto slot_at = [](uintptr_t half_base, uint32_t byte_offset) {
+        const u32x2 v = *(global_u32x2 *)(half_base + byte_offset);
+        return make_uint2(v.x, v.y);
+    };
+    const uint32_t not_lane = ~(uint32_t)lane;
+    const uint64_t up_to_lane = ~0ull >> (63 - lane);
+    n_pieces = __builtin_amdgcn_readfirstlane(n_pieces);
+    int result = -1;
+    for (int i = 0; i < n_pieces; ++i) {
+        int b = __builtin_amdgcn_readlane(b_of, i), left = __builtin_amdgcn_readlane(n_of, i), dst = b;
+        while (left > 0) {
+            int n = min(left, kWave);
+            uint32_t sym = lane < n ? *(global_u8 *)(bytes + (uint32_t)(b + lane)) : 0u;
+            uint32_t next = (uint32_t)wave_from_lane_above((int)sym, 0);
+            const uint32_t pair = lane + 1 < n ? byte_pairs[sym << 8 | next] : kNeverJoined;
+            uint64_t live = n == kWave ? ~0ull : (1ull << n) - 1;
+            uint64_t first = live & ~(__ballot(pair != kNeverJoined) << 1);        // where parts start
+            if (long_part(live & ~first)) break;
+            if (left > n) {        // the last part may go on: it comes next time (it is not the only one)
+                n = 63 - __builtin_clzll(first);
+                live = (1ull << n) - 1;
+                first &= live;
+            }
+            b += n;
+            left -= n;
+            sym |= (first >> lane & 1) ? kFirst : 0u;
+            const uint32_t rank0 = lane + 1 < n ? byte_pair_rank(pair) : kNoRank;
+            uint32_t q = rank0 == kNoRank ? 0u : ~rank0 | 63u;       // ~rank word, 0: none; the low bits are for the lane
+            for (;;) {
+                if (!__ballot(q != 0)) break;
+                const uint32_t key = q & not_lane;
+                const int start = 63 - __builtin_clzll((first & up_to_lane) | 1ull);
+                stage[lane] = 0;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __hip_atomic_fetch_max(&stage[start], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const uint32_t best = stage[start];
+                const bool sel = q != 0 && key == best;
+                const uint32_t rank = ~q >> kRankShift;
+                uint32_t merged = rank + (uint32_t)tv.merged_delta;
+                if (tv.merged_delta < 0) merged = merged_of[sel ? rank : 0u];
+                const uint64_t removed = __ballot(sel) << 1, kept = live & ~removed;
+                sym = sel ? merged | (sym & kFirst) | kNew : sym;
+                const int n_kept = __builtin_popcountll(kept);
+                // the symbols that stay close up, the others go behind them (a permutation of the lanes)
+                const bool stays = !((removed >> lane) & 1);
+                const int to = lane >= n ? lane : stays ? mbcnt(kept) : n_kept + mbcnt(removed);
+                sym = permute_push(to, sym);
+                q = permute_push(to, q);
+                n = n_kept;
+                live = (1ull << n) - 1;                      // (a merge has made it less than 64)
+                first = __ballot(sym & kFirst) & live;
+                next = (uint32_t)wave_from_lane_above((int)sym, 0);
+                const bool is_pair = lane + 1 < n && !(next & kFirst), fresh = is_pair && ((sym | next) & kNew);
+                SlotProbe slot = slot_probe(tv, sym, next);  // (the flags: see there)
+                slot.off1 = fresh ? slot.off1 : 0u;
+                slot.off2 = fresh ? slot.off2 : 0u;
+                const uint2 s1 = slot_at(lower, slot.off1), s2 = slot_at(upper, slot.off2);
+                q = is_pair ? q : 0u;
+                sym &= ~kNew;
+                const uint32_t rank1 = slot_match(s1, s2, slot.rest1, slot.rest2);
+                q = fresh ? (rank1 == kNoRank ? 0u : ~rank1 | 63u) : q;
+            }
+            if (lane < n) *(global_i32 *)(scratch + 4 * (uintptr_t)(uint32_t)(dst + lane)) = (int32_t)(sym & 0xFFFFFFu);
+            dst += n;
+        }
+        const int c = left > 0 ? -1 : dst - __builtin_amdgcn_readlane(b_of, i);
+        result = lane == i ? c : result;
+    }
+    return result;
 }
 
 // Stores the lane's final tokens (positions `alive` of its column) to dst[0 ...].

@@ -353,6 +353,21 @@ static void build_cuts(const int32_t *merges, const RuleOrder &ro, CutSets &cuts
     }
 }
 
+// kNeverJoined for the pairs of bytes x, y such that no rule joins a string that ends with x to one that starts with y.
+static void mark_never_joined(const int32_t *merges, const RuleOrder &ro, uint32_t *byte_pairs) {
+    std::vector<uint8_t> first(ro.made_at.size()), last(ro.made_at.size()), joined(65536);
+    for (int b = 0; b < 256; ++b) first[b] = last[b] = (uint8_t)b;
+    for (const auto &rule : ro.by_rank) {
+        const int64_t row = rule.second;
+        const int32_t a = merges[2 * row], b = merges[2 * row + 1];
+        first[ro.merged_row[row]] = first[a];
+        last[ro.merged_row[row]] = last[b];
+        joined[(size_t)last[a] << 8 | first[b]] = 1;
+    }
+    for (size_t i = 0; i < joined.size(); ++i)
+        if (!joined[i]) byte_pairs[i] = kNeverJoined;
+}
+
 // The one allocation of a table on the device: where its arrays start, and its size.
 struct DeviceLayout { size_t words, byte_pairs, merged_of, rank_of, sym_lr, total; };     // (the slots are first)
 
@@ -437,6 +452,7 @@ extern "C" int bpe_table_build(const int32_t *merges, const int32_t *ranks, cons
     }
     memcpy(blob.data() + at.words, words.slots.data(), words.slots.size() * 4);
     memcpy(blob.data() + at.byte_pairs, img.byte_pairs.data(), img.byte_pairs.size() * 4);
+    mark_never_joined(merges, ro, (uint32_t *)(blob.data() + at.byte_pairs));
     memcpy(blob.data() + at.merged_of, img.merged_of.data(), img.merged_of.size() * 4);
     memcpy(blob.data() + at.rank_of, img.rank_of.data(), img.rank_of.size() * 4);
     memcpy(blob.data() + at.sym_lr, img.sym_lr.data(), img.sym_lr.size() * 4);

@@ -51,17 +51,19 @@ namespace bpe {
 // wavefronts and the double buffer of the workgroup path share the same room; a barrier
 // separates the uses, and the tokens of short pieces are in the workspace (or in
 // registers) before the workgroup path begins.
-// Short pieces without a whole-piece token: as many as the wavefronts have rows of 16 lanes are merged
-// one per row, more of them one per lane.  Not two rounds of rows: a round is as long as its longest
-// chain (words of 13 to 16 bytes are never in the whole-piece table and take a dozen merges), and one
-// round of columns takes them all at once.  840 KB with the 100k table: 14.3 us with two rounds, 12.6 with
-// one; 13.5 MB with the 50k table 58.6 and 56.3; 60 KB with the 1k table 11.5 and 10.6.  (Except in
-// merge_raw_kernel: a tile per workgroup on grids of many rounds of the chip, where 17 left-over pieces
-// delay nobody; 64 MB from raw bytes 365 us with two rounds, 369 with one.)
+// Short pieces without a whole-piece token: as many as the wavefronts have rows of 16 lanes, and a quarter more, are merged
+// one per row, more of them one per lane.  A round of rows is as long as its longest chain (up to a dozen steps of 0.25 us), one of
+// columns takes them all at once in steps of 0.5 us; the quarter is for the few tiles of a call that have a few more than the
+// others, because the call waits for them.  Without it / with it (per call, us): 840 KB, 50k table 11.4 / 10.9, 600 KB, 100k table 11.3 / 10.7, 4 and 60 KB,
+// 1k table (60 left-over pieces per tile, 64 rows) 9.2 / 8.4 and 10.3 / 9.3.  Not two whole rounds: 115 left-over pieces
+// per tile with 64 rows 13.3 / 15.7, 31 with 16 rows 11.9 / 12.5.  (merge_raw_kernel takes two: a tile per workgroup on grids of many rounds of the chip, where 17
+// left-over pieces delay nobody; 64 MB from raw bytes 365 us with two rounds, 369 with one.)
 __host__ __device__ constexpr int row_pieces(int waves) { return waves * (kWave / kTinyMax); }
 // The single kernel has helper wavefronts for the rows on grids that leave the chip idle (at most one
 // tile per compute unit), where a tile of a table with few whole words leaves 60 pieces over.
 constexpr int kFusedWaves = 16;
+constexpr int kRowQuarters = 5;                // quarters of a round of rows
+__host__ __device__ constexpr int row_limit(int waves, int quarters) { return quarters * row_pieces(waves) / 4; }
 constexpr int kRunPiecesMax = 4;               // tiles in flight together, a piece of each per thread
 constexpr int kRunTilesMax = 16;
 constexpr int kRunLeft = 1360;                 // left-over pieces that the list holds
@@ -75,7 +77,7 @@ constexpr int kPartsPieces = 8;
 union MergeLds {
     TinyState tiny[kWavesPerGroup];
     struct { int32_t A[kLdsMaxLen]; int32_t B[kLdsMaxLen]; } group;
-    struct { uint4 bytes[kGroupThreads]; uint32_t tok[row_pieces(kFusedWaves)][kTinyMax]; } left;   // see merge_left_over
+    struct { uint4 bytes[kGroupThreads]; uint32_t tok[row_limit(kFusedWaves, kRowQuarters)][kTinyMax]; } left;   // see merge_left_over
     struct { uint4 bytes[kRunLeft]; int2 piece[kRunLeft]; } run;   // see merge_tile_run: {first byte, length << 16 | number in the run}
 };
 
@@ -170,7 +172,7 @@ __device__ __forceinline__ int left_slot_of(int e, const int (&n)[kWavesPerGroup
 constexpr int kAnyLonger = 1 << 16;
 
 // Returns whether the tile has longer pieces.
-template <int SRC, int WAVES, int ROUNDS>
+template <int SRC, int WAVES, int QUARTERS>
 __device__ __forceinline__ bool merge_left_over(const EncodeParams &p, TileShared &sh, TilePiece &t, int64_t tile_q0, int P,
                                                 bool keep_in_lds) {
     const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -187,7 +189,7 @@ __device__ __forceinline__ bool merge_left_over(const EncodeParams &p, TileShare
     auto record_of = [&](int owner) {
         return SRC == kFromBytes ? tile_q0 + owner : tile_q0 + (int64_t)(owner / kWave) * P + (owner % kWave);
     };
-    if (t.n_left <= ROUNDS * row_pieces(WAVES)) {
+    if (t.n_left <= row_limit(WAVES, QUARTERS)) {
         constexpr int kRows = kWave / kTinyMax;
         for (int e0 = wv * kRows; e0 < t.n_left; e0 += row_pieces(WAVES)) {
             const int j = lane & (kTinyMax - 1), e = e0 + lane / kTinyMax;
@@ -246,8 +248,8 @@ __device__ __forceinline__ bool merge_left_over(const EncodeParams &p, TileShare
 // the tile (if that is below bt.n_t), and its record goes to slot bt_q0 + that number.
 // WAVES: wavefronts of the workgroup; the ones beyond the tile's four only help with left-over pieces.
 // EAGER: see find_word.
-// ROUNDS: rounds of rows that left-over pieces may take (0: always one per lane); see row_pieces.
-template <int SRC = kFromOffsets, bool SKIP_LONG = false, int WAVES = kWavesPerGroup, bool EAGER = !SKIP_LONG, int ROUNDS = 1>
+// QUARTERS: quarters of a round of rows that left-over pieces may take (0: always one per lane); see row_pieces.
+template <int SRC = kFromOffsets, bool SKIP_LONG = false, int WAVES = kWavesPerGroup, bool EAGER = !SKIP_LONG, int QUARTERS = 4>
 __device__ __forceinline__ TilePiece merge_tile(const EncodeParams &p, TileShared &sh, int tile, bool keep_in_lds,
                                                 int n_pieces, int P, const ByteTile &bt = ByteTile{}, int64_t bt_q0 = 0) {
     const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
@@ -329,7 +331,7 @@ __device__ __forceinline__ TilePiece merge_tile(const EncodeParams &p, TileShare
     if (lane == 0 && (WAVES <= kWavesPerGroup || wv < kWavesPerGroup))
         sh.left_n[wv] = __builtin_popcountll(left_mask) | (wave_longer ? kAnyLonger : 0);
     __syncthreads();
-    const bool any_longer = merge_left_over<SRC, WAVES, ROUNDS>(p, sh, t, tile_q0, P, keep_in_lds);
+    const bool any_longer = merge_left_over<SRC, WAVES, QUARTERS>(p, sh, t, tile_q0, P, keep_in_lds);
 
     if (SKIP_LONG) {
         t.has_piece = t.has_piece && !is_wave && !is_long;     // whoever merges a piece writes its record
@@ -528,10 +530,10 @@ __device__ inline int tiles_of(const EncodeParams &p) {
 
 // Several-kernel path, first kernel: tokens and counts of every piece to the
 // workspace, the tile's token total to tile_sum.
-template <int SRC = kFromOffsets, bool SKIP_LONG = false, bool EAGER = !SKIP_LONG, int ROUNDS = 1>
+template <int SRC = kFromOffsets, bool SKIP_LONG = false, bool EAGER = !SKIP_LONG, int QUARTERS = 4>
 __device__ __forceinline__ void merge_and_count_tile(const EncodeParams &p, TileShared &sh, int *wave_tokens, int tile,
                                                      int n_pieces, int P) {
-    const TilePiece t = merge_tile<SRC, SKIP_LONG, kWavesPerGroup, EAGER, ROUNDS>(p, sh, tile, false, n_pieces, P);
+    const TilePiece t = merge_tile<SRC, SKIP_LONG, kWavesPerGroup, EAGER, QUARTERS>(p, sh, tile, false, n_pieces, P);
     if (t.has_piece && t.left_slot < 0) p.rec[t.q] = make_int2(t.cnt, t.tok0);
     const int wave_total = __builtin_amdgcn_readlane(wave_scan_inclusive(t.cnt + t.others_cnt), kWave - 1);
     if (lane_id() == 0) wave_tokens[threadIdx.x / kWave] = wave_total;
@@ -960,7 +962,7 @@ __device__ __forceinline__ void long_pieces_group(const EncodeParams &p, TileSha
 __global__ void __launch_bounds__(kGroupThreads) merge_tiles_kernel(EncodeParams p) {
     __shared__ TileShared sh;
     __shared__ int wave_tokens[kWavesPerGroup];
-    merge_and_count_tile(p, sh, wave_tokens, blockIdx.x, p.n_pieces, p.P);
+    merge_and_count_tile<kFromOffsets, false, true, kRowQuarters>(p, sh, wave_tokens, blockIdx.x, p.n_pieces, p.P);
 }
 
 // Word-sized pieces on average: the first p.n_long_groups workgroups take the long pieces (see
@@ -1042,7 +1044,7 @@ __global__ void __launch_bounds__(kGroupThreads) merge_raw_kernel(EncodeParams p
     __shared__ TileShared sh;
     __shared__ int wave_tokens[kWavesPerGroup];
     raw_geometry(p);
-    if ((int)blockIdx.x < tiles_of(p)) merge_and_count_tile<kFromOffsets, false, true, 2>(p, sh, wave_tokens, blockIdx.x, p.n_pieces, p.P);
+    if ((int)blockIdx.x < tiles_of(p)) merge_and_count_tile<kFromOffsets, false, true, 8>(p, sh, wave_tokens, blockIdx.x, p.n_pieces, p.P);
 }
 
 // The same for a caller who says that the pieces are word-sized (pieces_per_wave 64 given, not left
@@ -1244,7 +1246,7 @@ __global__ void __launch_bounds__(kGroupThreads) merge_bytes_kernel(EncodeParams
     bt.end_rel = end - lo;
     const int64_t q0 = (int64_t)tile * kByteTileStride;
     // the first 256 pieces: as in every other merge kernel
-    const TilePiece t = merge_tile<kFromBytes>(p, sh, 0, false, 0, kWave, bt, q0);
+    const TilePiece t = merge_tile<kFromBytes, false, kWavesPerGroup, true, kRowQuarters>(p, sh, 0, false, 0, kWave, bt, q0);
     if (t.has_piece) {
         if (t.left_slot < 0) p.rec[t.q] = make_int2(t.cnt, t.tok0);
         p.off_out[t.q] = t.o;
@@ -1327,7 +1329,8 @@ __global__ void __launch_bounds__(WAVES * kWave) encode_kernel(EncodeParams p, i
     if (tile == 0 && tid == 0) mark_call(p.status, p.call_id);
     const int32_t epoch = p.status[kStatusEpochEncode];
 
-    const TilePiece t = merge_tile<kFromOffsets, false, WAVES>(p, sh, tile, true, p.n_pieces, p.P);
+    constexpr int kQuarters = WAVES == kFusedWaves ? kRowQuarters : 4;
+    const TilePiece t = merge_tile<kFromOffsets, false, WAVES, true, kQuarters>(p, sh, tile, true, p.n_pieces, p.P);
     if (WAVES > kWavesPerGroup && wv >= kWavesPerGroup) return;          // the helpers are done; barriers wait for the wavefronts that are left
     const bool has_piece = t.has_piece;
     const int o = t.o, my_cnt = t.cnt;
@@ -1356,7 +1359,7 @@ __global__ void __launch_bounds__(WAVES * kWave) encode_kernel(EncodeParams p, i
         __syncthreads();
         int n[kWavesPerGroup];
         for (int w = 0; w < kWavesPerGroup; ++w) n[w] = __builtin_amdgcn_readfirstlane(sh.left_n[w]);
-        if (t.n_left <= row_pieces(WAVES)) {
+        if (t.n_left <= row_limit(WAVES, kQuarters)) {
             for (int i = tid; i < t.n_left * kTinyMax; i += kGroupThreads) {
                 const int slot = left_slot_of(i / kTinyMax, n), j = i % kTinyMax;
                 const int dst = sh.list[slot];

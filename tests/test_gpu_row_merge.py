@@ -34,3 +34,25 @@ def test_rows(numbered, form):
         want = oracle.encode(oracle.Table(merges, None, ids), data, off)
         got = B.encode(B.Table(merges, None, ids), torch.from_numpy(data.copy()).cuda(), torch.from_numpy(off).cuda(), B.EncodeOptions(**form))
         assert np.array_equal(got[1].cpu().numpy(), want[1]) and np.array_equal(got[0].cpu().numpy(), want[0]), trial
+
+
+@pytest.mark.parametrize("form", [{}, {"fused": -1}])
+def test_as_many_left_over_pieces_as_rows_hold(form):
+    """4 wavefronts have 16 rows, 16 have 64, and rows are taken for a quarter more: tiles of 256 with left-over pieces around
+    one round of either, that limit, and two rounds."""
+    import torch
+    import paper_2603_02597_amd as B
+    from workloads import configs as C
+    rng = np.random.default_rng(8)
+    merges = C.load_merges("t1k")
+    letters = np.frombuffer(b"etaoinshr", dtype=np.uint8)
+    pieces = []
+    for n_left in (0, 1, 15, 16, 17, 19, 20, 21, 32, 33, 63, 64, 65, 79, 80, 81, 128, 129, 255, 256):
+        tile = [b" " + rng.choice(letters, int(rng.integers(12, 16))).tobytes() for _ in range(n_left)] + [b"e"] * (256 - n_left)
+        pieces += [tile[k] for k in rng.permutation(256)]
+    data = np.frombuffer(b"".join(pieces), dtype=np.uint8)
+    off = np.concatenate([[0], np.cumsum([len(p) for p in pieces])]).astype(np.int32)
+    want = oracle.encode(oracle.Table(merges), data, off)
+    d, o = torch.from_numpy(data.copy()).cuda(), torch.from_numpy(off).cuda()
+    got = B.encode(B.Table(merges), d, o, B.EncodeOptions(pieces_per_wave=64, **form))
+    assert np.array_equal(got[1].cpu().numpy(), want[1]) and np.array_equal(got[0].cpu().numpy(), want[0])

@@ -3,10 +3,12 @@ per text and the kernel time out.  Marshalling only: the texts are concatenated
 behind their offsets into one pinned host buffer, a kernel brings them to the GPU,
 bpe_encode_raw does the rest (piece starts, merges, ids per text), and a kernel puts offsets and ids into
 pinned memory; decode_batch goes the other way through bpe_decode.  Buffers grow to
-the largest batch seen and are reused, so a steady stream of batches allocates nothing."""
+the largest batch seen and are reused, so a steady stream of batches allocates nothing; threads
+may share a Tokenizer and use these buffers one after the other."""
 from __future__ import annotations
 
 import ctypes
+import threading
 
 import numpy as np
 
@@ -30,6 +32,7 @@ class Tokenizer:
         import torch
         self._torch = torch
         self.device = torch.device(device)
+        self._lock = threading.Lock()      # held from the packing of a batch until its results are copied out
         with torch.cuda.device(self.device):
             self.table = B.Table(merges, ranks, merged_ids)
             self.vocab = B.Vocab(merges, ranks, merged_ids, output_ids)
@@ -106,7 +109,7 @@ class Tokenizer:
         n_bytes = len(joined)
         if n_bytes >= 2**31 - 1:
             raise ValueError("a batch must stay below 2^31 bytes")
-        with torch.cuda.device(self.device):
+        with torch.cuda.device(self.device), self._lock:
             self._reserve(n_bytes, n_seqs)
             lib = B.load_library()
             n_in = 4 * (n_seqs + 1)
@@ -190,7 +193,8 @@ class Tokenizer:
             return [b"" for _ in arrs]
         with torch.cuda.device(self.device):
             if n_tokens <= _DECODE_TOKENS_MAX:
-                texts = self._decode_pinned(arrs, sizes, n_tokens)
+                with self._lock:
+                    texts = self._decode_pinned(arrs, sizes, n_tokens)
                 if texts is not None:
                     return texts
             dev = self.device

@@ -56,6 +56,7 @@ class Tokenizer:
             return
         nb = max(n_bytes, 2 * self._cap_bytes, 1 << 16)
         ns = max(n_seqs, 2 * self._cap_seqs, 64)
+        self._cap_bytes = self._cap_seqs = 0          # until every buffer is there: an allocation may fail
         dev = self.device
         # One buffer each way:
         # in  = [sequence offsets int32 (n_seqs + 1) | bytes], packed per call;
@@ -144,6 +145,7 @@ class Tokenizer:
             return
         nt = min(max(n_tokens, 2 * self._cap_tokens, 1 << 14), _DECODE_TOKENS_MAX)
         nx = max(n_texts, 2 * self._cap_texts, 64)
+        self._cap_tokens = self._cap_texts = 0        # as in _reserve
         dev = self.device
         # in  = [ids int32 | index of every text's first id, and their number, int32 (n_texts + 1)], packed per call;
         # out = [first byte of every text int32 (n_texts + 1), up to a multiple of 16 bytes | bytes]

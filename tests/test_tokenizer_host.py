@@ -136,3 +136,22 @@ def test_threads_that_share_a_tokenizer(device):
     for t in threads:
         t.join()
     assert not failed
+
+
+@pytest.mark.parametrize("fail_at", range(8))
+def test_a_batch_whose_buffers_cannot_be_had(device, fail_at):
+    """Whichever allocation of a larger batch fails, later batches are right and stay within their buffers."""
+    tok = tokenizer_module.Tokenizer([])
+    small = [np.arange(65, 90, dtype=np.int32), np.full(300, 0xF00 + 97, dtype=np.int32)]
+    text = [b"ABCDEFGHIJKLMNOPQRSTUVWXY", b"a" * 4800]
+    between = np.full(70000, 0xF00 + 98, dtype=np.int32)              # 16 bytes per token: more than the first buffers hold
+    for grow, batches in ((lambda: tok.decode_batch([np.full(100000, 65, dtype=np.int32)] * 2),
+                           (lambda: tok.decode_batch(small) == text, lambda: tok.decode_batch([between]) == [b"b" * 1120000])),
+                          (lambda: tok.tokenize_batch([b"c" * 200000] * 100),
+                           (lambda: [bytes(a.tolist()) for a in tok.tokenize_batch(text)[0]] == text,))):
+        assert all(good() for good in batches[:1])
+        device.fail_at = fail_at
+        with contextlib.suppress(MemoryError):
+            grow()
+        device.fail_at = None
+        assert all(good() for good in batches)

@@ -127,12 +127,16 @@ class Tokenizer:
             stream = torch.cuda.current_stream()
             s, clock, ws = stream.cuda_stream, self._clock.data_ptr(), self._ws.data_ptr()
             d_in, d_out = self._d_in.data_ptr(), self._d_out.data_ptr()
-            self._check(lib.bpe_batch_in(self._h_in.data_ptr(), d_in, n_in + n_bytes, clock, s))
-            self._check(lib.bpe_encode_raw(self.table._h, d_in + n_in, n_bytes, d_in, n_seqs, 0, d_out + n_in, d_out,
-                                           None, None, None, ws, self._ws.numel(), None, s))
-            self._check(lib.bpe_batch_ids_out(self.vocab._h if self._use_output_ids else None, d_out, n_seqs + 1, n_bytes,
-                                              self._h_out.data_ptr(), ws, clock, self._head.data_ptr(), s))
-            st = self._finish(stream)
+            try:
+                self._check(lib.bpe_batch_in(self._h_in.data_ptr(), d_in, n_in + n_bytes, clock, s))
+                self._check(lib.bpe_encode_raw(self.table._h, d_in + n_in, n_bytes, d_in, n_seqs, 0, d_out + n_in, d_out,
+                                               None, None, None, ws, self._ws.numel(), None, s))
+                self._check(lib.bpe_batch_ids_out(self.vocab._h if self._use_output_ids else None, d_out, n_seqs + 1, n_bytes,
+                                                  self._h_out.data_ptr(), ws, clock, self._head.data_ptr(), s))
+                st = self._finish(stream)
+            except BaseException:
+                stream.synchronize()       # what is under way still writes to the buffers, and the next batch may be on another stream
+                raise
             if st != 0:
                 raise B.BpeError(st, lib.bpe_last_error().decode(errors="replace"))
             tok = self._h_out_np[:n_seqs + 1].tolist()
@@ -170,12 +174,17 @@ class Tokenizer:
         stream = self._torch.cuda.current_stream()
         s, clock, ws, tbo = stream.cuda_stream, self._clock.data_ptr(), self._dws.data_ptr(), self._dd_tbo.data_ptr()
         d_in, d_out, h_out, n_starts = self._dd_in.data_ptr(), self._dd_out.data_ptr(), self._hd_out.data_ptr(), _up16(4 * (n_texts + 1))
-        self._check(lib.bpe_batch_in(self._hd_in.data_ptr(), d_in, 4 * (n_tokens + n_texts + 1), clock, s))
-        self._check(lib.bpe_decode(self.vocab._h, d_in, n_tokens, None, 1 if self._use_output_ids else 0, d_out, self._decode_bytes, tbo,
-                                   None, ws, self._dws.numel(), s))
-        self._check(lib.bpe_batch_bytes_out(d_out, self._decode_bytes, tbo, n_tokens, d_in + 4 * n_tokens, n_texts + 1, h_out,
-                                            h_out + n_starts, ws, clock, self._head.data_ptr(), s))
-        if self._finish(stream) != 0:
+        try:
+            self._check(lib.bpe_batch_in(self._hd_in.data_ptr(), d_in, 4 * (n_tokens + n_texts + 1), clock, s))
+            self._check(lib.bpe_decode(self.vocab._h, d_in, n_tokens, None, 1 if self._use_output_ids else 0, d_out, self._decode_bytes, tbo,
+                                       None, ws, self._dws.numel(), s))
+            self._check(lib.bpe_batch_bytes_out(d_out, self._decode_bytes, tbo, n_tokens, d_in + 4 * n_tokens, n_texts + 1, h_out,
+                                                h_out + n_starts, ws, clock, self._head.data_ptr(), s))
+            st = self._finish(stream)
+        except BaseException:
+            stream.synchronize()           # as in tokenize_batch
+            raise
+        if st != 0:
             return None
         starts = self._hd_out_np[:4 * (n_texts + 1)].view(np.int32).tolist()
         text = self._hd_out_np[n_starts:]

@@ -155,3 +155,13 @@ def test_a_batch_whose_buffers_cannot_be_had(device, fail_at):
             grow()
         device.fail_at = None
         assert all(good() for good in batches)
+
+
+@pytest.mark.parametrize("refused", ["bpe_encode_raw", "bpe_batch_ids_out", "bpe_decode", "bpe_batch_bytes_out"])
+def test_a_batch_that_ends_early_leaves_nothing_under_way(device, refused):
+    tok = tokenizer_module.Tokenizer([])
+    setattr(device, refused, lambda *a: -1)
+    call = tok.tokenize_batch if refused in ("bpe_encode_raw", "bpe_batch_ids_out") else tok.decode_batch
+    with pytest.raises(RuntimeError):
+        call([b"abc"] if call == tok.tokenize_batch else [[65, 66]])
+    assert "in" in device.calls and device.calls[-1] == "synchronize"

@@ -96,15 +96,14 @@ class Tokenizer:
         n_seqs = len(texts)
         if n_seqs == 0:
             return [], 0.0
-        # text that is ASCII is copied from where it lies
-        source = None
-        if all(type(t) is str for t in texts):
+        # text that is ASCII is copied from where it lies (every string knows whether it is, so nothing is joined to find out)
+        if all(type(t) is str for t in texts) and all(map(str.isascii, texts)):
             joined = texts[0] if n_seqs == 1 else "".join(texts)
-            if joined.isascii():
-                size = ctypes.c_ssize_t()
-                source = _utf8(joined, ctypes.byref(size))
-                raw = texts
-        if source is None:
+            size = ctypes.c_ssize_t()
+            source = _utf8(joined, ctypes.byref(size))
+            raw = texts
+        else:
+            source = None
             raw = [t.encode("utf-8") if isinstance(t, str) else t for t in texts]
             joined = raw[0] if n_seqs == 1 else b"".join(raw)
         n_bytes = len(joined)

@@ -5,6 +5,7 @@ import ctypes
 import sys
 import threading
 import time
+import tracemalloc
 import types
 
 import numpy as np
@@ -165,3 +166,18 @@ def test_a_batch_that_ends_early_leaves_nothing_under_way(device, refused):
     with pytest.raises(RuntimeError):
         call([b"abc"] if call == tok.tokenize_batch else [[65, 66]])
     assert "in" in device.calls and device.calls[-1] == "synchronize"
+
+
+def test_texts_that_are_not_ascii_are_joined_once(device):
+    """As bytes: each text's bytes and their join, twice the batch, and no join of the strings beside them."""
+    tok = tokenizer_module.Tokenizer([])
+    texts = ["word " * 4000] * 49 + ["café " * 4000]
+    size = sum(len(t.encode()) for t in texts)
+    tok.tokenize_batch(texts)                          # (buffers are there)
+    device.bpe_batch_in = lambda *a: -1                # what follows the packing is not counted
+    tracemalloc.start()
+    with pytest.raises(RuntimeError):
+        tok.tokenize_batch(texts)
+    peak = tracemalloc.get_traced_memory()[1]
+    tracemalloc.stop()
+    assert peak < 2.5 * size

@@ -454,7 +454,8 @@ int bpe_map_ids(const bpe_vocab *vocab, const int32_t *ids_in, int32_t *ids_out,
  *   bpe_batch_ids_out    words: device int32, n_offsets offsets and behind them the ids, as many as the last offset says (at
  *                        most max_ids); host gets the same, with the output ids of vocab unless that is NULL
  *   bpe_batch_bytes_out  host_starts[k] = token_byte_offsets[bounds[k]], 0 <= k < n_bounds; host gets the first
- *                        token_byte_offsets[n_tokens] bytes, at most `capacity`
+ *                        token_byte_offsets[n_tokens] bytes, at most `capacity`, and none if bpe_decode had to cut them off
+ *                        (BPE_ERR_SIZE among the status words)
  *   host_head            host int32 [16]: [0 .. 8) the status words of `workspace` (see bpe_status_from_words), [8] the
  *                        time from the end of bpe_batch_in to the start of this kernel, in units of 10 ns
  */

@@ -162,7 +162,8 @@ class Tokenizer:
         self._cap_tokens, self._cap_texts = nt, nx
 
     def _decode_pinned(self, arrs, sizes, n_tokens: int):
-        """decode_batch of at most _DECODE_TOKENS_MAX tokens through the pinned buffers, or None if the bytes do not fit them."""
+        """decode_batch of at most _DECODE_TOKENS_MAX tokens through the pinned buffers.  If the bytes do not fit them, their
+        size is known by then: decoded once more, into memory of that size."""
         n_texts = len(arrs)
         self._reserve_decode(n_tokens, n_texts)
         lib = B.load_library()
@@ -180,13 +181,19 @@ class Tokenizer:
             self._check(lib.bpe_batch_bytes_out(d_out, self._decode_bytes, tbo, n_tokens, d_in + 4 * n_tokens, n_texts + 1, h_out,
                                                 h_out + n_starts, ws, clock, self._head.data_ptr(), s))
             st = self._finish(stream)
+            starts = self._hd_out_np[:4 * (n_texts + 1)].view(np.int32).tolist()
+            text = self._hd_out_np[n_starts:]
+            if st != 0:
+                if starts[-1] < 0:
+                    raise ValueError("the decoded text would exceed 2^31 bytes")
+                out = self._torch.empty(starts[-1], dtype=self._torch.uint8, device=self.device)
+                self._check(lib.bpe_decode(self.vocab._h, d_in, n_tokens, None, 1 if self._use_output_ids else 0, out.data_ptr(), starts[-1],
+                                           tbo, None, ws, self._dws.numel(), s))
+                self._check(B.bpe_encode_status(self._dws))
+                text = out.cpu().numpy()
         except BaseException:
             stream.synchronize()           # as in tokenize_batch
             raise
-        if st != 0:
-            return None
-        starts = self._hd_out_np[:4 * (n_texts + 1)].view(np.int32).tolist()
-        text = self._hd_out_np[n_starts:]
         return [text[a:b].tobytes() for a, b in zip(starts, starts[1:])]
 
     def decode_batch(self, ids_list):
@@ -204,9 +211,7 @@ class Tokenizer:
         with torch.cuda.device(self.device):
             if n_tokens <= _DECODE_TOKENS_MAX:
                 with self._lock:
-                    texts = self._decode_pinned(arrs, sizes, n_tokens)
-                if texts is not None:
-                    return texts
+                    return self._decode_pinned(arrs, sizes, n_tokens)
             dev = self.device
             bounds = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
             ids = torch.from_numpy(np.concatenate(arrs)).to(dev)

@@ -181,3 +181,13 @@ def test_texts_that_are_not_ascii_are_joined_once(device):
     peak = tracemalloc.get_traced_memory()[1]
     tracemalloc.stop()
     assert peak < 2.5 * size
+
+
+@pytest.mark.parametrize("n", [1, 5000, 70000])
+def test_long_tokens_are_decoded_twice_at_most(device, n):
+    """Beyond the buffers (16 bytes per token, 1 MiB at least): once to learn the size, once into memory of that size."""
+    tok = tokenizer_module.Tokenizer([])
+    per = (1 << 20) // n + 17
+    ids = np.full(n, (per - 1) << 8 | 97, dtype=np.int32)
+    assert tok.decode_batch([ids, [98]]) == [b"a" * (per * n), b"b"]
+    assert device.calls.count("decode") == 2

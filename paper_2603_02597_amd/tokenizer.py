@@ -15,8 +15,9 @@ import numpy as np
 from . import binding as B
 
 
-# decode_batch keeps buffers for batches of up to so many tokens, and of up to 16 bytes per token (pinned: 24 MiB at most).
-_DECODE_TOKENS_MAX = 1 << 20
+# decode_batch keeps buffers for batches of up to so many tokens, of up to 16 bytes per token, and of up to so many texts (pinned:
+# 4 + 16 bytes per token and 8 per text, 24 MiB at most).  Larger batches have memory of their own.
+_DECODE_TOKENS_MAX, _DECODE_TEXTS_MAX = 1 << 20, 1 << 18
 
 _utf8 = ctypes.pythonapi.PyUnicode_AsUTF8AndSize
 _utf8.restype = ctypes.c_void_p
@@ -147,7 +148,7 @@ class Tokenizer:
         if n_tokens <= self._cap_tokens and n_texts <= self._cap_texts:
             return
         nt = min(max(n_tokens, 2 * self._cap_tokens, 1 << 14), _DECODE_TOKENS_MAX)
-        nx = max(n_texts, 2 * self._cap_texts, 64)
+        nx = min(max(n_texts, 2 * self._cap_texts, 64), _DECODE_TEXTS_MAX)
         self._cap_tokens = self._cap_texts = 0        # as in _reserve
         dev = self.device
         # in  = [ids int32 | index of every text's first id, and their number, int32 (n_texts + 1)], packed per call;
@@ -162,7 +163,7 @@ class Tokenizer:
         self._cap_tokens, self._cap_texts = nt, nx
 
     def _decode_pinned(self, arrs, sizes, n_tokens: int):
-        """decode_batch of at most _DECODE_TOKENS_MAX tokens through the pinned buffers.  If the bytes do not fit them, their
+        """decode_batch of at most _DECODE_TOKENS_MAX tokens and _DECODE_TEXTS_MAX texts through the pinned buffers.  If the bytes do not fit them, their
         size is known by then: decoded once more, into memory of that size."""
         n_texts = len(arrs)
         self._reserve_decode(n_tokens, n_texts)
@@ -209,7 +210,7 @@ class Tokenizer:
         if n_tokens == 0:
             return [b"" for _ in arrs]
         with torch.cuda.device(self.device):
-            if n_tokens <= _DECODE_TOKENS_MAX:
+            if n_tokens <= _DECODE_TOKENS_MAX and len(arrs) <= _DECODE_TEXTS_MAX:
                 with self._lock:
                     return self._decode_pinned(arrs, sizes, n_tokens)
             dev = self.device

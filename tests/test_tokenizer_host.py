@@ -191,3 +191,11 @@ def test_long_tokens_are_decoded_twice_at_most(device, n):
     ids = np.full(n, (per - 1) << 8 | 97, dtype=np.int32)
     assert tok.decode_batch([ids, [98]]) == [b"a" * (per * n), b"b"]
     assert device.calls.count("decode") == 2
+
+
+def test_pinned_memory_for_decoding_is_bounded(device):
+    """By the number of texts as well as by that of the tokens, whichever batches came before."""
+    tok, empty = tokenizer_module.Tokenizer([]), np.zeros(0, dtype=np.int32)
+    for n_tokens, n_texts in ((1, 1 << 18), (1, 1 << 20), (1 << 20, 1), ((1 << 20) + 1, 1), (5, 100)):
+        assert tok.decode_batch([np.full(n_tokens, 66, dtype=np.int32)] + [empty] * (n_texts - 1)) == [b"B" * n_tokens] + [b""] * (n_texts - 1)
+        assert tok._hd_in.nbytes + tok._hd_out.nbytes <= 24 << 20

@@ -384,6 +384,24 @@ __device__ __forceinline__ WaveDeal wave_deal(int n_col, int n_entries, int wv) 
     return d;
 }
 
+// A piece by one wavefront: its parts while they are short, and from the first longer one on as a piece of its own (no token
+// reaches across a border of parts), whose tokens then move up behind the others.  Merged as a whole when a later part was too long, what
+// the parts had taken was lost (600 random bytes with a word of 50 at their end, one per tile, 16 tiles: 1,500 us per call without
+// parts, 1,530 that way, 70 now).
+static_assert(kWaveBoundHandOn < 1 << 15, "see kPartsLeft");
+__device__ __forceinline__ int encode_wave_piece_in_parts(const EncodeParams &p, int b, int n, uint32_t *X) {
+    const int merged = __builtin_amdgcn_readfirstlane(merge_pieces_in_parts(p, X, b, n, 1));
+    const int c = merged % kPartsLeft, left = merged / kPartsLeft;
+    if (left == 0) return c;
+    const int from = b + n - left;
+    const int more = encode_long_piece_bound(p, from, left, X, kWaveBoundMax, WaveScope{});
+    if (c < n - left) {
+        WaveScope{}.sync();
+        for (int i = lane_id_here(); i < more; i += kWave) p.scratch[b + c + i] = p.scratch[from + i];   // (downwards: a turn writes what it or one before it has read)
+    }
+    return c + more;
+}
+
 // Second half of merge_tile: the wavefront and workgroup paths of the tile's longer pieces.
 // P: pieces per wavefront of this launch (on the raw path the kernel may have chosen it).
 template <int SRC>
@@ -462,11 +480,7 @@ __device__ __forceinline__ TilePiece merge_tile_long_pieces(const EncodeParams &
             // well beyond what a wavefront keeps resident the whole workgroup is quicker (1,024 bytes
             // of text: 148 us against 272 us for one wavefront working through windows; even at 600)
             // (and at once when the piece has the workgroup to itself)
-            c = kLongMark;
-            if (n <= (p.W == 1 ? kWaveBoundMax : kWaveBoundHandOn)) {
-                c = __builtin_amdgcn_readfirstlane(merge_pieces_in_parts(p, &sh.lds.tiny[wv].S[0][0], b, n, 1));
-                if (c < 0) c = encode_long_piece_bound(p, b, n, &sh.lds.tiny[wv].S[0][0], kWaveBoundMax, WaveScope{});
-            }
+            c = n <= (p.W == 1 ? kWaveBoundMax : kWaveBoundHandOn) ? encode_wave_piece_in_parts(p, b, n, &sh.lds.tiny[wv].S[0][0]) : kLongMark;
         } else c = encode_wave_lds_piece(p, b, n, sh.lds.tiny[wv]);
         if (lane == 0) sh.cnt_back[owner] = c;
     }
@@ -829,11 +843,7 @@ __device__ __forceinline__ void merge_listed_pieces(const EncodeParams &p, Merge
         else if (n > p.wave_lds_max) c = kLongMark;
         else if (n <= p.wave_max) c = encode_wave_piece(p, b, n);
         else if (p.level >= 3 && !(p.runs_by_best_rank && piece_is_run_like(p, b, n, WaveScope{}))) {
-            c = kLongMark;
-            if (n <= kWaveBoundHandOn) {
-                c = __builtin_amdgcn_readfirstlane(merge_pieces_in_parts(p, &lds.tiny[wv].S[0][0], b, n, 1));
-                if (c < 0) c = encode_long_piece_bound(p, b, n, &lds.tiny[wv].S[0][0], kWaveBoundMax, WaveScope{});
-            }
+            c = n <= kWaveBoundHandOn ? encode_wave_piece_in_parts(p, b, n, &lds.tiny[wv].S[0][0]) : kLongMark;
         } else c = encode_wave_lds_piece(p, b, n, lds.tiny[wv]);
         if (lane == 0) {
             if (c == kLongMark) entry(n_listed + i) = ~(uint32_t)k;         // for the workgroup

@@ -464,12 +464,14 @@ __device__ __noinline__ typename ColumnGeometry<N>::Mask column_merge(const Enco
 // maximum at the place of its first symbol (`stage`, 64 words of the wavefront: cleared, joined into and read back in one round trip, since
 // a wavefront's LDS operations are done in order); then the symbols close up.  A pass is bound by its dependent steps, about 0.7 us: that
 // round trip, the cross-lane push, the lookup of the new pairs.  Lane i < n_pieces holds the first byte and the length
-// of piece i, and gets its number of tokens, which are in scratch[b ...], or -1 if a part is longer.  Every lane must call it.
+// of piece i, and gets its number of tokens, which are in scratch[b ...]; if a part is longer: of the tokens up to the last place before
+// it where parts were complete, plus kPartsLeft times the number of bytes from there on, which are not merged.  Every lane must call it.
 // (A function of its own for the reasons given at column_merge; many pieces per call, because it fetches its parameters anew.)
 // Per call, text with runs and random bytes, 100k table, before / with it: 4 MB 71 / 51 us (its 169 pieces of 65 bytes took 24 us each through
 // encode_long_piece_bound), 6 to 300 KB 34 to 37 / 20 to 35, 50k table 3 KB 19 / 10, raw bytes 13.6 MB 140 / 94, 500 KB 41 / 28, chunks of 2,000
 // bytes, 100 KB 38 / 25.  Two pieces at a time in one wavefront: no gain, a pass is instructions rather than waiting.
 constexpr int kPartMax = 40;
+constexpr int kPartsLeft = 1 << 16;            // (pieces are shorter than 2^15 bytes)
 // Whether symbols that do not start a part (bits of `rest`) are kPartMax in a row: then a part is longer.
 __device__ __forceinline__ bool long_part(uint64_t rest) {
 #pragma unroll
@@ -512,7 +514,7 @@ __device__ __noinline__ int merge_pieces_in_parts(const EncodeParams &p, uint32_
     const uint32_t not_lane = ~(uint32_t)lane;
     const uint64_t up_to_lane = ~0ull >> (63 - lane);
     n_pieces = __builtin_amdgcn_readfirstlane(n_pieces);
-    int result = -1;
+    int result = 0;
     for (int i = 0; i < n_pieces; ++i) {
         int b = __builtin_amdgcn_readlane(b_of, i), left = __builtin_amdgcn_readlane(n_of, i), dst = b;
         while (left > 0) {
@@ -571,7 +573,7 @@ __device__ __noinline__ int merge_pieces_in_parts(const EncodeParams &p, uint32_
             if (lane < n) *(global_i32 *)(scratch + 4 * (uintptr_t)(uint32_t)(dst + lane)) = (int32_t)(sym & 0xFFFFFFu);
             dst += n;
         }
-        const int c = left > 0 ? -1 : dst - __builtin_amdgcn_readlane(b_of, i);
+        const int c = dst - __builtin_amdgcn_readlane(b_of, i) + left * kPartsLeft;
         result = lane == i ? c : result;
     }
     return result;

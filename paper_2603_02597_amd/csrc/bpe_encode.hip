@@ -384,13 +384,40 @@ __device__ __forceinline__ WaveDeal wave_deal(int n_col, int n_entries, int wv) 
     return d;
 }
 
+// Whether all of a workgroup's n_listed (at most kPartsPieces) pieces of up to 64 bytes fall into short parts; lane e holds first byte and
+// length of piece e.  Where a wavefront merges two pieces one after the other, because they have more than 64 bytes together, the sum of
+// their longest parts stands against the longest piece of all, on which columns spend their time: up to a quarter more than that, parts are no
+// slower.  Words without spaces, six per tile, 400 tiles, columns / parts: 24 bytes, merged together, 25.8 / 23.5 us per call (31.5 one after the other), 40
+// bytes, half of each random, 33.6 / 31.6 to 33.6, 40 bytes, one part each, 35.1 / 43.0.  Four of these per tile 35.0 / 30.5.
+// The wavefront's own pieces, wv and wv + 4 of the list, are in lanes 0 and 1 afterwards.
+__device__ __forceinline__ bool listed_in_short_parts(const EncodeParams &p, int &b_of, int &n_of, int n_listed, int wv) {
+    static_assert(kPartsPieces <= 2 * kWavesPerGroup && kPartsPieces <= 16, "two per wavefront; the lengths are in one row");
+    const int e0 = __builtin_amdgcn_readfirstlane(wv), e1 = e0 + kWavesPerGroup;
+    const int b0 = __builtin_amdgcn_readlane(b_of, e0), n0 = __builtin_amdgcn_readlane(n_of, e0);     // (0: no such piece)
+    const int b1 = __builtin_amdgcn_readlane(b_of, e1), n1 = __builtin_amdgcn_readlane(n_of, e1);
+    bool fit = true;
+    if (n0) {
+        const uint64_t joined0 = joined_bytes(p, b0, n0);
+        fit = !long_part(joined0);
+        if (n1) {
+            const uint64_t joined1 = joined_bytes(p, b1, n1);
+            fit &= !long_part(joined1);
+            if (n0 + n1 > kWave)
+                fit &= 4 * (longest_row(joined0) + longest_row(joined1) + 2) <= 5 * (int)__builtin_amdgcn_readfirstlane(row_max_u32((uint32_t)n_of));
+        }
+    }
+    b_of = lane_id_here() == 0 ? b0 : b1;
+    n_of = lane_id_here() == 0 ? n0 : n1;
+    return __syncthreads_and(fit);
+}
+
 // A piece by one wavefront: its parts while they are short, and from the first longer one on as a piece of its own (no token
 // reaches across a border of parts), whose tokens then move up behind the others.  Merged as a whole when a later part was too long, what
 // the parts had taken was lost (600 random bytes with a word of 50 at their end, one per tile, 16 tiles: 1,500 us per call without
 // parts, 1,530 that way, 70 now).
 static_assert(kWaveBoundHandOn < 1 << 15, "see kPartsLeft");
 __device__ __forceinline__ int encode_wave_piece_in_parts(const EncodeParams &p, int b, int n, uint32_t *X) {
-    const int merged = __builtin_amdgcn_readfirstlane(merge_pieces_in_parts(p, X, b, n, 1));
+    const int merged = __builtin_amdgcn_readfirstlane(merge_pieces_in_parts<false>(p, X, b, n, 1));
     const int c = merged % kPartsLeft, left = merged / kPartsLeft;
     if (left == 0) return c;
     const int from = b + n - left;
@@ -424,22 +451,13 @@ __device__ __forceinline__ TilePiece merge_tile_long_pieces(const EncodeParams &
     const int n_listed = __builtin_amdgcn_readfirstlane(sh.list_n);
     int n_col = n_listed;
     if (n_listed && n_listed <= kPartsPieces) {
-        bool fit = true;
-        for (int e = __builtin_amdgcn_readfirstlane(wv); e < n_listed; e += kWavesPerGroup) {
-            int b, n;
-            piece_bounds<SRC>(p, bt, tile_q0, P, sh.list[e], b, n);
-            fit &= in_short_parts(p, __builtin_amdgcn_readfirstlane(b), __builtin_amdgcn_readfirstlane(n));
-        }
-        if (__syncthreads_and(fit)) {
+        int b_of = 0, n_of = 0;
+        if (lane < n_listed) piece_bounds<SRC>(p, bt, tile_q0, P, sh.list[lane], b_of, n_of);
+        if (listed_in_short_parts(p, b_of, n_of, n_listed, wv)) {
             const int e = wv + kWavesPerGroup * lane;
             const bool mine = e < n_listed;
-            int owner = 0, b = 0, n = 0;
-            if (mine) {
-                owner = sh.list[e];
-                piece_bounds<SRC>(p, bt, tile_q0, P, owner, b, n);
-            }
-            const int c = merge_pieces_in_parts(p, &sh.lds.tiny[wv].S[0][0], b, n, __builtin_popcountll(__ballot(mine)));
-            if (mine) sh.cnt_back[owner] = c;
+            const int c = merge_pieces_in_parts<true>(p, &sh.lds.tiny[wv].S[0][0], b_of, n_of, __builtin_popcountll(__ballot(mine)));
+            if (mine) sh.cnt_back[sh.list[e]] = c;
             n_col = 0;
         }
     }
@@ -795,22 +813,13 @@ __device__ __forceinline__ void merge_listed_pieces(const EncodeParams &p, Merge
     // wavefront; otherwise all of them in columns.
     const int n_listed = n_col;
     if (n_listed && n_listed <= kPartsPieces) {
-        bool fit = true;
-        for (int e = __builtin_amdgcn_readfirstlane(wv); e < n_listed; e += kWavesPerGroup) {
-            int b, n;
-            bounds((int)entry(e), b, n);
-            fit &= in_short_parts(p, __builtin_amdgcn_readfirstlane(b), __builtin_amdgcn_readfirstlane(n));
-        }
-        if (__syncthreads_and(fit)) {
+        int b_of = 0, n_of = 0;
+        if (lane < n_listed) bounds((int)entry(lane), b_of, n_of);
+        if (listed_in_short_parts(p, b_of, n_of, n_listed, wv)) {
             const int e = wv + kWavesPerGroup * lane;
             const bool mine = e < n_listed;
-            int k = 0, b = 0, n = 0;
-            if (mine) {
-                k = (int)entry(e);
-                bounds(k, b, n);
-            }
-            const int c = merge_pieces_in_parts(p, &lds.tiny[wv].S[0][0], b, n, __builtin_popcountll(__ballot(mine)));
-            if (mine) done(e, k, c);
+            const int c = merge_pieces_in_parts<true>(p, &lds.tiny[wv].S[0][0], b_of, n_of, __builtin_popcountll(__ballot(mine)));
+            if (mine) done(e, (int)entry(e), c);
             n_col = 0;
         }
     }

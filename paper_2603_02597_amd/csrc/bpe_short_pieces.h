@@ -460,7 +460,7 @@ __device__ __noinline__ typename ColumnGeometry<N>::Mask column_merge(const Enco
 // Pieces that fall into parts of at most kPartMax bytes where no rule joins two neighbouring bytes
 // (kNeverJoined): no token reaches from one part into another, so each part is merged as if it stood alone, one merge of
 // every part per pass.  Random bytes are such pieces: 64 of them take up to 28 merges one after the other with the 100k table, 3 to 6 passes.
-// One wavefront, a symbol per lane in registers, as many whole parts of a piece at a time as its 64 lanes hold.  The best pair of a part is found by an LDS
+// One wavefront, a symbol per lane in registers, as many whole parts of a piece, or of two pieces of 64 bytes together, at a time as its 64 lanes hold.  The best pair of a part is found by an LDS
 // maximum at the place of its first symbol (`stage`, 64 words of the wavefront: cleared, joined into and read back in one round trip, since
 // a wavefront's LDS operations are done in order); then the symbols close up.  A pass is bound by its dependent steps, about 0.7 us: that
 // round trip, the cross-lane push, the lookup of the new pairs.  Lane i < n_pieces holds the first byte and the length
@@ -478,14 +478,31 @@ __device__ __forceinline__ bool long_part(uint64_t rest) {
     for (int row = 1; row < kPartMax; row += min(row, kPartMax - row)) rest &= rest >> min(row, kPartMax - row);
     return rest != 0;
 }
-// Whether the piece of n <= 64 bytes from b on has no longer part.  Every lane must call it with the same arguments.
-__device__ __forceinline__ bool in_short_parts(const EncodeParams &p, int b, int n) {
+// Bit i: bytes i and i + 1 of the piece of n <= 64 bytes from b on may be joined.  Every lane must call it with the same arguments.
+__device__ __forceinline__ uint64_t joined_bytes(const EncodeParams &p, int b, int n) {
     const int lane = lane_id_here();
     const uint32_t sym = lane < n ? p.bytes[b + lane] : 0u;
     const uint32_t next = (uint32_t)wave_from_lane_above((int)sym, 0);
-    const bool joined = lane + 1 < n && p.table.byte_pairs[sym << 8 | next] != kNeverJoined;
-    return !long_part(__ballot(joined) << 1);
+    return __ballot(lane + 1 < n && p.table.byte_pairs[sym << 8 | next] != kNeverJoined);
 }
+// The most bits in a row in a word whose highest one is clear: one less than the bytes of the longest part.
+__device__ __forceinline__ int longest_row(uint64_t joined) {
+    uint64_t rows[6];                                // bit i of rows[k]: 2^k in a row from i on
+    rows[0] = joined;
+#pragma unroll
+    for (int k = 1; k < 6; ++k) rows[k] = rows[k - 1] & rows[k - 1] >> (1 << (k - 1));
+    uint64_t from = ~0ull;                           // where `row` of them are in a row
+    int row = 0;
+#pragma unroll
+    for (int k = 5; k >= 0; --k) {
+        const uint64_t more = from & rows[k] >> row;
+        row += more ? 1 << k : 0;
+        from = more ? more : from;
+    }
+    return row;
+}
+// LISTED: pieces of up to 64 bytes that all fit; otherwise there is one piece, of any length.
+template <bool LISTED>
 __device__ __noinline__ int merge_pieces_in_parts(const EncodeParams &p, uint32_t *stage_words, int b_of, int n_of, int n_pieces) {
     constexpr uint32_t kFirst = 1u << 24, kNew = 1u << 25;         // first symbol of its part; made in this pass
     typedef __attribute__((address_space(1))) const uint8_t global_u8;
@@ -513,23 +530,32 @@ __device__ __noinline__ int merge_pieces_in_parts(const EncodeParams &p, uint32_
     };
     const uint32_t not_lane = ~(uint32_t)lane;
     const uint64_t up_to_lane = ~0ull >> (63 - lane);
-    n_pieces = __builtin_amdgcn_readfirstlane(n_pieces);
+    n_pieces = LISTED ? __builtin_amdgcn_readfirstlane(n_pieces) : 1;
     int result = 0;
-    for (int i = 0; i < n_pieces; ++i) {
+    for (int i = 0, pieces; i < n_pieces; i += pieces) {
         int b = __builtin_amdgcn_readlane(b_of, i), left = __builtin_amdgcn_readlane(n_of, i), dst = b;
-        while (left > 0) {
+        // the next piece with it, as more parts, if both are within 64 bytes
+        const int n0 = left, n1 = i + 1 < n_pieces ? __builtin_amdgcn_readlane(n_of, i + 1) : kWave;
+        pieces = LISTED && n0 + n1 <= kWave ? 2 : 1;
+        const int b1 = pieces == 2 ? __builtin_amdgcn_readlane(b_of, i + 1) : 0;
+        int parts0 = 0, c1 = 0;                // parts of the first of two, tokens of the second
+        if (pieces == 2) left += n1;
+        while (left > 0) {                     // (once if LISTED)
             int n = min(left, kWave);
-            uint32_t sym = lane < n ? *(global_u8 *)(bytes + (uint32_t)(b + lane)) : 0u;
+            const int at = pieces == 2 && lane >= n0 ? b1 + lane - n0 : b + lane;
+            uint32_t sym = lane < n ? *(global_u8 *)(bytes + (uint32_t)at) : 0u;
             uint32_t next = (uint32_t)wave_from_lane_above((int)sym, 0);
-            const uint32_t pair = lane + 1 < n ? byte_pairs[sym << 8 | next] : kNeverJoined;
+            uint32_t pair = lane + 1 < n ? byte_pairs[sym << 8 | next] : kNeverJoined;
+            if (pieces == 2 && lane + 1 == n0) pair = kNeverJoined;
             uint64_t live = n == kWave ? ~0ull : (1ull << n) - 1;
             uint64_t first = live & ~(__ballot(pair != kNeverJoined) << 1);        // where parts start
-            if (long_part(live & ~first)) break;
-            if (left > n) {        // the last part may go on: it comes next time (it is not the only one)
+            if (!LISTED && long_part(live & ~first)) break;
+            if (!LISTED && left > n) {        // the last part may go on: it comes next time (it is not the only one)
                 n = 63 - __builtin_clzll(first);
                 live = (1ull << n) - 1;
                 first &= live;
             }
+            if (pieces == 2) parts0 = __builtin_popcountll(first & ((1ull << n0) - 1));      // (n0 < 64)
             b += n;
             left -= n;
             sym |= (first >> lane & 1) ? kFirst : 0u;
@@ -570,11 +596,18 @@ __device__ __noinline__ int merge_pieces_in_parts(const EncodeParams &p, uint32_
                 const uint32_t rank1 = slot_match(s1, s2, slot.rest1, slot.rest2);
                 q = fresh ? (rank1 == kNoRank ? 0u : ~rank1 | 63u) : q;
             }
-            if (lane < n) *(global_i32 *)(scratch + 4 * (uintptr_t)(uint32_t)(dst + lane)) = (int32_t)(sym & 0xFFFFFFu);
+            int to = dst + lane;
+            if (pieces == 2) {                 // merging leaves the number of parts: where the second piece's first one is by now
+                const int n_kept0 = __builtin_ctzll(__ballot((first >> lane & 1) && mbcnt(first) == parts0));
+                c1 = n - n_kept0;
+                n = n_kept0;
+                if (lane >= n_kept0) to = b1 + lane - n_kept0;
+            }
+            if (lane < n + c1) *(global_i32 *)(scratch + 4 * (uintptr_t)(uint32_t)to) = (int32_t)(sym & 0xFFFFFFu);
             dst += n;
         }
         const int c = dst - __builtin_amdgcn_readlane(b_of, i) + left * kPartsLeft;
-        result = lane == i ? c : result;
+        result = lane == i ? c : lane == i + 1 ? c1 : result;
     }
     return result;
 }

@@ -1,7 +1,7 @@
-"""Pieces of more than 16 bytes that fall into short parts (in_short_parts, merge_pieces_in_parts): parts around the longest that
-is taken and around the 64 bytes that a wavefront looks at together, at the start of a piece and near its end, pieces around those 64
-bytes and over several of them, as many per tile as one, one per wavefront, the most that are taken and one more, beside pieces that do not
-fit; merged ids of any kind; given pieces and raw bytes.  Exact against the oracle."""
+"""Pieces of more than 16 bytes that fall into short parts (listed_in_short_parts, merge_pieces_in_parts): parts around the longest
+that is taken and around the 64 bytes that a wavefront takes together, at the start of a piece and near its end; pieces around those 64
+bytes and over several of them, two of up to 64 bytes together and of more; as many per tile as one, one per wavefront, the most that
+are taken and one more, beside pieces that do not fit; merged ids of any kind; given pieces and raw bytes.  Exact against the oracle."""
 import numpy as np
 import pytest
 
@@ -58,11 +58,12 @@ def test_parts(numbered, per_tile):
     assert all((x, y) in joined for x in range(1, 7) for y in range(1, 7)) and all(max(pair) < 7 for pair in joined)
     table, want_table = B.Table(merges, None, ids), oracle.Table(merges, None, ids)
     sizes = [17, 18, 33, 63, 64, 65, 66, 127, 128, 129, 200, 257, 300, 640, 641]
+    small = [17, 18, 31, 32, 33, 46, 47, 63, 64]           # two of them: up to 64 bytes, and beyond
     seen, unfit_tiles, late = set(), 0, 0
     for longest in (3, 16, 17, PART - 1, PART, PART + 1, 64, 65, 100):
         pieces = []
         for i in range(45):
-            here = [_piece(rng, sizes[(i + j) % (5 if i % 2 else len(sizes))], longest, i % 4 > 1) for j in range(per_tile)]
+            here = [_piece(rng, int(rng.choice(small)) if i % 2 else sizes[(i + j) % len(sizes)], longest, i % 4 > 1) for j in range(per_tile)]
             parts = [_longest_part(x, joined) for x in here]
             seen.update(parts)
             listed = [k for x, k in zip(here, parts) if len(x) <= SHORT]

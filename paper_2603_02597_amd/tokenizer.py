@@ -87,7 +87,9 @@ class Tokenizer:
 
     def tokenize_batch(self, texts):
         """texts: list of bytes (or str, encoded as UTF-8).  Returns (list of int32
-        arrays, kernel_ms): the ids of every text and the GPU time of the kernels.
+        arrays, kernel_ms): the ids of every text and the GPU time from the end of the transfer in to the
+        start of the transfer out, that is of the encode kernels: neither transfer is in it, nor the
+        renumbering to output ids, which the transfer out does on the way.
         The texts are packed into pinned memory; a kernel brings them to the GPU, the encode kernels
         follow, and one more puts the ids, renumbered if need be, and the verdict into pinned memory
         (as many as there are: the number is on the GPU): one synchronisation."""

@@ -1,5 +1,5 @@
 """One Tokenizer in several threads, each on a stream of its own: batches that grow while others are under way, encoded and
-decoded beside each other.  Exact against the CPU oracle."""
+decoded beside each other, exact against the CPU oracle; and the kernel time that it reports."""
 import threading
 
 import numpy as np
@@ -49,4 +49,19 @@ def test_threads_that_share_a_tokenizer(renumber):
     for t in threads:
         t.join()
     assert not failed
+    tok.close()
+
+
+@pytest.mark.parametrize("renumber", [False, True])
+def test_kernel_time_is_within_the_call(renumber):
+    """A clock that is not written, or read before it is, would give none or hours."""
+    import time
+    import paper_2603_02597_amd as B
+    merges, data = C.load_merges("t1k"), C.make_eval("seq32k")["bytes"].tobytes()
+    tok = B.Tokenizer(merges, output_ids=np.arange(256 + len(merges), dtype=np.int32) if renumber else None)
+    for n in (1, 100, 30000, len(data)):
+        for _ in range(3):
+            t0 = time.perf_counter()
+            _, ms = tok.tokenize_batch([data[:n]])
+            assert 0 < ms <= (time.perf_counter() - t0) * 1e3
     tok.close()

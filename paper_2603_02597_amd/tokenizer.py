@@ -100,7 +100,7 @@ class Tokenizer:
         if n_seqs == 0:
             return [], 0.0
         # text that is ASCII is copied from where it lies (every string knows whether it is, so nothing is joined to find out)
-        if all(type(t) is str for t in texts) and all(map(str.isascii, texts)):
+        if set(map(type, texts)) == {str} and all(map(str.isascii, texts)):
             joined = texts[0] if n_seqs == 1 else "".join(texts)
             size = ctypes.c_ssize_t()
             source = _utf8(joined, ctypes.byref(size))

@@ -72,7 +72,7 @@ constexpr int kRunRounds = (kRunLeft + kGroupThreads - 1) / kGroupThreads;
 // each wavefront.  Such a piece takes a wavefront about 5 us, the columns take up to 16 pieces of a wavefront together in 25 to 30 (random
 // bytes, 100k table): 4 MB with 18 of them per workgroup 50.3 us per call with this line, 53 and 56 with 24 and 64 pieces in parts.  All or
 // none: parts and then columns are the sum of both (text without spaces in pieces of 40, 100 KB: 32 us without parts, 42 with a mixture, 31 so).
-// What cannot be cut pays for the look: the same text in pieces of 60 and 64 bytes 39.4 / 40.1 and 46.4 / 47.4.
+// What cannot be cut pays for the look: one and six words of 60 bytes without spaces per tile, 16 tiles, 40.2 / 40.4 and 42.3 / 42.7.
 constexpr int kPartsPieces = 8;
 union MergeLds {
     TinyState tiny[kWavesPerGroup];
@@ -810,7 +810,7 @@ __device__ __forceinline__ void merge_listed_pieces(const EncodeParams &p, Merge
                                                     const Entry &entry, const Bounds &bounds, const Done &done) {
     const int tid = threadIdx.x, lane = lane_id_here(), wv = tid / kWave;
     // Pieces of up to 64 bytes.  If they are few and all fall into short parts (random bytes do), each is merged by a
-    // wavefront; otherwise all of them in columns.
+    // wavefront, or two of them together; otherwise all of them in columns.
     const int n_listed = n_col;
     if (n_listed && n_listed <= kPartsPieces) {
         int b_of = 0, n_of = 0;

@@ -460,16 +460,17 @@ __device__ __noinline__ typename ColumnGeometry<N>::Mask column_merge(const Enco
 // Pieces that fall into parts of at most kPartMax bytes where no rule joins two neighbouring bytes
 // (kNeverJoined): no token reaches from one part into another, so each part is merged as if it stood alone, one merge of
 // every part per pass.  Random bytes are such pieces: 64 of them take up to 28 merges one after the other with the 100k table, 3 to 6 passes.
-// One wavefront, a symbol per lane in registers, as many whole parts of a piece, or of two pieces of 64 bytes together, at a time as its 64 lanes hold.  The best pair of a part is found by an LDS
-// maximum at the place of its first symbol (`stage`, 64 words of the wavefront: cleared, joined into and read back in one round trip, since
-// a wavefront's LDS operations are done in order); then the symbols close up.  A pass is bound by its dependent steps, about 0.7 us: that
+// One wavefront, a symbol per lane in registers, as many whole parts at a time as its 64 lanes hold, of one piece or of two that have at
+// most 64 bytes together.  The best pair of a part is found by an LDS maximum at the place of its first symbol (`stage`, 64 words of the
+// wavefront: cleared, joined into and read back in one round trip, since a wavefront's LDS operations are done in order); then the symbols close up.  A pass is bound by its dependent steps, about 0.7 us: that
 // round trip, the cross-lane push, the lookup of the new pairs.  Lane i < n_pieces holds the first byte and the length
 // of piece i, and gets its number of tokens, which are in scratch[b ...]; if a part is longer: of the tokens up to the last place before
 // it where parts were complete, plus kPartsLeft times the number of bytes from there on, which are not merged.  Every lane must call it.
 // (A function of its own for the reasons given at column_merge; many pieces per call, because it fetches its parameters anew.)
 // Per call, text with runs and random bytes, 100k table, before / with it: 4 MB 71 / 51 us (its 169 pieces of 65 bytes took 24 us each through
 // encode_long_piece_bound), 6 to 300 KB 34 to 37 / 20 to 35, 50k table 3 KB 19 / 10, raw bytes 13.6 MB 140 / 94, 500 KB 41 / 28, chunks of 2,000
-// bytes, 100 KB 38 / 25.  Two pieces at a time in one wavefront: no gain, a pass is instructions rather than waiting.
+// bytes, 100 KB 38 / 25.  Two pieces together (six words of 24 bytes per tile, 400 tiles, one after the other / together 31.5 / 23.5): a
+// pass is instructions rather than waiting and costs the same whatever the lanes hold.
 constexpr int kPartMax = 40;
 constexpr int kPartsLeft = 1 << 16;            // (pieces are shorter than 2^15 bytes)
 // Whether symbols that do not start a part (bits of `rest`) are kPartMax in a row: then a part is longer.
